@@ -223,56 +223,137 @@ __device__ inline A median9(A a0, A a1, A a2, A a3, A a4, A a5, A a6, A a7, A a8
 // when f and f* share their moments (eq. DelS).  Near x = 0 the closed form
 // cancels; there the alternating series x^2 sum_k (-x)^k / ((k+1)(k+2)) is
 // summed in Horner form.  The first omitted term bounds the truncation:
-// below 1e-17 relative for |x| <= 0.1 in FP64 (16 terms); in FP32 below
-// 1.4e-8 for |x| <= 1/8 (7 terms, the usual case) and 1.4e-9 for
-// |x| <= 0.5 (22 terms).
-__device__ inline double hkern(double x)
+// below 1e-17 relative in FP64 (8 terms for |x| <= 1/85, 16 for |x| <= 0.1);
+// in FP32 below 1.4e-8 for |x| <= 1/8 (7 terms, the usual case) and 1.4e-9
+// for |x| <= 0.5 (22 terms).
+template <int N, class A>
+__device__ __forceinline__ A h_series(A x)
 {
-    if (fabs(x) <= 0.1) {
-        double p = 1.0 / (16.0 * 17.0);
+    A p = A(1.0 / (N * (N + 1.0)));
 #pragma unroll
-        for (int k = 14; k >= 0; --k) p = 1.0 / ((k + 1.0) * (k + 2.0)) - x * p;
-        return x * x * p;
-    }
-    return (1.0 + x) * log1p(x) - x;
+    for (int k = N - 2; k >= 0; --k) p = A(1.0 / ((k + 1.0) * (k + 2.0))) - x * p;
+    return x * x * p;
 }
-__device__ inline float hkern(float x)
-{
-    if (fabsf(x) <= 0.125f) {
-        float p = 1.0f / (7.0f * 8.0f);
-#pragma unroll
-        for (int k = 5; k >= 0; --k) p = 1.0f / ((k + 1.0f) * (k + 2.0f)) - x * p;
-        return x * x * p;
-    }
-    if (fabsf(x) <= 0.5f) {
-        float p = 1.0f / (22.0f * 23.0f);
-#pragma unroll
-        for (int k = 20; k >= 0; --k) p = 1.0f / ((k + 1.0f) * (k + 2.0f)) - x * p;
-        return x * x * p;
-    }
-    return (1.0f + x) * log1pf(x) - x;
-}
-
-// h(x) with its derivative h'(x) = ln(1 + x).  Where hkern sums the series,
-// the logarithm follows from h itself, (1 + x) ln(1 + x) = h(x) + x, with no
-// cancellation (h is second order in x); elsewhere it is the logarithm that
-// h is built from.  h(-1) = 1 with h'(-1) = -inf (a population at zero).
+// |x| up to which the sums below take the series for every population, and up
+// to which a shorter one does
 template <class A>
-__device__ inline A hkern_slope(A x, A& dh)
+struct HRange;
+template <>
+struct HRange<double> {
+    static constexpr double near = 0.1, tiny = 1.0 / 85.0, mid = 0.1;
+    static constexpr int nnear = 16, ntiny = 8;
+};
+template <>
+struct HRange<float> {
+    static constexpr float near = 0.125f, tiny = 0.0f, mid = 0.5f;
+    static constexpr int nnear = 7, ntiny = 7;
+};
+// h and h' = ln(1 + x) beyond the short series (FP32: the long series up to
+// 1/2, then the logarithm).  h(-1) = 1 with h'(-1) = -inf (a population at
+// zero); below -1 the logarithm gives NaN, and h_far_closed that limit.
+template <class A>
+__device__ __forceinline__ A h_far(A x)
 {
-    constexpr A series = sizeof(A) == 8 ? A(0.1) : A(0.5);
+    if constexpr (sizeof(A) == 4) {
+        if (fabs(x) <= HRange<A>::mid) return h_series<22>(x);
+    }
+    return (A(1) + x) * log1p_(x) - x;
+}
+template <class A>
+__device__ __forceinline__ A h_far_slope(A x, A& dh)
+{
     if (x <= A(-1)) {
         dh = -A(__builtin_huge_val());
         return A(1);
     }
-    if (fabs(x) <= series) {
-        const A h = hkern(x);
-        dh = (h + x) * rcp(A(1) + x);
-        return h;
+    if constexpr (sizeof(A) == 4) {
+        if (fabs(x) <= HRange<A>::mid) {
+            const A h = h_series<22>(x);
+            dh = (h + x) * rcp(A(1) + x);
+            return h;
+        }
     }
     const A l = log1p_(x);
     dh = l;
     return (A(1) + x) * l - x;
+}
+// v[i] for an index that differs between lanes, without leaving registers
+template <int Q, class A>
+__device__ __forceinline__ A pick(const A (&v)[Q], int i)
+{
+    A r = v[0];
+#pragma unroll
+    for (int k = 1; k < Q; ++k) r = i == k ? v[k] : r;
+    return r;
+}
+
+// sum_i f*_i h(s x_i).  The populations whose argument is beyond the series
+// (few, at strongly nonequilibrium nodes) are marked on the way and added
+// afterwards by one loop, so the logarithm stands in the code once: with a
+// branch to it at each of the nine populations the FP64 collision kernel was
+// 2.5 times as long, held 246 registers and ran at the pace of its
+// instruction fetches.  CLOSED: arguments at or below -1 count as h(-1) = 1.
+template <bool CLOSED, int Q, class A>
+__device__ __forceinline__ A kull_sum(const A (&fs)[Q], const A (&x)[Q], A s)
+{
+    using R = HRange<A>;
+    A sum = A(0);
+    unsigned far = 0;
+    if constexpr (R::ntiny < R::nnear) {
+        A m = A(0);
+#pragma unroll
+        for (int i = 0; i < Q; ++i) m = fmax(m, fabs(x[i]));
+        if (m * fabs(s) <= R::tiny) {
+#pragma unroll
+            for (int i = 0; i < Q; ++i) sum += fs[i] * h_series<R::ntiny>(s * x[i]);
+            return sum;
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < Q; ++i) {
+        const A y = s * x[i];
+        const bool in = fabs(y) <= R::near;    // NaN: beyond
+        const A t = fs[i] * h_series<R::nnear>(y);
+        sum += in ? t : A(0);
+        far |= in ? 0u : 1u << i;
+    }
+    while (far) {
+        const int i = __builtin_ctz(far);
+        far &= far - 1;
+        const A y = s * pick(x, i);
+        sum += pick(fs, i) * ((CLOSED && y <= A(-1)) ? A(1) : h_far(y));
+    }
+    return sum;
+}
+// the same with the derivative in s, sum_i f*_i x_i h'(s x_i).  Where h is the
+// series the logarithm follows from h itself, (1 + x) ln(1 + x) = h(x) + x,
+// with no cancellation (h is second order in x).
+template <int Q, class A>
+__device__ __forceinline__ A kull_sum_slope(const A (&fs)[Q], const A (&x)[Q], A s, A& slope)
+{
+    using R = HRange<A>;
+    A sum = A(0), sl = A(0);
+    unsigned far = 0;
+#pragma unroll
+    for (int i = 0; i < Q; ++i) {
+        const A y = s * x[i];
+        const bool in = fabs(y) <= R::near;
+        const A h = h_series<R::nnear>(y);
+        const A t = fs[i] * h, u = fs[i] * x[i] * ((h + y) * rcp(A(1) + y));
+        sum += in ? t : A(0);
+        sl += in ? u : A(0);
+        far |= in ? 0u : 1u << i;
+    }
+    while (far) {
+        const int i = __builtin_ctz(far);
+        far &= far - 1;
+        const A xi = pick(x, i), fi = pick(fs, i);
+        A dh;
+        sum += fi * h_far_slope(s * xi, dh);
+        sl += fi * xi * dh;
+    }
+    slope = sl;
+    return sum;
 }
 
 // ---- quasiequilibria, excess form -------------------------------------------
@@ -487,13 +568,6 @@ __device__ __forceinline__ void moments_equilibrium(const A (&g)[Lat<LAT>::Q], A
     }
 }
 
-// h with its limit h(-1) = 1 (a population at exactly zero)
-template <class A>
-__device__ __forceinline__ A h_closed(A y)
-{
-    return y <= A(-1) ? A(1) : hkern(y);
-}
-
 // ELBM (eqs. elbm, entropy_estimate): alpha, the nontrivial root of
 // S(f~) = S(f) for f~ = (1 - alpha) f + alpha f*.  With the entropic f*,
 // S(f*) - S(g) = sum f*_i h(x_i(g)) on the line through f and f*, and f~ has
@@ -515,13 +589,13 @@ __device__ A elbm_alpha(const A (&fs)[Q], const A (&x)[Q], bool& posrule)
 {
     constexpr A eps = sizeof(A) == 8 ? A(2.220446049250313e-16) : A(1.1920929e-7);
     const A inf = A(__builtin_huge_val());
-    A smax = inf, target = A(0), m2 = A(0), m3 = A(0);
+    A smax = inf, m2 = A(0), m3 = A(0);
+    const A target = kull_sum<true>(fs, x, A(1));
     bool nonpos = false;
 #pragma unroll
     for (int i = 0; i < Q; ++i) {
         if (x[i] > A(0)) smax = fmin(smax, A(1) / x[i]);
         nonpos |= x[i] <= A(-1);
-        target += fs[i] * h_closed(x[i]);
         const A fx2 = fs[i] * x[i] * x[i];
         m2 += fx2;
         m3 += fx2 * x[i];
@@ -534,14 +608,8 @@ __device__ A elbm_alpha(const A (&fs)[Q], const A (&x)[Q], bool& posrule)
     }
     // G(s) and G'(s) = -sum f*_i x_i ln(1 - s x_i)
     auto eval = [&](A s, A& dg) {
-        A g = -target;
-        dg = A(0);
-#pragma unroll
-        for (int i = 0; i < Q; ++i) {
-            A dh;
-            g += fs[i] * hkern_slope(-s * x[i], dh);
-            dg -= fs[i] * x[i] * dh;
-        }
+        const A g = kull_sum_slope(fs, x, -s, dg) - target;
+        dg = -dg;
         return g;
     };
     A s = A(1);
@@ -645,12 +713,13 @@ __device__ __forceinline__ void collide_site(const A (&g)[Lat<LAT>::Q], A shift,
         A x[Q];
 #pragma unroll
         for (int i = 0; i < Q; ++i) x[i] = o.d[i] * rcp(fs[i]);
-        if (want_pre) {
-#pragma unroll
-            for (int i = 0; i < Q; ++i) dpre += fs[i] * hkern(x[i]);
+        // both scales through one copy of the sum
+#pragma unroll 1
+        for (int k = want_pre ? 0 : 1; k < 2; ++k) {
+            const A v = kull_sum<false>(fs, x, k ? -c : A(1));
+            if (k) dpost = v;
+            else dpre = v;
         }
-#pragma unroll
-        for (int i = 0; i < Q; ++i) dpost += fs[i] * hkern(-c * x[i]);
     }
     const A inf = A(__builtin_huge_val());
     if (!fs_ok) pre_ok = post_ok = false;
@@ -695,13 +764,13 @@ __device__ __forceinline__ A delta_s_scaled(const SiteState<LAT, A>& o, A shift,
     if constexpr (DS == kQuad) {
         return s * s * o.dpost;
     } else {
-        A sum = 0;
+        A fs[L::Q], x[L::Q];
 #pragma unroll
         for (int i = 0; i < L::Q; ++i) {
-            A fs = A(L::w(i)) * shift + o.gs[i];
-            sum += fs * hkern(-s * c * o.d[i] * rcp(fs));
+            fs[i] = A(L::w(i)) * shift + o.gs[i];
+            x[i] = o.d[i] * rcp(fs[i]);
         }
-        return sum;
+        return kull_sum<false>(fs, x, -s * c);
     }
 }
 
@@ -989,17 +1058,7 @@ __device__ A kullback_scale(const A (&fs)[Q], const A (&x)[Q], A t, A p0, A lo, 
 {
     constexpr A eps = sizeof(A) == 8 ? A(2.220446049250313e-16) : A(1.1920929e-7);
     // F(p) - t and F'(p) = sum f*_i x_i ln(1 + p x_i)
-    auto eval = [&](A p, A& df) {
-        A f = -t;
-        df = A(0);
-#pragma unroll
-        for (int i = 0; i < Q; ++i) {
-            A dh;
-            f += fs[i] * hkern_slope(p * x[i], dh);
-            df += fs[i] * x[i] * dh;
-        }
-        return f;
-    };
+    auto eval = [&](A p, A& df) { return kull_sum_slope(fs, x, p, df) - t; };
     A p = fmin(fmax(p0, lo), hi);
     A f = A(0), df;
     bool at_p = false;      // f = F(p) - t

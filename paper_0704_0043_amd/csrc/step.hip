@@ -237,6 +237,15 @@ __device__ __forceinline__ void diffusive_wall(gptr<T> dst, long long plane, lon
     }
 }
 
+// The exact homothety of a node to Delta S = t as a real call (its root solve,
+// needed by few nodes, would otherwise sit in the middle of every kernel).  The
+// state goes by value: a caller's own copy then stays in registers.
+template <class A>
+__device__ __attribute__((noinline)) A exact_homothety_call(SiteState<kD2Q9, A> o, A shift, A t)
+{
+    return exact_homothety<kD2Q9>(o, shift, t, o.dpost);
+}
+
 template <class T, int QE, int DS, int BC, bool ELBM = false>
 __global__ void __launch_bounds__(kThreads) k_collide2d(StepArgs a)
 {
@@ -299,7 +308,7 @@ __global__ void __launch_bounds__(kThreads) k_collide2d(StepArgs a)
                 A phi = trim_phi(D, S.dpost, mask);
                 if constexpr (DS == kExact) {
                     if (D.homothety && (mask & kMaskTrim) && !D.trim_mode && isfinite(S.dpost))
-                        phi = exact_homothety<kD2Q9>(S, shift, A(D.delta_trim), S.dpost);
+                        phi = exact_homothety_call(S, shift, A(D.delta_trim));
                 }
                 if (S.posrule) {
                     mask |= kMaskPos;
@@ -463,12 +472,10 @@ __device__ __attribute__((noinline)) typename Store<T>::A rescale_stored_exact(
         e[i] = (gl[i] - gs[i]) * rcp(fs[i]);
     }
     if (exact) {
-        A ds_s = A(0), emin = A(0);
+        const A ds_s = kull_sum<false>(fs, e, A(1));
+        A emin = A(0);
 #pragma unroll
-        for (int i = 0; i < Q; ++i) {
-            ds_s += fs[i] * hkern(e[i]);
-            emin = fmin(emin, e[i]);
-        }
+        for (int i = 0; i < Q; ++i) emin = fmin(emin, e[i]);
         r = A(1);
         if (ds_s > A(0)) {
             if (tgt < ds_s) r = kullback_scale<Q>(fs, e, tgt, sqrt_(tgt * rcp(ds_s)), A(0), A(1));
@@ -484,13 +491,7 @@ __device__ __attribute__((noinline)) typename Store<T>::A rescale_stored_exact(
 #pragma unroll
         for (int i = 0; i < Q; ++i) Store<T>::st(at_bytes(buf + (i * plane + rc), own), gs[i] + r * (gl[i] - gs[i]));
         if (isfinite(dc)) {
-            A ds_new = A(0), ds_old = A(0);
-#pragma unroll
-            for (int i = 0; i < Q; ++i) {
-                ds_old += fs[i] * hkern(e[i]);
-                ds_new += fs[i] * hkern(r * e[i]);
-            }
-            lim = ds_old - ds_new;
+            lim = kull_sum<false>(fs, e, A(1)) - kull_sum<false>(fs, e, r);
         }
     }
     return lim;
@@ -778,14 +779,6 @@ struct FusedDom {
     double* dS;
 };
 
-// the exact homothety as a real call (its root solve would otherwise be
-// inlined twice into the fused kernel's row loop)
-template <class A>
-__device__ __attribute__((noinline)) A exact_homothety_call(const SiteState<kD2Q9, A>& o, A shift, A t, A dpost)
-{
-    return exact_homothety<kD2Q9>(o, shift, t, dpost);
-}
-
 // Fused D2Q9 step: collision, trimming, positivity and the median filter of
 // Sec. 3.5 (cavity stencils of Sec. 4.4) in one pass, for domains without
 // ensemble-dependent limiters.  Each wave walks down 64 adjacent columns of a
@@ -902,7 +895,7 @@ __global__ void __launch_bounds__(kThreads) k_fused2d(StepArgs a)
                     phi = trim_phi(D, S.dpost, mask);
                     if constexpr (DS == kExact) {
                         if (D.homothety && (mask & kMaskTrim) && !D.trim_mode && isfinite(S.dpost))
-                            phi = exact_homothety_call(S, shift, A(D.delta_trim), S.dpost);
+                            phi = exact_homothety_call(S, shift, A(D.delta_trim));
                     }
                     if (D.limiter & kLimPos) {
                         const A pp = positivity_phi<kD2Q9>(S, shift);
@@ -973,7 +966,7 @@ __global__ void __launch_bounds__(kThreads) k_fused2d(StepArgs a)
                     bool done = false;
                     if constexpr (DS == kExact) {
                         if (D.homothety && isfinite(p_dpost)) {
-                            pm = exact_homothety_call(P, shift, thr, p_dpost);
+                            pm = exact_homothety_call(P, shift, thr);
                             done = true;
                         }
                     }
@@ -1228,12 +1221,8 @@ __global__ void __launch_bounds__(kThreads) k_ens1d(StepArgs a)
                             ds_old = pa * pa * d;
                             ds_new = r * r * pa * pa * d;
                         } else {
-                            ds_old = ds_new = A(0);
-#pragma unroll
-                            for (int i = 0; i < Q; ++i) {
-                                ds_old += fs[i] * hkern(e[i]);
-                                ds_new += fs[i] * hkern(r * e[i]);
-                            }
+                            ds_old = kull_sum<false>(fs, e, A(1));
+                            ds_new = kull_sum<false>(fs, e, r);
                         }
                         // the step kernel counted d - Delta S(stored)
                         acc.lim += ds_old - ds_new;
