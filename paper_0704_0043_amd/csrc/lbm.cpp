@@ -28,6 +28,7 @@ thread_local std::string g_err;
 
 constexpr size_t kAlign = 256;
 constexpr int kMinTuneH = 16;   // smallest median-tile height the tuner tries
+constexpr int kMinTileH = 4;    // rows of a second-pass tile on the smallest grids
 constexpr int kMinFusedH = 4;   // smallest fused-tile height the tuner tries
 constexpr int kMaxFusedH = 128; // tallest fused tile
 
@@ -52,6 +53,22 @@ bool fusable(const lbm_domain_desc* doms, int32_t nd)
         median = median || (doms[k].limiter & LBM_LIM_MEDIAN);
     }
     return median;
+}
+
+// Rows per second-pass tile when `th` are asked for: as many, unless the grid
+// then has fewer than kMinTiles tiles (three workgroups per CU).  A wave walks
+// its tile's rows in turn, so on a small grid tall tiles leave most CUs idle
+// behind a few long walks.  It depends on the domains alone, so that the FP64
+// sums of the pass come out the same for every height asked for there.
+constexpr int kMinTiles = 768;
+int second_height(const lbm_domain_desc* doms, int32_t nd, int th)
+{
+    for (int h = kMaxTileH; h > kMinTileH; h /= 2) {
+        long long tiles = 0;
+        for (int k = 0; k < nd; ++k) tiles += tiles_of(doms[k].lattice, doms[k].nx, doms[k].ny, h);
+        if (tiles >= kMinTiles) return std::min(th, h);
+    }
+    return std::min(th, kMinTileH);
 }
 
 // both forms of the step are kept and chosen between while the run goes
@@ -153,6 +170,7 @@ struct lbm_ctx {
     std::string err;
     std::vector<RowBlock> rows_host;
     std::vector<Tile> groups_host;
+    int cap_h = kMaxTileH;      // tallest second-pass tile of these domains (second_height)
     int narrow = 1;             // row blocks of 64 / 128 columns for narrow domains
     int tuned = 0;              // 1 when the tile shape was chosen by timing
 
@@ -355,7 +373,7 @@ void plan(std::vector<DomainHost>& dh, const lbm_domain_desc* doms, int32_t nd, 
         }
         off = plan_extras(h, storage, off);
         // the tile table is sized for the smallest height the tuner may pick
-        const int min_h = run->tile_h > 0 ? run->tile_h : kMinTuneH;
+        const int min_h = second_height(doms, nd, run->tile_h > 0 ? run->tile_h : kMinTuneH);
         int tiles = tiles_of(h.d.lattice, h.d.nx, h.d.ny, min_h);
         if (h.d.lattice == LBM_D2Q9 && run->tile_x == kFusedWidth)
             tiles = std::max(tiles, fused_tiles_of(h.d.nx, h.d.ny, run->tile_h > 0 ? run->tile_h : kMinFusedH));
@@ -527,7 +545,7 @@ int upload_domains(lbm_ctx* ctx)
 int set_tiles(lbm_ctx* ctx, int th, bool fused = false)
 {
     lbm_ctx::Slot& sl = ctx->act;
-    sl.tiles_host = build_tiles(ctx, th, fused);
+    sl.tiles_host = build_tiles(ctx, fused ? th : std::min(th, ctx->cap_h), fused);
     sl.fused = fused;
     if (int(sl.tiles_host.size()) > ctx->lay.max_tiles) return fail(ctx, LBM_EINVAL, "tile table overflow");
     sl.ntiles = int(sl.tiles_host.size());
@@ -549,6 +567,7 @@ StepArgs step_args(const lbm_ctx* ctx, int parity)
     a.ndomains = int(ctx->dom.size());
     a.median_pass = (ctx->median_pass || ctx->ens_pass) ? 1 : 0;
     a.ens_pass = ctx->ens_pass ? 1 : 0;
+    a.elbm = ctx->elbm ? 1 : 0;
     a.budget = ctx->budget ? 1 : 0;
     a.fused = ctx->act.fused ? 1 : 0;
     a.rows = ctx->d_rows();
@@ -724,7 +743,11 @@ int autotune(lbm_ctx* ctx, const lbm_run_desc* run, bool fused_alt = false)
     const bool second = ctx->median_pass || ctx->ens_pass;
     std::vector<int> heights;
     if (run->tile_h > 0) heights = {run->tile_h};
-    else if (second) heights = {16, 32, 64};
+    else if (second)
+        for (int h : {kMinTuneH, 32, kMaxTileH}) {
+            if (h < kMaxTileH && h >= ctx->cap_h) continue;   // the same tiles as the next
+            heights.push_back(h);
+        }
     else heights = {kMaxTileH};
     std::vector<Shape> cand;
     if (fused_alt) {
@@ -940,11 +963,12 @@ int read_stats(lbm_ctx* ctx, int32_t d, lbm_entropy_stats_t* out)
 // Layout of lbm_step_static's arrays in the static scratch array: one
 // domain, tight planes (plane = nx ny), no record planes, no probe.
 struct StaticLayout {
-    size_t off_dom = 0, off_tiles = 0, off_rows = 0, off_partials = 0, off_rowpart = 0, off_counter = 0, total = 0;
-    int ntiles = 0, nblocks = 0, nparts = 0;
+    size_t off_dom = 0, off_tiles = 0, off_groups = 0, off_rows = 0, off_partials = 0, off_rowpart = 0,
+           off_counter = 0, total = 0;
+    int th = 0, ntiles = 0, ngroups = 0, nblocks = 0, nparts = 0;
 };
 
-void plan_static(const lbm_domain_desc& d, int storage, DomainHost& h, StaticLayout& L)
+void plan_static(const lbm_domain_desc& d, int storage, int th, DomainHost& h, StaticLayout& L)
 {
     h.d = d;
     h.d.rho_init = h.d.u_init = h.d.f_init = nullptr;
@@ -952,14 +976,16 @@ void plan_static(const lbm_domain_desc& d, int storage, DomainHost& h, StaticLay
     h.n = size_t(d.nx) * d.ny;
     h.plane = (long long)h.n;
     h.shift = storage == LBM_F64 ? 0.0 : d.rho0;
-    // tiles of kMaxTileH rows, which are also the stats groups; narrow row blocks
-    L.ntiles = tiles_of(d.lattice, d.nx, d.ny, kMaxTileH);
+    // second-pass tiles of th rows, stats groups of kMaxTileH; narrow row blocks
+    L.th = th;
+    L.ntiles = tiles_of(d.lattice, d.nx, d.ny, th);
+    L.ngroups = tiles_of(d.lattice, d.nx, d.ny, kMaxTileH);
     L.nblocks = d.lattice == LBM_D2Q9 ? blocks_of(d.nx, d.ny, seg_width(d.nx, 1)) : 0;
     L.nparts = d.lattice == LBM_D2Q9 ? strips_of(d.nx) * d.ny : 0;
     h.tile_first = 0;
     h.tile_count = L.ntiles;
     h.group_first = 0;
-    h.group_count = L.ntiles;
+    h.group_count = L.ngroups;
     h.row_first = 0;
     h.row_count = L.nparts;
     size_t off = 0;
@@ -967,6 +993,12 @@ void plan_static(const lbm_domain_desc& d, int storage, DomainHost& h, StaticLay
     off = align_up(off + sizeof(DomainDev), kAlign);
     L.off_tiles = off;
     off = align_up(off + size_t(L.ntiles) * sizeof(Tile), kAlign);
+    // tiles of kMaxTileH rows are the stats groups themselves
+    L.off_groups = L.off_tiles;
+    if (L.ntiles != L.ngroups) {
+        L.off_groups = off;
+        off = align_up(off + size_t(L.ngroups) * sizeof(Tile), kAlign);
+    }
     L.off_rows = off;
     off = align_up(off + size_t(L.nblocks) * sizeof(RowBlock), kAlign);
     L.off_partials = off;
@@ -1055,6 +1087,7 @@ int lbm_create(const lbm_domain_desc* domains, int32_t n_domains, const lbm_run_
         ctx->ens_pass = ctx->ens_pass || deferred(h.d);
         ctx->budget = ctx->budget || (h.d.limiter & kLimEnsBudget) || is_topk(h.d);
     }
+    ctx->cap_h = second_height(domains, n_domains, kMaxTileH);
     ctx->fuse_ok = ctx->lattice == LBM_D2Q9 && !ctx->elbm && ctx->median_pass && !ctx->ens_pass;
 
     auto bail = [&](int code) {
@@ -1398,7 +1431,9 @@ int lbm_step_static(const lbm_domain_desc* domain, int32_t storage, void* stream
         return fail(nullptr, LBM_EINVAL, "no probe trace without a context (probe_x, probe_y must be -1)");
     DomainHost h;
     StaticLayout L;
-    plan_static(*domain, storage, h, L);
+    plan_static(*domain, storage, second_height(domain, 1, kMaxTileH), h, L);
+    // shorter tiles have more partials: never at the price of refusing a domain
+    if (L.total > kStaticScratchBytes) plan_static(*domain, storage, kMaxTileH, h, L);
     if (L.total > kStaticScratchBytes)
         return fail(nullptr, LBM_ENOMEM,
                     "lbm_step_static: the domain needs " + std::to_string(L.total) +
@@ -1416,7 +1451,9 @@ int lbm_step_static(const lbm_domain_desc* domain, int32_t storage, void* stream
     Tile* tiles = reinterpret_cast<Tile*>(base + L.off_tiles);
     RowBlock* rows = reinterpret_cast<RowBlock*>(base + L.off_rows);
     long long* counter = reinterpret_cast<long long*>(base + L.off_counter);
-    e = launch_static_setup(dd, domain->lattice, dom, tiles, L.ntiles, rows, L.nblocks, counter, s);
+    Tile* groups = reinterpret_cast<Tile*>(base + L.off_groups);
+    e = launch_static_setup(dd, domain->lattice, dom, tiles, L.ntiles, L.th, groups, L.ngroups, rows, L.nblocks, counter,
+                            s);
     if (e != hipSuccess) return fail(nullptr, LBM_EDEVICE, std::string("static setup: ") + hipGetErrorString(e));
     StepKind k;
     k.storage = storage;
@@ -1438,11 +1475,12 @@ int lbm_step_static(const lbm_domain_desc* domain, int32_t storage, void* stream
     a.partials = reinterpret_cast<double*>(base + L.off_partials);
     a.median_pass = (k.median_pass || k.ens_pass) ? 1 : 0;
     a.ens_pass = k.ens_pass ? 1 : 0;
+    a.elbm = k.elbm ? 1 : 0;
     a.budget = k.budget ? 1 : 0;
     a.rows = rows;
     a.nrows = L.nblocks;
-    a.groups = tiles;
-    a.ngroups = L.ntiles;
+    a.groups = groups;
+    a.ngroups = L.ngroups;
     a.pstride = L.ntiles;
     a.rowpart = reinterpret_cast<double*>(base + L.off_rowpart);
     a.counter = counter;

@@ -216,6 +216,7 @@ struct StepArgs {
     int fused = 0;          // 1: the fused step kernel runs alone over `tiles` (fused tiles)
                             // and writes every partial to set 1
     int ens_pass;           // 1 if some domain has an ensemble-dependent limiter
+    int elbm;               // 1 with ELBM collisions (all domains)
     int budget;             // 1 if some domain has the budget threshold
     const RowBlock* rows;   // D2Q9 row blocks in row-major order, one per collision workgroup
     int nrows;              // the D2Q9 collision grid has nrows blocks
@@ -229,8 +230,9 @@ struct StepArgs {
 constexpr size_t kStaticScratchBytes = LBM_STATIC_SCRATCH_BYTES;
 // its address on `device` (looked up once per device; `device` must be current)
 hipError_t static_scratch(int device, char** ptr);
-hipError_t launch_static_setup(const DomainDev& dd, int lattice, DomainDev* dom, Tile* tiles, int ntiles,
-                               RowBlock* rows, int nrows, long long* counter, hipStream_t s);
+hipError_t launch_static_setup(const DomainDev& dd, int lattice, DomainDev* dom, Tile* tiles, int ntiles, int th,
+                               Tile* groups, int ngroups, RowBlock* rows, int nrows, long long* counter,
+                               hipStream_t s);
 hipError_t launch_static_stats(const DomainDev* dom, double shift_mass, double* out, hipStream_t s);
 
 // Launchers (one per storage type / lattice), defined in the .hip files.

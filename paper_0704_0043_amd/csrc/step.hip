@@ -388,17 +388,14 @@ __global__ void __launch_bounds__(kThreads) k_collide2d(StepArgs a)
 
 // Second pass: median filter (Sec. 3.5; cavity stencils of Sec. 4.4) on the
 // Delta S' plane written by the collision kernel, and the ensemble-dependent
-// limiters.  Each thread walks down its column in chunks of kMedChunk rows:
-// the loads of a whole chunk (one per row; the neighbouring columns come from
-// the adjacent lanes) are issued together, then the decisions of the chunk
-// are taken from registers, row by row, and last the chunk's moved nodes are
-// rescaled with the loads of their stored states in flight together.  A node
-// rescaled on the spot would make every row of a wave wait for its loads and
-// for the acknowledgement of the previous row's stores; short chunks keep the
-// window and the deferred states in few enough registers for four waves per
-// SIMD.
+// limiters.  A wave walks down 64 adjacent columns in chunks of kMedChunk rows
+// (the loads of a chunk, one per row, are issued together; the neighbouring
+// columns come from the adjacent lanes), decides which nodes move and lists
+// them in LDS; after kListRows rows the listed nodes are moved, 64 at a time,
+// with every lane busy and all their loads in flight together.
 constexpr int kMedChunk = 4;
-constexpr int kPipe = 4;     // moved rows whose stored states are loaded together
+constexpr int kListRows = 8;                      // rows decided before their moved nodes are moved
+constexpr int kListCap = kListRows * kWave;
 
 // the filter's threshold and decision for a node with Delta S' = dc whose
 // stencil median is med (FLOOR or GATE reading of the tolerance delta)
@@ -439,70 +436,146 @@ __device__ __forceinline__ bool median_hit(const DD& D, int x, int y, int nx, in
     return median_decide(D, c[1], med, thr);
 }
 
-// A node the second pass moves further with the exact Delta S: rescale the
-// limited state that the collision kernel stored at it toward its f*, rebuilt
-// from the state's own moments (the limiter kept them): f* + r (f_stored - f*),
-// r = pq / pt (the new factor over the applied one).  With the exact homothety
-// the stored state's deviation e = pt x is scaled to the target directly, and
-// a direct factor is taken relative to f' = f* + e / pt.  Returns the change of
-// the limiter's entropy production (Delta S of the stored state minus Delta S
-// of the new one).  A real call: its root solves would otherwise be inlined
-// into every unrolled row of the median walk, and the walk's window would no
-// longer fit in registers.  (The quadratic form rescales after each chunk's
-// decisions, in the walk itself.)
-template <class T, int QE>
-__device__ __attribute__((noinline)) typename Store<T>::A rescale_stored_exact(
-    gptr<T> buf, long long plane, long long rc, unsigned own, typename Store<T>::A shift, typename Store<T>::A pq,
-    typename Store<T>::A pt, typename Store<T>::A tgt, typename Store<T>::A fac, typename Store<T>::A dc, bool exact)
+// Free flight into a fluid node whose row differs between the lanes of a wave
+// (a fluid node of the cavity has all its sources inside): one 32-bit lane
+// offset per population on a scalar base (Q nx ny < 2^31 elements, so a
+// plane's bytes fit 32 bits).
+template <int BC, class T>
+__device__ __forceinline__ void gather_node(gptr<const T> src, long long plane, int nx, int ny, int x, int y,
+                                            typename Store<T>::A (&g)[9])
+{
+    using L = Lat<kD2Q9>;
+    constexpr unsigned es = sizeof(T);
+    int xm = x - 1, xp = x + 1, ym = y - 1, yp = y + 1;
+    if constexpr (BC == kPeriodic) {
+        xm = x == 0 ? nx - 1 : xm;
+        xp = x == nx - 1 ? 0 : xp;
+        ym = y == 0 ? ny - 1 : ym;
+        yp = y == ny - 1 ? 0 : yp;
+    }
+    const unsigned r0 = unsigned(y) * unsigned(nx), rm = unsigned(ym) * unsigned(nx), rp = unsigned(yp) * unsigned(nx);
+#pragma unroll
+    for (int i = 0; i < 9; ++i) {
+        const unsigned rs = L::vy(i) > 0 ? rm : (L::vy(i) < 0 ? rp : r0);
+        const unsigned cs = unsigned(L::vx(i) > 0 ? xm : (L::vx(i) < 0 ? xp : x));
+        g[i] = Store<T>::ld(at_bytes(src + i * plane, es * (rs + cs)));
+    }
+}
+
+// One node the second pass moves, after LBGK collisions: its limited state is
+// formed anew from the populations that arrived (the buffer the step reads
+// still holds them), f* - phi c d with phi the smallest of its factors, as the
+// fused step forms it.  Returns the limiter's entropy production beyond what
+// the collision kernel counted for it.
+template <class T, int QE, int DS, int BC, class DD>
+__device__ __forceinline__ double form_node(const DD& D, gptr<const T> src, gptr<T> dst, long long plane, int x, int y,
+                                            typename Store<T>::A dc, typename Store<T>::A tgt,
+                                            typename Store<T>::A fac)
 {
     using A = typename Store<T>::A;
     constexpr int Q = 9;
+    const A inf = A(__builtin_huge_val());
+    const A shift = A(D.shift), c = A(D.c);
+    A g[Q];
+    gather_node<BC>(src, plane, D.nx, D.ny, x, y, g);
+    unsigned tmask = 0;
+    A pt = trim_phi(D, dc, tmask);     // the factor the collision kernel applied
+    SiteState<kD2Q9, A> S;
+    A dr, jx, jy, rho, ux, uy;
+    moments_equilibrium<kD2Q9, QE>(g, shift, dr, jx, jy, rho, ux, uy, S.gs);
+#pragma unroll
+    for (int i = 0; i < Q; ++i) S.d[i] = g[i] - S.gs[i];
+    S.dpost = dc;
+    S.c = c;
+    S.posrule = false;
+    A phi = pt;
+    bool done = false;
+    if constexpr (DS == kExact) {
+        if (D.homothety && isfinite(dc)) {
+            // targets reached exactly (Sec. 3.6); the smallest one decides
+            const bool hom = (tmask & kMaskTrim) && !D.trim_mode;
+            if (hom) pt = exact_homothety_call(S, shift, A(D.delta_trim));
+            phi = fmin(pt, fac);
+            if (tgt < inf && !(hom && tgt >= A(D.delta_trim))) phi = fmin(phi, exact_homothety_call(S, shift, tgt));
+            done = true;
+        }
+    }
+    if (!done) phi = fmin(pt, fmin(fac, tgt < inf ? sqrt_(tgt * rcp(dc)) : A(1)));
+    const A k = phi * c;
+    const unsigned own = unsigned(sizeof(T)) * (unsigned(y) * unsigned(D.nx) + unsigned(x));
+#pragma unroll
+    for (int i = 0; i < Q; ++i) Store<T>::st(at_bytes(dst + i * plane, own), S.gs[i] - k * S.d[i]);
+    if (!isfinite(dc)) return 0.0;
+    if constexpr (DS == kQuad) return double(dc * (pt * pt - phi * phi));
+    const A before = pt < A(1) ? delta_s_scaled<kD2Q9, DS>(S, shift, c, pt) : dc;
+    return double(before - delta_s_scaled<kD2Q9, DS>(S, shift, c, phi));
+}
+
+// The same after ELBM collisions, whose f' - f* = -(alpha beta - 1) d would
+// need the node's entropy root again: the limited state that the collision
+// kernel stored is rescaled toward its f*, rebuilt from the state's own
+// moments (the limiter kept them): f* + r (f_stored - f*), r = pq / pt (the new
+// factor over the applied one).  With the exact homothety the stored state's
+// deviation e = pt x is scaled to the target directly, and a direct factor is
+// taken relative to f' = f* + e / pt.
+template <class T, int QE, int DS, class DD>
+__device__ __forceinline__ double rescale_node(const DD& D, gptr<T> buf, long long plane, int x, int y,
+                                               typename Store<T>::A dc, typename Store<T>::A tgt,
+                                               typename Store<T>::A fac)
+{
+    using A = typename Store<T>::A;
+    constexpr int Q = 9;
+    const A inf = A(__builtin_huge_val());
+    const A shift = A(D.shift);
     const gptr<const T> lsrc = buf;
+    const unsigned own = unsigned(sizeof(T)) * (unsigned(y) * unsigned(D.nx) + unsigned(x));
     A gl[Q], gs[Q];
 #pragma unroll
-    for (int i = 0; i < Q; ++i) gl[i] = Store<T>::ld(at_bytes(lsrc + (i * plane + rc), own));
+    for (int i = 0; i < Q; ++i) gl[i] = Store<T>::ld(at_bytes(lsrc + i * plane, own));
     A dr, jx, jy, rho, ux, uy;
     moments_equilibrium<kD2Q9, QE>(gl, shift, dr, jx, jy, rho, ux, uy, gs);
-    A r = pq * rcp(pt);
-    // deviation of the stored state
+    unsigned tmask = 0;
+    const A pt = trim_phi(D, dc, tmask);
+    A r = fmin(fac, tgt < inf ? sqrt_(tgt * rcp(dc)) : A(1)) * rcp(pt);
     A fs[Q], e[Q];
-#pragma unroll
-    for (int i = 0; i < Q; ++i) {
-        fs[i] = A(Lat<kD2Q9>::w(i)) * shift + gs[i];
-        e[i] = (gl[i] - gs[i]) * rcp(fs[i]);
-    }
-    if (exact) {
-        const A ds_s = kull_sum<false>(fs, e, A(1));
+    if constexpr (DS == kExact) {
         A emin = A(0);
 #pragma unroll
-        for (int i = 0; i < Q; ++i) emin = fmin(emin, e[i]);
-        r = A(1);
-        if (ds_s > A(0)) {
-            if (tgt < ds_s) r = kullback_scale<Q>(fs, e, tgt, sqrt_(tgt * rcp(ds_s)), A(0), A(1));
-            if (fac < A(1)) {
-                const A lmax = emin < A(0) ? A(-1) / emin : A(__builtin_huge_val());
-                const A lam = pt < A(1) ? kullback_scale<Q>(fs, e, dc, sqrt_(dc * rcp(ds_s)), A(1), lmax) : A(1);
-                r = fmin(r, fac * lam);
+        for (int i = 0; i < Q; ++i) {
+            fs[i] = A(Lat<kD2Q9>::w(i)) * shift + gs[i];
+            e[i] = (gl[i] - gs[i]) * rcp(fs[i]);
+            emin = fmin(emin, e[i]);
+        }
+        if (D.homothety && isfinite(dc)) {
+            const A ds_s = kull_sum<false>(fs, e, A(1));
+            r = A(1);
+            if (ds_s > A(0)) {
+                if (tgt < ds_s) r = kullback_scale<Q>(fs, e, tgt, sqrt_(tgt * rcp(ds_s)), A(0), A(1));
+                if (fac < A(1)) {
+                    const A lmax = emin < A(0) ? A(-1) / emin : inf;
+                    const A lam = pt < A(1) ? kullback_scale<Q>(fs, e, dc, sqrt_(dc * rcp(ds_s)), A(1), lmax) : A(1);
+                    r = fmin(r, fac * lam);
+                }
             }
         }
     }
-    A lim = A(0);
-    if (r < A(1)) {
+    if (!(r < A(1))) return 0.0;
 #pragma unroll
-        for (int i = 0; i < Q; ++i) Store<T>::st(at_bytes(buf + (i * plane + rc), own), gs[i] + r * (gl[i] - gs[i]));
-        if (isfinite(dc)) {
-            lim = kull_sum<false>(fs, e, A(1)) - kull_sum<false>(fs, e, r);
-        }
-    }
-    return lim;
+    for (int i = 0; i < Q; ++i) Store<T>::st(at_bytes(buf + i * plane, own), gs[i] + r * (gl[i] - gs[i]));
+    if (!isfinite(dc)) return 0.0;
+    if constexpr (DS == kQuad) return double(pt * pt * dc * (A(1) - r * r));
+    return double(kull_sum<false>(fs, e, A(1)) - kull_sum<false>(fs, e, r));
 }
 
-template <class T, int QE, int DS, int BC, bool ENS>
+template <class T, int QE, int DS, int BC, bool ENS, bool ELBM>
 __device__ __forceinline__ void second_pass2d(const StepArgs& a)
 {
     using A = typename Store<T>::A;
-    constexpr int Q = 9;
     __shared__ double red[4 * kNStat];
+    // nodes to move, per wave: row and lane, smallest homothety target and
+    // (ensemble limiters) smallest factor given as phi itself
+    __shared__ unsigned short list_id[kThreads / kWave][kListCap];
+    __shared__ A list_tgt[kThreads / kWave][kListCap], list_fac[ENS ? kThreads / kWave : 1][ENS ? kListCap : 1];
     const int tidx = tile_of_block(a, 0);
     const Tile t = a.tiles[tidx];
     const DomainDev& D = a.dom[t.domain];
@@ -515,7 +588,6 @@ __device__ __forceinline__ void second_pass2d(const StepArgs& a)
     }
     AccT<A, double> acc;
     const int nx = D.nx, ny = D.ny;
-    const int x = t.x0 + int(threadIdx.x);
     // rows y0-1 .. y1 are read; y1 <= ny, so one wrap keeps them in range
     auto row_of = [&](int y) -> int {
         if constexpr (BC == kPeriodic)
@@ -589,11 +661,17 @@ __device__ __forceinline__ void second_pass2d(const StepArgs& a)
         if (threadIdx.x < kNStat) partial_slot(a, 1, tidx)[threadIdx.x] = 0.0;
         return;
     }
-    if (x < t.x1) {
+    const int wave = int(threadIdx.x) >> 6;
+    const int lane = int(threadIdx.x) & (kWave - 1);
+    const int xw = t.x0 + wave * kWave;        // the wave's first column
+    if (xw < t.x1) {                           // uniform per wave
         const long long plane = D.plane;
         const gptr<const A> dsb = to_global<A>(static_cast<const void*>(D.dsbuf));
-        const A shift = A(D.shift);
+        const gptr<T> dst = to_global<T>(D.buf[1 - a.parity]);
         const bool record = a.flags & kFlagRecord;
+        // lanes past the tile's last column repeat it and decide nothing
+        const bool in = xw + lane < t.x1;
+        const int x = in ? xw + lane : t.x1 - 1;
         int xm, xp;
         if constexpr (BC == kPeriodic) {
             xm = x == 0 ? nx - 1 : x - 1;
@@ -610,7 +688,6 @@ __device__ __forceinline__ void second_pass2d(const StepArgs& a)
         // columns x -+ 1 come from the neighbouring lanes.  Only the first
         // lane of a wave and the lane at the right end of a wave or of the
         // tile load their outside neighbour themselves.
-        const int lane = int(threadIdx.x) & (kWave - 1);
         const bool own_l = lane == 0;
         const bool own_r = lane == kWave - 1 || x == t.x1 - 1;
         auto load_raw = [&](int y, A (&r)[3]) {
@@ -629,14 +706,14 @@ __device__ __forceinline__ void second_pass2d(const StepArgs& a)
                 if (own_l && !((sflag[slot_m][ry] >> wxm) & 1)) r[0] = A(0);
                 if (own_r && !((sflag[slot_p][ry] >> wxp) & 1)) r[2] = A(0);
             }
-            // every active lane takes part in the shifts (no branch around them)
+            // every lane takes part in the shifts (no branch around them)
             const A l = lane_shift<-1>(r[1]), rr = lane_shift<+1>(r[1]);
             r[0] = own_l ? r[0] : l;
             r[2] = own_r ? r[2] : rr;
         };
         // w[k] holds row yb - 1 + k of the current chunk; the rows of the next
-        // chunk are loaded into nw before the current chunk's rescale, so
-        // waiting for them does not wait for that rescale's stores
+        // chunk are loaded into nw before the current chunk's nodes are moved,
+        // so waiting for them does not wait for those stores
         A w[kMedChunk + 2][3], nw[kMedChunk][3];
 #pragma unroll
         for (int k = 0; k < kMedChunk + 2; ++k) w[k][0] = w[k][2] = A(0);
@@ -649,6 +726,8 @@ __device__ __forceinline__ void second_pass2d(const StepArgs& a)
 #pragma unroll
         for (int k = 0; k < kMedChunk; ++k)
             if (t.y0 + k + 1 <= t.y1) load_raw(t.y0 + k + 1, nw[k]);
+        int listed = 0;                // nodes in the wave's list (uniform)
+        int ylist = t.y0;              // row of its first entries
         for (int yb = t.y0; yb < t.y1; yb += kMedChunk) {
 #pragma unroll
             for (int k = 0; k < kMedChunk; ++k)
@@ -657,56 +736,46 @@ __device__ __forceinline__ void second_pass2d(const StepArgs& a)
                     for (int q = 0; q < 3; ++q) w[k + 2][q] = nw[k][q];
                     complete(yb + k + 1, w[k + 2]);
                 }
-            // decisions for the rows of the chunk in order; with the exact
-            // Delta S a moved node is rescaled on the spot by its lane (its
-            // root solves are a real call), with the quadratic one after the
-            // chunk
-            unsigned mv = 0;          // rows of the chunk this lane rescales afterwards
-            A rr[kMedChunk];          // their factor over the applied one
 #pragma unroll
             for (int k = 0; k < kMedChunk; ++k) {
                 const int y = yb + k;
+                if (y >= t.y1) break;
                 const A dc = w[k + 1][1];
-                auto fluid = [&] { return y < t.y1 && node_class<BC>(x, y, nx, ny) == kNodeFluid; };
+                const bool fluid = in && node_class<BC>(x, y, nx, ny) == kNodeFluid;
                 // smallest homothety target and smallest direct factor of the
                 // limiters that act on this node (relative to f')
                 A tgt = A(__builtin_huge_val()), fac = A(1), thr;
                 SecondHit h;
-                if ((D.limiter & kLimMedian) && fluid() && median_hit<BC>(D, x, y, nx, ny, w[k], w[k + 1], w[k + 2], thr)) {
+                if ((D.limiter & kLimMedian) && fluid && median_hit<BC>(D, x, y, nx, ny, w[k], w[k + 1], w[k + 2], thr)) {
                     h.bits |= kMaskMedian;
                     tgt = thr;
                 }
                 if constexpr (ENS) {
-                    if ((D.limiter & kLimEns) && fluid()) ens_terms(D, ensv, dc, tgt, fac, h);
+                    if ((D.limiter & kLimEns) && fluid) ens_terms(D, ensv, dc, tgt, fac, h);
                 }
+                bool moves = false;
                 if (h.bits) {
                     if (h.bits & kMaskMedian) ++acc.filt;
                     acc.ens += h.ens;
                     acc.trim += h.trim;
-                    const long long rc = (long long)y * nx;
-                    if (record) to_global<unsigned char>(D.mask)[unsigned(rc) + unsigned(x)] |= (unsigned char)h.bits;
+                    if (record)
+                        to_global<unsigned char>(D.mask)[unsigned(y) * unsigned(nx) + unsigned(x)] |= (unsigned char)h.bits;
+                    // further than the collision kernel's trimming moved it;
+                    // the exact homothety decides by its roots
                     unsigned tmask = 0;
-                    // the factor the collision kernel applied (trimming)
                     const A pt = trim_phi(D, dc, tmask);
-                    const A pq = fmin(fac, tgt < A(__builtin_huge_val()) ? sqrt_(tgt * rcp(dc)) : A(1));
-                    bool exact = false;
-                    if constexpr (DS == kExact) exact = D.homothety && isfinite(dc);
-                    if constexpr (DS == kExact) {
-                        if (exact || pq < pt) {
-                            const gptr<T> buf = to_global<T>(D.buf[1 - a.parity]);
-                            const unsigned own = unsigned(sizeof(T)) * unsigned(x);
-                            acc.lim += rescale_stored_exact<T, QE>(buf, plane, rc, own, shift, pq, pt, tgt, fac, dc,
-                                                                   exact);
-                        }
-                    } else if (pq < pt) {
-                        // quadratic form: the factor is all the move needs
-                        // (the limiter's entropy production follows from it),
-                        // and the rescale is done after the chunk's decisions
-                        mv |= 1u << k;
-                        rr[k] = pq * rcp(pt);
-                        if (isfinite(dc)) acc.lim += pt * pt * dc * (A(1) - rr[k] * rr[k]);
-                    }
+                    moves = fmin(fac, tgt < A(__builtin_huge_val()) ? sqrt_(tgt * rcp(dc)) : A(1)) < pt;
+                    if constexpr (DS == kExact) moves = moves || (D.homothety && isfinite(dc) && pt > A(0));
                 }
+                const unsigned long long b = __ballot(moves);
+                if (moves) {
+                    const int at = listed + int(__builtin_amdgcn_mbcnt_hi(unsigned(b >> 32),
+                                                                        __builtin_amdgcn_mbcnt_lo(unsigned(b), 0)));
+                    list_id[wave][at] = (unsigned short)((y - ylist) * kWave + lane);
+                    list_tgt[wave][at] = tgt;
+                    if constexpr (ENS) list_fac[wave][at] = fac;
+                }
+                listed += __popcll(b);
             }
             {
                 const int yn = yb + kMedChunk;
@@ -714,60 +783,49 @@ __device__ __forceinline__ void second_pass2d(const StepArgs& a)
                 for (int k = 0; k < kMedChunk; ++k)
                     if (yn < t.y1 && yn + k + 1 <= t.y1) load_raw(yn + k + 1, nw[k]);
             }
-            if constexpr (DS != kExact) {
-                // rescale the chunk's moved nodes kPipe rows at a time: the
-                // loads of those rows are in flight together
-                if (mv) {
-                    const gptr<T> buf = to_global<T>(D.buf[1 - a.parity]);
-                    const gptr<const T> lsrc = buf;
-                    const unsigned own = unsigned(sizeof(T)) * unsigned(x);
-#pragma unroll
-                    for (int k0 = 0; k0 < kMedChunk; k0 += kPipe) {
-                        A gl[kPipe][Q];
-#pragma unroll
-                        for (int u = 0; u < kPipe; ++u)
-                            if ((mv >> (k0 + u)) & 1u) {
-                                const long long rc = (long long)(yb + k0 + u) * nx;
-#pragma unroll
-                                for (int i = 0; i < Q; ++i)
-                                    gl[u][i] = Store<T>::ld(at_bytes(lsrc + (i * plane + rc), own));
-                            }
-#pragma unroll
-                        for (int u = 0; u < kPipe; ++u)
-                            if ((mv >> (k0 + u)) & 1u) {
-                                const long long rc = (long long)(yb + k0 + u) * nx;
-                                A gs[Q], dr, jx, jy, rho, ux, uy;
-                                moments_equilibrium<kD2Q9, QE>(gl[u], shift, dr, jx, jy, rho, ux, uy, gs);
-                                const A r = rr[k0 + u];
-#pragma unroll
-                                for (int i = 0; i < Q; ++i)
-                                    Store<T>::st(at_bytes(buf + (i * plane + rc), own), gs[i] + r * (gl[u][i] - gs[i]));
-                            }
-                    }
-                }
-            }
 #pragma unroll
             for (int q = 0; q < 3; ++q) {
                 w[0][q] = w[kMedChunk][q];
                 w[1][q] = w[kMedChunk + 1][q];
             }
+            if (yb + kMedChunk - ylist < kListRows && yb + kMedChunk < t.y1) continue;
+            // the list is the wave's own: its LDS accesses stay in order
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+            for (int e = lane; e < listed; e += kWave) {
+                const int id = list_id[wave][e];
+                const int xn = xw + (id & (kWave - 1)), yn = ylist + (id >> 6);
+                const A tgt = list_tgt[wave][e];
+                A fac = A(1);
+                if constexpr (ENS) fac = list_fac[wave][e];
+                const A dc = Store<A>::ld(dsb + (unsigned(yn) * unsigned(nx) + unsigned(xn)));
+                if constexpr (ELBM)
+                    acc.lim += rescale_node<T, QE, DS>(D, dst, plane, xn, yn, dc, tgt, fac);
+                else
+                    acc.lim += form_node<T, QE, DS, BC>(D, to_global<T>(static_cast<const void*>(D.buf[a.parity])), dst,
+                                                        plane, xn, yn, dc, tgt, fac);
+            }
+            __builtin_amdgcn_wave_barrier();
+            listed = 0;
+            ylist = yb + kMedChunk;
         }
     }
     store_partial(acc, partial_slot(a, 1, tidx), red);
 }
 
 // the second D2Q9 pass without and with ensemble-dependent limiters (the
-// latter needs more registers)
-template <class T, int QE, int DS, int BC>
+// latter needs more registers), after LBGK and after ELBM collisions
+template <class T, int QE, int DS, int BC, bool ELBM = false>
 __global__ void __launch_bounds__(kThreads) k_median2d(StepArgs a)
 {
-    second_pass2d<T, QE, DS, BC, false>(a);
+    second_pass2d<T, QE, DS, BC, false, ELBM>(a);
 }
 
-template <class T, int QE, int DS, int BC>
+template <class T, int QE, int DS, int BC, bool ELBM = false>
 __global__ void __launch_bounds__(kThreads) k_median_ens2d(StepArgs a)
 {
-    second_pass2d<T, QE, DS, BC, true>(a);
+    second_pass2d<T, QE, DS, BC, true, ELBM>(a);
 }
 
 // The domain fields the fused step reads in its row loop.
@@ -1275,6 +1333,10 @@ hipError_t LBM_CAT(launch_step2d, LBM_SUFFIX)(int qe, int ds, int bc, const Step
         LBM_DISPATCH_ELBM(k_collide2d, 0, 1, dim3(a.nrows), dim3(kThreads), 0, s, a);
     else if (kernel == 3)
         LBM_DISPATCH(k_fused2d, 0, 1, dim3(a.ntiles), dim3(kThreads), 0, s, a);
+    else if (a.elbm && a.ens_pass)
+        LBM_DISPATCH_ELBM(k_median_ens2d, 0, 1, dim3(a.ntiles), dim3(kThreads), 0, s, a);
+    else if (a.elbm)
+        LBM_DISPATCH_ELBM(k_median2d, 0, 1, dim3(a.ntiles), dim3(kThreads), 0, s, a);
     else if (a.ens_pass)
         LBM_DISPATCH(k_median_ens2d, 0, 1, dim3(a.ntiles), dim3(kThreads), 0, s, a);
     else
