@@ -36,10 +36,11 @@ hipError_t launch_step1d(int storage, int qe, int ds, int bc, const StepArgs& a,
     return hipErrorInvalidValue;
 }
 
-__global__ void k_finalize(StepArgs a, int parity_done, long long step)
+// one workgroup per domain: the sums of the step just run
+__global__ void __launch_bounds__(kThreads) k_finalize(StepArgs a, int parity_done, long long step)
 {
-    __shared__ double red[4 * kNStat];
-    reduce_partials(a, parity_done, step, red);
+    __shared__ double red[kThreads];
+    reduce_domain(a, parity_done, a.dom[blockIdx.x], a.median_pass, step, red);
 }
 
 // D2Q9: the set-0 partial of each group (kMaxTileH rows of one strip) is the
@@ -63,46 +64,43 @@ __global__ void __launch_bounds__(kThreads) k_tile_rows(StepArgs a, int parity_d
 // reported mean_dS bit for bit.
 __global__ void __launch_bounds__(kThreads) k_ens_prepare(StepArgs a, int parity)
 {
-    __shared__ double red[4 * kNStat];
-    StepArgs b = a;
-    b.median_pass = 0;
-    reduce_partials(b, parity, a.counter[parity], red);
+    __shared__ double red[kThreads];
+    const DomainDev& D = a.dom[blockIdx.x];
+    if (!(D.limiter & kLimEns)) return;
+    reduce_domain(a, parity, D, false, a.counter[parity], red);
     __syncthreads();
-    for (int d = threadIdx.x; d < a.ndomains; d += blockDim.x) {
-        const DomainDev& D = a.dom[d];
-        if (!(D.limiter & kLimEns)) continue;
-        const double nf = D.stats[kSFluid];
-        const double mean = nf > 0.0 ? D.stats[kSDpost] / nf : 0.0;
-        D.ens[kEMean] = mean;
-        D.ens[kEThresh] = fmax(D.ens_c * mean, D.delta_ens);
-        D.ens[kESmoothA] = mean > 0.0 ? D.delta_ens / pow(mean, D.ens_k) : 0.0;
-        if (D.limiter & kLimEnsBudget) {
-            // eq. (EntThresh): the limiter may produce delta_0 times the
-            // entropy production of the LBGK step, [1 - (2 beta - 1)^2] sum Delta S
-            BudgetState& b = *D.bstate;
-            const double budget = D.ens_c * (1.0 - D.c * D.c) * D.stats[kSDpost];
-            b.prefix = 0;
-            b.budget = budget;
-            b.s_above = 0.0;
-            b.c_above = 0.0;
-            b.level = 0;
-            b.done = budget > 0.0 ? 0 : 1;
-            // no budget: the threshold sits at the largest value, nothing moves
-            D.ens[kEBudget] = fmax(budget > 0.0 ? 0.0 : D.stats[kSMax], D.delta_ens);
-        }
-        if (D.limiter & kLimTopK) {
-            // top-k trimming (Sec. 3.2): the k-th largest finite Delta S' by the
-            // same radix selection, counts only; -inf (every node above
-            // delta) until found
-            BudgetState& b = *D.bstate;
-            b.prefix = 0;
-            b.budget = double(D.top_k);
-            b.s_above = 0.0;
-            b.c_above = 0.0;
-            b.level = 0;
-            b.done = 0;
-            D.ens[kETopk] = -__builtin_huge_val();
-        }
+    if (threadIdx.x != 0) return;
+    const double nf = D.stats[kSFluid];
+    const double mean = nf > 0.0 ? D.stats[kSDpost] / nf : 0.0;
+    D.ens[kEMean] = mean;
+    D.ens[kEThresh] = fmax(D.ens_c * mean, D.delta_ens);
+    D.ens[kESmoothA] = mean > 0.0 ? D.delta_ens / pow(mean, D.ens_k) : 0.0;
+    if (D.limiter & kLimEnsBudget) {
+        // eq. (EntThresh): the limiter may produce delta_0 times the
+        // entropy production of the LBGK step, [1 - (2 beta - 1)^2] sum Delta S
+        BudgetState& b = *D.bstate;
+        const double budget = D.ens_c * (1.0 - D.c * D.c) * D.stats[kSDpost];
+        b.prefix = 0;
+        b.budget = budget;
+        b.s_above = 0.0;
+        b.c_above = 0.0;
+        b.level = 0;
+        b.done = budget > 0.0 ? 0 : 1;
+        // no budget: the threshold sits at the largest value, nothing moves
+        D.ens[kEBudget] = fmax(budget > 0.0 ? 0.0 : D.stats[kSMax], D.delta_ens);
+    }
+    if (D.limiter & kLimTopK) {
+        // top-k trimming (Sec. 3.2): the k-th largest finite Delta S' by the
+        // same radix selection, counts only; -inf (every node above
+        // delta) until found
+        BudgetState& b = *D.bstate;
+        b.prefix = 0;
+        b.budget = double(D.top_k);
+        b.s_above = 0.0;
+        b.c_above = 0.0;
+        b.level = 0;
+        b.done = 0;
+        D.ens[kETopk] = -__builtin_huge_val();
     }
 }
 
@@ -146,7 +144,8 @@ __device__ inline int key_exponent(typename K::U k)
 // (count and exact significand sum per bucket) of the values whose higher
 // digits match the prefix, added into the domain's histogram.  Each thread
 // walks one column of the tile and merges runs of equal buckets in registers
-// first (at most kMaxTileH values: the significand sum stays below 2^59).
+// first (at most kMaxTileH values: the significand sum stays below 2^59; a
+// wave's sum stays below 2^64 for any FP32 tile and FP64 tiles of 32 rows).
 template <class A, bool CAV>
 __global__ void __launch_bounds__(kThreads) k_budget_hist(StepArgs a, int level)
 {
@@ -173,11 +172,30 @@ __global__ void __launch_bounds__(kThreads) k_budget_hist(StepArgs a, int level)
         const unsigned long long old = atomicAdd(&hlo[b], sum);
         if (old + sum < old) atomicAdd(&hhi[b], 1u);
     };
+    // Neighbouring columns mostly hold values of one binary exponent: in the
+    // first level their 64 additions to one bucket would queue at one LDS
+    // address, so the lanes that share the first flushing lane's bucket are
+    // added up first.  Lanes take part with cnt = 0 when they have nothing.
+    auto flush_wave = [&](int b, unsigned cnt, unsigned long long sum) {
+        const unsigned long long have = __ballot(cnt != 0);
+        if (!have) return;
+        const int lead = __shfl(b, __builtin_ctzll(have), kWave);
+        const bool same = cnt != 0 && b == lead;
+        unsigned c = same ? cnt : 0u;
+        unsigned long long v = same ? sum : 0ull;
+#pragma unroll
+        for (int off = kWave / 2; off >= 1; off >>= 1) {
+            c += __shfl_xor(c, off, kWave);
+            v += __shfl_xor(v, off, kWave);
+        }
+        if ((int(threadIdx.x) & (kWave - 1)) == 0) flush(lead, c, v);
+        if (cnt && !same) flush(b, cnt, sum);
+    };
+    int cur = -1;
+    unsigned cnt = 0;
+    unsigned long long sum = 0;
     if (x < t.x1) {
         const A* ds = static_cast<const A*>(D.dsbuf);
-        int cur = -1;
-        unsigned cnt = 0;
-        unsigned long long sum = 0;
         for (int y = t.y0; y < t.y1; ++y) {
             if (CAV && (x == 0 || x == D.nx - 1 || y == 0 || y == D.ny - 1)) continue;   // walls and lid
             const A d = ds[(long long)y * D.nx + x];
@@ -194,8 +212,9 @@ __global__ void __launch_bounds__(kThreads) k_budget_hist(StepArgs a, int level)
             ++cnt;
             sum += key_significand<K>(k);
         }
-        if (cnt) flush(cur, cnt, sum);
     }
+    if (level == 0 && (!K::dbl || t.y1 - t.y0 <= 32)) flush_wave(cur, cnt, sum);
+    else if (cnt) flush(cur, cnt, sum);
     __syncthreads();
     BudgetBucket* gh = D.bhist;
     for (int k = threadIdx.x; k < kBudgetBuckets; k += kThreads)
@@ -205,6 +224,37 @@ __global__ void __launch_bounds__(kThreads) k_budget_hist(StepArgs a, int level)
             const unsigned long long hiadd = (unsigned long long)hhi[k] + (old + hlo[k] < old ? 1ull : 0ull);
             if (hiadd) atomicAdd(&gh[k].hi, hiadd);
         }
+}
+
+// Exclusive sums over the threads above (tid + 1 .. kThreads - 1) of one or two
+// values per thread, plus a start value: a shuffle scan in each wave, then the
+// totals of the waves above.  (One thread adding 256 LDS values in turn took
+// 10 of the 15 us of a select launch.)
+template <int N>
+__device__ inline void sums_above(double (&v)[N], const double (&start)[N], double* lds /* [kThreads / kWave * N] */)
+{
+    const int lane = int(threadIdx.x) & (kWave - 1), wave = int(threadIdx.x) / kWave;
+    constexpr int nw = kThreads / kWave;
+    double own[N];
+#pragma unroll
+    for (int k = 0; k < N; ++k) own[k] = v[k];
+#pragma unroll
+    for (int off = 1; off < kWave; off <<= 1)
+#pragma unroll
+        for (int k = 0; k < N; ++k) {
+            const double o = __shfl_down(v[k], off, kWave);
+            if (lane + off < kWave) v[k] += o;
+        }
+    if (lane == 0)
+#pragma unroll
+        for (int k = 0; k < N; ++k) lds[wave * N + k] = v[k];
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < N; ++k) {
+        double s = start[k];
+        for (int w = nw - 1; w > wave; --w) s += lds[w * N + k];
+        v[k] = s + (v[k] - own[k]);
+    }
 }
 
 // One level of the budget selection, one workgroup per domain.  With
@@ -220,7 +270,7 @@ __global__ void __launch_bounds__(kThreads) k_budget_select(StepArgs a, int leve
     using K = BKey<A>;
     using U = typename K::U;
     constexpr int per = kBudgetBuckets / kThreads;
-    __shared__ double ts[kThreads], tc[kThreads];
+    __shared__ double waves[2 * kThreads / kWave];
     __shared__ int best;
     const DomainDev& D = a.dom[blockIdx.x];
     if (!(D.limiter & kLimEnsBudget)) return;
@@ -246,25 +296,13 @@ __global__ void __launch_bounds__(kThreads) k_budget_select(StepArgs a, int leve
         my_s += s[i];
         my_c += c[i];
     }
-    ts[tid] = my_s;
-    tc[tid] = my_c;
     if (tid == 0) best = -1;
-    __syncthreads();
-    if (tid == 0) {
-        // sums above each thread's buckets, from the top down
-        double rs = bs->s_above, rc = bs->c_above;
-        for (int k = kThreads - 1; k >= 0; --k) {
-            const double vs = ts[k], vc = tc[k];
-            ts[k] = rs;
-            tc[k] = rc;
-            rs += vs;
-            rc += vc;
-        }
-    }
-    __syncthreads();
+    double above[2] = {my_s, my_c};
+    const double start[2] = {bs->s_above, bs->c_above};
+    sums_above<2>(above, start, waves);
     const double budget = bs->budget;
     const int nb = 1 << w;   // buckets of this digit (the rest stay empty)
-    double S = ts[tid], C = tc[tid];
+    double S = above[0], C = above[1];
     double sa = 0.0, ca = 0.0, sa0 = 0.0, ca0 = 0.0;
     int mine = -1;
 #pragma unroll
@@ -327,7 +365,7 @@ __global__ void __launch_bounds__(kThreads) k_topk_select(StepArgs a, int level)
     using K = BKey<A>;
     using U = typename K::U;
     constexpr int per = kBudgetBuckets / kThreads;
-    __shared__ double tc[kThreads];
+    __shared__ double waves[kThreads / kWave];
     __shared__ int best;
     const DomainDev& D = a.dom[blockIdx.x];
     if (!(D.limiter & kLimTopK)) return;
@@ -349,20 +387,12 @@ __global__ void __launch_bounds__(kThreads) k_topk_select(StepArgs a, int level)
         gb.hi = 0;
         my_c += c[i];
     }
-    tc[tid] = my_c;
     if (tid == 0) best = -1;
-    __syncthreads();
-    if (tid == 0) {
-        double rc = bs->c_above;
-        for (int k = kThreads - 1; k >= 0; --k) {
-            const double v = tc[k];
-            tc[k] = rc;
-            rc += v;
-        }
-    }
-    __syncthreads();
+    double above[1] = {my_c};
+    const double start[1] = {bs->c_above};
+    sums_above<1>(above, start, waves);
     const double kk = bs->budget;
-    double C = tc[tid], ca = 0.0, ca0 = 0.0;
+    double C = above[0], ca = 0.0, ca0 = 0.0;
     int mine = -1;
 #pragma unroll
     for (int i = per - 1; i >= 0; --i) {
@@ -398,29 +428,27 @@ __global__ void __launch_bounds__(kThreads) k_topk_select(StepArgs a, int level)
     }
 }
 
-hipError_t launch_budget(int storage, int bc, const StepArgs& a, hipStream_t s)
+template <class A>
+static hipError_t budget_levels_t(int bc, const StepArgs& a, hipStream_t s)
 {
-    const bool dbl = storage == kF64;
-    for (int level = 0; level < budget_levels(dbl); ++level) {
-        if (dbl) {
-            if (bc == kCavity)
-                hipLaunchKernelGGL((k_budget_hist<double, true>), dim3(a.ntiles), dim3(kThreads), 0, s, a, level);
-            else
-                hipLaunchKernelGGL((k_budget_hist<double, false>), dim3(a.ntiles), dim3(kThreads), 0, s, a, level);
-            hipLaunchKernelGGL(k_budget_select<double>, dim3(a.ndomains), dim3(kThreads), 0, s, a, level);
-            hipLaunchKernelGGL(k_topk_select<double>, dim3(a.ndomains), dim3(kThreads), 0, s, a, level);
-        } else {
-            if (bc == kCavity)
-                hipLaunchKernelGGL((k_budget_hist<float, true>), dim3(a.ntiles), dim3(kThreads), 0, s, a, level);
-            else
-                hipLaunchKernelGGL((k_budget_hist<float, false>), dim3(a.ntiles), dim3(kThreads), 0, s, a, level);
-            hipLaunchKernelGGL(k_budget_select<float>, dim3(a.ndomains), dim3(kThreads), 0, s, a, level);
-            hipLaunchKernelGGL(k_topk_select<float>, dim3(a.ndomains), dim3(kThreads), 0, s, a, level);
-        }
+    for (int level = 0; level < budget_levels(sizeof(A) == 8); ++level) {
+        if (bc == kCavity)
+            hipLaunchKernelGGL((k_budget_hist<A, true>), dim3(a.ntiles), dim3(kThreads), 0, s, a, level);
+        else
+            hipLaunchKernelGGL((k_budget_hist<A, false>), dim3(a.ntiles), dim3(kThreads), 0, s, a, level);
+        if (a.budget & kSelectBudget)
+            hipLaunchKernelGGL(k_budget_select<A>, dim3(a.ndomains), dim3(kThreads), 0, s, a, level);
+        if (a.budget & kSelectTopK)
+            hipLaunchKernelGGL(k_topk_select<A>, dim3(a.ndomains), dim3(kThreads), 0, s, a, level);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
     return hipSuccess;
+}
+
+hipError_t launch_budget(int storage, int bc, const StepArgs& a, hipStream_t s)
+{
+    return storage == kF64 ? budget_levels_t<double>(bc, a, s) : budget_levels_t<float>(bc, a, s);
 }
 
 hipError_t launch_ens_prepare(const StepArgs& a, hipStream_t s)
@@ -430,7 +458,7 @@ hipError_t launch_ens_prepare(const StepArgs& a, hipStream_t s)
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
-    hipLaunchKernelGGL(k_ens_prepare, dim3(1), dim3(kThreads), 0, s, a, a.parity);
+    hipLaunchKernelGGL(k_ens_prepare, dim3(a.ndomains), dim3(kThreads), 0, s, a, a.parity);
     return hipGetLastError();
 }
 
@@ -441,7 +469,7 @@ hipError_t launch_finalize(const StepArgs& a, int parity_done, long long steps_d
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
-    hipLaunchKernelGGL(k_finalize, dim3(1), dim3(kThreads), 0, s, a, parity_done, steps_done);
+    hipLaunchKernelGGL(k_finalize, dim3(a.ndomains), dim3(kThreads), 0, s, a, parity_done, steps_done);
     return hipGetLastError();
 }
 

@@ -42,6 +42,12 @@ bool is_topk(const lbm_domain_desc& d) { return (d.limiter & LBM_LIM_TRIM) && d.
 // limiters that need the whole domain's Delta S' before any node is limited
 bool deferred(const lbm_domain_desc& d) { return (d.limiter & kLimEns) || is_topk(d); }
 
+// the radix selections a domain's step runs
+int selections(const lbm_domain_desc& d)
+{
+    return ((d.limiter & kLimEnsBudget) ? kSelectBudget : 0) | (is_topk(d) ? kSelectTopK : 0);
+}
+
 // the fused step applies: D2Q9 LBGK domains, the median filter in some, no
 // ensemble-dependent limiter (nor top-k trimming) in any
 bool fusable(const lbm_domain_desc* doms, int32_t nd)
@@ -133,7 +139,7 @@ struct lbm_ctx {
     bool median_pass = false;   // D2Q9 with the median filter in some domain
     bool ens_pass = false;      // an ensemble-dependent limiter in some domain
     bool fuse_ok = false;       // the fused step applies (D2Q9 LBGK, median filter, no ensemble limiter)
-    bool budget = false;        // the budget threshold in some domain
+    int budget = 0;             // kSelect* bits: budget threshold, top-k trimming in some domain
     bool elbm = false;          // ELBM collisions (all domains)
     long long steps_done = 0, finalized_for = -1;
     // captured step sequences, for each starting parity: graph_chunk steps
@@ -568,7 +574,7 @@ StepArgs step_args(const lbm_ctx* ctx, int parity)
     a.median_pass = (ctx->median_pass || ctx->ens_pass) ? 1 : 0;
     a.ens_pass = ctx->ens_pass ? 1 : 0;
     a.elbm = ctx->elbm ? 1 : 0;
-    a.budget = ctx->budget ? 1 : 0;
+    a.budget = ctx->budget;
     a.fused = ctx->act.fused ? 1 : 0;
     a.rows = ctx->d_rows();
     a.nrows = int(ctx->rows_host.size());
@@ -586,7 +592,9 @@ StepArgs step_args(const lbm_ctx* ctx, int parity)
 // The kernels one step launches (what a context or a static call runs).
 struct StepKind {
     int storage, lattice, qe, ds, bc;
-    bool elbm, median_pass, ens_pass, budget, fused = false;
+    bool elbm, median_pass, ens_pass;
+    int budget;
+    bool fused = false;
 };
 
 // One step of every domain of `a`.  With `ev` (three events) the launches
@@ -1085,7 +1093,7 @@ int lbm_create(const lbm_domain_desc* domains, int32_t n_domains, const lbm_run_
     for (const auto& h : ctx->dom) {
         ctx->median_pass = ctx->median_pass || (h.d.lattice == LBM_D2Q9 && (h.d.limiter & LBM_LIM_MEDIAN));
         ctx->ens_pass = ctx->ens_pass || deferred(h.d);
-        ctx->budget = ctx->budget || (h.d.limiter & kLimEnsBudget) || is_topk(h.d);
+        ctx->budget |= selections(h.d);
     }
     ctx->cap_h = second_height(domains, n_domains, kMaxTileH);
     ctx->fuse_ok = ctx->lattice == LBM_D2Q9 && !ctx->elbm && ctx->median_pass && !ctx->ens_pass;
@@ -1464,7 +1472,7 @@ int lbm_step_static(const lbm_domain_desc* domain, int32_t storage, void* stream
     k.elbm = domain->collision == LBM_COLL_ELBM;
     k.median_pass = domain->lattice == LBM_D2Q9 && (domain->limiter & LBM_LIM_MEDIAN);
     k.ens_pass = deferred(*domain);
-    k.budget = (domain->limiter & kLimEnsBudget) || is_topk(*domain);
+    k.budget = selections(*domain);
     StepArgs a;
     a.dom = dom;
     a.tiles = tiles;
@@ -1476,7 +1484,7 @@ int lbm_step_static(const lbm_domain_desc* domain, int32_t storage, void* stream
     a.median_pass = (k.median_pass || k.ens_pass) ? 1 : 0;
     a.ens_pass = k.ens_pass ? 1 : 0;
     a.elbm = k.elbm ? 1 : 0;
-    a.budget = k.budget ? 1 : 0;
+    a.budget = k.budget;
     a.rows = rows;
     a.nrows = L.nblocks;
     a.groups = groups;

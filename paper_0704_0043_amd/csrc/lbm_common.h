@@ -53,6 +53,7 @@ enum { kEMean = 0, kEThresh, kESmoothA, kEBudget, kETopk, kNEns };
 // significands: the histogram does not depend on the order of the additions,
 // and neither does the threshold.
 constexpr int kBudgetBuckets = 2048;
+enum { kSelectBudget = 1, kSelectTopK = 2 };   // which selections a step runs
 struct BudgetState {
     unsigned long long prefix;   // digits chosen so far
     double budget;               // delta_0 [1 - (2 beta - 1)^2] sum Delta S'
@@ -217,7 +218,7 @@ struct StepArgs {
                             // and writes every partial to set 1
     int ens_pass;           // 1 if some domain has an ensemble-dependent limiter
     int elbm;               // 1 with ELBM collisions (all domains)
-    int budget;             // 1 if some domain has the budget threshold
+    int budget;             // kSelect* of the domains: budget threshold, top-k trimming
     const RowBlock* rows;   // D2Q9 row blocks in row-major order, one per collision workgroup
     int nrows;              // the D2Q9 collision grid has nrows blocks
     double* rowpart;        // [rows x strips][kNStat]: collision partials of the last step, one

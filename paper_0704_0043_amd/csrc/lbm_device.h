@@ -1099,76 +1099,40 @@ __device__ __forceinline__ A exact_homothety(const SiteState<LAT, A>& o, A shift
     return kullback_scale<L::Q>(fs, x, t, sqrt_(t * rcp(dpost)), A(0), A(1));
 }
 
-constexpr int kSmallDomainTiles = 32;
-
-__device__ inline void reduce_partials(const StepArgs& a, int parity, long long step, double* lds)
+// Sums of one domain's partials -> its stats, by one workgroup of kThreads
+// threads.  set 0: the collision partials per group (D2Q9: summed from the
+// rows on demand); set 1: the second pass per tile, when it ran.  Thread
+// (j, k) = (tid / 16, tid % 16) adds value k of the slots j, j + 16, ... (a
+// slot is one 128-byte line), then the 16 slices are added in order; the order
+// depends on the slot counts only, and where set 1 holds zeros (mass, Delta S')
+// on the groups alone.
+constexpr int kSlices = kThreads / kNStat;
+__device__ inline void reduce_domain(const StepArgs& a, int parity, const DomainDev& D, bool second, long long step,
+                                     double* lds /* [kThreads] */)
 {
-    const int tid = threadIdx.x + threadIdx.y * blockDim.x;
-    const int nthr = blockDim.x * blockDim.y;
-    // set 0: collision partials per group (D2Q9: summed from the rows on
-    // demand); set 1: the second pass per tile, when it ran
+    const int tid = int(threadIdx.x), k = tid % kNStat, j = tid / kNStat;
     const double* part = a.partials + (long long)parity * 2 * a.pstride * kNStat;
     // the fused step writes set 1 only
-    const int set0 = a.fused ? 1 : 0, nsets = (a.median_pass || a.fused) ? 2 : 1;
-    // domains with few slots: one thread each, slots summed in order
-    for (int d = tid; d < a.ndomains; d += nthr) {
-        const DomainDev& D = a.dom[d];
-        // the rule depends on the groups only, so that set 0 is summed in the
-        // same order whatever the tile height (set 1 adds zeros to its slots)
-        if (D.group_count > kSmallDomainTiles) continue;
-        double v[kNStat];
-#pragma unroll
-        for (int k = 0; k < kNStat; ++k) v[k] = 0;
-        for (int set = set0; set < nsets; ++set) {
-            const int first = set ? D.tile_first : D.group_first, count = set ? D.tile_count : D.group_count;
-            for (int t = 0; t < count; ++t) {
-                const double* p = part + ((long long)set * a.pstride + first + t) * kNStat;
-#pragma unroll
-                for (int k = 0; k < kNStat; ++k) v[k] = (k == kSMax) ? fmax(v[k], p[k]) : v[k] + p[k];
-            }
+    const int set0 = a.fused ? 1 : 0, nsets = second || a.fused ? 2 : 1;
+    double v = 0.0;
+    for (int set = set0; set < nsets; ++set) {
+        const int first = set ? D.tile_first : D.group_first, count = set ? D.tile_count : D.group_count;
+        const double* p = part + ((long long)set * a.pstride + first) * kNStat + k;
+#pragma unroll 4
+        for (int t = j; t < count; t += kSlices) {
+            const double x = p[(long long)t * kNStat];
+            v = k == kSMax ? fmax(v, x) : v + x;
         }
-#pragma unroll
-        for (int k = 0; k < kNStat; ++k) D.stats[k] = v[k];
-        D.stats[kNStat] = double(step);
     }
-    // large domains: the whole workgroup, fixed slices then a fixed tree
-    for (int d = 0; d < a.ndomains; ++d) {
-        const DomainDev& D = a.dom[d];
-        if (D.group_count <= kSmallDomainTiles) continue;
-        double v[kNStat];
+    lds[tid] = v;
+    __syncthreads();
+    if (tid < kNStat) {
+        double s = lds[tid];
 #pragma unroll
-        for (int k = 0; k < kNStat; ++k) v[k] = 0;
-        for (int set = set0; set < nsets; ++set) {
-            const int first = set ? D.tile_first : D.group_first, count = set ? D.tile_count : D.group_count;
-            for (int t = tid; t < count; t += nthr) {
-                const double* p = part + ((long long)set * a.pstride + first + t) * kNStat;
-#pragma unroll
-                for (int k = 0; k < kNStat; ++k) v[k] = (k == kSMax) ? fmax(v[k], p[k]) : v[k] + p[k];
-            }
-        }
-#pragma unroll
-        for (int off = 32; off >= 1; off >>= 1) {
-#pragma unroll
-            for (int k = 0; k < kNStat; ++k) {
-                double o = __shfl_xor(v[k], off, 64);
-                v[k] = (k == kSMax) ? fmax(v[k], o) : v[k] + o;
-            }
-        }
-        const int wave = tid >> 6, lane = tid & 63;
-        __syncthreads();
-        if (lane == 0) {
-#pragma unroll
-            for (int k = 0; k < kNStat; ++k) lds[wave * kNStat + k] = v[k];
-        }
-        __syncthreads();
-        if (tid < kNStat) {
-            const int nw = nthr >> 6;
-            double s = lds[tid];
-            for (int w = 1; w < nw; ++w) s = (tid == kSMax) ? fmax(s, lds[w * kNStat + tid]) : s + lds[w * kNStat + tid];
-            D.stats[tid] = s;
-        }
+        for (int w = 1; w < kSlices; ++w)
+            s = tid == kSMax ? fmax(s, lds[w * kNStat + tid]) : s + lds[w * kNStat + tid];
+        D.stats[tid] = s;
         if (tid == 0) D.stats[kNStat] = double(step);
-        __syncthreads();
     }
 }
 

@@ -63,14 +63,6 @@ __device__ inline int node_class(int x, int y, int nx, int ny)
     }
 }
 
-// reduction workgroup: previous step's partials -> stats, advance the counter
-__device__ inline void reduce_block(const StepArgs& a, double* red)
-{
-    const long long step = a.counter[a.parity];
-    if (step > 0) reduce_partials(a, 1 - a.parity, step, red);
-    if (threadIdx.x == 0 && threadIdx.y == 0) a.counter[1 - a.parity] = step + 1;
-}
-
 // spatial tile of a workgroup: blocks are spread over the XCDs so that each
 // XCD runs one contiguous stretch of tiles (rows sharing halo lines hit the
 // same L2).  `first` is the block id of tile 0.
@@ -1123,11 +1115,7 @@ __global__ void __launch_bounds__(kThreads) k_step1d(StepArgs a)
     __shared__ A ds[kThreads];
     __shared__ double red[4 * kNStat];
 
-    if (blockIdx.x == 0) {
-        reduce_block(a, red);
-        return;
-    }
-    const int tidx = tile_of_block(a, 1);
+    const int tidx = tile_of_block(a, 0);
     const Tile t = a.tiles[tidx];
     const DomainDev& D = a.dom[t.domain];
     const int tid = threadIdx.x;
@@ -1137,6 +1125,8 @@ __global__ void __launch_bounds__(kThreads) k_step1d(StepArgs a)
     const gptr<T> dst = to_global<T>(D.buf[1 - a.parity]);
     const A shift = A(D.shift), c = A(D.c);
     const long long step = a.counter[a.parity];
+    // the index of the next step, read by the next launch (which reads buffer 1 - parity)
+    if (blockIdx.x == 0 && tid == 0) a.counter[1 - a.parity] = step + 1;
 
     const int xr = t.x0 - 1 + tid;
     const bool inside = BC == kPeriodic ? true : (xr >= 0 && xr < nx);
@@ -1348,9 +1338,9 @@ hipError_t LBM_CAT(launch_step1d, LBM_SUFFIX)(int qe, int ds, int bc, const Step
                                              hipStream_t s)
 {
     if (kernel == 0)
-        LBM_DISPATCH(k_step1d, 0, 2, dim3(a.ntiles + 1), dim3(kThreads), 0, s, a);
+        LBM_DISPATCH(k_step1d, 0, 2, dim3(a.ntiles), dim3(kThreads), 0, s, a);
     else if (kernel == 2)
-        LBM_DISPATCH_ELBM(k_step1d, 0, 2, dim3(a.ntiles + 1), dim3(kThreads), 0, s, a);
+        LBM_DISPATCH_ELBM(k_step1d, 0, 2, dim3(a.ntiles), dim3(kThreads), 0, s, a);
     else
         LBM_DISPATCH(k_ens1d, 0, 2, dim3(a.ntiles), dim3(kThreads), 0, s, a);
     return hipGetLastError();
