@@ -42,6 +42,20 @@ bool is_topk(const lbm_domain_desc& d) { return (d.limiter & LBM_LIM_TRIM) && d.
 // limiters that need the whole domain's Delta S' before any node is limited
 bool deferred(const lbm_domain_desc& d) { return (d.limiter & kLimEns) || is_topk(d); }
 
+// the second pass forms every node of the domain (the smooth and the rational
+// factor move all or a fifth of them, so that storing a state first would only
+// be undone; ELBM's f' needs its root, so it keeps the stored state)
+bool dense(const lbm_domain_desc& d)
+{
+    return d.lattice == LBM_D2Q9 && d.collision != LBM_COLL_ELBM &&
+           (d.limiter & (LBM_LIM_ENS_SMOOTH | LBM_LIM_ENS_RATIONAL));
+}
+int second_kinds(const lbm_domain_desc& d)
+{
+    if (dense(d)) return kDenseSome;
+    return deferred(d) || (d.limiter & LBM_LIM_MEDIAN) ? kSparseSome : 0;
+}
+
 // the radix selections a domain's step runs
 int selections(const lbm_domain_desc& d)
 {
@@ -139,6 +153,7 @@ struct lbm_ctx {
     bool median_pass = false;   // D2Q9 with the median filter in some domain
     bool ens_pass = false;      // an ensemble-dependent limiter in some domain
     bool fuse_ok = false;       // the fused step applies (D2Q9 LBGK, median filter, no ensemble limiter)
+    int dense = 0;              // kDenseSome / kSparseSome: what second passes the domains need
     int budget = 0;             // kSelect* bits: budget threshold, top-k trimming in some domain
     bool elbm = false;          // ELBM collisions (all domains)
     long long steps_done = 0, finalized_for = -1;
@@ -526,6 +541,7 @@ DomainDev make_dev(const DomainHost& h, char* base, void* b0, void* b1, int prob
     d.delta_ens = h.d.delta_ens;
     d.diffusive = h.d.bc == LBM_BC_CAVITY_DIFFUSIVE ? 1 : 0;
     d.collision = h.d.collision;
+    d.dense = dense(h.d) ? 1 : 0;
     d.homothety = h.d.homothety;
     d.top_k = h.d.top_k;
     d.limiter = device_limiter(h.d);
@@ -575,6 +591,7 @@ StepArgs step_args(const lbm_ctx* ctx, int parity)
     a.ens_pass = ctx->ens_pass ? 1 : 0;
     a.elbm = ctx->elbm ? 1 : 0;
     a.budget = ctx->budget;
+    a.dense = ctx->dense;
     a.fused = ctx->act.fused ? 1 : 0;
     a.rows = ctx->d_rows();
     a.nrows = int(ctx->rows_host.size());
@@ -593,7 +610,7 @@ StepArgs step_args(const lbm_ctx* ctx, int parity)
 struct StepKind {
     int storage, lattice, qe, ds, bc;
     bool elbm, median_pass, ens_pass;
-    int budget;
+    int budget, dense;
     bool fused = false;
 };
 
@@ -621,10 +638,12 @@ hipError_t launch_step(const StepKind& k, const StepArgs& a, hipStream_t s, hipE
     if (e == hipSuccess && k.ens_pass) e = launch_ens_prepare(a, s);
     if (e == hipSuccess && k.budget) e = launch_budget(k.storage, k.bc, a, s);
     if (e == hipSuccess && (k.median_pass || k.ens_pass)) {
-        if (k.lattice == LBM_D2Q9)
-            e = launch_step2d(k.storage, k.qe, k.ds, k.bc, a, 1, s);
-        else
+        if (k.lattice == LBM_D2Q9) {
+            if (k.dense & kDenseSome) e = launch_step2d(k.storage, k.qe, k.ds, k.bc, a, 4, s);
+            if (e == hipSuccess && (k.dense & kSparseSome)) e = launch_step2d(k.storage, k.qe, k.ds, k.bc, a, 1, s);
+        } else {
             e = launch_step1d(k.storage, k.qe, k.ds, k.bc, a, 1, s);
+        }
     }
     if (e == hipSuccess && ev) e = hipEventRecord(ev[2], s);
     return e;
@@ -633,7 +652,7 @@ hipError_t launch_step(const StepKind& k, const StepArgs& a, hipStream_t s, hipE
 StepKind step_kind(const lbm_ctx* ctx)
 {
     return StepKind{ctx->storage, ctx->lattice, ctx->qe, ctx->ds, ctx->bc, ctx->elbm, ctx->median_pass,
-                    ctx->ens_pass, ctx->budget, ctx->act.fused};
+                    ctx->ens_pass, ctx->budget, ctx->dense, ctx->act.fused};
 }
 
 int launch_one(lbm_ctx* ctx, int parity, hipEvent_t* ev = nullptr, unsigned extra_flags = 0)
@@ -748,7 +767,8 @@ int autotune(lbm_ctx* ctx, const lbm_run_desc* run, bool fused_alt = false)
     if (run->tile_x == kThreads || !any_narrow) widths = {0};
     else if (run->tile_x == kWave) widths = {1};
     else widths = {1, 0};
-    const bool second = ctx->median_pass || ctx->ens_pass;
+    // (the dense domains' second pass runs over the row blocks)
+    const bool second = (ctx->median_pass || ctx->ens_pass) && (ctx->dense & kSparseSome);
     std::vector<int> heights;
     if (run->tile_h > 0) heights = {run->tile_h};
     else if (second)
@@ -1094,6 +1114,7 @@ int lbm_create(const lbm_domain_desc* domains, int32_t n_domains, const lbm_run_
         ctx->median_pass = ctx->median_pass || (h.d.lattice == LBM_D2Q9 && (h.d.limiter & LBM_LIM_MEDIAN));
         ctx->ens_pass = ctx->ens_pass || deferred(h.d);
         ctx->budget |= selections(h.d);
+        ctx->dense |= second_kinds(h.d);
     }
     ctx->cap_h = second_height(domains, n_domains, kMaxTileH);
     ctx->fuse_ok = ctx->lattice == LBM_D2Q9 && !ctx->elbm && ctx->median_pass && !ctx->ens_pass;
@@ -1473,6 +1494,7 @@ int lbm_step_static(const lbm_domain_desc* domain, int32_t storage, void* stream
     k.median_pass = domain->lattice == LBM_D2Q9 && (domain->limiter & LBM_LIM_MEDIAN);
     k.ens_pass = deferred(*domain);
     k.budget = selections(*domain);
+    k.dense = second_kinds(*domain);
     StepArgs a;
     a.dom = dom;
     a.tiles = tiles;
@@ -1485,6 +1507,7 @@ int lbm_step_static(const lbm_domain_desc* domain, int32_t storage, void* stream
     a.ens_pass = k.ens_pass ? 1 : 0;
     a.elbm = k.elbm ? 1 : 0;
     a.budget = k.budget;
+    a.dense = k.dense;
     a.rows = rows;
     a.nrows = L.nblocks;
     a.groups = groups;

@@ -76,6 +76,10 @@ __host__ __device__ constexpr int budget_hi(bool dbl, int level)   // one past t
     return level == 0 ? (dbl ? 63 : 31) : budget_lo(dbl, level - 1);
 }
 
+// Which kinds of domains need a second pass: ones whose every node it forms
+// (k_form2d), ones where it moves the nodes a limiter hits.
+enum { kDenseSome = 1, kSparseSome = 2 };
+
 // Per-domain parameters, device visible.  Pointers are device pointers.
 struct DomainDev {
     void* buf[2];           // population planes (storage type), A and B
@@ -88,6 +92,8 @@ struct DomainDev {
     int limiter, trim_mode, median_mode;
     int diffusive;          // cavity walls: 0 on-node bounce-back + equilibrium lid, 1 diffusive Maxwell
     int collision;          // kLBGK or kELBM
+    int dense;              // the smooth or rational factor (LBGK): every node's limited state is formed
+                            // by k_form2d, the collision kernel stores Delta S' only
     int homothety;          // 1: homothety targets reached exactly with the exact Delta S
     long long top_k;        // kLimTopK: trimming at the top_k largest finite Delta S' only
     int probe_x, probe_y, probe_cap;
@@ -214,6 +220,7 @@ struct StepArgs {
     int ngroups;
     int pstride;            // slots per set in `partials` (>= ntiles, ngroups)
     int median_pass;        // 1 if a second pass (median and/or ensemble limiters) writes set 1
+    int dense;              // kDense* of the domains
     int fused = 0;          // 1: the fused step kernel runs alone over `tiles` (fused tiles)
                             // and writes every partial to set 1
     int ens_pass;           // 1 if some domain has an ensemble-dependent limiter
@@ -239,7 +246,8 @@ hipError_t launch_static_stats(const DomainDev* dom, double shift_mass, double* 
 // Launchers (one per storage type / lattice), defined in the .hip files.
 // kernel 0: collision kernel (LBGK); kernel 2: the same with the ELBM collision;
 // kernel 1: the second pass (median filter, ensemble factors; after kernel 0 or 2);
-// kernel 3: the fused step (LBGK, trimming, positivity and median filter)
+// kernel 3: the fused step (LBGK, trimming, positivity and median filter);
+// kernel 4: the second pass of the dense domains (after kernel 0)
 hipError_t launch_step2d(int storage, int qe, int ds, int bc, const StepArgs& a, int kernel, hipStream_t s);
 // kernel 0: D1Q3 step (LBGK); kernel 2: the same with ELBM; kernel 1: D1Q3 ensemble pass
 hipError_t launch_step1d(int storage, int qe, int ds, int bc, const StepArgs& a, int kernel, hipStream_t s);

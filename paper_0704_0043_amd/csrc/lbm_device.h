@@ -1000,6 +1000,14 @@ __device__ inline void node_partial_rows(const AccT<S>& acc, double* out, long l
 // top-k Ehrenfests' step: 0).  The node's factor is min(fac, phi(tgt)), with
 // phi(tgt) = sqrt(tgt / d) in the quadratic reading of the homothety.
 // +inf (a non-positive population) gives 0; NaN moves nothing.
+// x^k for x > 0; the exponents in use are mostly 1/2 (k is uniform)
+template <class A>
+__device__ __forceinline__ A pow_of(A x, A k)
+{
+    if (k == A(0.5)) return sqrt_(x);
+    if (k == A(1)) return x;
+    return pow_(x, k);
+}
 struct SecondHit {
     unsigned bits = 0;
     int ens = 0, trim = 0;
@@ -1019,7 +1027,7 @@ __device__ __forceinline__ void ens_terms(const DomainDev& D, const double* ens,
     }
     const double mean = ens[kEMean];
     if ((lim & kLimEnsSmooth) && mean > 0.0 && d > A(0)) {
-        const A v = isinf(d) ? A(0) : A(1) / (A(1) + A(ens[kESmoothA]) * pow_(d, A(D.ens_k)));
+        const A v = isinf(d) ? A(0) : A(1) / (A(1) + A(ens[kESmoothA]) * pow_of(d, A(D.ens_k)));
         if (v < A(1)) {
             fac = fmin(fac, v);
             e = true;
@@ -1029,7 +1037,8 @@ __device__ __forceinline__ void ens_terms(const DomainDev& D, const double* ens,
         A v = A(0);
         if (!isinf(d)) {
             const A r = d / A(D.ens_c * mean);
-            v = (A(1) + pow_(r, A(D.ens_k - 0.5))) / (A(1) + pow_(r, A(D.ens_k)));
+            const A p = D.ens_k == 0.5 ? A(1) : pow_of(r, A(D.ens_k - 0.5));   // r^k = r^(k - 1/2) sqrt(r)
+            v = (A(1) + p) / (A(1) + p * sqrt_(r));
         }
         if (v < A(1)) {
             fac = fmin(fac, v);
@@ -1113,7 +1122,7 @@ __device__ inline void reduce_domain(const StepArgs& a, int parity, const Domain
     const int tid = int(threadIdx.x), k = tid % kNStat, j = tid / kNStat;
     const double* part = a.partials + (long long)parity * 2 * a.pstride * kNStat;
     // the fused step writes set 1 only
-    const int set0 = a.fused ? 1 : 0, nsets = second || a.fused ? 2 : 1;
+    const int set0 = a.fused ? 1 : 0, nsets = (second && !D.dense) || a.fused ? 2 : 1;
     double v = 0.0;
     for (int set = set0; set < nsets; ++set) {
         const int first = set ? D.tile_first : D.group_first, count = set ? D.tile_count : D.group_count;

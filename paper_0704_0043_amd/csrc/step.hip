@@ -261,6 +261,7 @@ __global__ void __launch_bounds__(kThreads) k_collide2d(StepArgs a)
     const bool record = a.flags & kFlagRecord;
     const bool want_ent = a.flags & kFlagEntropy;
     const bool keep_ds = D.limiter & (kLimMedian | kLimEns);
+    const bool dense = !ELBM && D.dense;       // k_form2d stores the fluid nodes
     const long long step = a.counter[a.parity];
     // the index of the next step, read by the next launch (which reads buffer 1 - parity)
     if (ridx == 0 && threadIdx.x == 0) a.counter[1 - a.parity] = step + 1;
@@ -314,7 +315,7 @@ __global__ void __launch_bounds__(kThreads) k_collide2d(StepArgs a)
                         phi = fmin(phi, pp);
                     }
                 }
-                store_limited<T>(dst, plane, row, cl.own, S, phi, S.c);
+                if (!dense) store_limited<T>(dst, plane, row, cl.own, S, phi, S.c);
                 if (keep_ds) {
                     // NaN counts as above: such a wave always stores its values
                     const bool up = (D.limiter & kLimMedian) && !(S.dpost <= A(D.delta_median));
@@ -454,25 +455,23 @@ __device__ __forceinline__ void gather_node(gptr<const T> src, long long plane, 
     }
 }
 
-// One node the second pass moves, after LBGK collisions: its limited state is
-// formed anew from the populations that arrived (the buffer the step reads
+// The limited state of a node after LBGK collisions, formed anew by a second
+// pass from the populations g that arrived there (the buffer the step reads
 // still holds them), f* - phi c d with phi the smallest of its factors, as the
-// fused step forms it.  Returns the limiter's entropy production beyond what
-// the collision kernel counted for it.
-template <class T, int QE, int DS, int BC, class DD>
-__device__ __forceinline__ double form_node(const DD& D, gptr<const T> src, gptr<T> dst, long long plane, int x, int y,
-                                            typename Store<T>::A dc, typename Store<T>::A tgt,
-                                            typename Store<T>::A fac)
+// fused step forms it.  Returns phi; `lim` is the limiter's entropy production
+// beyond what the collision kernel counted for the node.
+template <class T, int QE, int DS, class DD>
+__device__ __forceinline__ typename Store<T>::A form_state(const DD& D, const typename Store<T>::A (&g)[9],
+                                                           typename Store<T>::A dc, typename Store<T>::A tgt,
+                                                           typename Store<T>::A fac,
+                                                           SiteState<kD2Q9, typename Store<T>::A>& S, double& lim)
 {
     using A = typename Store<T>::A;
     constexpr int Q = 9;
     const A inf = A(__builtin_huge_val());
     const A shift = A(D.shift), c = A(D.c);
-    A g[Q];
-    gather_node<BC>(src, plane, D.nx, D.ny, x, y, g);
     unsigned tmask = 0;
     A pt = trim_phi(D, dc, tmask);     // the factor the collision kernel applied
-    SiteState<kD2Q9, A> S;
     A dr, jx, jy, rho, ux, uy;
     moments_equilibrium<kD2Q9, QE>(g, shift, dr, jx, jy, rho, ux, uy, S.gs);
 #pragma unroll
@@ -493,14 +492,34 @@ __device__ __forceinline__ double form_node(const DD& D, gptr<const T> src, gptr
         }
     }
     if (!done) phi = fmin(pt, fmin(fac, tgt < inf ? sqrt_(tgt * rcp(dc)) : A(1)));
-    const A k = phi * c;
+    lim = 0.0;
+    if (isfinite(dc) && phi < pt) {
+        if constexpr (DS == kQuad) {
+            lim = double(dc * (pt * pt - phi * phi));
+        } else {
+            const A before = pt < A(1) ? delta_s_scaled<kD2Q9, DS>(S, shift, c, pt) : dc;
+            lim = double(before - delta_s_scaled<kD2Q9, DS>(S, shift, c, phi));
+        }
+    }
+    return phi;
+}
+
+// one node of a wave's list
+template <class T, int QE, int DS, int BC, class DD>
+__device__ __forceinline__ double form_node(const DD& D, gptr<const T> src, gptr<T> dst, long long plane, int x, int y,
+                                            typename Store<T>::A dc, typename Store<T>::A tgt,
+                                            typename Store<T>::A fac)
+{
+    using A = typename Store<T>::A;
+    A g[9];
+    gather_node<BC>(src, plane, D.nx, D.ny, x, y, g);
+    SiteState<kD2Q9, A> S;
+    double lim;
+    const A k = form_state<T, QE, DS>(D, g, dc, tgt, fac, S, lim) * S.c;
     const unsigned own = unsigned(sizeof(T)) * (unsigned(y) * unsigned(D.nx) + unsigned(x));
 #pragma unroll
-    for (int i = 0; i < Q; ++i) Store<T>::st(at_bytes(dst + i * plane, own), S.gs[i] - k * S.d[i]);
-    if (!isfinite(dc)) return 0.0;
-    if constexpr (DS == kQuad) return double(dc * (pt * pt - phi * phi));
-    const A before = pt < A(1) ? delta_s_scaled<kD2Q9, DS>(S, shift, c, pt) : dc;
-    return double(before - delta_s_scaled<kD2Q9, DS>(S, shift, c, phi));
+    for (int i = 0; i < 9; ++i) Store<T>::st(at_bytes(dst + i * plane, own), S.gs[i] - k * S.d[i]);
+    return lim;
 }
 
 // The same after ELBM collisions, whose f' - f* = -(alpha beta - 1) d would
@@ -577,6 +596,8 @@ __device__ __forceinline__ void second_pass2d(const StepArgs& a)
             if (threadIdx.x < kNStat) partial_slot(a, 1, tidx)[threadIdx.x] = 0.0;
             return;
         }
+    } else {
+        if (!ELBM && D.dense) return;          // k_form2d's
     }
     AccT<A, double> acc;
     const int nx = D.nx, ny = D.ny;
@@ -818,6 +839,116 @@ template <class T, int QE, int DS, int BC, bool ELBM = false>
 __global__ void __launch_bounds__(kThreads) k_median_ens2d(StepArgs a)
 {
     second_pass2d<T, QE, DS, BC, true, ELBM>(a);
+}
+
+// Second pass of the domains whose every node it moves (the smooth and the
+// rational factor).  The collision kernel stored their Delta S' and no
+// populations, and this pass forms each fluid node's state once, one node per
+// thread over the same row blocks: 36 + 4 and 40 + 36 bytes per FP32 node in
+// the two passes, where storing the trimmed state and rescaling it in place
+// moved 36 + 40 and 40 + 36 and waited for the stored state besides.  Its
+// terms of the sums join the row's partial.
+template <class T, int QE, int DS, int BC>
+__global__ void __launch_bounds__(kThreads) k_form2d(StepArgs a)
+{
+    using A = typename Store<T>::A;
+    __shared__ double red[4 * kNStat];
+    const RowBlock t = a.rows[blockIdx.x];
+    const DomainDev& D = a.dom[t.domain];
+    if (!D.dense) return;
+    const int nx = D.nx, ny = D.ny;
+    const long long plane = D.plane;
+    const gptr<const T> src = to_global<T>(static_cast<const void*>(D.buf[a.parity]));
+    const gptr<T> dst = to_global<T>(D.buf[1 - a.parity]);
+    const gptr<const A> dsb = to_global<A>(static_cast<const void*>(D.dsbuf));
+    const bool record = a.flags & kFlagRecord;
+    double ensv[kNEns];
+#pragma unroll
+    for (int k = 0; k < kNEns; ++k) ensv[k] = D.ens[k];
+    AccT<A, double> acc;
+    auto visit = [&](const int y, const Cols<T, BC>& cl) {
+        const int x = cl.x, lane = int(threadIdx.x) & (kWave - 1);
+        const int yw = __builtin_amdgcn_readfirstlane(y);      // a wave covers one row
+        const long long row = (long long)yw * nx;
+        // the rows above and below and the columns beside (clamped at a
+        // cavity's edges, where no fluid node reads them)
+        int ym = yw - 1, yp = yw + 1, xm = x - 1, xp = x + 1;
+        if constexpr (BC == kPeriodic) {
+            ym = yw == 0 ? ny - 1 : ym;
+            yp = yw == ny - 1 ? 0 : yp;
+            xm = x == 0 ? nx - 1 : xm;
+            xp = x == nx - 1 ? 0 : xp;
+        } else {
+            ym = yw == 0 ? 0 : ym;
+            yp = yw == ny - 1 ? yw : yp;
+            xm = x == 0 ? 0 : xm;
+            xp = x == nx - 1 ? x : xp;
+        }
+        A w[3][3];
+        if (D.limiter & kLimMedian) {
+            const bool own_l = lane == 0, own_r = lane == kWave - 1 || x == t.x1 - 1;
+#pragma unroll
+            for (int k = 0; k < 3; ++k) {
+                const gptr<const A> r = dsb + (long long)(k == 0 ? ym : (k == 1 ? yw : yp)) * nx;
+                w[k][1] = Store<A>::ld(r + x);
+                w[k][0] = lane_shift<-1>(w[k][1]);
+                w[k][2] = lane_shift<+1>(w[k][1]);
+                if (own_l) w[k][0] = Store<A>::ld(r + xm);
+                if (own_r) w[k][2] = Store<A>::ld(r + xp);
+            }
+        } else {
+            w[1][1] = Store<A>::ld(dsb + row + x);
+        }
+        A g[9];
+        gather2d<BC>(src, plane, nx, ny, cl, y, g);
+        if (node_class<BC>(x, y, nx, ny) != kNodeFluid) return;
+        const A dc = w[1][1];
+        A tgt = A(__builtin_huge_val()), fac = A(1), thr;
+        SecondHit h;
+        if ((D.limiter & kLimMedian) && median_hit<BC>(D, x, y, nx, ny, w[0], w[1], w[2], thr)) {
+            h.bits |= kMaskMedian;
+            tgt = thr;
+            acc.filt = 1;
+        }
+        ens_terms(D, ensv, dc, tgt, fac, h);
+        acc.ens = h.ens;
+        acc.trim = h.trim;
+        if (record && h.bits) to_global<unsigned char>(D.mask)[unsigned(row) + unsigned(x)] |= (unsigned char)h.bits;
+        SiteState<kD2Q9, A> S;
+        const A phi = form_state<T, QE, DS>(D, g, dc, tgt, fac, S, acc.lim);
+        store_limited<T>(dst, plane, row, cl.own, S, phi, S.c);
+    };
+    if (t.width == kThreads) {
+        const int x = t.x0 + int(threadIdx.x);
+        const Cols<T, BC> cl(x, nx, x < t.x1);
+        if (cl.ok) visit(t.y0, cl);
+    } else {
+        const int lx = int(threadIdx.x) & (t.width - 1), ly = int(threadIdx.x) >> __builtin_ctz(unsigned(t.width));
+        const int y = t.y0 + ly;
+        const Cols<T, BC> cl(t.x0 + lx, nx, t.x0 + lx < t.x1 && y < t.y1);
+        if (cl.ok) visit(y, cl);
+    }
+    // one value per wave and term, then into the row's partial
+    const int wave = int(threadIdx.x) >> 6;
+    const double lim = wave_reduce<false>(acc.lim);
+    auto count = [](bool b) { return double(unsigned(__popcll(__ballot(b)))); };
+    const double nt = count(acc.trim != 0), nf = count(acc.filt != 0), ne = count(acc.ens != 0);
+    if ((threadIdx.x & (kWave - 1)) == kWave - 1) {
+        red[wave * 4] = lim;
+        red[wave * 4 + 1] = nt;
+        red[wave * 4 + 2] = nf;
+        red[wave * 4 + 3] = ne;
+    }
+    __syncthreads();
+    const int wpr = t.width / kWave, tid = int(threadIdx.x);
+    if (tid < 4 * (t.y1 - t.y0)) {
+        const int r = tid >> 2, k = tid & 3;
+        double s = 0.0;
+        for (int w = 0; w < wpr; ++w) s += red[(r * wpr + w) * 4 + k];
+        double* out = a.rowpart + ((long long)D.row_first + (long long)(t.y0 + r) * D.strips + t.x0 / kThreads) * kNStat;
+        const int slot = k == 0 ? kSLim : (k == 1 ? kSTrim : (k == 2 ? kSFilt : kSEns));
+        out[slot] += s;
+    }
 }
 
 // The domain fields the fused step reads in its row loop.
@@ -1323,6 +1454,8 @@ hipError_t LBM_CAT(launch_step2d, LBM_SUFFIX)(int qe, int ds, int bc, const Step
         LBM_DISPATCH_ELBM(k_collide2d, 0, 1, dim3(a.nrows), dim3(kThreads), 0, s, a);
     else if (kernel == 3)
         LBM_DISPATCH(k_fused2d, 0, 1, dim3(a.ntiles), dim3(kThreads), 0, s, a);
+    else if (kernel == 4)
+        LBM_DISPATCH(k_form2d, 0, 1, dim3(a.nrows), dim3(kThreads), 0, s, a);
     else if (a.elbm && a.ens_pass)
         LBM_DISPATCH_ELBM(k_median_ens2d, 0, 1, dim3(a.ntiles), dim3(kThreads), 0, s, a);
     else if (a.elbm)
