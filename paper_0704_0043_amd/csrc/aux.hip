@@ -140,33 +140,33 @@ __device__ inline int key_exponent(typename K::U k)
     return (e ? e : 1) - K::bias;
 }
 
-// One level of the budget selection: per tile, a histogram of the digit
-// (count and exact significand sum per bucket) of the values whose higher
-// digits match the prefix, added into the domain's histogram.  Each thread
-// walks one column of the tile and merges runs of equal buckets in registers
-// first (at most kMaxTileH values: the significand sum stays below 2^59; a
-// wave's sum stays below 2^64 for any FP32 tile and FP64 tiles of 32 rows).
+// One level of the budget selection: a histogram of the digit (count and exact
+// significand sum per bucket) of the values whose higher digits match the
+// prefix, added into the domain's histogram.  A workgroup of four times 256
+// columns takes a run of 64-row groups: what a level costs are the additions
+// of all workgroups to the few buckets that most values share, which queue at
+// their addresses (1000 workgroups: 40 us for the first level of a 1024 x 1000
+// grid, against 12 us with 64), so workgroups are few and large.  Each thread
+// walks 16 rows of a column and merges runs of equal buckets in registers
+// first (the significand sum of a wave stays below 2^63).
+constexpr int kHistThreads = 4 * kThreads, kHistRows = kMaxTileH / 4, kHistBlocks = 256;
 template <class A, bool CAV>
-__global__ void __launch_bounds__(kThreads) k_budget_hist(StepArgs a, int level)
+__global__ void __launch_bounds__(kHistThreads) k_budget_hist(StepArgs a, int level)
 {
     using K = BKey<A>;
     using U = typename K::U;
     __shared__ unsigned hn[kBudgetBuckets];
     __shared__ unsigned long long hlo[kBudgetBuckets];
     __shared__ unsigned hhi[kBudgetBuckets];
-    const Tile t = a.tiles[blockIdx.x];
-    const DomainDev& D = a.dom[t.domain];
-    if (!(D.limiter & (kLimEnsBudget | kLimTopK)) || D.bstate->done) return;
-    const unsigned long long prefix = D.bstate->prefix;
+    const int tid = int(threadIdx.x), lane = tid & (kWave - 1);
     const int lo = budget_lo(K::dbl, level), hi = budget_hi(K::dbl, level);
     const U dmask = (U(1) << (hi - lo)) - 1;
-    for (int k = threadIdx.x; k < kBudgetBuckets; k += kThreads) {
+    for (int k = tid; k < kBudgetBuckets; k += kHistThreads) {
         hn[k] = 0;
         hlo[k] = 0;
         hhi[k] = 0;
     }
     __syncthreads();
-    const int x = t.x0 + int(threadIdx.x);
     auto flush = [&](int b, unsigned cnt, unsigned long long sum) {
         atomicAdd(&hn[b], cnt);
         const unsigned long long old = atomicAdd(&hlo[b], sum);
@@ -188,42 +188,66 @@ __global__ void __launch_bounds__(kThreads) k_budget_hist(StepArgs a, int level)
             c += __shfl_xor(c, off, kWave);
             v += __shfl_xor(v, off, kWave);
         }
-        if ((int(threadIdx.x) & (kWave - 1)) == 0) flush(lead, c, v);
+        if (lane == 0) flush(lead, c, v);
         if (cnt && !same) flush(b, cnt, sum);
     };
-    int cur = -1;
-    unsigned cnt = 0;
-    unsigned long long sum = 0;
-    if (x < t.x1) {
-        const A* ds = static_cast<const A*>(D.dsbuf);
-        for (int y = t.y0; y < t.y1; ++y) {
-            if (CAV && (x == 0 || x == D.nx - 1 || y == 0 || y == D.ny - 1)) continue;   // walls and lid
-            const A d = ds[(long long)y * D.nx + x];
-            if (!isfinite(d)) continue;
-            const U k = K::key(d);
-            if ((unsigned long long)(k >> hi) != prefix) continue;
-            const int b = int((k >> lo) & dmask);
-            if (b != cur) {
-                if (cnt) flush(cur, cnt, sum);
-                cur = b;
-                cnt = 0;
-                sum = 0;
+    const int nb = int(gridDim.x), g0 = int((long long)blockIdx.x * a.ngroups / nb),
+              g1 = int((long long)(blockIdx.x + 1) * a.ngroups / nb);
+    for (int g = g0; g < g1; ++g) {
+        const Tile t = a.groups[g];
+        const DomainDev& D = a.dom[t.domain];
+        const bool run = (D.limiter & (kLimEnsBudget | kLimTopK)) && !D.bstate->done;
+        if (run) {
+            const unsigned long long prefix = D.bstate->prefix;
+            const int x = t.x0 + (tid & (kThreads - 1)), y0 = t.y0 + (tid / kThreads) * kHistRows;
+            const A* ds = static_cast<const A*>(D.dsbuf);
+            int cur = -1;
+            unsigned cnt = 0;
+            unsigned long long sum = 0;
+            constexpr int kAhead = 8;      // rows loaded together
+            for (int yb = y0; yb < y0 + kHistRows; yb += kAhead) {
+                A v[kAhead];
+#pragma unroll
+                for (int k = 0; k < kAhead; ++k)
+                    v[k] = (x < t.x1 && yb + k < t.y1) ? ds[(long long)(yb + k) * D.nx + x] : A(__builtin_huge_val());
+#pragma unroll
+                for (int k = 0; k < kAhead; ++k) {
+                    const int y = yb + k;
+                    if (CAV && (x == 0 || x == D.nx - 1 || y == 0 || y == D.ny - 1)) continue;   // walls and lid
+                    if (!isfinite(v[k])) continue;
+                    const U key = K::key(v[k]);
+                    if ((unsigned long long)(key >> hi) != prefix) continue;
+                    const int b = int((key >> lo) & dmask);
+                    if (b != cur) {
+                        if (cnt) flush(cur, cnt, sum);
+                        cur = b;
+                        cnt = 0;
+                        sum = 0;
+                    }
+                    ++cnt;
+                    sum += key_significand<K>(key);
+                }
             }
-            ++cnt;
-            sum += key_significand<K>(k);
+            if (level == 0) flush_wave(cur, cnt, sum);
+            else if (cnt) flush(cur, cnt, sum);
+        }
+        // into the domain's histogram after its last group here
+        if (run && (g + 1 == g1 || a.groups[g + 1].domain != t.domain)) {
+            __syncthreads();
+            BudgetBucket* gh = D.bhist;
+            for (int k = tid; k < kBudgetBuckets; k += kHistThreads)
+                if (hn[k]) {
+                    atomicAdd(&gh[k].n, (unsigned long long)hn[k]);
+                    const unsigned long long old = atomicAdd(&gh[k].lo, hlo[k]);
+                    const unsigned long long hiadd = (unsigned long long)hhi[k] + (old + hlo[k] < old ? 1ull : 0ull);
+                    if (hiadd) atomicAdd(&gh[k].hi, hiadd);
+                    hn[k] = 0;
+                    hlo[k] = 0;
+                    hhi[k] = 0;
+                }
+            __syncthreads();
         }
     }
-    if (level == 0 && (!K::dbl || t.y1 - t.y0 <= 32)) flush_wave(cur, cnt, sum);
-    else if (cnt) flush(cur, cnt, sum);
-    __syncthreads();
-    BudgetBucket* gh = D.bhist;
-    for (int k = threadIdx.x; k < kBudgetBuckets; k += kThreads)
-        if (hn[k]) {
-            atomicAdd(&gh[k].n, (unsigned long long)hn[k]);
-            const unsigned long long old = atomicAdd(&gh[k].lo, hlo[k]);
-            const unsigned long long hiadd = (unsigned long long)hhi[k] + (old + hlo[k] < old ? 1ull : 0ull);
-            if (hiadd) atomicAdd(&gh[k].hi, hiadd);
-        }
 }
 
 // Exclusive sums over the threads above (tid + 1 .. kThreads - 1) of one or two
@@ -432,10 +456,11 @@ template <class A>
 static hipError_t budget_levels_t(int bc, const StepArgs& a, hipStream_t s)
 {
     for (int level = 0; level < budget_levels(sizeof(A) == 8); ++level) {
+        const dim3 grid(a.ngroups < kHistBlocks ? a.ngroups : kHistBlocks), block(kHistThreads);
         if (bc == kCavity)
-            hipLaunchKernelGGL((k_budget_hist<A, true>), dim3(a.ntiles), dim3(kThreads), 0, s, a, level);
+            hipLaunchKernelGGL((k_budget_hist<A, true>), grid, block, 0, s, a, level);
         else
-            hipLaunchKernelGGL((k_budget_hist<A, false>), dim3(a.ntiles), dim3(kThreads), 0, s, a, level);
+            hipLaunchKernelGGL((k_budget_hist<A, false>), grid, block, 0, s, a, level);
         if (a.budget & kSelectBudget)
             hipLaunchKernelGGL(k_budget_select<A>, dim3(a.ndomains), dim3(kThreads), 0, s, a, level);
         if (a.budget & kSelectTopK)
