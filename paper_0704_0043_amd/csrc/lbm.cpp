@@ -91,6 +91,40 @@ int second_height(const lbm_domain_desc* doms, int32_t nd, int th)
     return std::min(th, kMinTileH);
 }
 
+// D1Q3: sites on either side that one step's result depends on (free flight,
+// and the Delta S' of the neighbours with the median filter)
+int reach1d(const lbm_domain_desc* doms, int32_t nd)
+{
+    int reach = 1;
+    for (int k = 0; k < nd; ++k)
+        if (doms[k].limiter & LBM_LIM_MEDIAN) reach = 2;
+    return reach;
+}
+// steps of the longest D1Q3 launch: 1 with an ensemble limiter (its pass
+// follows every step).  Long launches spare the most where launches and
+// latency are all there is; a large domain gains its memory traffic back
+// within a few steps, and a wider halo would only add sites.
+int max_steps1d(const lbm_domain_desc* doms, int32_t nd)
+{
+    long long sites = 0;
+    for (int k = 0; k < nd; ++k) {
+        if (deferred(doms[k])) return 1;
+        sites += doms[k].nx;
+    }
+    return reach1d(doms, nd) > 1 && sites > 65536 ? k1DMaxSteps / 2 : k1DMaxSteps;
+}
+// The next launch's share of `left` steps: odd, at most `most`, and such that
+// the rest can be split the same way (each launch swaps the buffers once, as a
+// step does), in launches of nearly equal length.
+int next_launch(long long left, int most)
+{
+    long long launches = (left + most - 1) / most;
+    if ((launches ^ left) & 1) ++launches;
+    long long n = (left + launches - 1) / launches;
+    if (n % 2 == 0) --n;
+    return int(std::max(n, left - (launches - 1) * most));
+}
+
 // both forms of the step are kept and chosen between while the run goes
 bool adaptive_run(const lbm_domain_desc* doms, int32_t nd, const lbm_run_desc* run)
 {
@@ -153,6 +187,7 @@ struct lbm_ctx {
     bool median_pass = false;   // D2Q9 with the median filter in some domain
     bool ens_pass = false;      // an ensemble-dependent limiter in some domain
     bool fuse_ok = false;       // the fused step applies (D2Q9 LBGK, median filter, no ensemble limiter)
+    int reach = 1, most1d = 1;  // D1Q3: reach of a step, steps of the longest launch
     int dense = 0;              // kDenseSome / kSparseSome: what second passes the domains need
     int budget = 0;             // kSelect* bits: budget threshold, top-k trimming in some domain
     bool elbm = false;          // ELBM collisions (all domains)
@@ -603,6 +638,7 @@ StepArgs step_args(const lbm_ctx* ctx, int parity)
     a.flags = ctx->flags & (LBM_RUN_RECORD | LBM_RUN_ENTROPY);
     a.partials = ctx->d_partials();
     a.counter = ctx->d_counter();
+    a.reach = ctx->reach;
     return a;
 }
 
@@ -655,10 +691,11 @@ StepKind step_kind(const lbm_ctx* ctx)
                     ctx->ens_pass, ctx->budget, ctx->dense, ctx->act.fused};
 }
 
-int launch_one(lbm_ctx* ctx, int parity, hipEvent_t* ev = nullptr, unsigned extra_flags = 0)
+int launch_one(lbm_ctx* ctx, int parity, hipEvent_t* ev = nullptr, unsigned extra_flags = 0, int steps = 1)
 {
     StepArgs a = step_args(ctx, parity);
     a.flags |= extra_flags;
+    a.steps = steps;
     const hipError_t e = launch_step(step_kind(ctx), a, ctx->stream, ev);
     if (e != hipSuccess) return fail(ctx, LBM_EDEVICE, std::string("step launch: ") + hipGetErrorString(e));
     return LBM_OK;
@@ -845,7 +882,11 @@ int capture(lbm_ctx* ctx, int parity, int64_t len)
     hipGraph_t g = nullptr;
     HIP_TRY(ctx, hipStreamBeginCapture(ctx->stream, hipStreamCaptureModeThreadLocal));
     int rc = LBM_OK;
-    for (int64_t k = 0; k < len && rc == LBM_OK; ++k) rc = launch_one(ctx, int((parity + k) % 2));
+    for (int64_t k = 0; k < len && rc == LBM_OK;) {
+        const int n = ctx->lattice == LBM_D1Q3 ? next_launch(len - k, ctx->most1d) : 1;
+        rc = launch_one(ctx, int((parity + k) % 2), nullptr, 0, n);
+        k += n;
+    }
     hipError_t e = hipStreamEndCapture(ctx->stream, &g);
     if (rc) {
         if (g) (void)hipGraphDestroy(g);
@@ -1115,6 +1156,10 @@ int lbm_create(const lbm_domain_desc* domains, int32_t n_domains, const lbm_run_
         ctx->ens_pass = ctx->ens_pass || deferred(h.d);
         ctx->budget |= selections(h.d);
         ctx->dense |= second_kinds(h.d);
+    }
+    if (ctx->lattice == LBM_D1Q3) {
+        ctx->reach = reach1d(domains, n_domains);
+        ctx->most1d = max_steps1d(domains, n_domains);
     }
     ctx->cap_h = second_height(domains, n_domains, kMaxTileH);
     ctx->fuse_ok = ctx->lattice == LBM_D2Q9 && !ctx->elbm && ctx->median_pass && !ctx->ens_pass;
@@ -1515,9 +1560,14 @@ int lbm_step_static(const lbm_domain_desc* domain, int32_t storage, void* stream
     a.pstride = L.ntiles;
     a.rowpart = reinterpret_cast<double*>(base + L.off_rowpart);
     a.counter = counter;
-    for (int64_t t = 0; t < n_steps && e == hipSuccess; ++t) {
+    const bool d1 = domain->lattice == LBM_D1Q3;
+    const int most = d1 ? max_steps1d(domain, 1) : 1;
+    if (d1) a.reach = reach1d(domain, 1);
+    for (int64_t t = 0; t < n_steps && e == hipSuccess;) {
         a.parity = int(t % 2);
+        a.steps = most > 1 ? next_launch(n_steps - t, most) : 1;
         e = launch_step(k, a, s);
+        t += a.steps;
     }
     if (e == hipSuccess && stats) {
         e = launch_finalize(a, int((n_steps - 1) % 2), n_steps, s);

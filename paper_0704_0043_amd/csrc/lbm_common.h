@@ -138,6 +138,15 @@ struct Tile {
 
 constexpr int k1DWidth = kThreads - 2;   // output sites of one D1Q3 workgroup
 
+// D1Q3 steps of one launch.  A workgroup computes its k1DWidth sites with a
+// halo that each further step eats `reach` sites of on either side (1, with
+// the median filter 2).  A launch reads one buffer and writes the other, so it
+// takes an odd number of steps.
+constexpr int k1DMaxSteps = 33;
+constexpr int k1DMaxThreads = 448;
+inline int threads1d(int reach, int steps) { return (k1DWidth + 2 * reach * steps + kWave - 1) / kWave * kWave; }
+static_assert(k1DWidth + 4 * k1DMaxSteps <= k1DMaxThreads, "the halo of the longest launch fits");
+
 // One D2Q9 collision workgroup: rows [y0, y1) by columns [x0, x1) of one
 // domain, `width` (64, 128 or 256) columns per row, kThreads / width rows.
 struct RowBlock {
@@ -231,6 +240,8 @@ struct StepArgs {
     double* rowpart;        // [rows x strips][kNStat]: collision partials of the last step, one
                             // per domain row and 256-column strip
     long long* counter;     // [2] step index by parity
+    int reach = 1;          // D1Q3: sites a step's result depends on, on either side
+    int steps = 1;          // D1Q3: steps of this launch (odd)
 };
 
 // Allocation-free stepping (lbm_step_static): bytes of the per-GPU static

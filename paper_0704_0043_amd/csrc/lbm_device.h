@@ -187,6 +187,12 @@ struct Store<__bf16> {
     }
 };
 
+// a value as storage keeps it, in LDS
+template <class T>
+__device__ __forceinline__ typename Store<T>::A ld_shared(const T* p) { return typename Store<T>::A(*p); }
+template <class T>
+__device__ __forceinline__ void st_shared(T* p, typename Store<T>::A v) { *p = (T)v; }
+
 // ---- arithmetic helpers ------------------------------------------------------
 // FP64: IEEE division and square root.  FP32: the hardware reciprocal and
 // square root (about 1 ulp), well inside the FP32 error budget.

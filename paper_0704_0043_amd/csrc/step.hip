@@ -1217,8 +1217,6 @@ __global__ void __launch_bounds__(kThreads) k_fused2d(StepArgs a)
     store_partial(tot, partial_slot(a, 1, tidx), red);
 }
 
-// D1Q3: each workgroup computes Delta S' at kThreads consecutive sites and
-// updates the inner ones (3-point median, Sec. 4.3.2).
 template <int BC, class T>
 __device__ inline void gather1d(gptr<const T> src, long long plane, int nx, int x,
                                 typename Store<T>::A (&g)[3])
@@ -1237,14 +1235,23 @@ __device__ inline void gather1d(gptr<const T> src, long long plane, int nx, int 
     }
 }
 
+// D1Q3: a.steps steps in one launch.  One site per thread; the populations that
+// leave the sites stay in LDS from one step to the next (rounded to storage,
+// as a store would), the outer sites of the workgroup go out of date by
+// a.reach per step and are not written.  A small tube is bound by latency: one
+// step per launch cost 6.5 us, of which a launch, the first load and the
+// reduction are 5; kept in LDS a step costs its arithmetic and one or two
+// barriers.  The sums, the mask and Delta S' belong to the last step alone.
 template <class T, int QE, int DS, int BC, bool ELBM = false>
-__global__ void __launch_bounds__(kThreads) k_step1d(StepArgs a)
+__global__ void __launch_bounds__(k1DMaxThreads) k_step1d(StepArgs a)
 {
     using A = typename Store<T>::A;
     constexpr int LAT = kD1Q3;
-    constexpr int Q = Lat<LAT>::Q;
-    __shared__ A ds[kThreads];
-    __shared__ double red[4 * kNStat];
+    using L = Lat<LAT>;
+    constexpr int Q = L::Q;
+    __shared__ T leaving[2][Q][k1DMaxThreads];
+    __shared__ A ds[k1DMaxThreads];
+    __shared__ double red[k1DMaxThreads / kWave * kNStat];
 
     const int tidx = tile_of_block(a, 0);
     const Tile t = a.tiles[tidx];
@@ -1256,76 +1263,106 @@ __global__ void __launch_bounds__(kThreads) k_step1d(StepArgs a)
     const gptr<T> dst = to_global<T>(D.buf[1 - a.parity]);
     const A shift = A(D.shift), c = A(D.c);
     const long long step = a.counter[a.parity];
-    // the index of the next step, read by the next launch (which reads buffer 1 - parity)
-    if (blockIdx.x == 0 && tid == 0) a.counter[1 - a.parity] = step + 1;
+    // the index of the step after this launch, read by the next one (which reads buffer 1 - parity)
+    if (blockIdx.x == 0 && tid == 0) a.counter[1 - a.parity] = step + a.steps;
 
-    const int xr = t.x0 - 1 + tid;
-    const bool inside = BC == kPeriodic ? true : (xr >= 0 && xr < nx);
+    const int halo = a.reach * a.steps;
+    const int xr = t.x0 - halo + tid;
+    const bool used = xr < t.x1 + halo;
+    const bool inside = used && (BC == kPeriodic || (xr >= 0 && xr < nx));
     const int x = BC == kPeriodic ? wrapi(xr, nx) : xr;
-    const bool owned = tid >= 1 && tid <= kThreads - 2 && xr >= t.x0 && xr < t.x1;
+    const bool owned = inside && xr >= t.x0 && xr < t.x1;
+    // neighbours in the workgroup (at its ends a site stands in for the
+    // missing one: nothing that is written depends on it)
+    const int last_tid = int(blockDim.x) - 1;
+    const int tl = tid > 0 ? tid - 1 : 0, tr = tid < last_tid ? tid + 1 : last_tid;
 
     Acc acc;
     A g[Q];
     SiteState<LAT, A> S;
     SiteScalars sc;
-    A dsv = A(0);
-    if (inside) {
-        gather1d<BC>(src, plane, nx, x, g);
-        collide_site<LAT, QE, DS, ELBM>(g, shift, c, S, sc, owned);
-        dsv = S.dpost;
-        if (owned) {
-            acc.moments(sc);
-            acc.fluid_site(sc, S.dpost);
-            if (a.flags & kFlagEntropy) {
-                const double e = entropy_site<LAT>(g, shift);
-                if (isfinite(e)) acc.ent += e;
-            }
-            if (x == D.probe_x) {
-                const gptr<float> p = to_global<float>(D.probe) + 2 * (step % D.probe_cap);
-                p[0] = sc.ux;
-                p[1] = 0.0f;
-            }
-        }
-    }
-    ds[tid] = dsv;
-    __syncthreads();
-    if (owned) {
-        unsigned mask = 0;
-        const bool has_med = (D.limiter & kLimMedian) && (BC == kPeriodic || (x >= 1 && x <= nx - 2));
-        const A med = has_med ? med3(ds[tid - 1], ds[tid], ds[tid + 1]) : A(0);
-        A tgt;
-        A phi = limiter_phi(S.dpost, has_med, med, D, mask, tgt);
-        if constexpr (DS == kExact) {
-            if (D.homothety && phi > A(0) && tgt < A(__builtin_huge_val()) && isfinite(S.dpost))
-                phi = exact_homothety<LAT>(S, shift, tgt, S.dpost);
-        }
-        if (S.posrule) {
-            mask |= kMaskPos;
-            ++acc.pos;
-        }
-        if (D.limiter & kLimPos) {
-            const A pp = positivity_phi<LAT>(S, shift);
-            if (pp < A(1)) {
-                mask |= kMaskPos;
-                ++acc.pos;
-                phi = fmin(phi, pp);
+    if (inside) gather1d<BC>(src, plane, nx, x, g);
+    for (int n = 0; n < a.steps; ++n) {
+        const bool last = n == a.steps - 1;
+        A dsv = A(0);
+        if (inside) {
+            collide_site<LAT, QE, DS, ELBM>(g, shift, c, S, sc, owned && last);
+            dsv = S.dpost;
+            if (owned) {
+                if (last) {
+                    acc.moments(sc);
+                    acc.fluid_site(sc, S.dpost);
+                    if (a.flags & kFlagEntropy) {
+                        const double e = entropy_site<LAT>(g, shift);
+                        if (isfinite(e)) acc.ent += e;
+                    }
+                }
+                if (x == D.probe_x) {
+                    const gptr<float> p = to_global<float>(D.probe) + 2 * ((step + n) % D.probe_cap);
+                    p[0] = sc.ux;
+                    p[1] = 0.0f;
+                }
             }
         }
-        const A k = phi * S.c;
+        const bool median = D.limiter & kLimMedian;
+        if (median) {
+            ds[tid] = dsv;
+            __syncthreads();
+        }
+        if (inside) {
+            unsigned mask = 0;
+            const bool has_med = median && (BC == kPeriodic || (x >= 1 && x <= nx - 2));
+            const A med = has_med ? med3(ds[tl], ds[tid], ds[tr]) : A(0);
+            A tgt;
+            A phi = limiter_phi(S.dpost, has_med, med, D, mask, tgt);
+            if constexpr (DS == kExact) {
+                if (D.homothety && phi > A(0) && tgt < A(__builtin_huge_val()) && isfinite(S.dpost))
+                    phi = exact_homothety<LAT>(S, shift, tgt, S.dpost);
+            }
+            bool pos = S.posrule;
+            if (D.limiter & kLimPos) {
+                const A pp = positivity_phi<LAT>(S, shift);
+                if (pp < A(1)) {
+                    pos = true;
+                    if (last && owned) ++acc.pos;
+                    phi = fmin(phi, pp);
+                }
+            }
+            if (pos) mask |= kMaskPos;
+            const A k = phi * S.c;
+            if (!last) {
 #pragma unroll
-        for (int i = 0; i < Q; ++i) Store<T>::st(dst + i * plane + x, S.gs[i] - k * S.d[i]);
-        if (mask & kMaskTrim) ++acc.trim;
-        if (mask & kMaskMedian) ++acc.filt;
-        if (phi < A(1) && isfinite(S.dpost)) acc.lim += double(S.dpost - delta_s_scaled<LAT, DS>(S, shift, S.c, phi));
-        if (sc.nonpos) mask |= kMaskNonpos;
-        if (a.flags & kFlagRecord) {
-            to_global<unsigned char>(D.mask)[x] = (unsigned char)mask;
-            to_global<double>(D.dS)[x] = double(S.dpost);
+                for (int i = 0; i < Q; ++i) st_shared<T>(&leaving[n & 1][i][tid], S.gs[i] - k * S.d[i]);
+            } else if (owned) {
+                if (S.posrule) ++acc.pos;
+#pragma unroll
+                for (int i = 0; i < Q; ++i) Store<T>::st(dst + i * plane + x, S.gs[i] - k * S.d[i]);
+                if (mask & kMaskTrim) ++acc.trim;
+                if (mask & kMaskMedian) ++acc.filt;
+                if (phi < A(1) && isfinite(S.dpost))
+                    acc.lim += double(S.dpost - delta_s_scaled<LAT, DS>(S, shift, S.c, phi));
+                if (sc.nonpos) mask |= kMaskNonpos;
+                if (a.flags & kFlagRecord) {
+                    to_global<unsigned char>(D.mask)[x] = (unsigned char)mask;
+                    to_global<double>(D.dS)[x] = double(S.dpost);
+                }
+                if (D.limiter & kLimEns) {
+                    // for the ensemble pass: Delta S' and the factor applied here
+                    Store<A>::st(to_global<A>(D.dsbuf) + x, S.dpost);
+                    Store<A>::st(to_global<A>(D.phibuf) + x, phi);
+                }
+            }
         }
-        if (D.limiter & kLimEns) {
-            // for the ensemble pass: Delta S' and the factor applied here
-            Store<A>::st(to_global<A>(D.dsbuf) + x, S.dpost);
-            Store<A>::st(to_global<A>(D.phibuf) + x, phi);
+        if (last) break;
+        // two buffers in turn: one barrier per step
+        __syncthreads();
+        if (inside) {
+#pragma unroll
+            for (int i = 0; i < Q; ++i) {
+                const bool off = BC != kPeriodic && L::vx(i) != 0 && x == (L::vx(i) > 0 ? 0 : nx - 1);
+                const int from = L::vx(i) == 0 ? tid : (L::vx(i) > 0 ? tl : tr);
+                g[i] = off ? ld_shared<T>(&leaving[n & 1][L::opp(i)][tid]) : ld_shared<T>(&leaving[n & 1][i][from]);
+            }
         }
     }
     store_partial(acc, partial_slot(a, 0, tidx), red);
@@ -1471,9 +1508,9 @@ hipError_t LBM_CAT(launch_step1d, LBM_SUFFIX)(int qe, int ds, int bc, const Step
                                              hipStream_t s)
 {
     if (kernel == 0)
-        LBM_DISPATCH(k_step1d, 0, 2, dim3(a.ntiles), dim3(kThreads), 0, s, a);
+        LBM_DISPATCH(k_step1d, 0, 2, dim3(a.ntiles), dim3(threads1d(a.reach, a.steps)), 0, s, a);
     else if (kernel == 2)
-        LBM_DISPATCH_ELBM(k_step1d, 0, 2, dim3(a.ntiles), dim3(kThreads), 0, s, a);
+        LBM_DISPATCH_ELBM(k_step1d, 0, 2, dim3(a.ntiles), dim3(threads1d(a.reach, a.steps)), 0, s, a);
     else
         LBM_DISPATCH(k_ens1d, 0, 2, dim3(a.ntiles), dim3(kThreads), 0, s, a);
     return hipGetLastError();
