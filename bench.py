@@ -60,7 +60,7 @@ BYTES_PER_SITE = {0: 144, 1: 72, 2: 36, 3: 36}     # read Q + write Q population
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "traffic_collide2d_f32_4096.json")
 KERNEL_SOURCES = ["paper_0704_0043_amd/csrc/step.hip", "paper_0704_0043_amd/csrc/lbm_device.h",
                   "paper_0704_0043_amd/csrc/lbm_common.h"]
-DOMINANT = "k_collide2d<float, 0, 1, 0, false>"
+DOMINANT = "k_collide2d<float, 0, 1, 0, false, false>"
 COPY_BYTES = 1 << 30
 
 
@@ -632,7 +632,7 @@ def main():
         # the roofline object is defined for the headline's collision kernel;
         # these workloads are reported by kernel time only
         if args.workload == "elbm":
-            out["kernels"]["dominant"] = "k_collide2d<float, 1, 1, 0, true>"
+            out["kernels"]["dominant"] = "k_collide2d<float, 1, 1, 0, true, false>"
         out["roofline"] = None
         out["note"] = "not the headline workload: kernel times only (no roofline, no traffic record)"
     if default and not args.no_active:

@@ -166,7 +166,7 @@ struct DomainHost {
 struct Layout {
     size_t off_dom = 0, off_tiles = 0, off_partials = 0, off_counter = 0, off_stage = 0, total = 0;
     size_t off_dom_alt = 0, off_tiles_alt = 0, off_adapt = 0;   // LBM_RUN_ADAPTIVE only
-    size_t off_rows = 0, off_rowpart = 0, off_groups = 0;
+    size_t off_rows = 0, off_rowpart = 0, off_above = 0, off_groups = 0;
     int max_tiles = 0, nrows = 0, ngroups = 0;
     size_t max_n = 0;
 };
@@ -227,6 +227,7 @@ struct lbm_ctx {
     std::vector<RowBlock> rows_host;
     std::vector<Tile> groups_host;
     int cap_h = kMaxTileH;      // tallest second-pass tile of these domains (second_height)
+    int nblocks = 0;            // D2Q9 row blocks of all domains (the collision grid)
     int narrow = 1;             // row blocks of 64 / 128 columns for narrow domains
     int tuned = 0;              // 1 when the tile shape was chosen by timing
 
@@ -236,6 +237,7 @@ struct lbm_ctx {
     RowBlock* d_rows() const { return reinterpret_cast<RowBlock*>(ws + lay.off_rows); }
     Tile* d_groups() const { return reinterpret_cast<Tile*>(ws + lay.off_groups); }
     double* d_rowpart() const { return reinterpret_cast<double*>(ws + lay.off_rowpart); }
+    unsigned* d_above() const { return reinterpret_cast<unsigned*>(ws + lay.off_above); }
     double* d_partials() const { return reinterpret_cast<double*>(ws + lay.off_partials); }
     long long* d_counter() const { return reinterpret_cast<long long*>(ws + lay.off_counter); }
     double* d_stage() const { return reinterpret_cast<double*>(ws + lay.off_stage); }
@@ -457,9 +459,11 @@ void plan(std::vector<DomainHost>& dh, const lbm_domain_desc* doms, int32_t nd, 
     L.off_partials = off;
     off = align_up(off + size_t(4) * L.max_tiles * kNStat * sizeof(double), kAlign);
     L.off_rows = off;
-    off = align_up(off + size_t(L.nrows) * sizeof(RowBlock), kAlign);
+    if (nd > 1) off = align_up(off + size_t(L.nrows) * sizeof(RowBlock), kAlign);
     L.off_rowpart = off;
     off = align_up(off + size_t(L.nrows) * kNStat * sizeof(double), kAlign);
+    L.off_above = off;
+    off = align_up(off + size_t(L.nrows) * sizeof(unsigned), kAlign);
     L.off_counter = off;
     off = align_up(off + 2 * sizeof(long long), kAlign);
     L.off_stage = off;
@@ -496,6 +500,7 @@ std::vector<Tile> build_tiles(lbm_ctx* ctx, int th, bool fused)
 void build_rows(lbm_ctx* ctx, int narrow)
 {
     ctx->rows_host.clear();
+    ctx->nblocks = 0;
     ctx->narrow = narrow;
     if (ctx->lattice != LBM_D2Q9) return;
     int part = 0;
@@ -506,7 +511,9 @@ void build_rows(lbm_ctx* ctx, int narrow)
         part += h.row_count;
         const int width = seg_width(h.d.nx, narrow);
         const int nb = blocks_of(h.d.nx, h.d.ny, width);
-        for (int i = 0; i < nb; ++i) ctx->rows_host.push_back(block_entry2d(int(k), h.d.nx, h.d.ny, width, i));
+        ctx->nblocks += nb;
+        if (ctx->dom.size() > 1)      // a single domain's blocks are computed (block_of)
+            for (int i = 0; i < nb; ++i) ctx->rows_host.push_back(block_entry2d(int(k), h.d.nx, h.d.ny, width, i));
     }
 }
 
@@ -615,6 +622,17 @@ int set_tiles(lbm_ctx* ctx, int th, bool fused = false)
     return LBM_OK;
 }
 
+// the row blocks of a single D2Q9 domain as a grid (several domains: the table)
+void set_grid(StepArgs& a, const lbm_domain_desc* d, int narrow)
+{
+    a.width = a.row_shift = a.grid_x = a.grid_y = 0;
+    if (!d || d->lattice != LBM_D2Q9) return;
+    a.width = seg_width(d->nx, narrow);
+    while ((a.width << a.row_shift) < kThreads) ++a.row_shift;
+    a.grid_x = (d->nx + a.width - 1) / a.width;
+    a.grid_y = (d->ny + (1 << a.row_shift) - 1) >> a.row_shift;
+}
+
 StepArgs step_args(const lbm_ctx* ctx, int parity)
 {
     StepArgs a;
@@ -629,11 +647,14 @@ StepArgs step_args(const lbm_ctx* ctx, int parity)
     a.dense = ctx->dense;
     a.fused = ctx->act.fused ? 1 : 0;
     a.rows = ctx->d_rows();
-    a.nrows = int(ctx->rows_host.size());
+    a.nrows = ctx->nblocks;
+    a.nparts = ctx->lay.nrows;
+    set_grid(a, ctx->dom.size() == 1 ? &ctx->dom[0].d : nullptr, ctx->narrow);
     a.groups = ctx->d_groups();
     a.ngroups = ctx->lay.ngroups;
     a.pstride = ctx->lay.max_tiles;
     a.rowpart = ctx->d_rowpart();
+    a.above = ctx->d_above();
     a.parity = parity;
     a.flags = ctx->flags & (LBM_RUN_RECORD | LBM_RUN_ENTROPY);
     a.partials = ctx->d_partials();
@@ -691,10 +712,12 @@ StepKind step_kind(const lbm_ctx* ctx)
                     ctx->ens_pass, ctx->budget, ctx->dense, ctx->act.fused};
 }
 
-int launch_one(lbm_ctx* ctx, int parity, hipEvent_t* ev = nullptr, unsigned extra_flags = 0, int steps = 1)
+// stats: the step's sums may be read (an ensemble limiter needs them anyway)
+int launch_one(lbm_ctx* ctx, int parity, bool stats, hipEvent_t* ev = nullptr, unsigned extra_flags = 0, int steps = 1)
 {
     StepArgs a = step_args(ctx, parity);
     a.flags |= extra_flags;
+    if (stats || ctx->ens_pass) a.flags |= kFlagStats;
     a.steps = steps;
     const hipError_t e = launch_step(step_kind(ctx), a, ctx->stream, ev);
     if (e != hipSuccess) return fail(ctx, LBM_EDEVICE, std::string("step launch: ") + hipGetErrorString(e));
@@ -781,9 +804,9 @@ int time_shape(lbm_ctx* ctx, int n, double& ms, unsigned extra_flags = 0)
     hipEvent_t e0 = nullptr, e1 = nullptr;
     int rc = LBM_OK;
     if (hipEventCreate(&e0) != hipSuccess || hipEventCreate(&e1) != hipSuccess) rc = fail(ctx, LBM_EDEVICE, "event");
-    if (!rc) rc = launch_one(ctx, 0, nullptr, extra_flags);   // untimed: first launch of this shape
+    if (!rc) rc = launch_one(ctx, 0, false, nullptr, extra_flags);   // untimed: first launch of this shape
     if (!rc && hipEventRecord(e0, ctx->stream) != hipSuccess) rc = fail(ctx, LBM_EDEVICE, "event record");
-    for (int k = 0; k < n && !rc; ++k) rc = launch_one(ctx, 0, nullptr, extra_flags);
+    for (int k = 0; k < n && !rc; ++k) rc = launch_one(ctx, 0, false, nullptr, extra_flags);
     float t = 0;
     if (!rc && (hipEventRecord(e1, ctx->stream) != hipSuccess || hipEventSynchronize(e1) != hipSuccess ||
                 hipEventElapsedTime(&t, e0, e1) != hipSuccess))
@@ -884,7 +907,7 @@ int capture(lbm_ctx* ctx, int parity, int64_t len)
     int rc = LBM_OK;
     for (int64_t k = 0; k < len && rc == LBM_OK;) {
         const int n = ctx->lattice == LBM_D1Q3 ? next_launch(len - k, ctx->most1d) : 1;
-        rc = launch_one(ctx, int((parity + k) % 2), nullptr, 0, n);
+        rc = launch_one(ctx, int((parity + k) % 2), k + n == len, nullptr, 0, n);
         k += n;
     }
     hipError_t e = hipStreamEndCapture(ctx->stream, &g);
@@ -1032,8 +1055,8 @@ int read_stats(lbm_ctx* ctx, int32_t d, lbm_entropy_stats_t* out)
 // Layout of lbm_step_static's arrays in the static scratch array: one
 // domain, tight planes (plane = nx ny), no record planes, no probe.
 struct StaticLayout {
-    size_t off_dom = 0, off_tiles = 0, off_groups = 0, off_rows = 0, off_partials = 0, off_rowpart = 0,
-           off_counter = 0, total = 0;
+    size_t off_dom = 0, off_tiles = 0, off_groups = 0, off_partials = 0, off_rowpart = 0,
+           off_above = 0, off_counter = 0, total = 0;
     int th = 0, ntiles = 0, ngroups = 0, nblocks = 0, nparts = 0;
 };
 
@@ -1068,12 +1091,12 @@ void plan_static(const lbm_domain_desc& d, int storage, int th, DomainHost& h, S
         L.off_groups = off;
         off = align_up(off + size_t(L.ngroups) * sizeof(Tile), kAlign);
     }
-    L.off_rows = off;
-    off = align_up(off + size_t(L.nblocks) * sizeof(RowBlock), kAlign);
     L.off_partials = off;
     off = align_up(off + size_t(4) * L.ntiles * kNStat * sizeof(double), kAlign);
     L.off_rowpart = off;
     off = align_up(off + size_t(L.nparts) * kNStat * sizeof(double), kAlign);
+    L.off_above = off;
+    off = align_up(off + size_t(L.nparts) * sizeof(unsigned), kAlign);
     L.off_counter = off;
     off = align_up(off + 2 * sizeof(long long), kAlign);
     L.total = plan_extras(h, storage, off);
@@ -1310,7 +1333,7 @@ int lbm_step(lbm_ctx* ctx, int64_t n_steps)
                 break;
             }
         if (done == 0) {
-            if ((rc = launch_one(ctx, parity))) return rc;
+            if ((rc = launch_one(ctx, parity, limit == 1))) return rc;
             done = 1;
         }
         ctx->steps_done += done;
@@ -1463,7 +1486,7 @@ int lbm_kernel_times(lbm_ctx* ctx, int64_t n_steps, double* ms)
             break;
         }
     for (int64_t k = 0; k < n_steps && rc == LBM_OK; ++k) {
-        rc = launch_one(ctx, int(ctx->steps_done % 2), &ev[size_t(3 * k)]);
+        rc = launch_one(ctx, int(ctx->steps_done % 2), k + 1 == n_steps, &ev[size_t(3 * k)]);
         if (rc == LBM_OK) ++ctx->steps_done;
     }
     double t[2] = {0, 0};
@@ -1523,11 +1546,9 @@ int lbm_step_static(const lbm_domain_desc* domain, int32_t storage, void* stream
     const DomainDev dd = make_dev(h, base, f0, f1, 1, 0);
     DomainDev* dom = reinterpret_cast<DomainDev*>(base + L.off_dom);
     Tile* tiles = reinterpret_cast<Tile*>(base + L.off_tiles);
-    RowBlock* rows = reinterpret_cast<RowBlock*>(base + L.off_rows);
     long long* counter = reinterpret_cast<long long*>(base + L.off_counter);
     Tile* groups = reinterpret_cast<Tile*>(base + L.off_groups);
-    e = launch_static_setup(dd, domain->lattice, dom, tiles, L.ntiles, L.th, groups, L.ngroups, rows, L.nblocks, counter,
-                            s);
+    e = launch_static_setup(dd, domain->lattice, dom, tiles, L.ntiles, L.th, groups, L.ngroups, counter, s);
     if (e != hipSuccess) return fail(nullptr, LBM_EDEVICE, std::string("static setup: ") + hipGetErrorString(e));
     StepKind k;
     k.storage = storage;
@@ -1553,12 +1574,15 @@ int lbm_step_static(const lbm_domain_desc* domain, int32_t storage, void* stream
     a.elbm = k.elbm ? 1 : 0;
     a.budget = k.budget;
     a.dense = k.dense;
-    a.rows = rows;
+    a.rows = nullptr;
     a.nrows = L.nblocks;
+    a.nparts = L.nparts;
+    set_grid(a, domain, 1);
     a.groups = groups;
     a.ngroups = L.ngroups;
     a.pstride = L.ntiles;
     a.rowpart = reinterpret_cast<double*>(base + L.off_rowpart);
+    a.above = reinterpret_cast<unsigned*>(base + L.off_above);
     a.counter = counter;
     const bool d1 = domain->lattice == LBM_D1Q3;
     const int most = d1 ? max_steps1d(domain, 1) : 1;
@@ -1566,6 +1590,7 @@ int lbm_step_static(const lbm_domain_desc* domain, int32_t storage, void* stream
     for (int64_t t = 0; t < n_steps && e == hipSuccess;) {
         a.parity = int(t % 2);
         a.steps = most > 1 ? next_launch(n_steps - t, most) : 1;
+        a.flags = k.ens_pass || (stats && t + a.steps == n_steps) ? kFlagStats : 0;
         e = launch_step(k, a, s);
         t += a.steps;
     }

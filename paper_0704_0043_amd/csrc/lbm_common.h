@@ -23,7 +23,9 @@ enum { kF64 = 0, kF32 = 1, kF16 = 2, kBF16 = 3 };
 enum : unsigned { kMaskTrim = 1, kMaskMedian = 2, kMaskNonpos = 4, kMaskNotFluid = 8, kMaskEns = 16, kMaskPos = 32 };
 // kFlagAllTiles makes the second pass walk every tile, as if each had a
 // candidate; only the tuner sets it, to time that pass's full work.
-enum : unsigned { kFlagRecord = 1, kFlagEntropy = 2, kFlagAllTiles = 4 };
+// kFlagStats: the step's sums will be read (the last step of a captured
+// sequence or of a call, and every step with an ensemble-dependent limiter).
+enum : unsigned { kFlagRecord = 1, kFlagEntropy = 2, kFlagAllTiles = 4, kFlagStats = 8 };
 
 constexpr int kThreads = 256;      // workgroup size of the step kernels (= D2Q9 tile width)
 constexpr int kWave = 64;          // wavefront size (CDNA)
@@ -36,8 +38,7 @@ enum {
     kSJx, kSJy,
     kSDpre, kSDpost, kSMax, kSLim, kSEnt,
     kSTrim, kSFilt, kSNonpos, kSNonfin, kSFluid,
-    kSAbove,      // median candidates (Delta S' > delta_median); in a collision partial: bit w set
-                  // when wave w of the segment holds one (that wave stored its Delta S')
+    kSUnused,
     kSEns,        // nodes an ensemble-dependent limiter moved
     kSPos         // nodes the positivity rule moved (limiter, or ELBM without a root)
 };
@@ -235,10 +236,16 @@ struct StepArgs {
     int ens_pass;           // 1 if some domain has an ensemble-dependent limiter
     int elbm;               // 1 with ELBM collisions (all domains)
     int budget;             // kSelect* of the domains: budget threshold, top-k trimming
-    const RowBlock* rows;   // D2Q9 row blocks in row-major order, one per collision workgroup
-    int nrows;              // the D2Q9 collision grid has nrows blocks
-    double* rowpart;        // [rows x strips][kNStat]: collision partials of the last step, one
-                            // per domain row and 256-column strip
+    const RowBlock* rows;   // D2Q9 row blocks in row-major order, one per collision workgroup; several
+                            // domains only (a single one's follow from the block's place in the grid)
+    int width, row_shift;   // single domain: columns of its row blocks, log2 of their rows (width 0: table)
+    int nrows;              // blocks of the D2Q9 collision grid (table)
+    int grid_x, grid_y;     // ... and its shape for a single domain
+    int nparts;             // row partials (rows x strips) of all domains
+    double* rowpart;        // [rows x strips][kNStat]: collision partials of a step with kFlagStats,
+                            // one per domain row and 256-column strip
+    unsigned* above;        // [rows x strips]: byte w is 1 when the 64-column wave w of the segment holds
+                            // a median candidate (Delta S' > delta_median) and stored its Delta S'
     long long* counter;     // [2] step index by parity
     int reach = 1;          // D1Q3: sites a step's result depends on, on either side
     int steps = 1;          // D1Q3: steps of this launch (odd)
@@ -250,8 +257,7 @@ constexpr size_t kStaticScratchBytes = LBM_STATIC_SCRATCH_BYTES;
 // its address on `device` (looked up once per device; `device` must be current)
 hipError_t static_scratch(int device, char** ptr);
 hipError_t launch_static_setup(const DomainDev& dd, int lattice, DomainDev* dom, Tile* tiles, int ntiles, int th,
-                               Tile* groups, int ngroups, RowBlock* rows, int nrows, long long* counter,
-                               hipStream_t s);
+                               Tile* groups, int ngroups, long long* counter, hipStream_t s);
 hipError_t launch_static_stats(const DomainDev* dom, double shift_mass, double* out, hipStream_t s);
 
 // Launchers (one per storage type / lattice), defined in the .hip files.

@@ -844,7 +844,7 @@ template <class S, class SL = S>
 struct AccT {
     S mass = 0, jx = 0, jy = 0, dpre = 0, dpost = 0, ent = 0, maxd = 0;
     SL lim = 0;
-    int trim = 0, filt = 0, nonpos = 0, nonfin = 0, fluid = 0, above = 0, ens = 0, pos = 0;
+    int trim = 0, filt = 0, nonpos = 0, nonfin = 0, fluid = 0, ens = 0, pos = 0;
 
     __device__ void moments(const SiteScalars& s)
     {
@@ -875,7 +875,7 @@ __device__ inline void store_partial(const AccT<S, SL>& acc, double* out, double
 {
     double v[kNStat] = {double(acc.mass), double(acc.jx), double(acc.jy), double(acc.dpre), double(acc.dpost),
                         double(acc.maxd), double(acc.lim), double(acc.ent), double(acc.trim), double(acc.filt),
-                        double(acc.nonpos), double(acc.nonfin), double(acc.fluid), double(acc.above),
+                        double(acc.nonpos), double(acc.nonfin), double(acc.fluid), 0.0,
                         double(acc.ens), double(acc.pos)};
 #pragma unroll
     for (int off = 32; off >= 1; off >>= 1) {
@@ -916,7 +916,7 @@ __device__ inline void store_partial_rows(const AccT<S>& acc, double* out, doubl
     }
     double v[kNStat] = {double(acc.mass), double(acc.jx), double(acc.jy), double(acc.dpre), double(acc.dpost),
                         double(acc.maxd), double(acc.lim), double(acc.ent), double(acc.trim), double(acc.filt),
-                        double(acc.nonpos), double(acc.nonfin), double(acc.fluid), double(acc.above),
+                        double(acc.nonpos), double(acc.nonfin), double(acc.fluid), 0.0,
                         double(acc.ens), double(acc.pos)};
 #pragma unroll
     for (int off = 32; off >= 1; off >>= 1) {
@@ -958,9 +958,7 @@ __device__ inline void store_partial_rows(const AccT<S>& acc, double* out, doubl
 // for reduced storage, FP64 for FP64 storage) by a fixed DPP scan in each
 // wave (the limiter and entropy sums only in waves that hold one), the 0/1
 // counts by ballots; then for each row its waves combined in FP64 in order,
-// written to out + r * stride (r < nrow).  kSAbove is a bit mask there: bit
-// w is set when wave w of the row holds a node above the median tolerance
-// (the median pass reads which waves stored Delta S').
+// written to out + r * stride (r < nrow).
 template <class S>
 __device__ inline void node_partial_rows(const AccT<S>& acc, double* out, long long stride, int wpr, int nrow,
                                          double* lds /* [4 * kNStat] */)
@@ -979,8 +977,7 @@ __device__ inline void node_partial_rows(const AccT<S>& acc, double* out, long l
     auto count = [](bool b) { return double(unsigned(__popcll(__ballot(b)))); };
     const double cnt[8] = {count(acc.trim != 0), count(acc.filt != 0), count(acc.nonpos != 0),
                            count(acc.nonfin != 0), count(acc.fluid != 0),
-                           __ballot(acc.above != 0) ? double(1u << (unsigned(wave) & unsigned(wpr - 1))) : 0.0,
-                           count(acc.ens != 0), count(acc.pos != 0)};
+                           0.0, count(acc.ens != 0), count(acc.pos != 0)};
     if (lane == 63) {
 #pragma unroll
         for (int k = 0; k < 8; ++k) lds[wave * kNStat + k] = double(v[k]);

@@ -43,11 +43,10 @@ hipError_t static_scratch(int device, char** ptr)
 // step counters, the stats and the selection histogram.
 __global__ void __launch_bounds__(kThreads) k_static_setup(DomainDev dd, int lattice, DomainDev* dom, Tile* tiles,
                                                            int ntiles, int th, Tile* groups, int ngroups,
-                                                           RowBlock* rows, int nrows, long long* counter)
+                                                           long long* counter)
 {
-    const int width = seg_width(dd.nx, 1);
     const int nb = dd.bhist ? kBudgetBuckets : 0;
-    const int n = max(max(ntiles, nrows), max(nb, kNStat + 1));
+    const int n = max(ntiles, max(nb, kNStat + 1));
     for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) {
         if (i == 0) {
             *dom = dd;
@@ -59,7 +58,6 @@ __global__ void __launch_bounds__(kThreads) k_static_setup(DomainDev dd, int lat
             tiles[i] = lattice == kD2Q9 ? tile_entry2d(0, dd.nx, dd.ny, th, i) : tile_entry1d(0, dd.nx, i);
         if (groups != tiles && i < ngroups)
             groups[i] = lattice == kD2Q9 ? tile_entry2d(0, dd.nx, dd.ny, kMaxTileH, i) : tile_entry1d(0, dd.nx, i);
-        if (i < nrows) rows[i] = block_entry2d(0, dd.nx, dd.ny, width, i);
         if (i < nb) dd.bhist[i] = BudgetBucket{0, 0, 0};
     }
 }
@@ -89,12 +87,12 @@ __global__ void k_static_stats(const DomainDev* dom, double shift_mass, double* 
 }
 
 hipError_t launch_static_setup(const DomainDev& dd, int lattice, DomainDev* dom, Tile* tiles, int ntiles, int th,
-                               Tile* groups, int ngroups, RowBlock* rows, int nrows, long long* counter, hipStream_t s)
+                               Tile* groups, int ngroups, long long* counter, hipStream_t s)
 {
-    const int n = std::max(std::max(ntiles, nrows), std::max(kBudgetBuckets, kNStat + 1));
+    const int n = std::max(ntiles, dd.bhist ? kBudgetBuckets : kNStat + 1);
     const int blocks = std::min((n + kThreads - 1) / kThreads, 1024);
     hipLaunchKernelGGL(k_static_setup, dim3(blocks), dim3(kThreads), 0, s, dd, lattice, dom, tiles, ntiles, th,
-                       groups, ngroups, rows, nrows, counter);
+                       groups, ngroups, counter);
     return hipGetLastError();
 }
 

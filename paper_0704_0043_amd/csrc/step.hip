@@ -78,6 +78,24 @@ __device__ inline double* partial_slot(const StepArgs& a, int set, int tile)
     return a.partials + (((long long)a.parity * 2 + set) * a.pstride + tile) * kNStat;
 }
 
+// Row block of a workgroup: its place in the grid with one domain (row_grid),
+// else looked up.
+constexpr int kGridRows = 32768;     // grid rows per grid plane
+__device__ __forceinline__ RowBlock block_of(const StepArgs& a)
+{
+    if (a.width == 0) return a.rows[blockIdx.x];
+    const int nx = a.dom[0].nx, ny = a.dom[0].ny;
+    const int x0 = int(blockIdx.x) * a.width, y0 = (int(blockIdx.z) * kGridRows + int(blockIdx.y)) << a.row_shift;
+    const int x1 = x0 + a.width, y1 = y0 + (1 << a.row_shift);
+    return RowBlock{0, x0, x1 < nx ? x1 : nx, y0, y1 < ny ? y1 : ny, a.width};
+}
+__device__ __forceinline__ bool first_block() { return (blockIdx.x | blockIdx.y | blockIdx.z) == 0; }
+static dim3 row_grid(const StepArgs& a)
+{
+    if (a.width == 0) return dim3(a.nrows);
+    return a.grid_y <= kGridRows ? dim3(a.grid_x, a.grid_y) : dim3(a.grid_x, kGridRows, (a.grid_y + kGridRows - 1) / kGridRows);
+}
+
 // trimming factor of one node (it depends on the node alone, Sec. 3.2/3.4)
 template <class A, class DD>
 __device__ __forceinline__ A trim_phi(const DD& D, A dpost, unsigned& mask)
@@ -238,42 +256,46 @@ __device__ __attribute__((noinline)) A exact_homothety_call(SiteState<kD2Q9, A> 
     return exact_homothety<kD2Q9>(o, shift, t, o.dpost);
 }
 
-template <class T, int QE, int DS, int BC, bool ELBM = false>
+// STATS: a step whose sums will be read.  The others (63 of 64 in a long run)
+// leave the sums out, and with them a third of the instructions, the barrier
+// and the partial at the end of every workgroup.
+template <class T, int QE, int DS, int BC, bool ELBM, bool STATS>
 __global__ void __launch_bounds__(kThreads) k_collide2d(StepArgs a)
 {
     using A = typename Store<T>::A;
     using L = Lat<kD2Q9>;
     constexpr int Q = 9;
-    __shared__ double red[4 * kNStat];
+    __shared__ double red[STATS ? 4 * kNStat : 1];
     // one row block per workgroup, in row-major order: the grid streams
     // through the domain a few rows at a time (DRAM pages and the rows that
     // neighbours pull from stay few), one node per thread; a block of a
     // narrow domain holds kThreads / width of its rows
-    const int ridx = int(blockIdx.x);
-    const RowBlock t = a.rows[ridx];
+    const RowBlock t = block_of(a);
     const DomainDev& D = a.dom[t.domain];
+    if (t.y0 >= t.y1) return;          // a grid of several planes ends past the last row
     const int nx = D.nx, ny = D.ny;
     const long long plane = D.plane;
     const gptr<const T> src = to_global<T>(static_cast<const void*>(D.buf[a.parity]));
     const gptr<T> dst = to_global<T>(D.buf[1 - a.parity]);
     const gptr<A> dsb = to_global<A>(D.dsbuf);
     const A shift = A(D.shift), c = A(D.c);
-    const bool record = a.flags & kFlagRecord;
-    const bool want_ent = a.flags & kFlagEntropy;
+    const bool record = STATS && (a.flags & kFlagRecord);
+    const bool want_ent = STATS && (a.flags & kFlagEntropy);
     const bool keep_ds = D.limiter & (kLimMedian | kLimEns);
     const bool dense = !ELBM && D.dense;       // k_form2d stores the fluid nodes
     const long long step = a.counter[a.parity];
     // the index of the next step, read by the next launch (which reads buffer 1 - parity)
-    if (ridx == 0 && threadIdx.x == 0) a.counter[1 - a.parity] = step + 1;
+    if (first_block() && threadIdx.x == 0) a.counter[1 - a.parity] = step + 1;
 
     // The ensemble limiters and the GATE reading of the median use every
     // Delta S'.  The FLOOR median only needs the values above delta: its
     // threshold max(median, delta) and its decision are unchanged when every
     // value at or below delta is replaced by 0.  So there a wave with no node
     // above delta stores nothing, and the median pass reads its 64 columns as
-    // zeros (the segment's partial records which waves stored).
+    // zeros (a.above records which waves stored).
     const bool every = (D.limiter & kLimEns) || D.median_mode != 0;
     AccT<A> acc;
+    bool any_up = false;       // a fluid node of the wave is a median candidate
     // the node (cl.x, y) of this thread
     auto visit = [&](const int y, const Cols<T, BC>& cl) {
         {
@@ -285,9 +307,11 @@ __global__ void __launch_bounds__(kThreads) k_collide2d(StepArgs a)
             if (cls == kNodeFluid) {
                 SiteState<kD2Q9, A> S;
                 SiteScalars sc;
-                collide_site<kD2Q9, QE, DS, ELBM>(g, shift, c, S, sc, true);
-                acc.moments(sc);
-                acc.fluid_site(sc, S.dpost);
+                collide_site<kD2Q9, QE, DS, ELBM>(g, shift, c, S, sc, STATS);
+                if constexpr (STATS) {
+                    acc.moments(sc);
+                    acc.fluid_site(sc, S.dpost);
+                }
                 if (want_ent) {
                     const double e = entropy_site<kD2Q9>(g, shift);
                     if (isfinite(e)) acc.ent += A(e);
@@ -305,13 +329,13 @@ __global__ void __launch_bounds__(kThreads) k_collide2d(StepArgs a)
                 }
                 if (S.posrule) {
                     mask |= kMaskPos;
-                    ++acc.pos;
+                    if constexpr (STATS) ++acc.pos;
                 }
                 if (D.limiter & kLimPos) {
                     const A pp = positivity_phi<kD2Q9>(S, shift);
                     if (pp < A(1)) {
                         mask |= kMaskPos;
-                        ++acc.pos;
+                        if constexpr (STATS) ++acc.pos;
                         phi = fmin(phi, pp);
                     }
                 }
@@ -319,12 +343,15 @@ __global__ void __launch_bounds__(kThreads) k_collide2d(StepArgs a)
                 if (keep_ds) {
                     // NaN counts as above: such a wave always stores its values
                     const bool up = (D.limiter & kLimMedian) && !(S.dpost <= A(D.delta_median));
-                    if (up) acc.above = 1;
-                    if (every || __ballot(up) != 0) Store<A>::st(dsb + node, S.dpost);
+                    any_up = __ballot(up) != 0;
+                    if (every || any_up) Store<A>::st(dsb + node, S.dpost);
                 }
-                if (mask & kMaskTrim) ++acc.trim;
-                if (phi < A(1) && isfinite(S.dpost)) acc.lim += S.dpost - delta_s_scaled<kD2Q9, DS>(S, shift, S.c, phi);
-                if (sc.nonpos) mask |= kMaskNonpos;
+                if constexpr (STATS) {
+                    if (mask & kMaskTrim) ++acc.trim;
+                    if (phi < A(1) && isfinite(S.dpost))
+                        acc.lim += S.dpost - delta_s_scaled<kD2Q9, DS>(S, shift, S.c, phi);
+                    if (sc.nonpos) mask |= kMaskNonpos;
+                }
                 if (record) {
                     to_global<unsigned char>(D.mask)[node] = (unsigned char)mask;
                     to_global<double>(D.dS)[node] = double(S.dpost);
@@ -350,9 +377,11 @@ __global__ void __launch_bounds__(kThreads) k_collide2d(StepArgs a)
                     for (int i = 0; i < Q; ++i)
                         Store<T>::st(at_bytes(dst + (i * plane + row), cl.own), A(L::w(i)) * ((r0 - shift) + r0 * E[i]));
                 }
-                SiteScalars sc;
-                moments_fp64(g, sc.dr, sc.jx, sc.jy);
-                acc.moments(sc);
+                if constexpr (STATS) {
+                    SiteScalars sc;
+                    moments_fp64(g, sc.dr, sc.jx, sc.jy);
+                    acc.moments(sc);
+                }
                 if (record) {
                     to_global<unsigned char>(D.mask)[node] = (unsigned char)kMaskNotFluid;
                     to_global<double>(D.dS)[node] = 0.0;
@@ -374,9 +403,16 @@ __global__ void __launch_bounds__(kThreads) k_collide2d(StepArgs a)
         const Cols<T, BC> cl(t.x0 + lx, nx, t.x0 + lx < t.x1 && y < t.y1);
         if (cl.ok) visit(y, cl);
     }
+    const long long part = (long long)D.row_first + (long long)t.y0 * D.strips + t.x0 / kThreads;
+    if (D.limiter & kLimMedian) {
+        // which waves hold candidates; the lanes of wall nodes do not know
+        const int wpr = t.width / kWave, wave = int(threadIdx.x) / kWave, r = wave / wpr;
+        const bool some = __ballot(any_up) != 0;
+        if ((threadIdx.x & (kWave - 1)) == 0 && t.y0 + r < t.y1)
+            to_global<unsigned char>(a.above + part + (long long)r * D.strips)[wave - r * wpr] = some ? 1 : 0;
+    }
     // one partial per row of the block (row y, strip x0 / kThreads)
-    node_partial_rows(acc, a.rowpart + ((long long)D.row_first + (long long)t.y0 * D.strips + t.x0 / kThreads) * kNStat,
-                      D.strips, t.width / kWave, t.y1 - t.y0, red);
+    if constexpr (STATS) node_partial_rows(acc, a.rowpart + part * kNStat, D.strips, t.width / kWave, t.y1 - t.y0, red);
 }
 
 // Second pass: median filter (Sec. 3.5; cavity stencils of Sec. 4.4) on the
@@ -610,11 +646,11 @@ __device__ __forceinline__ void second_pass2d(const StepArgs& a)
     };
     // FLOOR median only: the 64 columns of a collision wave in which no node
     // exceeded delta hold no Delta S' of this step and read as zeros.  Which
-    // waves stored (bit w of the segment's candidate count) is staged in LDS
+    // waves stored (byte w of the segment's word) is staged in LDS
     // for the tile's rows and halo rows, for its own column strip and the two
     // neighbouring ones: [0] left, [1] own, [2] right.
     const bool sparse = !((D.limiter & kLimEns) || D.median_mode != 0);
-    __shared__ int sflag[3][kMaxTileH + 2];
+    __shared__ unsigned sflag[3][kMaxTileH + 2];
     const int strip = t.x0 / kThreads;
     int strip_l, strip_r;
     if constexpr (BC == kPeriodic) {
@@ -644,12 +680,18 @@ __device__ __forceinline__ void second_pass2d(const StepArgs& a)
         const long long r0 = (long long)D.row_first + (long long)t.y0 * D.strips + t.x0 / kThreads;
         const int rows = t.y1 - t.y0;
         bool cand = false;
+        // (the bytes of columns past the grid are never written)
+        auto stored = [&](long long seg, int s3) {
+            const int cols = nx - s3 * kThreads;
+            return a.above[seg] & (cols > 3 * kWave ? ~0u : (1u << (8 * ((cols + kWave - 1) / kWave))) - 1u);
+        };
         if (int(threadIdx.x) < rows) {
-            const double* rp = a.rowpart + (r0 + (long long)threadIdx.x * D.strips) * kNStat;
-            const A mx = A(rp[kSMax]);
-            const bool inf = rp[kSNonpos] > 0.0;
-            if (D.limiter & kLimMedian) cand = cand || rp[kSAbove] > 0.0;
+            const long long seg = r0 + (long long)threadIdx.x * D.strips;
+            if (D.limiter & kLimMedian) cand = stored(seg, strip) != 0;
             if constexpr (ENS) {
+                const double* rp = a.rowpart + seg * kNStat;
+                const A mx = A(rp[kSMax]);
+                const bool inf = rp[kSNonpos] > 0.0;
                 if (D.limiter & (kLimEnsSmooth | kLimEnsRational)) cand = cand || rp[kSFluid] > 0.0;
                 if (D.limiter & kLimEnsThresh) cand = cand || inf || mx > A(ensv[kEThresh]);
                 if (D.limiter & kLimEnsBudget) cand = cand || inf || mx > A(ensv[kEBudget]);
@@ -664,7 +706,7 @@ __device__ __forceinline__ void second_pass2d(const StepArgs& a)
                 const int slot = idx / nr, ry = idx - slot * nr;
                 const int s3 = slot == 0 ? strip_l : (slot == 1 ? strip : strip_r);
                 const long long seg = (long long)D.row_first + (long long)row_of(t.y0 - 1 + ry) * D.strips + s3;
-                sflag[slot][ry] = int(a.rowpart[seg * kNStat + kSAbove]);
+                sflag[slot][ry] = stored(seg, s3);
             }
             __syncthreads();
         }
@@ -681,7 +723,7 @@ __device__ __forceinline__ void second_pass2d(const StepArgs& a)
         const long long plane = D.plane;
         const gptr<const A> dsb = to_global<A>(static_cast<const void*>(D.dsbuf));
         const gptr<T> dst = to_global<T>(D.buf[1 - a.parity]);
-        const bool record = a.flags & kFlagRecord;
+        const bool record = (a.flags & kFlagRecord) && (a.flags & kFlagStats);
         // lanes past the tile's last column repeat it and decide nothing
         const bool in = xw + lane < t.x1;
         const int x = in ? xw + lane : t.x1 - 1;
@@ -715,9 +757,9 @@ __device__ __forceinline__ void second_pass2d(const StepArgs& a)
         auto complete = [&](int y, A (&r)[3]) {
             if (sparse) {
                 const int ry = y - (t.y0 - 1);
-                if (!((sflag[1][ry] >> wx) & 1)) r[1] = A(0);
-                if (own_l && !((sflag[slot_m][ry] >> wxm) & 1)) r[0] = A(0);
-                if (own_r && !((sflag[slot_p][ry] >> wxp) & 1)) r[2] = A(0);
+                if (!((sflag[1][ry] >> (8 * wx)) & 1)) r[1] = A(0);
+                if (own_l && !((sflag[slot_m][ry] >> (8 * wxm)) & 1)) r[0] = A(0);
+                if (own_r && !((sflag[slot_p][ry] >> (8 * wxp)) & 1)) r[2] = A(0);
             }
             // every lane takes part in the shifts (no branch around them)
             const A l = lane_shift<-1>(r[1]), rr = lane_shift<+1>(r[1]);
@@ -824,18 +866,18 @@ __device__ __forceinline__ void second_pass2d(const StepArgs& a)
             ylist = yb + kMedChunk;
         }
     }
-    store_partial(acc, partial_slot(a, 1, tidx), red);
+    if (a.flags & kFlagStats) store_partial(acc, partial_slot(a, 1, tidx), red);
 }
 
 // the second D2Q9 pass without and with ensemble-dependent limiters (the
 // latter needs more registers), after LBGK and after ELBM collisions
-template <class T, int QE, int DS, int BC, bool ELBM = false>
+template <class T, int QE, int DS, int BC, bool ELBM>
 __global__ void __launch_bounds__(kThreads) k_median2d(StepArgs a)
 {
     second_pass2d<T, QE, DS, BC, false, ELBM>(a);
 }
 
-template <class T, int QE, int DS, int BC, bool ELBM = false>
+template <class T, int QE, int DS, int BC, bool ELBM>
 __global__ void __launch_bounds__(kThreads) k_median_ens2d(StepArgs a)
 {
     second_pass2d<T, QE, DS, BC, true, ELBM>(a);
@@ -853,9 +895,9 @@ __global__ void __launch_bounds__(kThreads) k_form2d(StepArgs a)
 {
     using A = typename Store<T>::A;
     __shared__ double red[4 * kNStat];
-    const RowBlock t = a.rows[blockIdx.x];
+    const RowBlock t = block_of(a);
     const DomainDev& D = a.dom[t.domain];
-    if (!D.dense) return;
+    if (!D.dense || t.y0 >= t.y1) return;
     const int nx = D.nx, ny = D.ny;
     const long long plane = D.plane;
     const gptr<const T> src = to_global<T>(static_cast<const void*>(D.buf[a.parity]));
@@ -973,13 +1015,13 @@ struct FusedDom {
 // and median factors (as in eq. (LimGenF) with the factors of Sec. 3).  The
 // gathers of the next row are issued before the current row is computed.  No
 // Delta S' plane is written; one FP64 partial per tile goes to set 1.
-template <class T, int QE, int DS, int BC>
+template <class T, int QE, int DS, int BC, bool STATS>
 __global__ void __launch_bounds__(kThreads) k_fused2d(StepArgs a)
 {
     using A = typename Store<T>::A;
     using L = Lat<kD2Q9>;
     constexpr int Q = 9;
-    __shared__ double red[4 * kNStat];
+    __shared__ double red[STATS ? 4 * kNStat : 1];
     // the pending row's f* and nonequilibrium part, one column per thread
     // (each thread reads back only its own slots)
     __shared__ A pend[2 * Q][kThreads];
@@ -997,8 +1039,8 @@ __global__ void __launch_bounds__(kThreads) k_fused2d(StepArgs a)
     const gptr<const T> src = to_global<T>(static_cast<const void*>(Dt.buf[a.parity]));
     const gptr<T> dst = to_global<T>(Dt.buf[1 - a.parity]);
     const A shift = A(Dt.shift), c = A(Dt.c);
-    const bool record = a.flags & kFlagRecord;
-    const bool want_ent = a.flags & kFlagEntropy;
+    const bool record = STATS && (a.flags & kFlagRecord);
+    const bool want_ent = STATS && (a.flags & kFlagEntropy);
     const bool median = D.limiter & kLimMedian;
     const long long step = a.counter[a.parity];
     // the index of the next step, read by the next launch (which reads buffer 1 - parity)
@@ -1056,14 +1098,16 @@ __global__ void __launch_bounds__(kThreads) k_fused2d(StepArgs a)
             unsigned mask = 0;
             A phi = A(1);
             if (cls == kNodeFluid) {
-                collide_site<kD2Q9, QE, DS, false>(g, shift, c, S, sc, true);
+                collide_site<kD2Q9, QE, DS, false>(g, shift, c, S, sc, STATS);
                 dcur = S.dpost;
                 if (own) {
-                    am += sc.dr;
-                    ax += sc.jx;
-                    ay += sc.jy;
-                    if (!(isfinite(sc.dr) && isfinite(sc.jx) && isfinite(sc.jy))) ++acc.nonfin;
-                    acc.fluid_site(sc, S.dpost);
+                    if constexpr (STATS) {
+                        am += sc.dr;
+                        ax += sc.jx;
+                        ay += sc.jy;
+                        if (!(isfinite(sc.dr) && isfinite(sc.jx) && isfinite(sc.jy))) ++acc.nonfin;
+                        acc.fluid_site(sc, S.dpost);
+                    }
                     if (want_ent) {
                         const double e = entropy_site<kD2Q9>(g, shift);
                         if (isfinite(e)) acc.ent += A(e);
@@ -1082,7 +1126,7 @@ __global__ void __launch_bounds__(kThreads) k_fused2d(StepArgs a)
                         const A pp = positivity_phi<kD2Q9>(S, shift);
                         if (pp < A(1)) {
                             mask |= kMaskPos;
-                            ++acc.pos;
+                            if constexpr (STATS) ++acc.pos;
                             phi = fmin(phi, pp);
                         }
                     }
@@ -1109,12 +1153,14 @@ __global__ void __launch_bounds__(kThreads) k_fused2d(StepArgs a)
                     for (int i = 0; i < Q; ++i)
                         Store<T>::st(at_bytes(dst + (i * plane + row), ob), A(L::w(i)) * ((r0 - shift) + r0 * E[i]));
                 }
-                double dr, jx, jy;
-                moments_fp64(g, dr, jx, jy);
-                am += dr;
-                ax += jx;
-                ay += jy;
-                if (!(isfinite(dr) && isfinite(jx) && isfinite(jy))) ++acc.nonfin;
+                if constexpr (STATS) {
+                    double dr, jx, jy;
+                    moments_fp64(g, dr, jx, jy);
+                    am += dr;
+                    ax += jx;
+                    ay += jy;
+                    if (!(isfinite(dr) && isfinite(jx) && isfinite(jy))) ++acc.nonfin;
+                }
                 if (record) {
                     to_global<unsigned char>(D.mask)[node] = (unsigned char)kMaskNotFluid;
                     to_global<double>(D.dS)[node] = 0.0;
@@ -1142,7 +1188,7 @@ __global__ void __launch_bounds__(kThreads) k_fused2d(StepArgs a)
                 A thr;
                 if (median && median_hit<BC>(D, xc, ydr, nx, ny, wb, wm, wn, thr)) {
                     p_mask |= kMaskMedian;
-                    ++acc.filt;
+                    if constexpr (STATS) ++acc.filt;
                     A pm = A(1);
                     bool done = false;
                     if constexpr (DS == kExact) {
@@ -1155,8 +1201,11 @@ __global__ void __launch_bounds__(kThreads) k_fused2d(StepArgs a)
                     p_phi = fmin(p_phi, pm);
                 }
                 store_limited<T, false>(dst, plane, drow, cl.own, P, p_phi, c);
-                if (p_mask & kMaskTrim) ++acc.trim;
-                if (p_phi < A(1) && isfinite(p_dpost)) acc.lim += double(p_dpost - delta_s_scaled<kD2Q9, DS>(P, shift, c, p_phi));
+                if constexpr (STATS) {
+                    if (p_mask & kMaskTrim) ++acc.trim;
+                    if (p_phi < A(1) && isfinite(p_dpost))
+                        acc.lim += double(p_dpost - delta_s_scaled<kD2Q9, DS>(P, shift, c, p_phi));
+                }
                 if (record) to_global<unsigned char>(D.mask)[unsigned(drow) + unsigned(xc)] = (unsigned char)p_mask;
             }
             // this row becomes the pending one
@@ -1199,6 +1248,7 @@ __global__ void __launch_bounds__(kThreads) k_fused2d(StepArgs a)
             if (y + 3 > t.y1) break;
         }
     }
+    if constexpr (!STATS) return;
     AccT<double> tot;
     tot.mass = am;
     tot.jx = ax;
@@ -1242,7 +1292,7 @@ __device__ inline void gather1d(gptr<const T> src, long long plane, int nx, int 
 // step per launch cost 6.5 us, of which a launch, the first load and the
 // reduction are 5; kept in LDS a step costs its arithmetic and one or two
 // barriers.  The sums, the mask and Delta S' belong to the last step alone.
-template <class T, int QE, int DS, int BC, bool ELBM = false>
+template <class T, int QE, int DS, int BC, bool ELBM>
 __global__ void __launch_bounds__(k1DMaxThreads) k_step1d(StepArgs a)
 {
     using A = typename Store<T>::A;
@@ -1450,70 +1500,65 @@ __global__ void __launch_bounds__(kThreads) k_ens1d(StepArgs a)
     store_partial(acc, partial_slot(a, 1, tidx), red);
 }
 
-// one instantiation per (quasiequilibrium, Delta S form, boundary) in use:
-// the 2-D kernel serves periodic and cavity grids, the 1-D one periodic and tube
-#define LBM_CASE(KER, Q_, D_, B_, ...) \
-    case Q_ * 100 + D_ * 10 + B_: hipLaunchKernelGGL((KER<StT, Q_, D_, B_>), __VA_ARGS__); break;
-#define LBM_DISPATCH(KER, B0, B1, ...)                                                                 \
-    do {                                                                                               \
-        switch (qe * 100 + ds * 10 + bc) {                                                             \
-            LBM_CASE(KER, 0, 0, B0, __VA_ARGS__)                                                       \
-            LBM_CASE(KER, 0, 0, B1, __VA_ARGS__)                                                       \
-            LBM_CASE(KER, 0, 1, B0, __VA_ARGS__)                                                       \
-            LBM_CASE(KER, 0, 1, B1, __VA_ARGS__)                                                       \
-            LBM_CASE(KER, 1, 0, B0, __VA_ARGS__)                                                       \
-            LBM_CASE(KER, 1, 0, B1, __VA_ARGS__)                                                       \
-            LBM_CASE(KER, 1, 1, B0, __VA_ARGS__)                                                       \
-            LBM_CASE(KER, 1, 1, B1, __VA_ARGS__)                                                       \
-        default: return hipErrorInvalidValue;                                                          \
-        }                                                                                              \
-    } while (0)
-// ELBM needs the entropic f*: kernels for qe = 1 only
-#define LBM_CASE_E(KER, D_, B_, ...) \
-    case 100 + D_ * 10 + B_: hipLaunchKernelGGL((KER<StT, 1, D_, B_, true>), __VA_ARGS__); break;
-#define LBM_DISPATCH_ELBM(KER, B0, B1, ...)                                                            \
-    do {                                                                                               \
-        switch (qe * 100 + ds * 10 + bc) {                                                             \
-            LBM_CASE_E(KER, 0, B0, __VA_ARGS__)                                                        \
-            LBM_CASE_E(KER, 0, B1, __VA_ARGS__)                                                        \
-            LBM_CASE_E(KER, 1, B0, __VA_ARGS__)                                                        \
-            LBM_CASE_E(KER, 1, B1, __VA_ARGS__)                                                        \
-        default: return hipErrorInvalidValue;                                                          \
-        }                                                                                              \
-    } while (0)
+// one instantiation per (quasiequilibrium, Delta S form, boundary) in use: the
+// 2-D kernels serve periodic and cavity grids, the 1-D ones periodic and tube,
+// ELBM the entropic f* only.  `f` launches for the three as constants.
+template <int B0, int B1, bool ELBM = false, class F>
+static hipError_t dispatch(int qe, int ds, int bc, F f)
+{
+    using I0 = std::integral_constant<int, 0>;
+    using I1 = std::integral_constant<int, 1>;
+    auto with_bc = [&](auto q, auto d) {
+        if (bc == B0) f(q, d, std::integral_constant<int, B0>());
+        else if (bc == B1) f(q, d, std::integral_constant<int, B1>());
+        else return hipErrorInvalidValue;
+        return hipSuccess;
+    };
+    auto with_ds = [&](auto q) {
+        return ds == 0 ? with_bc(q, I0()) : (ds == 1 ? with_bc(q, I1()) : hipErrorInvalidValue);
+    };
+    hipError_t e = hipErrorInvalidValue;
+    if (qe == 1) e = with_ds(I1());
+    if constexpr (!ELBM) {
+        if (qe == 0) e = with_ds(I0());
+    }
+    return e == hipSuccess ? hipGetLastError() : e;
+}
+// a launch of KER<storage, f*, Delta S form, boundary, ...>
+#define LBM_LAUNCH(GRID, BLOCK, KER, ...)                                                                \
+    [&](auto q, auto d, auto b) {                                                                        \
+        constexpr int QE = decltype(q)::value, DS = decltype(d)::value, BC = decltype(b)::value;         \
+        hipLaunchKernelGGL((KER<StT, QE, DS, BC, ##__VA_ARGS__>), dim3(GRID), dim3(BLOCK), 0, s, a);      \
+    }
 
 hipError_t LBM_CAT(launch_step2d, LBM_SUFFIX)(int qe, int ds, int bc, const StepArgs& a, int kernel,
                                              hipStream_t s)
 {
+    const bool stats = a.flags & kFlagStats;
     if (kernel == 0)
-        LBM_DISPATCH(k_collide2d, 0, 1, dim3(a.nrows), dim3(kThreads), 0, s, a);
-    else if (kernel == 2)
-        LBM_DISPATCH_ELBM(k_collide2d, 0, 1, dim3(a.nrows), dim3(kThreads), 0, s, a);
-    else if (kernel == 3)
-        LBM_DISPATCH(k_fused2d, 0, 1, dim3(a.ntiles), dim3(kThreads), 0, s, a);
-    else if (kernel == 4)
-        LBM_DISPATCH(k_form2d, 0, 1, dim3(a.nrows), dim3(kThreads), 0, s, a);
-    else if (a.elbm && a.ens_pass)
-        LBM_DISPATCH_ELBM(k_median_ens2d, 0, 1, dim3(a.ntiles), dim3(kThreads), 0, s, a);
-    else if (a.elbm)
-        LBM_DISPATCH_ELBM(k_median2d, 0, 1, dim3(a.ntiles), dim3(kThreads), 0, s, a);
-    else if (a.ens_pass)
-        LBM_DISPATCH(k_median_ens2d, 0, 1, dim3(a.ntiles), dim3(kThreads), 0, s, a);
-    else
-        LBM_DISPATCH(k_median2d, 0, 1, dim3(a.ntiles), dim3(kThreads), 0, s, a);
-    return hipGetLastError();
+        return stats ? dispatch<0, 1>(qe, ds, bc, LBM_LAUNCH(row_grid(a), kThreads, k_collide2d, false, true))
+                     : dispatch<0, 1>(qe, ds, bc, LBM_LAUNCH(row_grid(a), kThreads, k_collide2d, false, false));
+    if (kernel == 2)
+        return stats ? dispatch<0, 1, true>(qe, ds, bc, LBM_LAUNCH(row_grid(a), kThreads, k_collide2d, true, true))
+                     : dispatch<0, 1, true>(qe, ds, bc, LBM_LAUNCH(row_grid(a), kThreads, k_collide2d, true, false));
+    if (kernel == 3)
+        return stats ? dispatch<0, 1>(qe, ds, bc, LBM_LAUNCH(a.ntiles, kThreads, k_fused2d, true))
+                     : dispatch<0, 1>(qe, ds, bc, LBM_LAUNCH(a.ntiles, kThreads, k_fused2d, false));
+    if (kernel == 4) return dispatch<0, 1>(qe, ds, bc, LBM_LAUNCH(row_grid(a), kThreads, k_form2d));
+    if (a.elbm)
+        return a.ens_pass ? dispatch<0, 1, true>(qe, ds, bc, LBM_LAUNCH(a.ntiles, kThreads, k_median_ens2d, true))
+                          : dispatch<0, 1, true>(qe, ds, bc, LBM_LAUNCH(a.ntiles, kThreads, k_median2d, true));
+    return a.ens_pass ? dispatch<0, 1>(qe, ds, bc, LBM_LAUNCH(a.ntiles, kThreads, k_median_ens2d, false))
+                      : dispatch<0, 1>(qe, ds, bc, LBM_LAUNCH(a.ntiles, kThreads, k_median2d, false));
 }
 
 hipError_t LBM_CAT(launch_step1d, LBM_SUFFIX)(int qe, int ds, int bc, const StepArgs& a, int kernel,
                                              hipStream_t s)
 {
-    if (kernel == 0)
-        LBM_DISPATCH(k_step1d, 0, 2, dim3(a.ntiles), dim3(threads1d(a.reach, a.steps)), 0, s, a);
-    else if (kernel == 2)
-        LBM_DISPATCH_ELBM(k_step1d, 0, 2, dim3(a.ntiles), dim3(threads1d(a.reach, a.steps)), 0, s, a);
-    else
-        LBM_DISPATCH(k_ens1d, 0, 2, dim3(a.ntiles), dim3(kThreads), 0, s, a);
-    return hipGetLastError();
+    const int threads = threads1d(a.reach, a.steps);
+    if (kernel == 0) return dispatch<0, 2>(qe, ds, bc, LBM_LAUNCH(a.ntiles, threads, k_step1d, false));
+    if (kernel == 2) return dispatch<0, 2, true>(qe, ds, bc, LBM_LAUNCH(a.ntiles, threads, k_step1d, true));
+    return dispatch<0, 2>(qe, ds, bc, LBM_LAUNCH(a.ntiles, kThreads, k_ens1d));
 }
 
 }  // namespace lbm
