@@ -43,24 +43,20 @@ __global__ void __launch_bounds__(kThreads) k_finalize(StepArgs a, int parity_do
     reduce_domain(a, parity_done, a.dom[blockIdx.x], a.median_pass, step, red);
 }
 
-// D2Q9: the set-0 partial of each group (kMaxTileH rows of one strip) is the
-// sum of the collision partials of its rows (index row_first + y strips +
-// strip), in row order.
-__global__ void __launch_bounds__(kThreads) k_tile_rows(StepArgs a, int parity_done)
+// D2Q9: the set-0 partial of each group is the sum of the collision partials
+// of its workgroups, in order.
+__global__ void __launch_bounds__(kThreads) k_group_sums(StepArgs a, int parity_done)
 {
-    __shared__ double red[4 * kNStat];
-    __shared__ double rowbuf[kMaxTileH * kNStat + 8 * kNStat];
-    const Tile t = a.groups[blockIdx.x];
-    const DomainDev& D = a.dom[t.domain];
-    const long long r0 = (long long)D.row_first + (long long)t.y0 * D.strips + t.x0 / kThreads;
-    const Acc none;
-    store_partial_rows(none, a.partials + ((long long)parity_done * 2 * a.pstride + blockIdx.x) * kNStat, red,
-                       a.rowpart + r0 * kNStat, t.y1 - t.y0, D.strips, rowbuf);
+    __shared__ double buf[kGroupParts * kNStat + 8 * kNStat];
+    const Group t = a.groups[blockIdx.x];
+    const long long p0 = (long long)a.dom[t.domain].part_first + t.n0 / kThreads;
+    sum_partials(a.partials + ((long long)parity_done * 2 * a.pstride + blockIdx.x) * kNStat, a.blockpart + p0 * kNStat,
+                 (t.n1 - t.n0 + kThreads - 1) / kThreads, buf);
 }
 
 // E(Delta S') of this step and the thresholds of the ensemble limiters, per
-// domain (Sec. 3.3, 3.4): the collision partials (set 0; for D2Q9 summed from
-// the rows beforehand) are reduced exactly as the stats are, so E equals the
+// domain (Sec. 3.3, 3.4): the collision partials (set 0; for D2Q9 summed per
+// group beforehand) are reduced exactly as the stats are, so E equals the
 // reported mean_dS bit for bit.
 __global__ void __launch_bounds__(kThreads) k_ens_prepare(StepArgs a, int parity)
 {
@@ -142,14 +138,14 @@ __device__ inline int key_exponent(typename K::U k)
 
 // One level of the budget selection: a histogram of the digit (count and exact
 // significand sum per bucket) of the values whose higher digits match the
-// prefix, added into the domain's histogram.  A workgroup of four times 256
-// columns takes a run of 64-row groups: what a level costs are the additions
+// prefix, added into the domain's histogram.  A workgroup of 1024 threads
+// takes a run of groups (16384 consecutive nodes each): what a level costs are the additions
 // of all workgroups to the few buckets that most values share, which queue at
 // their addresses (1000 workgroups: 40 us for the first level of a 1024 x 1000
 // grid, against 12 us with 64), so workgroups are few and large.  Each thread
-// walks 16 rows of a column and merges runs of equal buckets in registers
-// first (the significand sum of a wave stays below 2^63).
-constexpr int kHistThreads = 4 * kThreads, kHistRows = kMaxTileH / 4, kHistBlocks = 256;
+// takes 16 nodes of a group, one of every 1024, and merges runs of equal buckets
+// in registers first (the significand sum of a wave stays below 2^63).
+constexpr int kHistThreads = 1024, kHistBlocks = 256;
 template <class A, bool CAV>
 __global__ void __launch_bounds__(kHistThreads) k_budget_hist(StepArgs a, int level)
 {
@@ -194,27 +190,30 @@ __global__ void __launch_bounds__(kHistThreads) k_budget_hist(StepArgs a, int le
     const int nb = int(gridDim.x), g0 = int((long long)blockIdx.x * a.ngroups / nb),
               g1 = int((long long)(blockIdx.x + 1) * a.ngroups / nb);
     for (int g = g0; g < g1; ++g) {
-        const Tile t = a.groups[g];
+        const Group t = a.groups[g];
         const DomainDev& D = a.dom[t.domain];
         const bool run = (D.limiter & (kLimEnsBudget | kLimTopK)) && !D.bstate->done;
         if (run) {
             const unsigned long long prefix = D.bstate->prefix;
-            const int x = t.x0 + (tid & (kThreads - 1)), y0 = t.y0 + (tid / kThreads) * kHistRows;
             const A* ds = static_cast<const A*>(D.dsbuf);
             int cur = -1;
             unsigned cnt = 0;
             unsigned long long sum = 0;
-            constexpr int kAhead = 8;      // rows loaded together
-            for (int yb = y0; yb < y0 + kHistRows; yb += kAhead) {
+            constexpr int kAhead = 8;      // nodes loaded together
+            for (int n = t.n0 + tid; n < t.n1; n += kAhead * kHistThreads) {
                 A v[kAhead];
 #pragma unroll
-                for (int k = 0; k < kAhead; ++k)
-                    v[k] = (x < t.x1 && yb + k < t.y1) ? ds[(long long)(yb + k) * D.nx + x] : A(__builtin_huge_val());
+                for (int k = 0; k < kAhead; ++k) {
+                    const int nk = n + k * kHistThreads;
+                    v[k] = nk < t.n1 ? ds[nk] : A(__builtin_huge_val());
+                }
 #pragma unroll
                 for (int k = 0; k < kAhead; ++k) {
-                    const int y = yb + k;
-                    if (CAV && (x == 0 || x == D.nx - 1 || y == 0 || y == D.ny - 1)) continue;   // walls and lid
                     if (!isfinite(v[k])) continue;
+                    if (CAV) {
+                        const int nk = n + k * kHistThreads, y = nk / D.nx, x = nk - y * D.nx;
+                        if (x == 0 || x == D.nx - 1 || y == 0 || y == D.ny - 1) continue;   // walls and lid
+                    }
                     const U key = K::key(v[k]);
                     if ((unsigned long long)(key >> hi) != prefix) continue;
                     const int b = int((key >> lo) & dmask);
@@ -478,8 +477,8 @@ hipError_t launch_budget(int storage, int bc, const StepArgs& a, hipStream_t s)
 
 hipError_t launch_ens_prepare(const StepArgs& a, hipStream_t s)
 {
-    if (a.nparts > 0) {
-        hipLaunchKernelGGL(k_tile_rows, dim3(a.ngroups), dim3(kThreads), 0, s, a, a.parity);
+    if (a.nblocks > 0) {
+        hipLaunchKernelGGL(k_group_sums, dim3(a.ngroups), dim3(kThreads), 0, s, a, a.parity);
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
@@ -489,8 +488,8 @@ hipError_t launch_ens_prepare(const StepArgs& a, hipStream_t s)
 
 hipError_t launch_finalize(const StepArgs& a, int parity_done, long long steps_done, hipStream_t s)
 {
-    if (a.nparts > 0 && !a.fused) {
-        hipLaunchKernelGGL(k_tile_rows, dim3(a.ngroups), dim3(kThreads), 0, s, a, parity_done);
+    if (a.nblocks > 0 && !a.fused) {
+        hipLaunchKernelGGL(k_group_sums, dim3(a.ngroups), dim3(kThreads), 0, s, a, parity_done);
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }

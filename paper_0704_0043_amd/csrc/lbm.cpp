@@ -32,9 +32,6 @@ constexpr int kMinTileH = 4;    // rows of a second-pass tile on the smallest gr
 constexpr int kMinFusedH = 4;   // smallest fused-tile height the tuner tries
 constexpr int kMaxFusedH = 128; // tallest fused tile
 
-// D2Q9 tiles: kThreads consecutive columns
-int strips_of(int nx) { return (nx + kThreads - 1) / kThreads; }
-
 bool is_cavity(int bc) { return bc == LBM_BC_CAVITY || bc == LBM_BC_CAVITY_DIFFUSIVE; }
 
 // trimming limited to the top_k largest Delta S' (a second-pass limiter)
@@ -159,15 +156,15 @@ struct DomainHost {
     bool dsbuf = false, phibuf = false;
     double shift = 0;
     int tile_first = 0, tile_count = 0;
-    int row_first = 0, row_count = 0;
+    int part_first = 0, part_count = 0;
     int group_first = 0, group_count = 0;
 };
 
 struct Layout {
     size_t off_dom = 0, off_tiles = 0, off_partials = 0, off_counter = 0, off_stage = 0, total = 0;
     size_t off_dom_alt = 0, off_tiles_alt = 0, off_adapt = 0;   // LBM_RUN_ADAPTIVE only
-    size_t off_rows = 0, off_rowpart = 0, off_above = 0, off_groups = 0;
-    int max_tiles = 0, nrows = 0, ngroups = 0;
+    size_t off_blocks = 0, off_blockpart = 0, off_above = 0, off_groups = 0;
+    int max_tiles = 0, nblocks = 0, ngroups = 0;
     size_t max_n = 0;
 };
 
@@ -224,19 +221,18 @@ struct lbm_ctx {
     bool adapt_pending[2] = {false, false};
     long long adapt_points = 0, next_check = 0;
     std::string err;
-    std::vector<RowBlock> rows_host;
-    std::vector<Tile> groups_host;
+    std::vector<Block> blocks_host;
+    std::vector<Group> groups_host;
     int cap_h = kMaxTileH;      // tallest second-pass tile of these domains (second_height)
-    int nblocks = 0;            // D2Q9 row blocks of all domains (the collision grid)
-    int narrow = 1;             // row blocks of 64 / 128 columns for narrow domains
+    int narrow = 1;             // report row blocks of 64 / 128 columns for narrow domains
     int tuned = 0;              // 1 when the tile shape was chosen by timing
 
     DomainDev* d_dom() const { return reinterpret_cast<DomainDev*>(ws + act.off_dom); }
     Tile* d_tiles() const { return reinterpret_cast<Tile*>(ws + act.off_tiles); }
     double* d_adapt() const { return reinterpret_cast<double*>(ws + lay.off_adapt); }
-    RowBlock* d_rows() const { return reinterpret_cast<RowBlock*>(ws + lay.off_rows); }
-    Tile* d_groups() const { return reinterpret_cast<Tile*>(ws + lay.off_groups); }
-    double* d_rowpart() const { return reinterpret_cast<double*>(ws + lay.off_rowpart); }
+    Block* d_blocks() const { return reinterpret_cast<Block*>(ws + lay.off_blocks); }
+    Group* d_groups() const { return reinterpret_cast<Group*>(ws + lay.off_groups); }
+    double* d_blockpart() const { return reinterpret_cast<double*>(ws + lay.off_blockpart); }
     unsigned* d_above() const { return reinterpret_cast<unsigned*>(ws + lay.off_above); }
     double* d_partials() const { return reinterpret_cast<double*>(ws + lay.off_partials); }
     long long* d_counter() const { return reinterpret_cast<long long*>(ws + lay.off_counter); }
@@ -403,7 +399,7 @@ void plan(std::vector<DomainHost>& dh, const lbm_domain_desc* doms, int32_t nd, 
     const bool adaptive = adaptive_run(doms, nd, run);
     size_t off = 0;
     L.max_tiles = 0;
-    L.nrows = 0;
+    L.nblocks = 0;
     L.ngroups = 0;
     L.max_n = 0;
     dh.resize(nd);
@@ -438,8 +434,12 @@ void plan(std::vector<DomainHost>& dh, const lbm_domain_desc* doms, int32_t nd, 
         // adaptive: the fused tiles (any tuned height) share the partial slots
         if (h.d.lattice == LBM_D2Q9 && adaptive) tiles = std::max(tiles, fused_tiles_of(h.d.nx, h.d.ny, kMinFusedH));
         L.max_tiles += tiles;
-        L.ngroups += tiles_of(h.d.lattice, h.d.nx, h.d.ny, kMaxTileH);
-        if (h.d.lattice == LBM_D2Q9) L.nrows += strips_of(h.d.nx) * h.d.ny;
+        if (h.d.lattice == LBM_D2Q9) {
+            L.nblocks += blocks_of(h.d.nx, h.d.ny);
+            L.ngroups += groups_of(h.d.nx, h.d.ny);
+        } else {
+            L.ngroups += tiles_of(h.d.lattice, h.d.nx, h.d.ny, 1);
+        }
         L.max_n = std::max(L.max_n, h.n);
     }
     L.off_dom = off;
@@ -455,15 +455,15 @@ void plan(std::vector<DomainHost>& dh, const lbm_domain_desc* doms, int32_t nd, 
         off = align_up(off + sizeof(double), kAlign);
     }
     L.off_groups = off;
-    off = align_up(off + L.ngroups * sizeof(Tile), kAlign);
+    off = align_up(off + L.ngroups * sizeof(Group), kAlign);
     L.off_partials = off;
-    off = align_up(off + size_t(4) * L.max_tiles * kNStat * sizeof(double), kAlign);
-    L.off_rows = off;
-    if (nd > 1) off = align_up(off + size_t(L.nrows) * sizeof(RowBlock), kAlign);
-    L.off_rowpart = off;
-    off = align_up(off + size_t(L.nrows) * kNStat * sizeof(double), kAlign);
+    off = align_up(off + size_t(4) * std::max(L.max_tiles, L.ngroups) * kNStat * sizeof(double), kAlign);
+    L.off_blocks = off;
+    if (nd > 1) off = align_up(off + size_t(L.nblocks) * sizeof(Block), kAlign);
+    L.off_blockpart = off;
+    off = align_up(off + size_t(L.nblocks) * kNStat * sizeof(double), kAlign);
     L.off_above = off;
-    off = align_up(off + size_t(L.nrows) * sizeof(unsigned), kAlign);
+    off = align_up(off + size_t(L.nblocks) * sizeof(unsigned), kAlign);
     L.off_counter = off;
     off = align_up(off + 2 * sizeof(long long), kAlign);
     L.off_stage = off;
@@ -493,52 +493,42 @@ std::vector<Tile> build_tiles(lbm_ctx* ctx, int th, bool fused)
     return spatial;
 }
 
-// D2Q9 row blocks, row-major within each domain: the collision kernel runs
-// one workgroup per block in this order.  Every domain row has one collision
-// partial per 256-column strip (row_first + y strips + strip), whatever the
-// blocks; `narrow` gives narrow domains blocks of several rows.
-void build_rows(lbm_ctx* ctx, int narrow)
+// D2Q9 collision workgroups, domain by domain in row-major order (a single
+// domain's need no table), and the groups of collision partials that are
+// summed together for the stats and E(Delta S') (D1Q3: its tiles).
+void build_blocks(lbm_ctx* ctx)
 {
-    ctx->rows_host.clear();
-    ctx->nblocks = 0;
-    ctx->narrow = narrow;
-    if (ctx->lattice != LBM_D2Q9) return;
+    ctx->blocks_host.clear();
+    ctx->groups_host.clear();
     int part = 0;
     for (size_t k = 0; k < ctx->dom.size(); ++k) {
         DomainHost& h = ctx->dom[k];
-        h.row_first = part;
-        h.row_count = strips_of(h.d.nx) * h.d.ny;
-        part += h.row_count;
-        const int width = seg_width(h.d.nx, narrow);
-        const int nb = blocks_of(h.d.nx, h.d.ny, width);
-        ctx->nblocks += nb;
-        if (ctx->dom.size() > 1)      // a single domain's blocks are computed (block_of)
-            for (int i = 0; i < nb; ++i) ctx->rows_host.push_back(block_entry2d(int(k), h.d.nx, h.d.ny, width, i));
-    }
-}
-
-// The groups of kMaxTileH rows whose collision partials are summed together
-// for the stats and E(Delta S'), fixed so that those sums do not depend on
-// the tile height in use (D1Q3: its tiles).
-void build_groups(lbm_ctx* ctx)
-{
-    ctx->groups_host.clear();
-    for (size_t k = 0; k < ctx->dom.size(); ++k) {
-        DomainHost& h = ctx->dom[k];
+        const int nx = h.d.nx, ny = h.d.ny, n = nx * ny;
         h.group_first = int(ctx->groups_host.size());
-        const int nx = h.d.nx, ny = h.d.ny;
-        const int count = tiles_of(ctx->lattice, nx, ny, kMaxTileH);
-        for (int i = 0; i < count; ++i)
-            ctx->groups_host.push_back(ctx->lattice == LBM_D2Q9 ? tile_entry2d(int(k), nx, ny, kMaxTileH, i)
-                                                                : tile_entry1d(int(k), nx, i));
-        h.group_count = count;
+        if (ctx->lattice == LBM_D2Q9) {
+            h.part_first = part;
+            h.part_count = blocks_of(nx, ny);
+            part += h.part_count;
+            if (ctx->dom.size() > 1)
+                for (int i = 0; i < h.part_count; ++i) ctx->blocks_host.push_back(Block{int(k), i});
+            h.group_count = groups_of(nx, ny);
+            for (int i = 0; i < h.group_count; ++i) ctx->groups_host.push_back(group_entry2d(int(k), n, i));
+        } else {
+            h.group_count = tiles_of(ctx->lattice, nx, ny, 1);
+            for (int i = 0; i < h.group_count; ++i) {
+                const Tile t = tile_entry1d(int(k), nx, i);
+                ctx->groups_host.push_back(Group{int(k), t.x0, t.x1});
+            }
+        }
     }
 }
 
-int upload_rows(lbm_ctx* ctx)
+int upload_blocks(lbm_ctx* ctx)
 {
-    if (ctx->rows_host.empty()) return LBM_OK;
-    HIP_TRY(ctx, hipMemcpyAsync(ctx->d_rows(), ctx->rows_host.data(), ctx->rows_host.size() * sizeof(RowBlock),
+    HIP_TRY(ctx, hipMemcpyAsync(ctx->d_groups(), ctx->groups_host.data(), ctx->groups_host.size() * sizeof(Group),
+                                hipMemcpyHostToDevice, ctx->stream));
+    if (ctx->blocks_host.empty()) return LBM_OK;
+    HIP_TRY(ctx, hipMemcpyAsync(ctx->d_blocks(), ctx->blocks_host.data(), ctx->blocks_host.size() * sizeof(Block),
                                 hipMemcpyHostToDevice, ctx->stream));
     return LBM_OK;
 }
@@ -569,9 +559,9 @@ DomainDev make_dev(const DomainHost& h, char* base, void* b0, void* b1, int prob
     d.dS = (flags & LBM_RUN_RECORD) ? reinterpret_cast<double*>(base + h.off_ds) : nullptr;
     d.tile_first = h.tile_first;
     d.tile_count = h.tile_count;
-    d.strips = strips_of(h.d.nx);
-    d.row_first = h.row_first;
-    d.row_count = h.row_count;
+    d.inv_nx = inverse_nx(h.d.nx);
+    d.part_first = h.part_first;
+    d.part_count = h.part_count;
     d.group_first = h.group_first;
     d.group_count = h.group_count;
     d.stats = reinterpret_cast<double*>(base + h.off_stats);
@@ -622,17 +612,6 @@ int set_tiles(lbm_ctx* ctx, int th, bool fused = false)
     return LBM_OK;
 }
 
-// the row blocks of a single D2Q9 domain as a grid (several domains: the table)
-void set_grid(StepArgs& a, const lbm_domain_desc* d, int narrow)
-{
-    a.width = a.row_shift = a.grid_x = a.grid_y = 0;
-    if (!d || d->lattice != LBM_D2Q9) return;
-    a.width = seg_width(d->nx, narrow);
-    while ((a.width << a.row_shift) < kThreads) ++a.row_shift;
-    a.grid_x = (d->nx + a.width - 1) / a.width;
-    a.grid_y = (d->ny + (1 << a.row_shift) - 1) >> a.row_shift;
-}
-
 StepArgs step_args(const lbm_ctx* ctx, int parity)
 {
     StepArgs a;
@@ -646,14 +625,12 @@ StepArgs step_args(const lbm_ctx* ctx, int parity)
     a.budget = ctx->budget;
     a.dense = ctx->dense;
     a.fused = ctx->act.fused ? 1 : 0;
-    a.rows = ctx->d_rows();
-    a.nrows = ctx->nblocks;
-    a.nparts = ctx->lay.nrows;
-    set_grid(a, ctx->dom.size() == 1 ? &ctx->dom[0].d : nullptr, ctx->narrow);
+    a.blocks = ctx->blocks_host.empty() ? nullptr : ctx->d_blocks();
+    a.nblocks = ctx->lay.nblocks;
     a.groups = ctx->d_groups();
     a.ngroups = ctx->lay.ngroups;
-    a.pstride = ctx->lay.max_tiles;
-    a.rowpart = ctx->d_rowpart();
+    a.pstride = std::max(ctx->lay.max_tiles, ctx->lay.ngroups);
+    a.blockpart = ctx->d_blockpart();
     a.above = ctx->d_above();
     a.parity = parity;
     a.flags = ctx->flags & (LBM_RUN_RECORD | LBM_RUN_ENTROPY);
@@ -792,9 +769,8 @@ std::string tune_key(const lbm_ctx* ctx, const lbm_run_desc* run)
 
 int apply_shape(lbm_ctx* ctx, const Shape& sh)
 {
-    build_rows(ctx, sh.narrow);
-    int rc = upload_rows(ctx);
-    return rc ? rc : set_tiles(ctx, sh.th, sh.fused);
+    ctx->narrow = sh.narrow;
+    return set_tiles(ctx, sh.th, sh.fused);
 }
 
 // average milliseconds of `n` steps that all read buffer 0 (the initial state
@@ -821,13 +797,10 @@ int time_shape(lbm_ctx* ctx, int n, double& ms, unsigned extra_flags = 0)
 // row blocks of the two-kernel form stay as tuned)
 int autotune(lbm_ctx* ctx, const lbm_run_desc* run, bool fused_alt = false)
 {
-    bool any_narrow = false;
-    for (const auto& h : ctx->dom) any_narrow = any_narrow || seg_width(h.d.nx, 1) < kThreads;
-    std::vector<int> widths;
-    if (run->tile_x == kThreads || !any_narrow) widths = {0};
-    else if (run->tile_x == kWave) widths = {1};
-    else widths = {1, 0};
-    // (the dense domains' second pass runs over the row blocks)
+    // (the collision kernel takes consecutive nodes whatever the rows: the
+    // width asked for is only reported)
+    const int narrow = run->tile_x != kThreads;
+    // (the dense domains' second pass has no tiles)
     const bool second = (ctx->median_pass || ctx->ens_pass) && (ctx->dense & kSparseSome);
     std::vector<int> heights;
     if (run->tile_h > 0) heights = {run->tile_h};
@@ -842,22 +815,21 @@ int autotune(lbm_ctx* ctx, const lbm_run_desc* run, bool fused_alt = false)
         for (int th : {kMinFusedH, 8, 16, 32, 64}) cand.push_back({ctx->narrow, th, true});
         if (ctx->flags & LBM_RUN_NO_TUNE) return apply_shape(ctx, {ctx->narrow, 8, true});
     } else if (run->tile_x != kFusedWidth)
-        for (int w : widths)
-            for (int th : heights) cand.push_back({w, th, false});
+        for (int th : heights) cand.push_back({narrow, th, false});
     // the fused step only when asked for: at creation no node has moved yet,
     // and the tuner cannot see how much of the flow the filter will move
     if (!fused_alt && ctx->fuse_ok && run->tile_x == kFusedWidth) {
         const std::vector<int> fh = run->tile_h > 0 ? std::vector<int>{run->tile_h}
                                                     : std::vector<int>{kMinFusedH, 8, 16, 32, 64};
-        for (int th : fh) cand.push_back({widths[0], th, true});
+        for (int th : fh) cand.push_back({narrow, th, true});
     }
     ctx->tuned = 0;
     if (cand.size() == 1) return apply_shape(ctx, cand[0]);
     if (ctx->flags & LBM_RUN_NO_TUNE) {
         // narrow row blocks where a domain allows them, tile_h or 64 rows
         // for the second pass; the fused step only when asked for
-        if (run->tile_x == kFusedWidth) return apply_shape(ctx, {widths[0], run->tile_h > 0 ? run->tile_h : 64, true});
-        return apply_shape(ctx, {widths[0], heights.back(), false});
+        if (run->tile_x == kFusedWidth) return apply_shape(ctx, {narrow, run->tile_h > 0 ? run->tile_h : 64, true});
+        return apply_shape(ctx, {narrow, heights.back(), false});
     }
     const std::string key = tune_key(ctx, run) + (fused_alt ? "/fused form" : "");
     {
@@ -1055,9 +1027,9 @@ int read_stats(lbm_ctx* ctx, int32_t d, lbm_entropy_stats_t* out)
 // Layout of lbm_step_static's arrays in the static scratch array: one
 // domain, tight planes (plane = nx ny), no record planes, no probe.
 struct StaticLayout {
-    size_t off_dom = 0, off_tiles = 0, off_groups = 0, off_partials = 0, off_rowpart = 0,
+    size_t off_dom = 0, off_tiles = 0, off_groups = 0, off_partials = 0, off_blockpart = 0,
            off_above = 0, off_counter = 0, total = 0;
-    int th = 0, ntiles = 0, ngroups = 0, nblocks = 0, nparts = 0;
+    int th = 0, ntiles = 0, ngroups = 0, nblocks = 0;
 };
 
 void plan_static(const lbm_domain_desc& d, int storage, int th, DomainHost& h, StaticLayout& L)
@@ -1068,35 +1040,30 @@ void plan_static(const lbm_domain_desc& d, int storage, int th, DomainHost& h, S
     h.n = size_t(d.nx) * d.ny;
     h.plane = (long long)h.n;
     h.shift = storage == LBM_F64 ? 0.0 : d.rho0;
-    // second-pass tiles of th rows, stats groups of kMaxTileH; narrow row blocks
+    const bool d2 = d.lattice == LBM_D2Q9;
     L.th = th;
     L.ntiles = tiles_of(d.lattice, d.nx, d.ny, th);
-    L.ngroups = tiles_of(d.lattice, d.nx, d.ny, kMaxTileH);
-    L.nblocks = d.lattice == LBM_D2Q9 ? blocks_of(d.nx, d.ny, seg_width(d.nx, 1)) : 0;
-    L.nparts = d.lattice == LBM_D2Q9 ? strips_of(d.nx) * d.ny : 0;
+    L.ngroups = d2 ? groups_of(d.nx, d.ny) : L.ntiles;
+    L.nblocks = d2 ? blocks_of(d.nx, d.ny) : 0;
     h.tile_first = 0;
     h.tile_count = L.ntiles;
     h.group_first = 0;
     h.group_count = L.ngroups;
-    h.row_first = 0;
-    h.row_count = L.nparts;
+    h.part_first = 0;
+    h.part_count = L.nblocks;
     size_t off = 0;
     L.off_dom = off;
     off = align_up(off + sizeof(DomainDev), kAlign);
     L.off_tiles = off;
     off = align_up(off + size_t(L.ntiles) * sizeof(Tile), kAlign);
-    // tiles of kMaxTileH rows are the stats groups themselves
-    L.off_groups = L.off_tiles;
-    if (L.ntiles != L.ngroups) {
-        L.off_groups = off;
-        off = align_up(off + size_t(L.ngroups) * sizeof(Tile), kAlign);
-    }
+    L.off_groups = off;
+    off = align_up(off + size_t(L.ngroups) * sizeof(Group), kAlign);
     L.off_partials = off;
-    off = align_up(off + size_t(4) * L.ntiles * kNStat * sizeof(double), kAlign);
-    L.off_rowpart = off;
-    off = align_up(off + size_t(L.nparts) * kNStat * sizeof(double), kAlign);
+    off = align_up(off + size_t(4) * std::max(L.ntiles, L.ngroups) * kNStat * sizeof(double), kAlign);
+    L.off_blockpart = off;
+    off = align_up(off + size_t(L.nblocks) * kNStat * sizeof(double), kAlign);
     L.off_above = off;
-    off = align_up(off + size_t(L.nparts) * sizeof(unsigned), kAlign);
+    off = align_up(off + size_t(L.nblocks) * sizeof(unsigned), kAlign);
     L.off_counter = off;
     off = align_up(off + 2 * sizeof(long long), kAlign);
     L.total = plan_extras(h, storage, off);
@@ -1263,12 +1230,13 @@ int lbm_create(const lbm_domain_desc* domains, int32_t n_domains, const lbm_run_
         if (e == hipSuccess) e = hipStreamSynchronize(ctx->stream);
         if (e != hipSuccess) return bail(fail(nullptr, LBM_EDEVICE, std::string("init: ") + hipGetErrorString(e)));
     }
-    build_groups(ctx);
+    build_blocks(ctx);
     if (int(ctx->groups_host.size()) != ctx->lay.ngroups)
         return bail(fail(nullptr, LBM_EINVAL, "group table size mismatch"));
-    e = hipMemcpyAsync(ctx->d_groups(), ctx->groups_host.data(), ctx->groups_host.size() * sizeof(Tile),
-                       hipMemcpyHostToDevice, ctx->stream);
-    if (e != hipSuccess) return bail(fail(nullptr, LBM_EDEVICE, std::string("groups: ") + hipGetErrorString(e)));
+    if ((rc = upload_blocks(ctx))) {
+        g_err = ctx->err;
+        return bail(rc);
+    }
     // the tuner runs steps: the step counters must hold valid indices first
     rc = reset_counters(ctx);
     if (!rc) rc = ctx->lattice == LBM_D2Q9 ? autotune(ctx, run) : apply_shape(ctx, Shape{0, 1, false});
@@ -1547,7 +1515,7 @@ int lbm_step_static(const lbm_domain_desc* domain, int32_t storage, void* stream
     DomainDev* dom = reinterpret_cast<DomainDev*>(base + L.off_dom);
     Tile* tiles = reinterpret_cast<Tile*>(base + L.off_tiles);
     long long* counter = reinterpret_cast<long long*>(base + L.off_counter);
-    Tile* groups = reinterpret_cast<Tile*>(base + L.off_groups);
+    Group* groups = reinterpret_cast<Group*>(base + L.off_groups);
     e = launch_static_setup(dd, domain->lattice, dom, tiles, L.ntiles, L.th, groups, L.ngroups, counter, s);
     if (e != hipSuccess) return fail(nullptr, LBM_EDEVICE, std::string("static setup: ") + hipGetErrorString(e));
     StepKind k;
@@ -1574,14 +1542,12 @@ int lbm_step_static(const lbm_domain_desc* domain, int32_t storage, void* stream
     a.elbm = k.elbm ? 1 : 0;
     a.budget = k.budget;
     a.dense = k.dense;
-    a.rows = nullptr;
-    a.nrows = L.nblocks;
-    a.nparts = L.nparts;
-    set_grid(a, domain, 1);
+    a.blocks = nullptr;
+    a.nblocks = L.nblocks;
     a.groups = groups;
     a.ngroups = L.ngroups;
-    a.pstride = L.ntiles;
-    a.rowpart = reinterpret_cast<double*>(base + L.off_rowpart);
+    a.pstride = std::max(L.ntiles, L.ngroups);
+    a.blockpart = reinterpret_cast<double*>(base + L.off_blockpart);
     a.above = reinterpret_cast<unsigned*>(base + L.off_above);
     a.counter = counter;
     const bool d1 = domain->lattice == LBM_D1Q3;

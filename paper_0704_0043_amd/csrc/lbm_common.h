@@ -105,9 +105,9 @@ struct DomainDev {
     double ens_c, ens_k, delta_ens;   // ensemble limiter parameters
     double* ens;                  // [kNEns]: E(Delta S') and the thresholds of this step
     void* phibuf;                 // D1Q3 with ensemble limiters: phi applied by the first pass
-    int strips;                   // D2Q9: column strips of kThreads columns
-    int row_first, row_count;     // D2Q9: this domain's range of row partials (one per row and strip)
-    int group_first, group_count; // this domain's range of collision-partial groups (kMaxTileH rows)
+    unsigned inv_nx;              // ceil(2^32 / nx) (nx >= 64 only), see row_of_node
+    int part_first, part_count;   // D2Q9: this domain's range of collision partials (one per workgroup)
+    int group_first, group_count; // this domain's range of collision-partial groups
     BudgetState* bstate;          // budget threshold: search state (budget limiter only)
     BudgetBucket* bhist;          // [kBudgetBuckets], left zero between levels
     double* stats;          // [kNStat + 1]: last finalised sums, then the step index
@@ -148,24 +148,50 @@ constexpr int k1DMaxThreads = 448;
 inline int threads1d(int reach, int steps) { return (k1DWidth + 2 * reach * steps + kWave - 1) / kWave * kWave; }
 static_assert(k1DWidth + 4 * k1DMaxSteps <= k1DMaxThreads, "the halo of the longest launch fits");
 
-// One D2Q9 collision workgroup: rows [y0, y1) by columns [x0, x1) of one
-// domain, `width` (64, 128 or 256) columns per row, kThreads / width rows.
-struct RowBlock {
-    int domain, x0, x1, y0, y1, width;
+// The D2Q9 collision kernel walks a domain's nodes in row-major order, kThreads
+// consecutive nodes per workgroup, whatever the rows: every store (and every
+// load without a shift) of a wave is one aligned piece, the last workgroup of
+// the domain alone is short, and the grid streams through a narrow band of
+// rows.  Workgroup `first` of domain `domain` takes the nodes from
+// first * kThreads.
+struct Block {
+    int domain, first;
 };
+inline int blocks_of(int nx, int ny) { return int(((long long)nx * ny + kThreads - 1) / kThreads); }
 
-// Columns of a domain's row blocks: with `narrow`, the narrowest of 64, 128
-// and 256 that spans a row of a narrow domain (several of its rows then share
-// a workgroup and fewer lanes idle), else 256.
-__host__ __device__ inline int seg_width(int nx, int narrow)
+// Row of node n by the reciprocal ceil(2^32 / nx): the product is at most one
+// too large.
+__host__ __device__ inline int row_of_node(unsigned n, int nx, unsigned inv_nx)
+{
+    const unsigned r = unsigned(((unsigned long long)n * inv_nx) >> 32);
+    return int(r * unsigned(nx) > n ? r - 1 : r);
+}
+inline unsigned inverse_nx(int nx) { return nx > 1 ? unsigned(((1ull << 32) + nx - 1) / nx) : 0u; }
+
+// Collision partials (and the nodes) summed together for the stats and
+// E(Delta S'), the nodes [n0, n1) of a domain: kGroupParts workgroups of the
+// D2Q9 kernel, one D1Q3 tile.
+constexpr int kGroupParts = 64;
+struct Group {
+    int domain, n0, n1;
+};
+__host__ __device__ inline Group group_entry2d(int domain, int n, int i)
+{
+    constexpr int w = kGroupParts * kThreads;
+    return Group{domain, i * w, (i + 1) * w < n ? (i + 1) * w : n};
+}
+inline int groups_of(int nx, int ny) { return (blocks_of(nx, ny) + kGroupParts - 1) / kGroupParts; }
+
+// Columns reported for a domain's row blocks: with `narrow` 64 or 128 for a
+// domain that narrow, else 256.
+inline int seg_width(int nx, int narrow)
 {
     return (narrow && nx <= 64) ? 64 : ((narrow && nx <= 128) ? 128 : kThreads);
 }
 
 // Entry i of a domain's work tables (host and device build them alike):
 // D2Q9 tiles of kThreads columns by th rows in spatial order (row chunk, then
-// column strip); D2Q9 row blocks in row-major order; D1Q3 tiles of k1DWidth
-// sites.
+// column strip); D1Q3 tiles of k1DWidth sites.
 __host__ __device__ inline Tile tile_entry2d(int domain, int nx, int ny, int th, int i)
 {
     const int strips = (nx + kThreads - 1) / kThreads;
@@ -173,17 +199,6 @@ __host__ __device__ inline Tile tile_entry2d(int domain, int nx, int ny, int th,
     const int r = i / strips, x0 = (i - r * strips) * kThreads;
     return Tile{domain, x0, x0 + kThreads < nx ? x0 + kThreads : nx, r * th, r * th + th < ny ? r * th + th : ny,
                 r, chunks, (ny - r + chunks - 1) / chunks};
-}
-__host__ __device__ inline int blocks_of(int nx, int ny, int width)
-{
-    const int rows = kThreads / width;
-    return ((nx + width - 1) / width) * ((ny + rows - 1) / rows);
-}
-__host__ __device__ inline RowBlock block_entry2d(int domain, int nx, int ny, int width, int i)
-{
-    const int cols = (nx + width - 1) / width, rows = kThreads / width;
-    const int r = i / cols, x0 = (i - r * cols) * width, y0 = r * rows;
-    return RowBlock{domain, x0, x0 + width < nx ? x0 + width : nx, y0, y0 + rows < ny ? y0 + rows : ny, width};
 }
 __host__ __device__ inline Tile tile_entry1d(int domain, int nx, int i)
 {
@@ -223,10 +238,9 @@ struct StepArgs {
     int parity;             // read buf[parity], write buf[1 - parity]
     unsigned flags;
     double* partials;       // [2 parities][2 sets][pstride][kNStat]: FP64 stats, set 0 (collision)
-                            // per group of kMaxTileH rows, set 1 (second pass) per tile
-    const Tile* groups;     // the collision-partial groups: tiles of kMaxTileH rows, fixed, so
-                            // that the set-0 sums (and E(Delta S')) do not depend on the tile
-                            // height; D1Q3: the tiles
+                            // per group, set 1 (second pass) per tile
+    const Group* groups;    // the collision-partial groups: fixed, so that the set-0 sums (and
+                            // E(Delta S')) do not depend on the tile height
     int ngroups;
     int pstride;            // slots per set in `partials` (>= ntiles, ngroups)
     int median_pass;        // 1 if a second pass (median and/or ensemble limiters) writes set 1
@@ -236,15 +250,11 @@ struct StepArgs {
     int ens_pass;           // 1 if some domain has an ensemble-dependent limiter
     int elbm;               // 1 with ELBM collisions (all domains)
     int budget;             // kSelect* of the domains: budget threshold, top-k trimming
-    const RowBlock* rows;   // D2Q9 row blocks in row-major order, one per collision workgroup; several
-                            // domains only (a single one's follow from the block's place in the grid)
-    int width, row_shift;   // single domain: columns of its row blocks, log2 of their rows (width 0: table)
-    int nrows;              // blocks of the D2Q9 collision grid (table)
-    int grid_x, grid_y;     // ... and its shape for a single domain
-    int nparts;             // row partials (rows x strips) of all domains
-    double* rowpart;        // [rows x strips][kNStat]: collision partials of a step with kFlagStats,
-                            // one per domain row and 256-column strip
-    unsigned* above;        // [rows x strips]: byte w is 1 when the 64-column wave w of the segment holds
+    const Block* blocks;    // D2Q9 collision workgroups of several domains; null for one (block b is
+                            // workgroup b of the domain)
+    int nblocks;            // the D2Q9 collision grid has nblocks blocks
+    double* blockpart;      // [nblocks][kNStat]: collision partials of a step with kFlagStats
+    unsigned* above;        // [nblocks]: byte w is 1 when wave w of the block (64 consecutive nodes) holds
                             // a median candidate (Delta S' > delta_median) and stored its Delta S'
     long long* counter;     // [2] step index by parity
     int reach = 1;          // D1Q3: sites a step's result depends on, on either side
@@ -257,7 +267,7 @@ constexpr size_t kStaticScratchBytes = LBM_STATIC_SCRATCH_BYTES;
 // its address on `device` (looked up once per device; `device` must be current)
 hipError_t static_scratch(int device, char** ptr);
 hipError_t launch_static_setup(const DomainDev& dd, int lattice, DomainDev* dom, Tile* tiles, int ntiles, int th,
-                               Tile* groups, int ngroups, long long* counter, hipStream_t s);
+                               Group* groups, int ngroups, long long* counter, hipStream_t s);
 hipError_t launch_static_stats(const DomainDev* dom, double shift_mass, double* out, hipStream_t s);
 
 // Launchers (one per storage type / lattice), defined in the .hip files.

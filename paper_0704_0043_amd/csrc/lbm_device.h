@@ -900,42 +900,19 @@ __device__ inline void store_partial(const AccT<S, SL>& acc, double* out, double
     }
 }
 
-// The same, plus the rn <= kMaxTileH partials rp[0], rp[rstride kNStat], ...
-// written by an earlier kernel: they are fetched by the whole workgroup at
-// once, summed in fixed segments of eight, and the segments added after the
-// waves in order.  rowbuf holds kMaxTileH * kNStat + 8 * kNStat doubles.
-template <class S>
-__device__ inline void store_partial_rows(const AccT<S>& acc, double* out, double* lds, const double* rp, int rn,
-                                          long long rstride, double* rowbuf)
+// The sum of the rn <= kGroupParts partials rp[0], rp[kNStat], ... written by an
+// earlier kernel: fetched by the whole workgroup at once, summed in fixed
+// segments of eight, and the segments added in order.  rowbuf holds
+// kGroupParts * kNStat + 8 * kNStat doubles.
+__device__ inline void sum_partials(double* out, const double* rp, int rn, double* rowbuf)
 {
-    const int tid = threadIdx.x + threadIdx.y * blockDim.x;
-    const int nthr = blockDim.x * blockDim.y;
-    for (int e = tid; e < rn * kNStat; e += nthr) {
-        const int j = e / kNStat, k = e - j * kNStat;
-        rowbuf[e] = rp[j * rstride * kNStat + k];
-    }
-    double v[kNStat] = {double(acc.mass), double(acc.jx), double(acc.jy), double(acc.dpre), double(acc.dpost),
-                        double(acc.maxd), double(acc.lim), double(acc.ent), double(acc.trim), double(acc.filt),
-                        double(acc.nonpos), double(acc.nonfin), double(acc.fluid), 0.0,
-                        double(acc.ens), double(acc.pos)};
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) {
-#pragma unroll
-        for (int k = 0; k < kNStat; ++k) {
-            double o = __shfl_xor(v[k], off, 64);
-            v[k] = (k == kSMax) ? fmax(v[k], o) : v[k] + o;
-        }
-    }
-    const int wave = tid >> 6, lane = tid & 63;
-    if (lane == 0) {
-#pragma unroll
-        for (int k = 0; k < kNStat; ++k) lds[wave * kNStat + k] = v[k];
-    }
+    const int tid = threadIdx.x;
+    for (int e = tid; e < rn * kNStat; e += kThreads) rowbuf[e] = rp[e];
     __syncthreads();
-    double* seg = rowbuf + kMaxTileH * kNStat;     // [kNStat][8]
+    double* seg = rowbuf + kGroupParts * kNStat;     // [kNStat][8]
     if (tid < 8 * kNStat) {
         const int k = tid >> 3, g = tid & 7;
-        double s = k == kSMax ? -__builtin_huge_val() : 0.0;
+        double s = 0.0;      // (the largest Delta S' is never negative)
         for (int j = 8 * g; j < rn && j < 8 * g + 8; ++j) {
             const double r = rowbuf[j * kNStat + k];
             s = (k == kSMax) ? fmax(s, r) : s + r;
@@ -944,24 +921,19 @@ __device__ inline void store_partial_rows(const AccT<S>& acc, double* out, doubl
     }
     __syncthreads();
     if (tid < kNStat) {
-        const int nw = nthr >> 6;
-        double s = lds[tid];
-        for (int w = 1; w < nw; ++w) s = (tid == kSMax) ? fmax(s, lds[w * kNStat + tid]) : s + lds[w * kNStat + tid];
+        double s = 0.0;
 #pragma unroll
         for (int g = 0; g < 8; ++g) s = (tid == kSMax) ? fmax(s, seg[tid * 8 + g]) : s + seg[tid * 8 + g];
         out[tid] = s;
     }
 }
 
-// Partials of a workgroup whose threads hold at most one node each, covering
-// `nrow` rows of `wpr` waves each (a row of 64 wpr columns): the sums (FP32
-// for reduced storage, FP64 for FP64 storage) by a fixed DPP scan in each
+// Partial of a workgroup whose threads hold at most one node each: the sums
+// (FP32 for reduced storage, FP64 for FP64 storage) by a fixed DPP scan in each
 // wave (the limiter and entropy sums only in waves that hold one), the 0/1
-// counts by ballots; then for each row its waves combined in FP64 in order,
-// written to out + r * stride (r < nrow).
+// counts by ballots; then the waves combined in FP64 in order.
 template <class S>
-__device__ inline void node_partial_rows(const AccT<S>& acc, double* out, long long stride, int wpr, int nrow,
-                                         double* lds /* [4 * kNStat] */)
+__device__ inline void node_partial(const AccT<S>& acc, double* out, double* lds /* [4 * kNStat] */)
 {
     S v[8] = {acc.mass, acc.jx, acc.jy, acc.dpre, acc.dpost, acc.maxd, acc.lim, acc.ent};
 #pragma unroll
@@ -971,9 +943,9 @@ __device__ inline void node_partial_rows(const AccT<S>& acc, double* out, long l
         }
         v[k] = k == kSMax ? wave_reduce<true>(v[k]) : wave_reduce<false>(v[k]);
     }
-    const int tid = threadIdx.x + threadIdx.y * blockDim.x;
+    const int tid = threadIdx.x;
     const int wave = tid >> 6, lane = tid & 63;
-    // counts of a wave fit 32 bits; wpr is a power of two
+    // counts of a wave fit 32 bits
     auto count = [](bool b) { return double(unsigned(__popcll(__ballot(b)))); };
     const double cnt[8] = {count(acc.trim != 0), count(acc.filt != 0), count(acc.nonpos != 0),
                            count(acc.nonfin != 0), count(acc.fluid != 0),
@@ -985,12 +957,12 @@ __device__ inline void node_partial_rows(const AccT<S>& acc, double* out, long l
         for (int k = 0; k < 8; ++k) lds[wave * kNStat + 8 + k] = cnt[k];
     }
     __syncthreads();
-    if (tid < nrow * kNStat) {
-        const int r = tid / kNStat, k = tid - r * kNStat;
-        const double* row = lds + r * wpr * kNStat;
-        double s = row[k];
-        for (int w = 1; w < wpr; ++w) s = (k == kSMax) ? fmax(s, row[w * kNStat + k]) : s + row[w * kNStat + k];
-        out[r * stride * kNStat + k] = s;
+    if (tid < kNStat) {
+        double s = lds[tid];
+#pragma unroll
+        for (int w = 1; w < kThreads / kWave; ++w)
+            s = (tid == kSMax) ? fmax(s, lds[w * kNStat + tid]) : s + lds[w * kNStat + tid];
+        out[tid] = s;
     }
 }
 

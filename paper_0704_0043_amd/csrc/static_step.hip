@@ -42,11 +42,11 @@ hipError_t static_scratch(int device, char** ptr)
 // builds them for a context) and clears what a run must start from: the
 // step counters, the stats and the selection histogram.
 __global__ void __launch_bounds__(kThreads) k_static_setup(DomainDev dd, int lattice, DomainDev* dom, Tile* tiles,
-                                                           int ntiles, int th, Tile* groups, int ngroups,
+                                                           int ntiles, int th, Group* groups, int ngroups,
                                                            long long* counter)
 {
     const int nb = dd.bhist ? kBudgetBuckets : 0;
-    const int n = max(ntiles, max(nb, kNStat + 1));
+    const int n = max(max(ntiles, ngroups), max(nb, kNStat + 1));
     for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) {
         if (i == 0) {
             *dom = dd;
@@ -56,8 +56,10 @@ __global__ void __launch_bounds__(kThreads) k_static_setup(DomainDev dd, int lat
         if (i <= kNStat) dd.stats[i] = 0.0;
         if (i < ntiles)
             tiles[i] = lattice == kD2Q9 ? tile_entry2d(0, dd.nx, dd.ny, th, i) : tile_entry1d(0, dd.nx, i);
-        if (groups != tiles && i < ngroups)
-            groups[i] = lattice == kD2Q9 ? tile_entry2d(0, dd.nx, dd.ny, kMaxTileH, i) : tile_entry1d(0, dd.nx, i);
+        if (i < ngroups) {
+            const Tile t = tile_entry1d(0, dd.nx, i);
+            groups[i] = lattice == kD2Q9 ? group_entry2d(0, dd.nx * dd.ny, i) : Group{0, t.x0, t.x1};
+        }
         if (i < nb) dd.bhist[i] = BudgetBucket{0, 0, 0};
     }
 }
@@ -87,9 +89,9 @@ __global__ void k_static_stats(const DomainDev* dom, double shift_mass, double* 
 }
 
 hipError_t launch_static_setup(const DomainDev& dd, int lattice, DomainDev* dom, Tile* tiles, int ntiles, int th,
-                               Tile* groups, int ngroups, long long* counter, hipStream_t s)
+                               Group* groups, int ngroups, long long* counter, hipStream_t s)
 {
-    const int n = std::max(ntiles, dd.bhist ? kBudgetBuckets : kNStat + 1);
+    const int n = std::max(std::max(ntiles, ngroups), dd.bhist ? kBudgetBuckets : kNStat + 1);
     const int blocks = std::min((n + kThreads - 1) / kThreads, 1024);
     hipLaunchKernelGGL(k_static_setup, dim3(blocks), dim3(kThreads), 0, s, dd, lattice, dom, tiles, ntiles, th,
                        groups, ngroups, counter);

@@ -78,22 +78,38 @@ __device__ inline double* partial_slot(const StepArgs& a, int set, int tile)
     return a.partials + (((long long)a.parity * 2 + set) * a.pstride + tile) * kNStat;
 }
 
-// Row block of a workgroup: its place in the grid with one domain (row_grid),
-// else looked up.
-constexpr int kGridRows = 32768;     // grid rows per grid plane
-__device__ __forceinline__ RowBlock block_of(const StepArgs& a)
+// The node of a thread of the collision kernel and of k_form2d: 64 consecutive
+// nodes per wave.  `inner` (uniform in the wave) when all of them lie in rows
+// 1 .. ny - 2 of a domain at least 64 wide, so that every neighbour is at a
+// fixed distance (up to the wrap of the columns); the rest is the first and
+// last rows and very narrow domains.
+struct Node {
+    unsigned n;
+    int x, y;
+    bool in, inner;
+};
+__device__ __forceinline__ Node node_of(const DomainDev& D, int block)
 {
-    if (a.width == 0) return a.rows[blockIdx.x];
-    const int nx = a.dom[0].nx, ny = a.dom[0].ny;
-    const int x0 = int(blockIdx.x) * a.width, y0 = (int(blockIdx.z) * kGridRows + int(blockIdx.y)) << a.row_shift;
-    const int x1 = x0 + a.width, y1 = y0 + (1 << a.row_shift);
-    return RowBlock{0, x0, x1 < nx ? x1 : nx, y0, y1 < ny ? y1 : ny, a.width};
-}
-__device__ __forceinline__ bool first_block() { return (blockIdx.x | blockIdx.y | blockIdx.z) == 0; }
-static dim3 row_grid(const StepArgs& a)
-{
-    if (a.width == 0) return dim3(a.nrows);
-    return a.grid_y <= kGridRows ? dim3(a.grid_x, a.grid_y) : dim3(a.grid_x, kGridRows, (a.grid_y + kGridRows - 1) / kGridRows);
+    const int nx = D.nx, ny = D.ny;
+    const unsigned all = unsigned(nx) * unsigned(ny);
+    const int wave = __builtin_amdgcn_readfirstlane(int(threadIdx.x) / kWave);
+    const unsigned nw = unsigned(block) * kThreads + unsigned(wave) * kWave;
+    Node r;
+    r.n = nw + (threadIdx.x & (kWave - 1));
+    r.in = r.n < all;
+    if (nx >= kWave) {
+        const int yw = row_of_node(nw, nx, D.inv_nx);
+        r.x = int(nw - unsigned(yw) * unsigned(nx)) + int(threadIdx.x & (kWave - 1));
+        const bool next = r.x >= nx;
+        r.x -= next ? nx : 0;
+        r.y = yw + (next ? 1 : 0);
+        r.inner = yw > 0 && nw + kWave <= all - unsigned(nx);
+    } else {
+        r.y = int(r.n / unsigned(nx));
+        r.x = int(r.n - unsigned(r.y) * unsigned(nx));
+        r.inner = false;
+    }
+    return r;
 }
 
 // trimming factor of one node (it depends on the node alone, Sec. 3.2/3.4)
@@ -114,8 +130,7 @@ template <class T, int BC>
 struct Cols {
     unsigned m, c, p, own;
     int x;
-    bool ok;
-    __device__ Cols(int x_, int nx, bool in) : x(x_), ok(in)
+    __device__ Cols(int x_, int nx) : x(x_)
     {
         constexpr unsigned es = sizeof(T);
         if constexpr (BC == kPeriodic) {
@@ -175,6 +190,66 @@ __device__ __forceinline__ void gather2d(gptr<const T> src, long long plane, int
             const bool in = (L::vx(i) > 0 ? xm : (L::vx(i) < 0 ? xp : true)) &&
                             (L::vy(i) > 0 ? ym : (L::vy(i) < 0 ? yp : true));
             if (!in) g[i] = Store<T>::ld(at_bytes(src + (L::opp(i) * plane + r0), cc));
+        }
+    }
+}
+
+// The same into the node of a thread (Node): in inner waves the nine sources
+// are three lane offsets (columns x - 1, x, x + 1) on scalar bases, else they
+// are computed per lane.
+template <int BC, class T>
+__device__ __forceinline__ void gather_at(gptr<const T> src, long long plane, int nx, int ny, const Node& v,
+                                          typename Store<T>::A (&g)[9])
+{
+    using L = Lat<kD2Q9>;
+    constexpr unsigned es = sizeof(T);
+    const int x = v.x, y = v.y;
+    const bool xm = x > 0, xp = x < nx - 1;
+    const unsigned c = es * v.n;
+    if (v.inner) {
+        unsigned m = c - es, p = c + es;
+        if constexpr (BC == kPeriodic) {
+            m += xm ? 0u : es * unsigned(nx);
+            p -= xp ? 0u : es * unsigned(nx);
+        }
+        // (at a cavity's side walls these are the neighbouring rows' ends)
+#pragma unroll
+        for (int i = 0; i < 9; ++i) {
+            const long long up = L::vy(i) > 0 ? -(long long)nx : (L::vy(i) < 0 ? (long long)nx : 0);
+            g[i] = Store<T>::ld(at_bytes(src + (i * plane + up), L::vx(i) > 0 ? m : (L::vx(i) < 0 ? p : c)));
+        }
+    } else {
+        int left = x - 1, right = x + 1, below = y - 1, top = y + 1;
+        if constexpr (BC == kPeriodic) {
+            left = xm ? left : nx - 1;
+            right = xp ? right : 0;
+            below = y > 0 ? below : ny - 1;
+            top = y < ny - 1 ? top : 0;
+        } else {
+            left = xm ? left : 0;
+            right = xp ? right : x;
+            below = y > 0 ? below : 0;
+            top = y < ny - 1 ? top : y;
+        }
+        const unsigned r0 = unsigned(y) * unsigned(nx), rm = unsigned(below) * unsigned(nx), rp = unsigned(top) * unsigned(nx);
+#pragma unroll
+        for (int i = 0; i < 9; ++i) {
+            const unsigned at = (L::vy(i) > 0 ? rm : (L::vy(i) < 0 ? rp : r0)) +
+                                unsigned(L::vx(i) > 0 ? left : (L::vx(i) < 0 ? right : x));
+            g[i] = Store<T>::ld(at_bytes(src + i * plane, es * at));
+        }
+    }
+    if constexpr (BC != kPeriodic) {
+        // a source off the domain (at wall and lid nodes only): the node's own
+        // opposite population
+        const bool ym = y > 0, yp = y < ny - 1;
+        if (!(xm && xp && ym && yp)) {
+#pragma unroll
+            for (int i = 1; i < 9; ++i) {
+                const bool in = (L::vx(i) > 0 ? xm : (L::vx(i) < 0 ? xp : true)) &&
+                                (L::vy(i) > 0 ? ym : (L::vy(i) < 0 ? yp : true));
+                if (!in) g[i] = Store<T>::ld(at_bytes(src + L::opp(i) * plane, c));
+            }
         }
     }
 }
@@ -266,13 +341,9 @@ __global__ void __launch_bounds__(kThreads) k_collide2d(StepArgs a)
     using L = Lat<kD2Q9>;
     constexpr int Q = 9;
     __shared__ double red[STATS ? 4 * kNStat : 1];
-    // one row block per workgroup, in row-major order: the grid streams
-    // through the domain a few rows at a time (DRAM pages and the rows that
-    // neighbours pull from stay few), one node per thread; a block of a
-    // narrow domain holds kThreads / width of its rows
-    const RowBlock t = block_of(a);
+    // one node per thread, kThreads consecutive nodes per workgroup
+    const Block t = a.blocks ? a.blocks[blockIdx.x] : Block{0, int(blockIdx.x)};
     const DomainDev& D = a.dom[t.domain];
-    if (t.y0 >= t.y1) return;          // a grid of several planes ends past the last row
     const int nx = D.nx, ny = D.ny;
     const long long plane = D.plane;
     const gptr<const T> src = to_global<T>(static_cast<const void*>(D.buf[a.parity]));
@@ -285,25 +356,25 @@ __global__ void __launch_bounds__(kThreads) k_collide2d(StepArgs a)
     const bool dense = !ELBM && D.dense;       // k_form2d stores the fluid nodes
     const long long step = a.counter[a.parity];
     // the index of the next step, read by the next launch (which reads buffer 1 - parity)
-    if (first_block() && threadIdx.x == 0) a.counter[1 - a.parity] = step + 1;
+    if (blockIdx.x == 0 && threadIdx.x == 0) a.counter[1 - a.parity] = step + 1;
 
     // The ensemble limiters and the GATE reading of the median use every
     // Delta S'.  The FLOOR median only needs the values above delta: its
     // threshold max(median, delta) and its decision are unchanged when every
     // value at or below delta is replaced by 0.  So there a wave with no node
-    // above delta stores nothing, and the median pass reads its 64 columns as
+    // above delta stores nothing, and the median pass reads its 64 nodes as
     // zeros (a.above records which waves stored).
     const bool every = (D.limiter & kLimEns) || D.median_mode != 0;
     AccT<A> acc;
     bool any_up = false;       // a fluid node of the wave is a median candidate
-    // the node (cl.x, y) of this thread
-    auto visit = [&](const int y, const Cols<T, BC>& cl) {
-        {
+    const Node v = node_of(D, t.first);
+    {
+        const int x = v.x, y = v.y;
+        const unsigned node = v.n, own = unsigned(sizeof(T)) * v.n;
+        if (v.in) {
             A g[Q];
-            gather2d<BC>(src, plane, nx, ny, cl, y, g);
-            const long long row = (long long)y * nx;
-            const unsigned node = unsigned(row) + unsigned(cl.x);
-            const int cls = node_class<BC>(cl.x, y, nx, ny);
+            gather_at<BC>(src, plane, nx, ny, v, g);
+            const int cls = node_class<BC>(x, y, nx, ny);
             if (cls == kNodeFluid) {
                 SiteState<kD2Q9, A> S;
                 SiteScalars sc;
@@ -316,7 +387,7 @@ __global__ void __launch_bounds__(kThreads) k_collide2d(StepArgs a)
                     const double e = entropy_site<kD2Q9>(g, shift);
                     if (isfinite(e)) acc.ent += A(e);
                 }
-                if (cl.x == D.probe_x && y == D.probe_y) {
+                if (x == D.probe_x && y == D.probe_y) {
                     const gptr<float> p = to_global<float>(D.probe) + 2 * (step % D.probe_cap);
                     p[0] = sc.ux;
                     p[1] = sc.uy;
@@ -339,7 +410,7 @@ __global__ void __launch_bounds__(kThreads) k_collide2d(StepArgs a)
                         phi = fmin(phi, pp);
                     }
                 }
-                if (!dense) store_limited<T>(dst, plane, row, cl.own, S, phi, S.c);
+                if (!dense) store_limited<T>(dst, plane, 0, own, S, phi, S.c);
                 if (keep_ds) {
                     // NaN counts as above: such a wave always stores its values
                     const bool up = (D.limiter & kLimMedian) && !(S.dpost <= A(D.delta_median));
@@ -357,17 +428,17 @@ __global__ void __launch_bounds__(kThreads) k_collide2d(StepArgs a)
                     to_global<double>(D.dS)[node] = double(S.dpost);
                 }
             } else {
-                const bool corner = (cl.x == 0 || cl.x == nx - 1) && (y == 0 || y == ny - 1);
+                const bool corner = (x == 0 || x == nx - 1) && (y == 0 || y == ny - 1);
                 if (D.diffusive && !corner) {
                     // diffusive Maxwell wall; the lid moves with (u0, 0)
-                    const int mx = cl.x == 0 ? 1 : (cl.x == nx - 1 ? -1 : 0);
+                    const int mx = x == 0 ? 1 : (x == nx - 1 ? -1 : 0);
                     const int my = y == 0 ? 1 : (y == ny - 1 ? -1 : 0);
-                    diffusive_wall<T, QE>(dst, plane, row, cl.own, g, shift, my != 0 ? 0 : mx, my,
+                    diffusive_wall<T, QE>(dst, plane, 0, own, g, shift, my != 0 ? 0 : mx, my,
                                           y == ny - 1 ? A(D.lid_ux) : A(0));
                 } else if (cls == kNodeWall) {
                     // bounce-back: every population leaves reversed, no collision
 #pragma unroll
-                    for (int i = 0; i < Q; ++i) Store<T>::st(at_bytes(dst + (i * plane + row), cl.own), g[L::opp(i)]);
+                    for (int i = 0; i < Q; ++i) Store<T>::st(at_bytes(dst + i * plane, own), g[L::opp(i)]);
                 } else {
                     // lid: f*(rho0, (u0, 0)) in shift form
                     A E[Q];
@@ -375,7 +446,7 @@ __global__ void __launch_bounds__(kThreads) k_collide2d(StepArgs a)
                     const A r0 = A(D.rho0);
 #pragma unroll
                     for (int i = 0; i < Q; ++i)
-                        Store<T>::st(at_bytes(dst + (i * plane + row), cl.own), A(L::w(i)) * ((r0 - shift) + r0 * E[i]));
+                        Store<T>::st(at_bytes(dst + i * plane, own), A(L::w(i)) * ((r0 - shift) + r0 * E[i]));
                 }
                 if constexpr (STATS) {
                     SiteScalars sc;
@@ -388,31 +459,15 @@ __global__ void __launch_bounds__(kThreads) k_collide2d(StepArgs a)
                 }
             }
         }
-    };
-    if (t.width == kThreads) {
-        // one row per block: its index is uniform, so are the row offsets
-        // of every load and store (scalar bases, 32-bit lane offsets)
-        const int x = t.x0 + int(threadIdx.x);
-        const Cols<T, BC> cl(x, nx, x < t.x1);
-        if (cl.ok) visit(t.y0, cl);
-    } else {
-        // a block of a narrow domain (its width a power of two: 64 or 128,
-        // so that a wave never spans two rows, as the cavity gather needs)
-        const int lx = int(threadIdx.x) & (t.width - 1), ly = int(threadIdx.x) >> __builtin_ctz(unsigned(t.width));
-        const int y = t.y0 + ly;
-        const Cols<T, BC> cl(t.x0 + lx, nx, t.x0 + lx < t.x1 && y < t.y1);
-        if (cl.ok) visit(y, cl);
     }
-    const long long part = (long long)D.row_first + (long long)t.y0 * D.strips + t.x0 / kThreads;
+    const int wave = int(threadIdx.x) / kWave;
+    const long long part = (long long)D.part_first + t.first;
     if (D.limiter & kLimMedian) {
         // which waves hold candidates; the lanes of wall nodes do not know
-        const int wpr = t.width / kWave, wave = int(threadIdx.x) / kWave, r = wave / wpr;
         const bool some = __ballot(any_up) != 0;
-        if ((threadIdx.x & (kWave - 1)) == 0 && t.y0 + r < t.y1)
-            to_global<unsigned char>(a.above + part + (long long)r * D.strips)[wave - r * wpr] = some ? 1 : 0;
+        if ((threadIdx.x & (kWave - 1)) == 0) to_global<unsigned char>(a.above + part)[wave] = some ? 1 : 0;
     }
-    // one partial per row of the block (row y, strip x0 / kThreads)
-    if constexpr (STATS) node_partial_rows(acc, a.rowpart + part * kNStat, D.strips, t.width / kWave, t.y1 - t.y0, red);
+    if constexpr (STATS) node_partial(acc, a.blockpart + part * kNStat, red);
 }
 
 // Second pass: median filter (Sec. 3.5; cavity stencils of Sec. 4.4) on the
@@ -644,22 +699,23 @@ __device__ __forceinline__ void second_pass2d(const StepArgs& a)
         else
             return y < 0 ? 0 : (y >= ny ? ny - 1 : y);
     };
-    // FLOOR median only: the 64 columns of a collision wave in which no node
-    // exceeded delta hold no Delta S' of this step and read as zeros.  Which
-    // waves stored (byte w of the segment's word) is staged in LDS
-    // for the tile's rows and halo rows, for its own column strip and the two
-    // neighbouring ones: [0] left, [1] own, [2] right.
+    // FLOOR median only: the 64 consecutive nodes of a collision wave in which
+    // no node exceeded delta hold no Delta S' of this step and read as zeros.
+    // Which waves stored is staged in LDS for the tile's rows and halo rows:
+    // [0] and [kFlagSlots - 1] the waves of the columns left and right of the
+    // tile, between them those of its columns (at most five).
     const bool sparse = !((D.limiter & kLimEns) || D.median_mode != 0);
-    __shared__ unsigned sflag[3][kMaxTileH + 2];
-    const int strip = t.x0 / kThreads;
-    int strip_l, strip_r;
+    constexpr int kFlagSlots = 8;
+    __shared__ unsigned char sflag[kMaxTileH + 2][kFlagSlots];
+    int xl = t.x0 - 1, xr = t.x1;      // the columns beside the tile
     if constexpr (BC == kPeriodic) {
-        strip_l = (t.x0 == 0 ? nx - 1 : t.x0 - 1) / kThreads;
-        strip_r = (t.x1 == nx ? 0 : t.x1) / kThreads;
+        xl = xl < 0 ? nx - 1 : xl;
+        xr = xr == nx ? 0 : xr;
     } else {
-        strip_l = (t.x0 == 0 ? 0 : t.x0 - 1) / kThreads;
-        strip_r = (t.x1 == nx ? nx - 1 : t.x1) / kThreads;
+        xl = xl < 0 ? 0 : xl;
+        xr = xr == nx ? nx - 1 : xr;
     }
+    const auto wave_flags = reinterpret_cast<const unsigned char*>(a.above + D.part_first);
     // The filter's threshold is never below delta (FLOOR: max(median, delta);
     // GATE: only nodes above delta), so a tile none of whose nodes has
     // Delta S' > delta (the collision kernel counted them, in the same
@@ -677,19 +733,28 @@ __device__ __forceinline__ void second_pass2d(const StepArgs& a)
         }
     }
     if (D.limiter & (kLimMedian | kLimEns)) {
-        const long long r0 = (long long)D.row_first + (long long)t.y0 * D.strips + t.x0 / kThreads;
         const int rows = t.y1 - t.y0;
         bool cand = false;
-        // (the bytes of columns past the grid are never written)
-        auto stored = [&](long long seg, int s3) {
-            const int cols = nx - s3 * kThreads;
-            return a.above[seg] & (cols > 3 * kWave ? ~0u : (1u << (8 * ((cols + kWave - 1) / kWave))) - 1u);
-        };
-        if (int(threadIdx.x) < rows) {
-            const long long seg = r0 + (long long)threadIdx.x * D.strips;
-            if (D.limiter & kLimMedian) cand = stored(seg, strip) != 0;
-            if constexpr (ENS) {
-                const double* rp = a.rowpart + seg * kNStat;
+        if (D.limiter & kLimMedian) {
+            for (int idx = int(threadIdx.x); idx < (rows + 2) * kFlagSlots; idx += kThreads) {
+                const int ry = idx / kFlagSlots, slot = idx % kFlagSlots;
+                const unsigned r = unsigned(row_of(t.y0 - 1 + ry)) * unsigned(nx);
+                const unsigned first = (r + unsigned(t.x0)) / kWave, last = (r + unsigned(t.x1 - 1)) / kWave;
+                const unsigned at = slot == 0 ? (r + unsigned(xl)) / kWave
+                                              : (slot == kFlagSlots - 1 ? (r + unsigned(xr)) / kWave : first + unsigned(slot - 1));
+                const bool own = slot > 0 && slot < kFlagSlots - 1;
+                const unsigned char f = own && at > last ? 0 : wave_flags[at];
+                sflag[ry][slot] = f;
+                // (a wave may reach into the neighbouring tiles' columns)
+                cand = cand || (f && own && ry > 0 && ry <= rows);
+            }
+        }
+        if constexpr (ENS) {
+            // the collision workgroups of a row's columns: at most two
+            if (int(threadIdx.x) < 2 * rows) {
+                const unsigned r = unsigned(t.y0 + int(threadIdx.x) / 2) * unsigned(nx);
+                const unsigned b = (threadIdx.x & 1) ? (r + unsigned(t.x1 - 1)) / kThreads : (r + unsigned(t.x0)) / kThreads;
+                const double* rp = a.blockpart + ((long long)D.part_first + b) * kNStat;
                 const A mx = A(rp[kSMax]);
                 const bool inf = rp[kSNonpos] > 0.0;
                 if (D.limiter & (kLimEnsSmooth | kLimEnsRational)) cand = cand || rp[kSFluid] > 0.0;
@@ -699,17 +764,6 @@ __device__ __forceinline__ void second_pass2d(const StepArgs& a)
             }
         }
         active = __syncthreads_or(cand || (a.flags & kFlagAllTiles));
-        // staged only for a tile that has something to filter
-        if (active && (D.limiter & kLimMedian) && sparse) {
-            const int nr = rows + 2;
-            for (int idx = int(threadIdx.x); idx < 3 * nr; idx += kThreads) {
-                const int slot = idx / nr, ry = idx - slot * nr;
-                const int s3 = slot == 0 ? strip_l : (slot == 1 ? strip : strip_r);
-                const long long seg = (long long)D.row_first + (long long)row_of(t.y0 - 1 + ry) * D.strips + s3;
-                sflag[slot][ry] = stored(seg, s3);
-            }
-            __syncthreads();
-        }
     }
     // nothing to filter in this tile: its partial is zero (no reduction)
     if (!active) {
@@ -736,9 +790,6 @@ __device__ __forceinline__ void second_pass2d(const StepArgs& a)
             xm = x > 0 ? x - 1 : x;
             xp = x < nx - 1 ? x + 1 : x;
         }
-        const int sx = x / kThreads, sxm = xm / kThreads, sxp = xp / kThreads;
-        const int wx = (x % kThreads) / kWave, wxm = (xm % kThreads) / kWave, wxp = (xp % kThreads) / kWave;
-        const int slot_m = sxm == sx ? 1 : 0, slot_p = sxp == sx ? 1 : 2;
         // Each lane loads its own column (one aligned load per row); the
         // columns x -+ 1 come from the neighbouring lanes.  Only the first
         // lane of a wave and the lane at the right end of a wave or of the
@@ -756,10 +807,12 @@ __device__ __forceinline__ void second_pass2d(const StepArgs& a)
         // then the columns x -+ 1 from the neighbouring lanes
         auto complete = [&](int y, A (&r)[3]) {
             if (sparse) {
-                const int ry = y - (t.y0 - 1);
-                if (!((sflag[1][ry] >> (8 * wx)) & 1)) r[1] = A(0);
-                if (own_l && !((sflag[slot_m][ry] >> (8 * wxm)) & 1)) r[0] = A(0);
-                if (own_r && !((sflag[slot_p][ry] >> (8 * wxp)) & 1)) r[2] = A(0);
+                const unsigned char* f = sflag[y - (t.y0 - 1)];
+                const unsigned r0 = unsigned(row_of(y)) * unsigned(nx), first = (r0 + unsigned(t.x0)) / kWave;
+                auto slot = [&](int xs) { return f[1 + int((r0 + unsigned(xs)) / kWave - first)]; };
+                if (!slot(x)) r[1] = A(0);
+                if (own_l && !(x == t.x0 ? f[0] : slot(x - 1))) r[0] = A(0);
+                if (own_r && !(x == t.x1 - 1 ? f[kFlagSlots - 1] : slot(x + 1))) r[2] = A(0);
             }
             // every lane takes part in the shifts (no branch around them)
             const A l = lane_shift<-1>(r[1]), rr = lane_shift<+1>(r[1]);
@@ -886,18 +939,18 @@ __global__ void __launch_bounds__(kThreads) k_median_ens2d(StepArgs a)
 // Second pass of the domains whose every node it moves (the smooth and the
 // rational factor).  The collision kernel stored their Delta S' and no
 // populations, and this pass forms each fluid node's state once, one node per
-// thread over the same row blocks: 36 + 4 and 40 + 36 bytes per FP32 node in
+// thread over the same nodes: 36 + 4 and 40 + 36 bytes per FP32 node in
 // the two passes, where storing the trimmed state and rescaling it in place
 // moved 36 + 40 and 40 + 36 and waited for the stored state besides.  Its
-// terms of the sums join the row's partial.
+// terms of the sums join the workgroup's partial.
 template <class T, int QE, int DS, int BC>
 __global__ void __launch_bounds__(kThreads) k_form2d(StepArgs a)
 {
     using A = typename Store<T>::A;
     __shared__ double red[4 * kNStat];
-    const RowBlock t = block_of(a);
+    const Block t = a.blocks ? a.blocks[blockIdx.x] : Block{0, int(blockIdx.x)};
     const DomainDev& D = a.dom[t.domain];
-    if (!D.dense || t.y0 >= t.y1) return;
+    if (!D.dense) return;
     const int nx = D.nx, ny = D.ny;
     const long long plane = D.plane;
     const gptr<const T> src = to_global<T>(static_cast<const void*>(D.buf[a.parity]));
@@ -908,88 +961,72 @@ __global__ void __launch_bounds__(kThreads) k_form2d(StepArgs a)
 #pragma unroll
     for (int k = 0; k < kNEns; ++k) ensv[k] = D.ens[k];
     AccT<A, double> acc;
-    auto visit = [&](const int y, const Cols<T, BC>& cl) {
-        const int x = cl.x, lane = int(threadIdx.x) & (kWave - 1);
-        const int yw = __builtin_amdgcn_readfirstlane(y);      // a wave covers one row
-        const long long row = (long long)yw * nx;
-        // the rows above and below and the columns beside (clamped at a
-        // cavity's edges, where no fluid node reads them)
-        int ym = yw - 1, yp = yw + 1, xm = x - 1, xp = x + 1;
-        if constexpr (BC == kPeriodic) {
-            ym = yw == 0 ? ny - 1 : ym;
-            yp = yw == ny - 1 ? 0 : yp;
-            xm = x == 0 ? nx - 1 : xm;
-            xp = x == nx - 1 ? 0 : xp;
-        } else {
-            ym = yw == 0 ? 0 : ym;
-            yp = yw == ny - 1 ? yw : yp;
-            xm = x == 0 ? 0 : xm;
-            xp = x == nx - 1 ? x : xp;
-        }
+    const Node v = node_of(D, t.first);
+    const int x = v.x, y = v.y, lane = int(threadIdx.x) & (kWave - 1);
+    if (v.in) {
+        const unsigned n = v.n;
         A w[3][3];
         if (D.limiter & kLimMedian) {
-            const bool own_l = lane == 0, own_r = lane == kWave - 1 || x == t.x1 - 1;
+            // rows y - 1, y, y + 1 of Delta S'; the columns beside come from the
+            // neighbouring lanes, the wave's end lanes and the row's end nodes
+            // load theirs (clamped at a cavity's edges, where no fluid node
+            // reads them)
+            const unsigned all = unsigned(nx) * unsigned(ny);
+            const bool end_l = x == 0, end_r = x == nx - 1;
+            const unsigned wrap = BC == kPeriodic ? unsigned(nx) : 1u;
+            const bool own_l = lane == 0 || end_l, own_r = lane == kWave - 1 || end_r || n + 1 == all;
 #pragma unroll
             for (int k = 0; k < 3; ++k) {
-                const gptr<const A> r = dsb + (long long)(k == 0 ? ym : (k == 1 ? yw : yp)) * nx;
-                w[k][1] = Store<A>::ld(r + x);
+                unsigned r = k == 0 ? n - unsigned(nx) : (k == 1 ? n : n + unsigned(nx));
+                if (k == 0 && y == 0) r = BC == kPeriodic ? n + all - unsigned(nx) : n;
+                if (k == 2 && y == ny - 1) r = BC == kPeriodic ? n + unsigned(nx) - all : n;
+                w[k][1] = Store<A>::ld(dsb + r);
                 w[k][0] = lane_shift<-1>(w[k][1]);
                 w[k][2] = lane_shift<+1>(w[k][1]);
-                if (own_l) w[k][0] = Store<A>::ld(r + xm);
-                if (own_r) w[k][2] = Store<A>::ld(r + xp);
+                if (own_l) w[k][0] = Store<A>::ld(dsb + (end_l ? r + wrap - 1 : r - 1));
+                if (own_r) w[k][2] = Store<A>::ld(dsb + (end_r ? r + 1 - wrap : r + 1));
             }
         } else {
-            w[1][1] = Store<A>::ld(dsb + row + x);
+            w[1][1] = Store<A>::ld(dsb + n);
         }
         A g[9];
-        gather2d<BC>(src, plane, nx, ny, cl, y, g);
-        if (node_class<BC>(x, y, nx, ny) != kNodeFluid) return;
-        const A dc = w[1][1];
-        A tgt = A(__builtin_huge_val()), fac = A(1), thr;
-        SecondHit h;
-        if ((D.limiter & kLimMedian) && median_hit<BC>(D, x, y, nx, ny, w[0], w[1], w[2], thr)) {
-            h.bits |= kMaskMedian;
-            tgt = thr;
-            acc.filt = 1;
+        gather_at<BC>(src, plane, nx, ny, v, g);
+        if (node_class<BC>(x, y, nx, ny) == kNodeFluid) {
+            const A dc = w[1][1];
+            A tgt = A(__builtin_huge_val()), fac = A(1), thr;
+            SecondHit h;
+            if ((D.limiter & kLimMedian) && median_hit<BC>(D, x, y, nx, ny, w[0], w[1], w[2], thr)) {
+                h.bits |= kMaskMedian;
+                tgt = thr;
+                acc.filt = 1;
+            }
+            ens_terms(D, ensv, dc, tgt, fac, h);
+            acc.ens = h.ens;
+            acc.trim = h.trim;
+            if (record && h.bits) to_global<unsigned char>(D.mask)[n] |= (unsigned char)h.bits;
+            SiteState<kD2Q9, A> S;
+            const A phi = form_state<T, QE, DS>(D, g, dc, tgt, fac, S, acc.lim);
+            store_limited<T>(dst, plane, 0, unsigned(sizeof(T)) * n, S, phi, S.c);
         }
-        ens_terms(D, ensv, dc, tgt, fac, h);
-        acc.ens = h.ens;
-        acc.trim = h.trim;
-        if (record && h.bits) to_global<unsigned char>(D.mask)[unsigned(row) + unsigned(x)] |= (unsigned char)h.bits;
-        SiteState<kD2Q9, A> S;
-        const A phi = form_state<T, QE, DS>(D, g, dc, tgt, fac, S, acc.lim);
-        store_limited<T>(dst, plane, row, cl.own, S, phi, S.c);
-    };
-    if (t.width == kThreads) {
-        const int x = t.x0 + int(threadIdx.x);
-        const Cols<T, BC> cl(x, nx, x < t.x1);
-        if (cl.ok) visit(t.y0, cl);
-    } else {
-        const int lx = int(threadIdx.x) & (t.width - 1), ly = int(threadIdx.x) >> __builtin_ctz(unsigned(t.width));
-        const int y = t.y0 + ly;
-        const Cols<T, BC> cl(t.x0 + lx, nx, t.x0 + lx < t.x1 && y < t.y1);
-        if (cl.ok) visit(y, cl);
     }
-    // one value per wave and term, then into the row's partial
+    // one value per wave and term, then added to the workgroup's partial
+    // (nobody else's: the atomic add only spares the wait for the old value)
     const int wave = int(threadIdx.x) >> 6;
     const double lim = wave_reduce<false>(acc.lim);
     auto count = [](bool b) { return double(unsigned(__popcll(__ballot(b)))); };
     const double nt = count(acc.trim != 0), nf = count(acc.filt != 0), ne = count(acc.ens != 0);
-    if ((threadIdx.x & (kWave - 1)) == kWave - 1) {
+    if (lane == kWave - 1) {
         red[wave * 4] = lim;
         red[wave * 4 + 1] = nt;
         red[wave * 4 + 2] = nf;
         red[wave * 4 + 3] = ne;
     }
     __syncthreads();
-    const int wpr = t.width / kWave, tid = int(threadIdx.x);
-    if (tid < 4 * (t.y1 - t.y0)) {
-        const int r = tid >> 2, k = tid & 3;
-        double s = 0.0;
-        for (int w = 0; w < wpr; ++w) s += red[(r * wpr + w) * 4 + k];
-        double* out = a.rowpart + ((long long)D.row_first + (long long)(t.y0 + r) * D.strips + t.x0 / kThreads) * kNStat;
+    const int k = int(threadIdx.x);
+    if (k < 4) {
+        const double s = (red[k] + red[4 + k]) + (red[8 + k] + red[12 + k]);
         const int slot = k == 0 ? kSLim : (k == 1 ? kSTrim : (k == 2 ? kSFilt : kSEns));
-        out[slot] += s;
+        unsafeAtomicAdd(a.blockpart + ((long long)D.part_first + t.first) * kNStat + slot, s);
     }
 }
 
@@ -1067,7 +1104,7 @@ __global__ void __launch_bounds__(kThreads) k_fused2d(StepArgs a)
             in_x = xe >= 0 && xe < nx;
             xc = xe < 0 ? 0 : (xe >= nx ? nx - 1 : xe);
         }
-        const Cols<T, BC> cl(xc, nx, true);
+        const Cols<T, BC> cl(xc, nx);
         // rows y0 - 1 .. y1; off a cavity they are no nodes (clamped loads)
         auto row_of = [&](int y) -> int {
             if constexpr (BC == kPeriodic) return y < 0 ? y + ny : (y >= ny ? y - ny : y);
@@ -1536,15 +1573,15 @@ hipError_t LBM_CAT(launch_step2d, LBM_SUFFIX)(int qe, int ds, int bc, const Step
 {
     const bool stats = a.flags & kFlagStats;
     if (kernel == 0)
-        return stats ? dispatch<0, 1>(qe, ds, bc, LBM_LAUNCH(row_grid(a), kThreads, k_collide2d, false, true))
-                     : dispatch<0, 1>(qe, ds, bc, LBM_LAUNCH(row_grid(a), kThreads, k_collide2d, false, false));
+        return stats ? dispatch<0, 1>(qe, ds, bc, LBM_LAUNCH(a.nblocks, kThreads, k_collide2d, false, true))
+                     : dispatch<0, 1>(qe, ds, bc, LBM_LAUNCH(a.nblocks, kThreads, k_collide2d, false, false));
     if (kernel == 2)
-        return stats ? dispatch<0, 1, true>(qe, ds, bc, LBM_LAUNCH(row_grid(a), kThreads, k_collide2d, true, true))
-                     : dispatch<0, 1, true>(qe, ds, bc, LBM_LAUNCH(row_grid(a), kThreads, k_collide2d, true, false));
+        return stats ? dispatch<0, 1, true>(qe, ds, bc, LBM_LAUNCH(a.nblocks, kThreads, k_collide2d, true, true))
+                     : dispatch<0, 1, true>(qe, ds, bc, LBM_LAUNCH(a.nblocks, kThreads, k_collide2d, true, false));
     if (kernel == 3)
         return stats ? dispatch<0, 1>(qe, ds, bc, LBM_LAUNCH(a.ntiles, kThreads, k_fused2d, true))
                      : dispatch<0, 1>(qe, ds, bc, LBM_LAUNCH(a.ntiles, kThreads, k_fused2d, false));
-    if (kernel == 4) return dispatch<0, 1>(qe, ds, bc, LBM_LAUNCH(row_grid(a), kThreads, k_form2d));
+    if (kernel == 4) return dispatch<0, 1>(qe, ds, bc, LBM_LAUNCH(a.nblocks, kThreads, k_form2d));
     if (a.elbm)
         return a.ens_pass ? dispatch<0, 1, true>(qe, ds, bc, LBM_LAUNCH(a.ntiles, kThreads, k_median_ens2d, true))
                           : dispatch<0, 1, true>(qe, ds, bc, LBM_LAUNCH(a.ntiles, kThreads, k_median2d, true));
