@@ -53,6 +53,16 @@ int second_kinds(const lbm_domain_desc& d)
     return deferred(d) || (d.limiter & LBM_LIM_MEDIAN) ? kSparseSome : 0;
 }
 
+// Delta S form of the kernels: the exact one with the root solve of the exact
+// homothety where some domain asks for it
+int ds_kernel(const lbm_domain_desc* doms, int32_t nd)
+{
+    if (doms[0].ds_form == LBM_DS_QUADRATIC) return kQuad;
+    for (int k = 0; k < nd; ++k)
+        if (doms[k].homothety) return kExactHom;
+    return kExact;
+}
+
 // the radix selections a domain's step runs
 int selections(const lbm_domain_desc& d)
 {
@@ -1132,7 +1142,7 @@ int lbm_create(const lbm_domain_desc* domains, int32_t n_domains, const lbm_run_
     ctx->storage = run->storage;
     ctx->lattice = domains[0].lattice;
     ctx->qe = domains[0].qe;
-    ctx->ds = domains[0].ds_form;
+    ctx->ds = ds_kernel(domains, n_domains);
     // both cavity kinds run the cavity kernels; the wall rule is per domain
     ctx->bc = is_cavity(domains[0].bc) ? kCavity : domains[0].bc;
     ctx->elbm = domains[0].collision == LBM_COLL_ELBM;
@@ -1522,7 +1532,7 @@ int lbm_step_static(const lbm_domain_desc* domain, int32_t storage, void* stream
     k.storage = storage;
     k.lattice = domain->lattice;
     k.qe = domain->qe;
-    k.ds = domain->ds_form;
+    k.ds = ds_kernel(domain, 1);
     k.bc = is_cavity(domain->bc) ? kCavity : domain->bc;
     k.elbm = domain->collision == LBM_COLL_ELBM;
     k.median_pass = domain->lattice == LBM_D2Q9 && (domain->limiter & LBM_LIM_MEDIAN);

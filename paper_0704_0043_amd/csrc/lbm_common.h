@@ -10,7 +10,9 @@ namespace lbm {
 
 enum { kD1Q3 = 1, kD2Q9 = 2 };
 enum { kPoly = 0, kEntropic = 1 };
-enum { kExact = 0, kQuad = 1 };
+// Delta S form of a kernel; kExactHom: exact, with the exact homothety in some
+// domain (the root solve's registers would halve the occupancy of the others)
+enum { kExact = 0, kQuad = 1, kExactHom = 2 };
 enum { kPeriodic = 0, kCavity = 1, kTube = 2 };
 enum { kLimTrim = 1, kLimMedian = 2, kLimEnsThresh = 4, kLimEnsSmooth = 8, kLimEnsRational = 16,
        kLimEnsBudget = 32, kLimPos = 64,

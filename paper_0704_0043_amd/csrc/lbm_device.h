@@ -246,7 +246,7 @@ template <class A>
 struct HRange;
 template <>
 struct HRange<double> {
-    static constexpr double near = 0.1, tiny = 1.0 / 85.0, mid = 0.1;
+    static constexpr double near = 0.1, tiny = 1.0 / 85.0, mid = 0.5;
     static constexpr int nnear = 16, ntiny = 8;
 };
 template <>
@@ -254,15 +254,28 @@ struct HRange<float> {
     static constexpr float near = 0.125f, tiny = 0.0f, mid = 0.5f;
     static constexpr int nnear = 7, ntiny = 7;
 };
-// h and h' = ln(1 + x) beyond the short series (FP32: the long series up to
-// 1/2, then the logarithm).  h(-1) = 1 with h'(-1) = -inf (a population at
-// zero); below -1 the logarithm gives NaN, and h_far_closed that limit.
+// h and h' = ln(1 + x) beyond the short series: up to 1/2 a longer one, then
+// the logarithm.  FP64: with z = x / (2 + x), ln(1 + x) = 2 atanh z gives
+// h = (2 + x) z^2 [1 + (1 + z) z (1/3 + z^2/5 + z^4/7 + ...)], |z| <= 1/3, 17
+// terms below 1e-17 (two Horner chains side by side); it cancels nowhere and
+// costs a third of a logarithm's latency, which a lone wave has to sit out.
+// h(-1) = 1 with h'(-1) = -inf (a population at zero).
+__device__ __forceinline__ double h_mid(double x)
+{
+    const double z = x / (2.0 + x), y = z * z, y2 = y * y;
+    double e = 1.0 / 35.0, o = 1.0 / 33.0;      // even and odd powers of y
+#pragma unroll
+    for (int k = 14; k >= 0; k -= 2) {
+        e = 1.0 / (2.0 * k + 3.0) + y2 * e;
+        if (k >= 2) o = 1.0 / (2.0 * k + 1.0) + y2 * o;
+    }
+    return (2.0 + x) * y * (1.0 + (1.0 + z) * z * (e + y * o));
+}
+__device__ __forceinline__ float h_mid(float x) { return h_series<22>(x); }
 template <class A>
 __device__ __forceinline__ A h_far(A x)
 {
-    if constexpr (sizeof(A) == 4) {
-        if (fabs(x) <= HRange<A>::mid) return h_series<22>(x);
-    }
+    if (fabs(x) <= HRange<A>::mid) return h_mid(x);
     return (A(1) + x) * log1p_(x) - x;
 }
 template <class A>
@@ -272,24 +285,27 @@ __device__ __forceinline__ A h_far_slope(A x, A& dh)
         dh = -A(__builtin_huge_val());
         return A(1);
     }
-    if constexpr (sizeof(A) == 4) {
-        if (fabs(x) <= HRange<A>::mid) {
-            const A h = h_series<22>(x);
-            dh = (h + x) * rcp(A(1) + x);
-            return h;
-        }
+    if (fabs(x) <= HRange<A>::mid) {
+        const A h = h_mid(x);
+        dh = (h + x) * rcp(A(1) + x);
+        return h;
     }
     const A l = log1p_(x);
     dh = l;
     return (A(1) + x) * l - x;
 }
-// v[i] for an index that differs between lanes, without leaving registers
+// v[i] for an index that differs between lanes, without leaving registers (the
+// empty asm keeps the compiler from seeing an array access in the selects and
+// moving the whole array to scratch memory)
 template <int Q, class A>
 __device__ __forceinline__ A pick(const A (&v)[Q], int i)
 {
     A r = v[0];
 #pragma unroll
-    for (int k = 1; k < Q; ++k) r = i == k ? v[k] : r;
+    for (int k = 1; k < Q; ++k) {
+        r = i == k ? v[k] : r;
+        asm("" : "+v"(r));
+    }
     return r;
 }
 
@@ -322,6 +338,19 @@ __device__ __forceinline__ A kull_sum(const A (&fs)[Q], const A (&x)[Q], A s)
         const A t = fs[i] * h_series<R::nnear>(y);
         sum += in ? t : A(0);
         far |= in ? 0u : 1u << i;
+    }
+    if constexpr (Q == 3 && sizeof(A) == 8) {
+        // a tube's shock: three chains side by side instead of one by one
+        if (far) {
+#pragma unroll
+            for (int i = 0; i < Q; ++i) {
+                const A y = s * x[i];
+                const bool mid = (far >> i & 1u) && fabs(y) <= R::mid;
+                const A t = fs[i] * h_mid(y);
+                sum += mid ? t : A(0);
+                far &= mid ? ~(1u << i) : ~0u;
+            }
+        }
     }
     while (far) {
         const int i = __builtin_ctz(far);

@@ -335,7 +335,7 @@ __device__ __attribute__((noinline)) A exact_homothety_call(SiteState<kD2Q9, A> 
 // leave the sums out, and with them a third of the instructions, the barrier
 // and the partial at the end of every workgroup.
 template <class T, int QE, int DS, int BC, bool ELBM, bool STATS>
-__global__ void __launch_bounds__(kThreads) k_collide2d(StepArgs a)
+__global__ void __launch_bounds__(kThreads, DS == kExact && !STATS && !ELBM ? 4 : 1) k_collide2d(StepArgs a)
 {
     using A = typename Store<T>::A;
     using L = Lat<kD2Q9>;
@@ -394,7 +394,7 @@ __global__ void __launch_bounds__(kThreads) k_collide2d(StepArgs a)
                 }
                 unsigned mask = 0;
                 A phi = trim_phi(D, S.dpost, mask);
-                if constexpr (DS == kExact) {
+                if constexpr (DS == kExactHom) {
                     if (D.homothety && (mask & kMaskTrim) && !D.trim_mode && isfinite(S.dpost))
                         phi = exact_homothety_call(S, shift, A(D.delta_trim));
                 }
@@ -549,12 +549,12 @@ __device__ __forceinline__ void gather_node(gptr<const T> src, long long plane, 
 // The limited state of a node after LBGK collisions, formed anew by a second
 // pass from the populations g that arrived there (the buffer the step reads
 // still holds them), f* - phi c d with phi the smallest of its factors, as the
-// fused step forms it.  Returns phi; `lim` is the limiter's entropy production
-// beyond what the collision kernel counted for the node.
+// fused step forms it.  Returns phi; `lim` (0 unless wanted) is the limiter's
+// entropy production beyond what the collision kernel counted for the node.
 template <class T, int QE, int DS, class DD>
 __device__ __forceinline__ typename Store<T>::A form_state(const DD& D, const typename Store<T>::A (&g)[9],
                                                            typename Store<T>::A dc, typename Store<T>::A tgt,
-                                                           typename Store<T>::A fac,
+                                                           typename Store<T>::A fac, bool want_lim,
                                                            SiteState<kD2Q9, typename Store<T>::A>& S, double& lim)
 {
     using A = typename Store<T>::A;
@@ -572,7 +572,7 @@ __device__ __forceinline__ typename Store<T>::A form_state(const DD& D, const ty
     S.posrule = false;
     A phi = pt;
     bool done = false;
-    if constexpr (DS == kExact) {
+    if constexpr (DS == kExactHom) {
         if (D.homothety && isfinite(dc)) {
             // targets reached exactly (Sec. 3.6); the smallest one decides
             const bool hom = (tmask & kMaskTrim) && !D.trim_mode;
@@ -584,7 +584,7 @@ __device__ __forceinline__ typename Store<T>::A form_state(const DD& D, const ty
     }
     if (!done) phi = fmin(pt, fmin(fac, tgt < inf ? sqrt_(tgt * rcp(dc)) : A(1)));
     lim = 0.0;
-    if (isfinite(dc) && phi < pt) {
+    if (want_lim && isfinite(dc) && phi < pt) {
         if constexpr (DS == kQuad) {
             lim = double(dc * (pt * pt - phi * phi));
         } else {
@@ -599,14 +599,14 @@ __device__ __forceinline__ typename Store<T>::A form_state(const DD& D, const ty
 template <class T, int QE, int DS, int BC, class DD>
 __device__ __forceinline__ double form_node(const DD& D, gptr<const T> src, gptr<T> dst, long long plane, int x, int y,
                                             typename Store<T>::A dc, typename Store<T>::A tgt,
-                                            typename Store<T>::A fac)
+                                            typename Store<T>::A fac, bool want_lim)
 {
     using A = typename Store<T>::A;
     A g[9];
     gather_node<BC>(src, plane, D.nx, D.ny, x, y, g);
     SiteState<kD2Q9, A> S;
     double lim;
-    const A k = form_state<T, QE, DS>(D, g, dc, tgt, fac, S, lim) * S.c;
+    const A k = form_state<T, QE, DS>(D, g, dc, tgt, fac, want_lim, S, lim) * S.c;
     const unsigned own = unsigned(sizeof(T)) * (unsigned(y) * unsigned(D.nx) + unsigned(x));
 #pragma unroll
     for (int i = 0; i < 9; ++i) Store<T>::st(at_bytes(dst + i * plane, own), S.gs[i] - k * S.d[i]);
@@ -640,14 +640,17 @@ __device__ __forceinline__ double rescale_node(const DD& D, gptr<T> buf, long lo
     const A pt = trim_phi(D, dc, tmask);
     A r = fmin(fac, tgt < inf ? sqrt_(tgt * rcp(dc)) : A(1)) * rcp(pt);
     A fs[Q], e[Q];
-    if constexpr (DS == kExact) {
-        A emin = A(0);
+    if constexpr (DS != kQuad) {
 #pragma unroll
         for (int i = 0; i < Q; ++i) {
             fs[i] = A(Lat<kD2Q9>::w(i)) * shift + gs[i];
             e[i] = (gl[i] - gs[i]) * rcp(fs[i]);
-            emin = fmin(emin, e[i]);
         }
+    }
+    if constexpr (DS == kExactHom) {
+        A emin = A(0);
+#pragma unroll
+        for (int i = 0; i < Q; ++i) emin = fmin(emin, e[i]);
         if (D.homothety && isfinite(dc)) {
             const A ds_s = kull_sum<false>(fs, e, A(1));
             r = A(1);
@@ -873,7 +876,7 @@ __device__ __forceinline__ void second_pass2d(const StepArgs& a)
                     unsigned tmask = 0;
                     const A pt = trim_phi(D, dc, tmask);
                     moves = fmin(fac, tgt < A(__builtin_huge_val()) ? sqrt_(tgt * rcp(dc)) : A(1)) < pt;
-                    if constexpr (DS == kExact) moves = moves || (D.homothety && isfinite(dc) && pt > A(0));
+                    if constexpr (DS == kExactHom) moves = moves || (D.homothety && isfinite(dc) && pt > A(0));
                 }
                 const unsigned long long b = __ballot(moves);
                 if (moves) {
@@ -912,7 +915,7 @@ __device__ __forceinline__ void second_pass2d(const StepArgs& a)
                     acc.lim += rescale_node<T, QE, DS>(D, dst, plane, xn, yn, dc, tgt, fac);
                 else
                     acc.lim += form_node<T, QE, DS, BC>(D, to_global<T>(static_cast<const void*>(D.buf[a.parity])), dst,
-                                                        plane, xn, yn, dc, tgt, fac);
+                                                        plane, xn, yn, dc, tgt, fac, a.flags & kFlagStats);
             }
             __builtin_amdgcn_wave_barrier();
             listed = 0;
@@ -1005,7 +1008,7 @@ __global__ void __launch_bounds__(kThreads) k_form2d(StepArgs a)
             acc.trim = h.trim;
             if (record && h.bits) to_global<unsigned char>(D.mask)[n] |= (unsigned char)h.bits;
             SiteState<kD2Q9, A> S;
-            const A phi = form_state<T, QE, DS>(D, g, dc, tgt, fac, S, acc.lim);
+            const A phi = form_state<T, QE, DS>(D, g, dc, tgt, fac, true, S, acc.lim);
             store_limited<T>(dst, plane, 0, unsigned(sizeof(T)) * n, S, phi, S.c);
         }
     }
@@ -1155,7 +1158,7 @@ __global__ void __launch_bounds__(kThreads) k_fused2d(StepArgs a)
                         pr[1] = sc.uy;
                     }
                     phi = trim_phi(D, S.dpost, mask);
-                    if constexpr (DS == kExact) {
+                    if constexpr (DS == kExactHom) {
                         if (D.homothety && (mask & kMaskTrim) && !D.trim_mode && isfinite(S.dpost))
                             phi = exact_homothety_call(S, shift, A(D.delta_trim));
                     }
@@ -1228,7 +1231,7 @@ __global__ void __launch_bounds__(kThreads) k_fused2d(StepArgs a)
                     if constexpr (STATS) ++acc.filt;
                     A pm = A(1);
                     bool done = false;
-                    if constexpr (DS == kExact) {
+                    if constexpr (DS == kExactHom) {
                         if (D.homothety && isfinite(p_dpost)) {
                             pm = exact_homothety_call(P, shift, thr);
                             done = true;
@@ -1402,7 +1405,7 @@ __global__ void __launch_bounds__(k1DMaxThreads) k_step1d(StepArgs a)
             const A med = has_med ? med3(ds[tl], ds[tid], ds[tr]) : A(0);
             A tgt;
             A phi = limiter_phi(S.dpost, has_med, med, D, mask, tgt);
-            if constexpr (DS == kExact) {
+            if constexpr (DS == kExactHom) {
                 if (D.homothety && phi > A(0) && tgt < A(__builtin_huge_val()) && isfinite(S.dpost))
                     phi = exact_homothety<LAT>(S, shift, tgt, S.dpost);
             }
@@ -1486,7 +1489,7 @@ __global__ void __launch_bounds__(kThreads) k_ens1d(StepArgs a)
             if (a.flags & kFlagRecord) to_global<unsigned char>(D.mask)[x] |= (unsigned char)h.bits;
             const A pq = fmin(fac, tgt < A(__builtin_huge_val()) ? sqrt_(tgt * rcp(d)) : A(1));
             bool exact = false;
-            if constexpr (DS == kExact) exact = D.homothety && isfinite(d) && pa > A(0);
+            if constexpr (DS == kExactHom) exact = D.homothety && isfinite(d) && pa > A(0);
             if (exact || pq < pa) {
                 const long long plane = D.plane;
                 const A shift = A(D.shift);
@@ -1504,7 +1507,7 @@ __global__ void __launch_bounds__(kThreads) k_ens1d(StepArgs a)
                     e[i] = (gl[i] - gs[i]) * rcp(fs[i]);
                 }
                 A r = pq * rcp(pa);
-                if constexpr (DS == kExact) {
+                if constexpr (DS == kExactHom) {
                     if (exact) {
                         // exact homothety from f' = f* + e / pa (Sec. 3.6)
                         A xp[Q];
@@ -1552,7 +1555,9 @@ static hipError_t dispatch(int qe, int ds, int bc, F f)
         return hipSuccess;
     };
     auto with_ds = [&](auto q) {
-        return ds == 0 ? with_bc(q, I0()) : (ds == 1 ? with_bc(q, I1()) : hipErrorInvalidValue);
+        if (ds == kExact) return with_bc(q, std::integral_constant<int, kExact>());
+        if (ds == kQuad) return with_bc(q, std::integral_constant<int, kQuad>());
+        return ds == kExactHom ? with_bc(q, std::integral_constant<int, kExactHom>()) : hipErrorInvalidValue;
     };
     hipError_t e = hipErrorInvalidValue;
     if (qe == 1) e = with_ds(I1());
