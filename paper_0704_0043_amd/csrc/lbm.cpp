@@ -132,6 +132,42 @@ int next_launch(long long left, int most)
     return int(std::max(n, left - (launches - 1) * most));
 }
 
+// The small-domain form (k_block2d): tiles of w x h nodes, up to `steps` steps a
+// launch (w = 0: the domains keep the other forms).  Fusable domains of at most
+// kBlockNodes nodes in all take it: there launches and memory latency cost
+// more than the halo's work.  Three steps a launch while the halo leaves at
+// most two waves per SIMD (kBlockWaves), else one.  The tile is the one with
+// the fewest waves in all.
+struct BlockForm {
+    int w = 0, h = 0, steps = 1;
+};
+constexpr long long kBlockNodes = 400000;
+constexpr int kBlockWaves = 2048, kBlockThreads = 512;
+BlockForm block_form(const lbm_domain_desc* doms, int32_t nd, const lbm_run_desc* run)
+{
+    BlockForm best;
+    if (!fusable(doms, nd) || run->tile_x == kFusedWidth || (run->flags & LBM_RUN_ADAPTIVE)) return best;
+    long long nodes = 0;
+    for (int k = 0; k < nd; ++k) nodes += (long long)doms[k].nx * doms[k].ny;
+    if (nodes > kBlockNodes) return best;
+    for (int steps : {3, 1}) {
+        const int halo = 2 * steps - 1;
+        long long fewest = -1;
+        for (int w = 4; w + 2 * halo <= 64; ++w)
+            for (int h = 4; (w + 2 * halo) * (h + 2 * halo) <= kBlockThreads; ++h) {
+                long long tiles = 0;
+                for (int k = 0; k < nd; ++k) tiles += block_tiles_of(doms[k].nx, doms[k].ny, w, h);
+                const long long waves = tiles * (((w + 2 * halo) * (h + 2 * halo) + kWave - 1) / kWave);
+                if (fewest < 0 || waves < fewest) {
+                    fewest = waves;
+                    best = BlockForm{w, h, steps};
+                }
+            }
+        if (fewest <= kBlockWaves) break;
+    }
+    return best;
+}
+
 // both forms of the step are kept and chosen between while the run goes
 bool adaptive_run(const lbm_domain_desc* doms, int32_t nd, const lbm_run_desc* run)
 {
@@ -194,7 +230,8 @@ struct lbm_ctx {
     bool median_pass = false;   // D2Q9 with the median filter in some domain
     bool ens_pass = false;      // an ensemble-dependent limiter in some domain
     bool fuse_ok = false;       // the fused step applies (D2Q9 LBGK, median filter, no ensemble limiter)
-    int reach = 1, most1d = 1;  // D1Q3: reach of a step, steps of the longest launch
+    int reach = 1, most = 1;    // D1Q3: reach of a step; steps of the longest launch
+    BlockForm block;            // the small-domain form (w = 0: not taken)
     int dense = 0;              // kDenseSome / kSparseSome: what second passes the domains need
     int budget = 0;             // kSelect* bits: budget threshold, top-k trimming in some domain
     bool elbm = false;          // ELBM collisions (all domains)
@@ -407,6 +444,7 @@ void plan(std::vector<DomainHost>& dh, const lbm_domain_desc* doms, int32_t nd, 
     const unsigned flags = run->flags;
     const int cap = run->probe_capacity > 0 ? run->probe_capacity : 4096;
     const bool adaptive = adaptive_run(doms, nd, run);
+    const BlockForm block = block_form(doms, nd, run);
     size_t off = 0;
     L.max_tiles = 0;
     L.nblocks = 0;
@@ -441,6 +479,7 @@ void plan(std::vector<DomainHost>& dh, const lbm_domain_desc* doms, int32_t nd, 
         int tiles = tiles_of(h.d.lattice, h.d.nx, h.d.ny, min_h);
         if (h.d.lattice == LBM_D2Q9 && run->tile_x == kFusedWidth)
             tiles = std::max(tiles, fused_tiles_of(h.d.nx, h.d.ny, run->tile_h > 0 ? run->tile_h : kMinFusedH));
+        if (block.w) tiles = block_tiles_of(h.d.nx, h.d.ny, block.w, block.h);
         // adaptive: the fused tiles (any tuned height) share the partial slots
         if (h.d.lattice == LBM_D2Q9 && adaptive) tiles = std::max(tiles, fused_tiles_of(h.d.nx, h.d.ny, kMinFusedH));
         L.max_tiles += tiles;
@@ -493,9 +532,11 @@ std::vector<Tile> build_tiles(lbm_ctx* ctx, int th, bool fused)
         DomainHost& h = ctx->dom[k];
         h.tile_first = int(spatial.size());
         const int nx = h.d.nx, ny = h.d.ny;
-        const int count = fused ? fused_tiles_of(nx, ny, th) : tiles_of(ctx->lattice, nx, ny, th);
+        const BlockForm& b = ctx->block;
+        const int count = b.w ? block_tiles_of(nx, ny, b.w, b.h)
+                              : (fused ? fused_tiles_of(nx, ny, th) : tiles_of(ctx->lattice, nx, ny, th));
         for (int i = 0; i < count; ++i)
-            spatial.push_back(fused ? fused_tile_entry(int(k), nx, ny, th, i)
+            spatial.push_back(b.w ? block_tile_entry(int(k), nx, ny, b.w, b.h, i) : fused ? fused_tile_entry(int(k), nx, ny, th, i)
                                     : (ctx->lattice == LBM_D2Q9 ? tile_entry2d(int(k), nx, ny, th, i)
                                                                 : tile_entry1d(int(k), nx, i)));
         h.tile_count = count;
@@ -634,7 +675,9 @@ StepArgs step_args(const lbm_ctx* ctx, int parity)
     a.elbm = ctx->elbm ? 1 : 0;
     a.budget = ctx->budget;
     a.dense = ctx->dense;
-    a.fused = ctx->act.fused ? 1 : 0;
+    a.fused = ctx->block.w ? 2 : (ctx->act.fused ? 1 : 0);
+    a.block_w = ctx->block.w;
+    a.block_h = ctx->block.h;
     a.blocks = ctx->blocks_host.empty() ? nullptr : ctx->d_blocks();
     a.nblocks = ctx->lay.nblocks;
     a.groups = ctx->d_groups();
@@ -655,10 +698,10 @@ struct StepKind {
     int storage, lattice, qe, ds, bc;
     bool elbm, median_pass, ens_pass;
     int budget, dense;
-    bool fused = false;
+    int fused = 0;     // StepArgs::fused
 };
 
-// One step of every domain of `a`.  With `ev` (three events) the launches
+// One step (or a.steps) of every domain of `a`.  With `ev` (three events) the launches
 // are bracketed for per-kernel timing: ev[0] | collision | ev[1] | rest | ev[2].
 hipError_t launch_step(const StepKind& k, const StepArgs& a, hipStream_t s, hipEvent_t* ev = nullptr)
 {
@@ -666,7 +709,7 @@ hipError_t launch_step(const StepKind& k, const StepArgs& a, hipStream_t s, hipE
     if (ev) e = hipEventRecord(ev[0], s);
     if (k.fused) {
         // one kernel: collision and median filter together
-        if (e == hipSuccess) e = launch_step2d(k.storage, k.qe, k.ds, k.bc, a, 3, s);
+        if (e == hipSuccess) e = launch_step2d(k.storage, k.qe, k.ds, k.bc, a, k.fused == 2 ? 5 : 3, s);
         if (e == hipSuccess && ev) e = hipEventRecord(ev[1], s);
         if (e == hipSuccess && ev) e = hipEventRecord(ev[2], s);
         return e;
@@ -696,7 +739,7 @@ hipError_t launch_step(const StepKind& k, const StepArgs& a, hipStream_t s, hipE
 StepKind step_kind(const lbm_ctx* ctx)
 {
     return StepKind{ctx->storage, ctx->lattice, ctx->qe, ctx->ds, ctx->bc, ctx->elbm, ctx->median_pass,
-                    ctx->ens_pass, ctx->budget, ctx->dense, ctx->act.fused};
+                    ctx->ens_pass, ctx->budget, ctx->dense, ctx->block.w ? 2 : (ctx->act.fused ? 1 : 0)};
 }
 
 // stats: the step's sums may be read (an ensemble limiter needs them anyway)
@@ -834,6 +877,8 @@ int autotune(lbm_ctx* ctx, const lbm_run_desc* run, bool fused_alt = false)
         for (int th : fh) cand.push_back({narrow, th, true});
     }
     ctx->tuned = 0;
+    // the small-domain form has no shapes to choose from; the height is only reported
+    if (ctx->block.w) return apply_shape(ctx, cand.back());
     if (cand.size() == 1) return apply_shape(ctx, cand[0]);
     if (ctx->flags & LBM_RUN_NO_TUNE) {
         // narrow row blocks where a domain allows them, tile_h or 64 rows
@@ -888,7 +933,7 @@ int capture(lbm_ctx* ctx, int parity, int64_t len)
     HIP_TRY(ctx, hipStreamBeginCapture(ctx->stream, hipStreamCaptureModeThreadLocal));
     int rc = LBM_OK;
     for (int64_t k = 0; k < len && rc == LBM_OK;) {
-        const int n = ctx->lattice == LBM_D1Q3 ? next_launch(len - k, ctx->most1d) : 1;
+        const int n = ctx->most > 1 ? next_launch(len - k, ctx->most) : 1;
         rc = launch_one(ctx, int((parity + k) % 2), k + n == len, nullptr, 0, n);
         k += n;
     }
@@ -1042,7 +1087,7 @@ struct StaticLayout {
     int th = 0, ntiles = 0, ngroups = 0, nblocks = 0;
 };
 
-void plan_static(const lbm_domain_desc& d, int storage, int th, DomainHost& h, StaticLayout& L)
+void plan_static(const lbm_domain_desc& d, int storage, int th, const BlockForm& block, DomainHost& h, StaticLayout& L)
 {
     h.d = d;
     h.d.rho_init = h.d.u_init = h.d.f_init = nullptr;
@@ -1051,8 +1096,8 @@ void plan_static(const lbm_domain_desc& d, int storage, int th, DomainHost& h, S
     h.plane = (long long)h.n;
     h.shift = storage == LBM_F64 ? 0.0 : d.rho0;
     const bool d2 = d.lattice == LBM_D2Q9;
-    L.th = th;
-    L.ntiles = tiles_of(d.lattice, d.nx, d.ny, th);
+    L.th = block.w ? block.h : th;
+    L.ntiles = block.w ? block_tiles_of(d.nx, d.ny, block.w, block.h) : tiles_of(d.lattice, d.nx, d.ny, th);
     L.ngroups = d2 ? groups_of(d.nx, d.ny) : L.ntiles;
     L.nblocks = d2 ? blocks_of(d.nx, d.ny) : 0;
     h.tile_first = 0;
@@ -1159,8 +1204,10 @@ int lbm_create(const lbm_domain_desc* domains, int32_t n_domains, const lbm_run_
     }
     if (ctx->lattice == LBM_D1Q3) {
         ctx->reach = reach1d(domains, n_domains);
-        ctx->most1d = max_steps1d(domains, n_domains);
+        ctx->most = max_steps1d(domains, n_domains);
     }
+    ctx->block = block_form(domains, n_domains, run);
+    if (ctx->block.w) ctx->most = ctx->block.steps;
     ctx->cap_h = second_height(domains, n_domains, kMaxTileH);
     ctx->fuse_ok = ctx->lattice == LBM_D2Q9 && !ctx->elbm && ctx->median_pass && !ctx->ens_pass;
 
@@ -1482,7 +1529,7 @@ int lbm_kernel_times(lbm_ctx* ctx, int64_t n_steps, double* ms)
         if (e) (void)hipEventDestroy(e);
     if (rc) return rc;
     ms[0] = t[0] / double(n_steps);
-    ms[1] = ((ctx->median_pass || ctx->ens_pass) && !ctx->act.fused) ? t[1] / double(n_steps) : 0.0;
+    ms[1] = ((ctx->median_pass || ctx->ens_pass) && !ctx->act.fused && !ctx->block.w) ? t[1] / double(n_steps) : 0.0;
     return LBM_OK;
 }
 
@@ -1506,9 +1553,13 @@ int lbm_step_static(const lbm_domain_desc* domain, int32_t storage, void* stream
         return fail(nullptr, LBM_EINVAL, "no probe trace without a context (probe_x, probe_y must be -1)");
     DomainHost h;
     StaticLayout L;
-    plan_static(*domain, storage, second_height(domain, 1, kMaxTileH), h, L);
+    BlockForm block = block_form(domain, 1, &run);
+    plan_static(*domain, storage, second_height(domain, 1, kMaxTileH), block, h, L);
     // shorter tiles have more partials: never at the price of refusing a domain
-    if (L.total > kStaticScratchBytes) plan_static(*domain, storage, kMaxTileH, h, L);
+    if (L.total > kStaticScratchBytes) {
+        block = BlockForm();
+        plan_static(*domain, storage, kMaxTileH, block, h, L);
+    }
     if (L.total > kStaticScratchBytes)
         return fail(nullptr, LBM_ENOMEM,
                     "lbm_step_static: the domain needs " + std::to_string(L.total) +
@@ -1526,7 +1577,7 @@ int lbm_step_static(const lbm_domain_desc* domain, int32_t storage, void* stream
     Tile* tiles = reinterpret_cast<Tile*>(base + L.off_tiles);
     long long* counter = reinterpret_cast<long long*>(base + L.off_counter);
     Group* groups = reinterpret_cast<Group*>(base + L.off_groups);
-    e = launch_static_setup(dd, domain->lattice, dom, tiles, L.ntiles, L.th, groups, L.ngroups, counter, s);
+    e = launch_static_setup(dd, domain->lattice, dom, tiles, L.ntiles, L.th, block.w, groups, L.ngroups, counter, s);
     if (e != hipSuccess) return fail(nullptr, LBM_EDEVICE, std::string("static setup: ") + hipGetErrorString(e));
     StepKind k;
     k.storage = storage;
@@ -1561,7 +1612,10 @@ int lbm_step_static(const lbm_domain_desc* domain, int32_t storage, void* stream
     a.above = reinterpret_cast<unsigned*>(base + L.off_above);
     a.counter = counter;
     const bool d1 = domain->lattice == LBM_D1Q3;
-    const int most = d1 ? max_steps1d(domain, 1) : 1;
+    const int most = d1 ? max_steps1d(domain, 1) : (block.w ? block.steps : 1);
+    k.fused = a.fused = block.w ? 2 : 0;
+    a.block_w = block.w;
+    a.block_h = block.h;
     if (d1) a.reach = reach1d(domain, 1);
     for (int64_t t = 0; t < n_steps && e == hipSuccess;) {
         a.parity = int(t % 2);

@@ -232,6 +232,18 @@ __host__ __device__ inline Tile fused_tile_entry(int domain, int nx, int ny, int
                 r, chunks, 1};
 }
 
+// Tiles of bw x bh nodes of the small-domain kernel (k_block2d)
+__host__ __device__ inline int block_tiles_of(int nx, int ny, int bw, int bh)
+{
+    return ((nx + bw - 1) / bw) * ((ny + bh - 1) / bh);
+}
+__host__ __device__ inline Tile block_tile_entry(int domain, int nx, int ny, int bw, int bh, int i)
+{
+    const int cols = (nx + bw - 1) / bw;
+    const int r = i / cols, x0 = (i - r * cols) * bw, y0 = r * bh;
+    return Tile{domain, x0, x0 + bw < nx ? x0 + bw : nx, y0, y0 + bh < ny ? y0 + bh : ny, 0, 1, 1};
+}
+
 struct StepArgs {
     const DomainDev* dom;
     const Tile* tiles;      // spatial order (domain, row chunk, column strip)
@@ -247,8 +259,9 @@ struct StepArgs {
     int pstride;            // slots per set in `partials` (>= ntiles, ngroups)
     int median_pass;        // 1 if a second pass (median and/or ensemble limiters) writes set 1
     int dense;              // kDense* of the domains
-    int fused = 0;          // 1: the fused step kernel runs alone over `tiles` (fused tiles)
-                            // and writes every partial to set 1
+    int fused = 0;          // 1: the fused step kernel (2: the small-domain kernel) runs alone over
+                            // `tiles` (its own) and writes every partial to set 1
+    int block_w = 0, block_h = 0;   // small-domain kernel: nodes of a tile
     int ens_pass;           // 1 if some domain has an ensemble-dependent limiter
     int elbm;               // 1 with ELBM collisions (all domains)
     int budget;             // kSelect* of the domains: budget threshold, top-k trimming
@@ -260,7 +273,7 @@ struct StepArgs {
                             // a median candidate (Delta S' > delta_median) and stored its Delta S'
     long long* counter;     // [2] step index by parity
     int reach = 1;          // D1Q3: sites a step's result depends on, on either side
-    int steps = 1;          // D1Q3: steps of this launch (odd)
+    int steps = 1;          // D1Q3 and the small-domain kernel: steps of this launch (odd)
 };
 
 // Allocation-free stepping (lbm_step_static): bytes of the per-GPU static
@@ -269,14 +282,15 @@ constexpr size_t kStaticScratchBytes = LBM_STATIC_SCRATCH_BYTES;
 // its address on `device` (looked up once per device; `device` must be current)
 hipError_t static_scratch(int device, char** ptr);
 hipError_t launch_static_setup(const DomainDev& dd, int lattice, DomainDev* dom, Tile* tiles, int ntiles, int th,
-                               Group* groups, int ngroups, long long* counter, hipStream_t s);
+                               int block_w, Group* groups, int ngroups, long long* counter, hipStream_t s);
 hipError_t launch_static_stats(const DomainDev* dom, double shift_mass, double* out, hipStream_t s);
 
 // Launchers (one per storage type / lattice), defined in the .hip files.
 // kernel 0: collision kernel (LBGK); kernel 2: the same with the ELBM collision;
 // kernel 1: the second pass (median filter, ensemble factors; after kernel 0 or 2);
 // kernel 3: the fused step (LBGK, trimming, positivity and median filter);
-// kernel 4: the second pass of the dense domains (after kernel 0)
+// kernel 4: the second pass of the dense domains (after kernel 0);
+// kernel 5: whole steps of small domains (LBGK, trimming, positivity and median filter)
 hipError_t launch_step2d(int storage, int qe, int ds, int bc, const StepArgs& a, int kernel, hipStream_t s);
 // kernel 0: D1Q3 step (LBGK); kernel 2: the same with ELBM; kernel 1: D1Q3 ensemble pass
 hipError_t launch_step1d(int storage, int qe, int ds, int bc, const StepArgs& a, int kernel, hipStream_t s);

@@ -962,7 +962,7 @@ __device__ inline void sum_partials(double* out, const double* rp, int rn, doubl
 // wave (the limiter and entropy sums only in waves that hold one), the 0/1
 // counts by ballots; then the waves combined in FP64 in order.
 template <class S>
-__device__ inline void node_partial(const AccT<S>& acc, double* out, double* lds /* [4 * kNStat] */)
+__device__ inline void node_partial(const AccT<S>& acc, double* out, double* lds /* [waves * kNStat] */)
 {
     S v[8] = {acc.mass, acc.jx, acc.jy, acc.dpre, acc.dpost, acc.maxd, acc.lim, acc.ent};
 #pragma unroll
@@ -988,8 +988,8 @@ __device__ inline void node_partial(const AccT<S>& acc, double* out, double* lds
     __syncthreads();
     if (tid < kNStat) {
         double s = lds[tid];
-#pragma unroll
-        for (int w = 1; w < kThreads / kWave; ++w)
+        const int nw = int(blockDim.x) / kWave;
+        for (int w = 1; w < nw; ++w)
             s = (tid == kSMax) ? fmax(s, lds[w * kNStat + tid]) : s + lds[w * kNStat + tid];
         out[tid] = s;
     }

@@ -42,8 +42,8 @@ hipError_t static_scratch(int device, char** ptr)
 // builds them for a context) and clears what a run must start from: the
 // step counters, the stats and the selection histogram.
 __global__ void __launch_bounds__(kThreads) k_static_setup(DomainDev dd, int lattice, DomainDev* dom, Tile* tiles,
-                                                           int ntiles, int th, Group* groups, int ngroups,
-                                                           long long* counter)
+                                                           int ntiles, int th, int block_w, Group* groups,
+                                                           int ngroups, long long* counter)
 {
     const int nb = dd.bhist ? kBudgetBuckets : 0;
     const int n = max(max(ntiles, ngroups), max(nb, kNStat + 1));
@@ -55,7 +55,9 @@ __global__ void __launch_bounds__(kThreads) k_static_setup(DomainDev dd, int lat
         }
         if (i <= kNStat) dd.stats[i] = 0.0;
         if (i < ntiles)
-            tiles[i] = lattice == kD2Q9 ? tile_entry2d(0, dd.nx, dd.ny, th, i) : tile_entry1d(0, dd.nx, i);
+            tiles[i] = lattice != kD2Q9 ? tile_entry1d(0, dd.nx, i)
+                                        : (block_w ? block_tile_entry(0, dd.nx, dd.ny, block_w, th, i)
+                                                   : tile_entry2d(0, dd.nx, dd.ny, th, i));
         if (i < ngroups) {
             const Tile t = tile_entry1d(0, dd.nx, i);
             groups[i] = lattice == kD2Q9 ? group_entry2d(0, dd.nx * dd.ny, i) : Group{0, t.x0, t.x1};
@@ -89,12 +91,12 @@ __global__ void k_static_stats(const DomainDev* dom, double shift_mass, double* 
 }
 
 hipError_t launch_static_setup(const DomainDev& dd, int lattice, DomainDev* dom, Tile* tiles, int ntiles, int th,
-                               Group* groups, int ngroups, long long* counter, hipStream_t s)
+                               int block_w, Group* groups, int ngroups, long long* counter, hipStream_t s)
 {
     const int n = std::max(std::max(ntiles, ngroups), dd.bhist ? kBudgetBuckets : kNStat + 1);
     const int blocks = std::min((n + kThreads - 1) / kThreads, 1024);
     hipLaunchKernelGGL(k_static_setup, dim3(blocks), dim3(kThreads), 0, s, dd, lattice, dom, tiles, ntiles, th,
-                       groups, ngroups, counter);
+                       block_w, groups, ngroups, counter);
     return hipGetLastError();
 }
 

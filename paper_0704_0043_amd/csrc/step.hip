@@ -293,32 +293,44 @@ __device__ __forceinline__ void store_limited(gptr<T> dst, long long plane, long
     }
 }
 
-// Diffusive Maxwell wall node (Sec. 4.4.2), inward normal (mx, my), wall
-// velocity (uw, 0): the populations pointing into the fluid become
-// gamma f*_i(1, u_wall), gamma = (mass that arrived from the fluid) / (mass of
-// those f*_i), the others keep what free flight brought.  No collision.
-template <class T, int QE>
-__device__ __forceinline__ void diffusive_wall(gptr<T> dst, long long plane, long long row, unsigned own,
-                                               const typename Store<T>::A (&g)[9], typename Store<T>::A shift,
-                                               int mx, int my, typename Store<T>::A uw)
+// What leaves a wall or lid node (no collision).  Bounce-back: every population
+// reversed.  Lid: f*(rho0, (u0, 0)).  Diffusive Maxwell walls (Sec. 4.4.2, the
+// lid moves with (u0, 0), corners reflect): the populations pointing into the
+// fluid become gamma f*_i(1, u_wall), gamma = (mass that arrived from the fluid)
+// / (mass of those f*_i), the others keep what free flight brought.
+template <int QE, class A, class DD>
+__device__ __forceinline__ void wall_state(const DD& D, int cls, int x, int y, int nx, int ny, const A (&g)[9], A shift,
+                                           A (&out)[9])
 {
-    using A = typename Store<T>::A;
     using L = Lat<kD2Q9>;
-    A E[9];
-    eq_excess<kD2Q9, QE>(uw, A(0), E);
-    A sum_in = A(0), sum_arrived = A(0);
+    const bool corner = (x == 0 || x == nx - 1) && (y == 0 || y == ny - 1);
+    if (D.diffusive && !corner) {
+        const int my = y == 0 ? 1 : (y == ny - 1 ? -1 : 0);
+        const int mx = my != 0 ? 0 : (x == 0 ? 1 : -1);
+        A E[9] = {A(0), A(0), A(0), A(0), A(0), A(0), A(0), A(0), A(0)};    // a resting wall's f* is w_i
+        if (y == ny - 1) eq_excess<kD2Q9, QE>(A(D.lid_ux), A(0), E);
+        A sum_in = A(0), sum_arrived = A(0);
 #pragma unroll
-    for (int i = 0; i < 9; ++i) {
-        const int d = L::vx(i) * mx + L::vy(i) * my;
-        if (d > 0) sum_in += A(L::w(i)) * (A(1) + E[i]);
-        if (d < 0) sum_arrived += A(L::w(i)) * shift + g[i];
-    }
-    const A gamma = sum_arrived / sum_in;
+        for (int i = 0; i < 9; ++i) {
+            const int d = L::vx(i) * mx + L::vy(i) * my;
+            if (d > 0) sum_in += A(L::w(i)) * (A(1) + E[i]);
+            if (d < 0) sum_arrived += A(L::w(i)) * shift + g[i];
+        }
+        const A gamma = sum_arrived / sum_in;
 #pragma unroll
-    for (int i = 0; i < 9; ++i) {
-        const int d = L::vx(i) * mx + L::vy(i) * my;
-        const A v = d > 0 ? gamma * (A(L::w(i)) * (A(1) + E[i])) - A(L::w(i)) * shift : g[i];
-        Store<T>::st(at_bytes(dst + (i * plane + row), own), v);
+        for (int i = 0; i < 9; ++i) {
+            const int d = L::vx(i) * mx + L::vy(i) * my;
+            out[i] = d > 0 ? gamma * (A(L::w(i)) * (A(1) + E[i])) - A(L::w(i)) * shift : g[i];
+        }
+    } else if (cls == kNodeWall) {
+#pragma unroll
+        for (int i = 0; i < 9; ++i) out[i] = g[L::opp(i)];
+    } else {
+        A E[9];
+        eq_excess<kD2Q9, QE>(A(D.lid_ux), A(0), E);
+        const A r0 = A(D.rho0);
+#pragma unroll
+        for (int i = 0; i < 9; ++i) out[i] = A(L::w(i)) * ((r0 - shift) + r0 * E[i]);
     }
 }
 
@@ -338,7 +350,6 @@ template <class T, int QE, int DS, int BC, bool ELBM, bool STATS>
 __global__ void __launch_bounds__(kThreads, DS == kExact && !STATS && !ELBM ? 4 : 1) k_collide2d(StepArgs a)
 {
     using A = typename Store<T>::A;
-    using L = Lat<kD2Q9>;
     constexpr int Q = 9;
     __shared__ double red[STATS ? 4 * kNStat : 1];
     // one node per thread, kThreads consecutive nodes per workgroup
@@ -428,26 +439,10 @@ __global__ void __launch_bounds__(kThreads, DS == kExact && !STATS && !ELBM ? 4 
                     to_global<double>(D.dS)[node] = double(S.dpost);
                 }
             } else {
-                const bool corner = (x == 0 || x == nx - 1) && (y == 0 || y == ny - 1);
-                if (D.diffusive && !corner) {
-                    // diffusive Maxwell wall; the lid moves with (u0, 0)
-                    const int mx = x == 0 ? 1 : (x == nx - 1 ? -1 : 0);
-                    const int my = y == 0 ? 1 : (y == ny - 1 ? -1 : 0);
-                    diffusive_wall<T, QE>(dst, plane, 0, own, g, shift, my != 0 ? 0 : mx, my,
-                                          y == ny - 1 ? A(D.lid_ux) : A(0));
-                } else if (cls == kNodeWall) {
-                    // bounce-back: every population leaves reversed, no collision
+                A out[Q];
+                wall_state<QE>(D, cls, x, y, nx, ny, g, shift, out);
 #pragma unroll
-                    for (int i = 0; i < Q; ++i) Store<T>::st(at_bytes(dst + i * plane, own), g[L::opp(i)]);
-                } else {
-                    // lid: f*(rho0, (u0, 0)) in shift form
-                    A E[Q];
-                    eq_excess<kD2Q9, QE>(A(D.lid_ux), A(0), E);
-                    const A r0 = A(D.rho0);
-#pragma unroll
-                    for (int i = 0; i < Q; ++i)
-                        Store<T>::st(at_bytes(dst + i * plane, own), A(L::w(i)) * ((r0 - shift) + r0 * E[i]));
-                }
+                for (int i = 0; i < Q; ++i) Store<T>::st(at_bytes(dst + i * plane, own), out[i]);
                 if constexpr (STATS) {
                     SiteScalars sc;
                     moments_fp64(g, sc.dr, sc.jx, sc.jy);
@@ -1059,7 +1054,6 @@ template <class T, int QE, int DS, int BC, bool STATS>
 __global__ void __launch_bounds__(kThreads) k_fused2d(StepArgs a)
 {
     using A = typename Store<T>::A;
-    using L = Lat<kD2Q9>;
     constexpr int Q = 9;
     __shared__ double red[STATS ? 4 * kNStat : 1];
     // the pending row's f* and nonequilibrium part, one column per thread
@@ -1175,24 +1169,10 @@ __global__ void __launch_bounds__(kThreads) k_fused2d(StepArgs a)
                 }
             } else if (own && cls != kNodeNone) {
                 // walls and lid: no collision, no limiter; stored at once
-                const unsigned ob = cl.own;
-                const bool corner = (xc == 0 || xc == nx - 1) && (yr == 0 || yr == ny - 1);
-                if (D.diffusive && !corner) {
-                    const int mx = xc == 0 ? 1 : (xc == nx - 1 ? -1 : 0);
-                    const int my = yr == 0 ? 1 : (yr == ny - 1 ? -1 : 0);
-                    diffusive_wall<T, QE>(dst, plane, row, ob, g, shift, my != 0 ? 0 : mx, my,
-                                          yr == ny - 1 ? A(D.lid_ux) : A(0));
-                } else if (cls == kNodeWall) {
+                A out[Q];
+                wall_state<QE>(D, cls, xc, yr, nx, ny, g, shift, out);
 #pragma unroll
-                    for (int i = 0; i < Q; ++i) Store<T>::st(at_bytes(dst + (i * plane + row), ob), g[L::opp(i)]);
-                } else {
-                    A E[Q];
-                    eq_excess<kD2Q9, QE>(A(D.lid_ux), A(0), E);
-                    const A r0 = A(D.rho0);
-#pragma unroll
-                    for (int i = 0; i < Q; ++i)
-                        Store<T>::st(at_bytes(dst + (i * plane + row), ob), A(L::w(i)) * ((r0 - shift) + r0 * E[i]));
-                }
+                for (int i = 0; i < Q; ++i) Store<T>::st(at_bytes(dst + (i * plane + row), cl.own), out[i]);
                 if constexpr (STATS) {
                     double dr, jx, jy;
                     moments_fp64(g, dr, jx, jy);
@@ -1307,6 +1287,207 @@ __global__ void __launch_bounds__(kThreads) k_fused2d(StepArgs a)
     store_partial(tot, partial_slot(a, 1, tidx), red);
 }
 
+// Small D2Q9 domains (LBGK, no ensemble limiter): whole steps of a tile in one
+// workgroup, one node per thread, a.steps (odd) of them.  A step needs the
+// populations of the nodes around and, for the median, their Delta S', so the
+// threads cover the tile and a halo of 2 a.steps - 1 nodes; populations go from
+// step to step in LDS (rounded to storage, as a store would), Delta S' within a
+// step.  What bounds a small domain is latency: the collision kernel and the
+// second pass each take a launch and a chain of memory accesses of
+// microseconds (7 + 8 us for a 100 x 100 FP64 cavity), here a step is its
+// arithmetic and two barriers.  Decisions and states are those of the other
+// forms; the sums belong to the last step, one partial per tile in set 1.
+constexpr int kBlockMax = 512;      // threads of a workgroup
+template <class T, int QE, int DS, int BC, bool STATS>
+__global__ void __launch_bounds__(kBlockMax) k_block2d(StepArgs a)
+{
+    using A = typename Store<T>::A;
+    using L = Lat<kD2Q9>;
+    constexpr int Q = 9;
+    __shared__ T leaving[Q][kBlockMax];
+    __shared__ A ds[kBlockMax];
+    __shared__ double red[STATS ? kBlockMax / kWave * kNStat : 1];
+    const int tidx = tile_of_block(a, 0);
+    const Tile t = a.tiles[tidx];
+    const DomainDev& D = a.dom[t.domain];
+    const int nx = D.nx, ny = D.ny;
+    const long long plane = D.plane;
+    const gptr<const T> src = to_global<T>(static_cast<const void*>(D.buf[a.parity]));
+    const gptr<T> dst = to_global<T>(D.buf[1 - a.parity]);
+    const A shift = A(D.shift), c = A(D.c);
+    const bool record = STATS && (a.flags & kFlagRecord);
+    const bool want_ent = STATS && (a.flags & kFlagEntropy);
+    const bool median = D.limiter & kLimMedian;
+    const long long step = a.counter[a.parity];
+    if (blockIdx.x == 0 && threadIdx.x == 0) a.counter[1 - a.parity] = step + a.steps;
+
+    const int halo = 2 * a.steps - 1, bw = a.block_w + 2 * halo, bh = a.block_h + 2 * halo;
+    // the first threads take the tile's own nodes in row-major order, the others
+    // the frame of the halo (so that the sums do not depend on a.steps): the
+    // rows below the tile, the rows above it, the columns left and right
+    const int tid = int(threadIdx.x), w = a.block_w, own_nodes = w * a.block_h;
+    int lx, ly;
+    if (tid < own_nodes) {
+        ly = tid / w;
+        lx = tid - ly * w + halo;
+        ly += halo;
+    } else if (tid < own_nodes + 2 * halo * bw) {
+        const int r = tid - own_nodes;
+        ly = r / bw;
+        lx = r - ly * bw;
+        ly += ly < halo ? 0 : a.block_h;
+    } else {
+        const int r = tid - own_nodes - 2 * halo * bw;
+        ly = r / (2 * halo);
+        lx = r - ly * 2 * halo;
+        lx += lx < halo ? 0 : w;
+        ly = tid < bw * bh ? ly + halo : bh;        // past the frame: no node
+    }
+    const int pos = ly * bw + lx;          // place in LDS
+    // the thread's node; off a cavity, and past the halo of a short last tile,
+    // there is none
+    const int X = t.x0 - halo + lx, Y = t.y0 - halo + ly;
+    bool inside = ly < bh && X < t.x1 + halo && Y < t.y1 + halo;
+    int x = X, y = Y;
+    if constexpr (BC == kPeriodic) {
+        x = wrapi(X, nx);
+        y = wrapi(Y, ny);
+    } else {
+        inside = inside && X >= 0 && X < nx && Y >= 0 && Y < ny;
+    }
+    const bool owned = inside && X >= t.x0 && X < t.x1 && Y >= t.y0 && Y < t.y1;
+    const int cls = inside ? node_class<BC>(x, y, nx, ny) : int(kNodeNone);
+    const unsigned node = unsigned(y) * unsigned(nx) + unsigned(x);
+    // neighbours in the workgroup (at its ends a node stands in for the
+    // missing one: nothing that is stored depends on it)
+    const int dl = lx > 0 ? -1 : 0, dr = lx < bw - 1 ? 1 : 0;
+    const int db = ly > 0 ? -bw : 0, dt = ly < bh - 1 ? bw : 0;
+    const int at = ly < bh ? pos : 0;
+
+    AccT<A> acc;
+    A g[Q];
+    if (inside) gather_at<BC>(src, plane, nx, ny, Node{node, x, y, true, false}, g);
+    for (int n = 0; n < a.steps; ++n) {
+        const bool last = n == a.steps - 1;
+        SiteState<kD2Q9, A> S;
+        SiteScalars sc;
+        A out[Q];
+        A phi = A(1);
+        unsigned mask = 0;
+        A dsv = A(0);
+        if (cls == kNodeFluid) {
+            collide_site<kD2Q9, QE, DS, false>(g, shift, c, S, sc, STATS && last);
+            dsv = S.dpost;
+            if constexpr (STATS) {
+                if (last && owned) {
+                    acc.moments(sc);
+                    acc.fluid_site(sc, S.dpost);
+                    if (want_ent) {
+                        const double e = entropy_site<kD2Q9>(g, shift);
+                        if (isfinite(e)) acc.ent += A(e);
+                    }
+                }
+            }
+            if (owned && x == D.probe_x && y == D.probe_y) {
+                const gptr<float> p = to_global<float>(D.probe) + 2 * ((step + n) % D.probe_cap);
+                p[0] = sc.ux;
+                p[1] = sc.uy;
+            }
+        } else if (cls != kNodeNone) {
+            wall_state<QE>(D, cls, x, y, nx, ny, g, shift, out);
+            if constexpr (STATS) {
+                if (last && owned) {
+                    moments_fp64(g, sc.dr, sc.jx, sc.jy);
+                    acc.moments(sc);
+                    if (record) {
+                        to_global<unsigned char>(D.mask)[node] = (unsigned char)kMaskNotFluid;
+                        to_global<double>(D.dS)[node] = 0.0;
+                    }
+                }
+            }
+        }
+        if (median) {
+            if (ly < bh) ds[pos] = dsv;
+            __syncthreads();
+        }
+        if (cls == kNodeFluid) {
+            phi = trim_phi(D, S.dpost, mask);
+            if constexpr (DS == kExactHom) {
+                if (D.homothety && (mask & kMaskTrim) && !D.trim_mode && isfinite(S.dpost))
+                    phi = exact_homothety_call(S, shift, A(D.delta_trim));
+            }
+            if (D.limiter & kLimPos) {
+                const A pp = positivity_phi<kD2Q9>(S, shift);
+                if (pp < A(1)) {
+                    mask |= kMaskPos;
+                    if (STATS && last && owned) ++acc.pos;
+                    phi = fmin(phi, pp);
+                }
+            }
+            if (median) {
+                const A* r = ds + at;
+                const A b[3] = {r[db + dl], r[db], r[db + dr]}, m[3] = {r[dl], dsv, r[dr]},
+                        u[3] = {r[dt + dl], r[dt], r[dt + dr]};
+                A thr;
+                if (median_hit<BC>(D, x, y, nx, ny, b, m, u, thr)) {
+                    mask |= kMaskMedian;
+                    if (STATS && last && owned) ++acc.filt;
+                    A pm = A(1);
+                    bool done = false;
+                    if constexpr (DS == kExactHom) {
+                        if (D.homothety && isfinite(dsv)) {
+                            pm = exact_homothety_call(S, shift, thr);
+                            done = true;
+                        }
+                    }
+                    if (!done) pm = sqrt_(thr * rcp(dsv));
+                    phi = fmin(phi, pm);
+                }
+            }
+            const A k = phi * c;
+#pragma unroll
+            for (int i = 0; i < Q; ++i) out[i] = S.gs[i] - k * S.d[i];
+            if constexpr (STATS) {
+                if (last && owned) {
+                    if (mask & kMaskTrim) ++acc.trim;
+                    if (phi < A(1) && isfinite(dsv)) acc.lim += dsv - delta_s_scaled<kD2Q9, DS>(S, shift, c, phi);
+                    if (record) {
+                        if (sc.nonpos) mask |= kMaskNonpos;
+                        to_global<unsigned char>(D.mask)[node] = (unsigned char)mask;
+                        to_global<double>(D.dS)[node] = double(dsv);
+                    }
+                }
+            }
+        }
+        if (last) {
+            if (owned) {
+#pragma unroll
+                for (int i = 0; i < Q; ++i) Store<T>::st(at_bytes(dst + i * plane, unsigned(sizeof(T)) * node), out[i]);
+            }
+            break;
+        }
+        if (inside) {
+#pragma unroll
+            for (int i = 0; i < Q; ++i) st_shared<T>(&leaving[i][pos], out[i]);
+        }
+        __syncthreads();
+        if (inside) {
+#pragma unroll
+            for (int i = 0; i < Q; ++i) {
+                const int from = at + (L::vx(i) > 0 ? dl : (L::vx(i) < 0 ? dr : 0)) + (L::vy(i) > 0 ? db : (L::vy(i) < 0 ? dt : 0));
+                bool off = false;
+                if constexpr (BC != kPeriodic)
+                    off = (L::vx(i) > 0 && x == 0) || (L::vx(i) < 0 && x == nx - 1) || (L::vy(i) > 0 && y == 0) ||
+                          (L::vy(i) < 0 && y == ny - 1);
+                g[i] = ld_shared<T>(off ? &leaving[L::opp(i)][pos] : &leaving[i][from]);
+            }
+        }
+        // without the median filter there is no other barrier before the next store
+        if (!median) __syncthreads();
+    }
+    if constexpr (STATS) node_partial(acc, partial_slot(a, 1, tidx), red);
+}
+
 template <int BC, class T>
 __device__ inline void gather1d(gptr<const T> src, long long plane, int nx, int x,
                                 typename Store<T>::A (&g)[3])
@@ -1356,16 +1537,19 @@ __global__ void __launch_bounds__(k1DMaxThreads) k_step1d(StepArgs a)
     // the index of the step after this launch, read by the next one (which reads buffer 1 - parity)
     if (blockIdx.x == 0 && tid == 0) a.counter[1 - a.parity] = step + a.steps;
 
+    // the first threads take the tile's own sites, the others the halo (so that
+    // the sums do not depend on a.steps)
     const int halo = a.reach * a.steps;
-    const int xr = t.x0 - halo + tid;
-    const bool used = xr < t.x1 + halo;
+    const int pos = tid < k1DWidth ? tid + halo : (tid < k1DWidth + halo ? tid - k1DWidth : tid);
+    const int xr = t.x0 - halo + pos;
+    const int last_pos = k1DWidth + 2 * halo - 1;
+    const bool used = pos <= last_pos && xr < t.x1 + halo;
     const bool inside = used && (BC == kPeriodic || (xr >= 0 && xr < nx));
     const int x = BC == kPeriodic ? wrapi(xr, nx) : xr;
     const bool owned = inside && xr >= t.x0 && xr < t.x1;
     // neighbours in the workgroup (at its ends a site stands in for the
     // missing one: nothing that is written depends on it)
-    const int last_tid = int(blockDim.x) - 1;
-    const int tl = tid > 0 ? tid - 1 : 0, tr = tid < last_tid ? tid + 1 : last_tid;
+    const int tl = pos > 0 ? pos - 1 : 0, tr = pos < last_pos ? pos + 1 : last_pos;
 
     Acc acc;
     A g[Q];
@@ -1396,33 +1580,33 @@ __global__ void __launch_bounds__(k1DMaxThreads) k_step1d(StepArgs a)
         }
         const bool median = D.limiter & kLimMedian;
         if (median) {
-            ds[tid] = dsv;
+            ds[pos] = dsv;
             __syncthreads();
         }
         if (inside) {
             unsigned mask = 0;
             const bool has_med = median && (BC == kPeriodic || (x >= 1 && x <= nx - 2));
-            const A med = has_med ? med3(ds[tl], ds[tid], ds[tr]) : A(0);
+            const A med = has_med ? med3(ds[tl], ds[pos], ds[tr]) : A(0);
             A tgt;
             A phi = limiter_phi(S.dpost, has_med, med, D, mask, tgt);
             if constexpr (DS == kExactHom) {
                 if (D.homothety && phi > A(0) && tgt < A(__builtin_huge_val()) && isfinite(S.dpost))
                     phi = exact_homothety<LAT>(S, shift, tgt, S.dpost);
             }
-            bool pos = S.posrule;
+            bool posrule = S.posrule;
             if (D.limiter & kLimPos) {
                 const A pp = positivity_phi<LAT>(S, shift);
                 if (pp < A(1)) {
-                    pos = true;
+                    posrule = true;
                     if (last && owned) ++acc.pos;
                     phi = fmin(phi, pp);
                 }
             }
-            if (pos) mask |= kMaskPos;
+            if (posrule) mask |= kMaskPos;
             const A k = phi * S.c;
             if (!last) {
 #pragma unroll
-                for (int i = 0; i < Q; ++i) st_shared<T>(&leaving[n & 1][i][tid], S.gs[i] - k * S.d[i]);
+                for (int i = 0; i < Q; ++i) st_shared<T>(&leaving[n & 1][i][pos], S.gs[i] - k * S.d[i]);
             } else if (owned) {
                 if (S.posrule) ++acc.pos;
 #pragma unroll
@@ -1450,8 +1634,8 @@ __global__ void __launch_bounds__(k1DMaxThreads) k_step1d(StepArgs a)
 #pragma unroll
             for (int i = 0; i < Q; ++i) {
                 const bool off = BC != kPeriodic && L::vx(i) != 0 && x == (L::vx(i) > 0 ? 0 : nx - 1);
-                const int from = L::vx(i) == 0 ? tid : (L::vx(i) > 0 ? tl : tr);
-                g[i] = off ? ld_shared<T>(&leaving[n & 1][L::opp(i)][tid]) : ld_shared<T>(&leaving[n & 1][i][from]);
+                const int from = L::vx(i) == 0 ? pos : (L::vx(i) > 0 ? tl : tr);
+                g[i] = off ? ld_shared<T>(&leaving[n & 1][L::opp(i)][pos]) : ld_shared<T>(&leaving[n & 1][i][from]);
             }
         }
     }
@@ -1586,6 +1770,12 @@ hipError_t LBM_CAT(launch_step2d, LBM_SUFFIX)(int qe, int ds, int bc, const Step
     if (kernel == 3)
         return stats ? dispatch<0, 1>(qe, ds, bc, LBM_LAUNCH(a.ntiles, kThreads, k_fused2d, true))
                      : dispatch<0, 1>(qe, ds, bc, LBM_LAUNCH(a.ntiles, kThreads, k_fused2d, false));
+    if (kernel == 5) {
+        const int halo = 2 * a.steps - 1;
+        const int threads = ((a.block_w + 2 * halo) * (a.block_h + 2 * halo) + kWave - 1) / kWave * kWave;
+        return stats ? dispatch<0, 1>(qe, ds, bc, LBM_LAUNCH(a.ntiles, threads, k_block2d, true))
+                     : dispatch<0, 1>(qe, ds, bc, LBM_LAUNCH(a.ntiles, threads, k_block2d, false));
+    }
     if (kernel == 4) return dispatch<0, 1>(qe, ds, bc, LBM_LAUNCH(a.nblocks, kThreads, k_form2d));
     if (a.elbm)
         return a.ens_pass ? dispatch<0, 1, true>(qe, ds, bc, LBM_LAUNCH(a.ntiles, kThreads, k_median_ens2d, true))
