@@ -122,9 +122,12 @@ int max_steps1d(const lbm_domain_desc* doms, int32_t nd)
 }
 // The next launch's share of `left` steps: odd, at most `most`, and such that
 // the rest can be split the same way (each launch swaps the buffers once, as a
-// step does), in launches of nearly equal length.
-int next_launch(long long left, int most)
+// step does), in launches of nearly equal length.  With `alone` the last step
+// is a launch of its own (the small-domain kernel forms the sums there).
+int next_launch(long long left, int most, bool alone)
 {
+    if (most == 1 || (alone && left == 1)) return 1;
+    if (alone) --left;
     long long launches = (left + most - 1) / most;
     if ((launches ^ left) & 1) ++launches;
     long long n = (left + launches - 1) / launches;
@@ -933,7 +936,7 @@ int capture(lbm_ctx* ctx, int parity, int64_t len)
     HIP_TRY(ctx, hipStreamBeginCapture(ctx->stream, hipStreamCaptureModeThreadLocal));
     int rc = LBM_OK;
     for (int64_t k = 0; k < len && rc == LBM_OK;) {
-        const int n = ctx->most > 1 ? next_launch(len - k, ctx->most) : 1;
+        const int n = next_launch(len - k, ctx->most, ctx->block.w);
         rc = launch_one(ctx, int((parity + k) % 2), k + n == len, nullptr, 0, n);
         k += n;
     }
@@ -1619,7 +1622,7 @@ int lbm_step_static(const lbm_domain_desc* domain, int32_t storage, void* stream
     if (d1) a.reach = reach1d(domain, 1);
     for (int64_t t = 0; t < n_steps && e == hipSuccess;) {
         a.parity = int(t % 2);
-        a.steps = most > 1 ? next_launch(n_steps - t, most) : 1;
+        a.steps = next_launch(n_steps - t, most, block.w);
         a.flags = k.ens_pass || (stats && t + a.steps == n_steps) ? kFlagStats : 0;
         e = launch_step(k, a, s);
         t += a.steps;

@@ -968,21 +968,35 @@ __global__ void __launch_bounds__(kThreads) k_form2d(StepArgs a)
             // rows y - 1, y, y + 1 of Delta S'; the columns beside come from the
             // neighbouring lanes, the wave's end lanes and the row's end nodes
             // load theirs (clamped at a cavity's edges, where no fluid node
-            // reads them)
+            // reads them), the left one mostly: a second load serves a lane that
+            // needs the right one
             const unsigned all = unsigned(nx) * unsigned(ny);
             const bool end_l = x == 0, end_r = x == nx - 1;
             const unsigned wrap = BC == kPeriodic ? unsigned(nx) : 1u;
-            const bool own_l = lane == 0 || end_l, own_r = lane == kWave - 1 || end_r || n + 1 == all;
+            const bool own_l = lane == 0 || end_l, own_r = lane == kWave - 1 || end_r;
+            const unsigned to_l = end_l ? wrap - 1 : ~0u, to_r = end_r ? 1u - wrap : 1u;   // offsets mod 2^32
+            unsigned r[3];
 #pragma unroll
             for (int k = 0; k < 3; ++k) {
-                unsigned r = k == 0 ? n - unsigned(nx) : (k == 1 ? n : n + unsigned(nx));
-                if (k == 0 && y == 0) r = BC == kPeriodic ? n + all - unsigned(nx) : n;
-                if (k == 2 && y == ny - 1) r = BC == kPeriodic ? n + unsigned(nx) - all : n;
-                w[k][1] = Store<A>::ld(dsb + r);
-                w[k][0] = lane_shift<-1>(w[k][1]);
-                w[k][2] = lane_shift<+1>(w[k][1]);
-                if (own_l) w[k][0] = Store<A>::ld(dsb + (end_l ? r + wrap - 1 : r - 1));
-                if (own_r) w[k][2] = Store<A>::ld(dsb + (end_r ? r + 1 - wrap : r + 1));
+                r[k] = k == 0 ? n - unsigned(nx) : (k == 1 ? n : n + unsigned(nx));
+                if (k == 0 && y == 0) r[k] = BC == kPeriodic ? n + all - unsigned(nx) : n;
+                if (k == 2 && y == ny - 1) r[k] = BC == kPeriodic ? n + unsigned(nx) - all : n;
+                w[k][1] = Store<A>::ld(dsb + r[k]);
+            }
+            A beside[3] = {A(0), A(0), A(0)};
+            if (own_l || own_r) {
+#pragma unroll
+                for (int k = 0; k < 3; ++k) beside[k] = Store<A>::ld(dsb + (r[k] + (own_l ? to_l : to_r)));
+            }
+#pragma unroll
+            for (int k = 0; k < 3; ++k) {
+                const A l = lane_shift<-1>(w[k][1]), rr = lane_shift<+1>(w[k][1]);
+                w[k][0] = own_l ? beside[k] : l;
+                w[k][2] = own_r ? beside[k] : rr;
+            }
+            if (own_l && own_r) {      // a row's end at a wave's end
+#pragma unroll
+                for (int k = 0; k < 3; ++k) w[k][2] = Store<A>::ld(dsb + (r[k] + to_r));
             }
         } else {
             w[1][1] = Store<A>::ld(dsb + n);
@@ -1297,14 +1311,16 @@ __global__ void __launch_bounds__(kThreads) k_fused2d(StepArgs a)
 // microseconds (7 + 8 us for a 100 x 100 FP64 cavity), here a step is its
 // arithmetic and two barriers.  Decisions and states are those of the other
 // forms; the sums belong to the last step, one partial per tile in set 1.
+// MULTI: several steps (then without sums); the single step, with or without
+// them, needs no loop, whose hoisted constants cost it a wave per SIMD.
 constexpr int kBlockMax = 512;      // threads of a workgroup
-template <class T, int QE, int DS, int BC, bool STATS>
+template <class T, int QE, int DS, int BC, bool STATS, bool MULTI>
 __global__ void __launch_bounds__(kBlockMax) k_block2d(StepArgs a)
 {
     using A = typename Store<T>::A;
     using L = Lat<kD2Q9>;
     constexpr int Q = 9;
-    __shared__ T leaving[Q][kBlockMax];
+    __shared__ T leaving[MULTI ? Q : 1][MULTI ? kBlockMax : 1];
     __shared__ A ds[kBlockMax];
     __shared__ double red[STATS ? kBlockMax / kWave * kNStat : 1];
     const int tidx = tile_of_block(a, 0);
@@ -1319,9 +1335,10 @@ __global__ void __launch_bounds__(kBlockMax) k_block2d(StepArgs a)
     const bool want_ent = STATS && (a.flags & kFlagEntropy);
     const bool median = D.limiter & kLimMedian;
     const long long step = a.counter[a.parity];
-    if (blockIdx.x == 0 && threadIdx.x == 0) a.counter[1 - a.parity] = step + a.steps;
+    const int steps = MULTI ? a.steps : 1;
+    if (blockIdx.x == 0 && threadIdx.x == 0) a.counter[1 - a.parity] = step + steps;
 
-    const int halo = 2 * a.steps - 1, bw = a.block_w + 2 * halo, bh = a.block_h + 2 * halo;
+    const int halo = 2 * steps - 1, bw = a.block_w + 2 * halo, bh = a.block_h + 2 * halo;
     // the first threads take the tile's own nodes in row-major order, the others
     // the frame of the halo (so that the sums do not depend on a.steps): the
     // rows below the tile, the rows above it, the columns left and right
@@ -1367,8 +1384,8 @@ __global__ void __launch_bounds__(kBlockMax) k_block2d(StepArgs a)
     AccT<A> acc;
     A g[Q];
     if (inside) gather_at<BC>(src, plane, nx, ny, Node{node, x, y, true, false}, g);
-    for (int n = 0; n < a.steps; ++n) {
-        const bool last = n == a.steps - 1;
+    for (int n = 0; n < steps; ++n) {
+        const bool last = !MULTI || n == steps - 1;
         SiteState<kD2Q9, A> S;
         SiteScalars sc;
         A out[Q];
@@ -1379,7 +1396,7 @@ __global__ void __launch_bounds__(kBlockMax) k_block2d(StepArgs a)
             collide_site<kD2Q9, QE, DS, false>(g, shift, c, S, sc, STATS && last);
             dsv = S.dpost;
             if constexpr (STATS) {
-                if (last && owned) {
+                if (owned) {
                     acc.moments(sc);
                     acc.fluid_site(sc, S.dpost);
                     if (want_ent) {
@@ -1396,7 +1413,7 @@ __global__ void __launch_bounds__(kBlockMax) k_block2d(StepArgs a)
         } else if (cls != kNodeNone) {
             wall_state<QE>(D, cls, x, y, nx, ny, g, shift, out);
             if constexpr (STATS) {
-                if (last && owned) {
+                if (owned) {
                     moments_fp64(g, sc.dr, sc.jx, sc.jy);
                     acc.moments(sc);
                     if (record) {
@@ -1420,7 +1437,7 @@ __global__ void __launch_bounds__(kBlockMax) k_block2d(StepArgs a)
                 const A pp = positivity_phi<kD2Q9>(S, shift);
                 if (pp < A(1)) {
                     mask |= kMaskPos;
-                    if (STATS && last && owned) ++acc.pos;
+                    if (STATS && owned) ++acc.pos;
                     phi = fmin(phi, pp);
                 }
             }
@@ -1431,7 +1448,7 @@ __global__ void __launch_bounds__(kBlockMax) k_block2d(StepArgs a)
                 A thr;
                 if (median_hit<BC>(D, x, y, nx, ny, b, m, u, thr)) {
                     mask |= kMaskMedian;
-                    if (STATS && last && owned) ++acc.filt;
+                    if (STATS && owned) ++acc.filt;
                     A pm = A(1);
                     bool done = false;
                     if constexpr (DS == kExactHom) {
@@ -1448,7 +1465,7 @@ __global__ void __launch_bounds__(kBlockMax) k_block2d(StepArgs a)
 #pragma unroll
             for (int i = 0; i < Q; ++i) out[i] = S.gs[i] - k * S.d[i];
             if constexpr (STATS) {
-                if (last && owned) {
+                if (owned) {
                     if (mask & kMaskTrim) ++acc.trim;
                     if (phi < A(1) && isfinite(dsv)) acc.lim += dsv - delta_s_scaled<kD2Q9, DS>(S, shift, c, phi);
                     if (record) {
@@ -1466,24 +1483,26 @@ __global__ void __launch_bounds__(kBlockMax) k_block2d(StepArgs a)
             }
             break;
         }
-        if (inside) {
+        if constexpr (MULTI) {
+            if (inside) {
 #pragma unroll
-            for (int i = 0; i < Q; ++i) st_shared<T>(&leaving[i][pos], out[i]);
-        }
-        __syncthreads();
-        if (inside) {
-#pragma unroll
-            for (int i = 0; i < Q; ++i) {
-                const int from = at + (L::vx(i) > 0 ? dl : (L::vx(i) < 0 ? dr : 0)) + (L::vy(i) > 0 ? db : (L::vy(i) < 0 ? dt : 0));
-                bool off = false;
-                if constexpr (BC != kPeriodic)
-                    off = (L::vx(i) > 0 && x == 0) || (L::vx(i) < 0 && x == nx - 1) || (L::vy(i) > 0 && y == 0) ||
-                          (L::vy(i) < 0 && y == ny - 1);
-                g[i] = ld_shared<T>(off ? &leaving[L::opp(i)][pos] : &leaving[i][from]);
+                for (int i = 0; i < Q; ++i) st_shared<T>(&leaving[i][pos], out[i]);
             }
+            __syncthreads();
+            if (inside) {
+#pragma unroll
+                for (int i = 0; i < Q; ++i) {
+                    const int from = at + (L::vx(i) > 0 ? dl : (L::vx(i) < 0 ? dr : 0)) + (L::vy(i) > 0 ? db : (L::vy(i) < 0 ? dt : 0));
+                    bool off = false;
+                    if constexpr (BC != kPeriodic)
+                        off = (L::vx(i) > 0 && x == 0) || (L::vx(i) < 0 && x == nx - 1) || (L::vy(i) > 0 && y == 0) ||
+                              (L::vy(i) < 0 && y == ny - 1);
+                    g[i] = ld_shared<T>(off ? &leaving[L::opp(i)][pos] : &leaving[i][from]);
+                }
+            }
+            // without the median filter there is no other barrier before the next store
+            if (!median) __syncthreads();
         }
-        // without the median filter there is no other barrier before the next store
-        if (!median) __syncthreads();
     }
     if constexpr (STATS) node_partial(acc, partial_slot(a, 1, tidx), red);
 }
@@ -1773,8 +1792,9 @@ hipError_t LBM_CAT(launch_step2d, LBM_SUFFIX)(int qe, int ds, int bc, const Step
     if (kernel == 5) {
         const int halo = 2 * a.steps - 1;
         const int threads = ((a.block_w + 2 * halo) * (a.block_h + 2 * halo) + kWave - 1) / kWave * kWave;
-        return stats ? dispatch<0, 1>(qe, ds, bc, LBM_LAUNCH(a.ntiles, threads, k_block2d, true))
-                     : dispatch<0, 1>(qe, ds, bc, LBM_LAUNCH(a.ntiles, threads, k_block2d, false));
+        if (a.steps > 1) return dispatch<0, 1>(qe, ds, bc, LBM_LAUNCH(a.ntiles, threads, k_block2d, false, true));
+        return stats ? dispatch<0, 1>(qe, ds, bc, LBM_LAUNCH(a.ntiles, threads, k_block2d, true, false))
+                     : dispatch<0, 1>(qe, ds, bc, LBM_LAUNCH(a.ntiles, threads, k_block2d, false, false));
     }
     if (kernel == 4) return dispatch<0, 1>(qe, ds, bc, LBM_LAUNCH(a.nblocks, kThreads, k_form2d));
     if (a.elbm)
