@@ -963,6 +963,9 @@ __global__ void __launch_bounds__(kThreads) k_form2d(StepArgs a)
     const int x = v.x, y = v.y, lane = int(threadIdx.x) & (kWave - 1);
     if (v.in) {
         const unsigned n = v.n;
+        // (first: they are in flight while the window below is put together)
+        A g[9];
+        gather_at<BC>(src, plane, nx, ny, v, g);
         A w[3][3];
         if (D.limiter & kLimMedian) {
             // rows y - 1, y, y + 1 of Delta S'; the columns beside come from the
@@ -1001,8 +1004,6 @@ __global__ void __launch_bounds__(kThreads) k_form2d(StepArgs a)
         } else {
             w[1][1] = Store<A>::ld(dsb + n);
         }
-        A g[9];
-        gather_at<BC>(src, plane, nx, ny, v, g);
         if (node_class<BC>(x, y, nx, ny) == kNodeFluid) {
             const A dc = w[1][1];
             A tgt = A(__builtin_huge_val()), fac = A(1), thr;
