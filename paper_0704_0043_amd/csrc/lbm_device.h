@@ -624,17 +624,18 @@ __device__ A elbm_alpha(const A (&fs)[Q], const A (&x)[Q], bool& posrule)
 {
     constexpr A eps = sizeof(A) == 8 ? A(2.220446049250313e-16) : A(1.1920929e-7);
     const A inf = A(__builtin_huge_val());
-    A smax = inf, m2 = A(0), m3 = A(0);
+    A xmax = A(0), m2 = A(0), m3 = A(0);
     const A target = kull_sum<true>(fs, x, A(1));
     bool nonpos = false;
 #pragma unroll
     for (int i = 0; i < Q; ++i) {
-        if (x[i] > A(0)) smax = fmin(smax, A(1) / x[i]);
+        xmax = fmax(xmax, x[i]);
         nonpos |= x[i] <= A(-1);
         const A fx2 = fs[i] * x[i] * x[i];
         m2 += fx2;
         m3 += fx2 * x[i];
     }
+    const A smax = A(1) / xmax;            // where the first population vanishes
     posrule = false;
     if (!(smax < inf)) return A(2);        // f = f*: every alpha gives f
     if (nonpos) {
