@@ -182,6 +182,10 @@ int device_limiter(const lbm_domain_desc& d)
     return is_topk(d) ? ((d.limiter & ~kLimTrim) | kLimTopK) : d.limiter;
 }
 
+// Transfers of up to kHostLimit bytes (moments of a 200 x 200 domain) go through
+// the context's pinned buffer; the copy engine has the higher rate for more.
+constexpr size_t kHostLimit = size_t(1) << 20;
+
 size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 
 int q_of(int lattice) { return lattice == LBM_D2Q9 ? 9 : 3; }
@@ -267,6 +271,10 @@ struct lbm_ctx {
     bool adaptive = false;
     double fluid_total = 0;             // fluid nodes of all domains
     double* adapt_host = nullptr;       // [2] pinned
+    // small transfers go through pinned host memory that kernels read and write
+    // (kHostLimit); every call that uses it has waited before it returns
+    char* host = nullptr;
+    size_t host_bytes = 0;
     hipEvent_t adapt_ev[2] = {nullptr, nullptr};
     bool adapt_pending[2] = {false, false};
     long long adapt_points = 0, next_check = 0;
@@ -1027,6 +1035,26 @@ int finalize_stats(lbm_ctx* ctx)
     return LBM_OK;
 }
 
+// `bytes` of the ring of `cap` bytes at workspace offset `off`, from `first` on
+// (all multiples of 4, bytes <= host_bytes, first < cap), to host memory
+int read_words(lbm_ctx* ctx, void* to, size_t off, size_t first, size_t bytes, size_t cap)
+{
+    const char* ring = ctx->ws + off;
+    int device = -1;
+    if (hipGetDevice(&device) == hipSuccess && device == ctx->device) {
+        const hipError_t e = launch_read(ring, ctx->host, int(bytes / 4), int(first / 4), int(cap / 4), ctx->stream);
+        if (e != hipSuccess) return fail(ctx, LBM_EDEVICE, std::string("read: ") + hipGetErrorString(e));
+    } else {                        // a copy needs no current device
+        const size_t head = std::min(bytes, cap - first);
+        HIP_TRY(ctx, hipMemcpyAsync(ctx->host, ring + first, head, hipMemcpyDeviceToHost, ctx->stream));
+        if (head < bytes)
+            HIP_TRY(ctx, hipMemcpyAsync(ctx->host + head, ring, bytes - head, hipMemcpyDeviceToHost, ctx->stream));
+    }
+    HIP_TRY(ctx, hipStreamSynchronize(ctx->stream));
+    std::memcpy(to, ctx->host, bytes);
+    return LBM_OK;
+}
+
 int read_stats(lbm_ctx* ctx, int32_t d, lbm_entropy_stats_t* out)
 {
     int rc = finalize_stats(ctx);
@@ -1035,8 +1063,7 @@ int read_stats(lbm_ctx* ctx, int32_t d, lbm_entropy_stats_t* out)
     double raw[kNStat + 1];
     std::memset(raw, 0, sizeof(raw));
     if (ctx->steps_done > 0) {
-        HIP_TRY(ctx, hipMemcpyAsync(raw, ctx->ws + h.off_stats, sizeof(raw), hipMemcpyDeviceToHost, ctx->stream));
-        HIP_TRY(ctx, hipStreamSynchronize(ctx->stream));
+        if ((rc = read_words(ctx, raw, h.off_stats, 0, sizeof(raw), sizeof(raw)))) return rc;
     }
     lbm_entropy_stats_t s;
     std::memset(&s, 0, sizeof(s));
@@ -1063,8 +1090,7 @@ int read_stats(lbm_ctx* ctx, int32_t d, lbm_entropy_stats_t* out)
     if (h.d.limiter & (LBM_LIM_ENS_THRESHOLD | LBM_LIM_ENS_BUDGET)) {
         double ev[kNEns] = {0, 0, 0, 0};
         if (ctx->steps_done > 0) {
-            HIP_TRY(ctx, hipMemcpyAsync(ev, ctx->ws + h.off_ens, sizeof(ev), hipMemcpyDeviceToHost, ctx->stream));
-            HIP_TRY(ctx, hipStreamSynchronize(ctx->stream));
+            if ((rc = read_words(ctx, ev, h.off_ens, 0, sizeof(ev), sizeof(ev)))) return rc;
         }
         s.ens_threshold = (h.d.limiter & LBM_LIM_ENS_BUDGET) ? ev[kEBudget] : ev[kEThresh];
     }
@@ -1135,6 +1161,7 @@ void release(lbm_ctx* ctx)
     for (hipEvent_t& e : ctx->adapt_ev)
         if (e) (void)hipEventDestroy(e);
     if (ctx->adapt_host) (void)hipHostFree(ctx->adapt_host);
+    if (ctx->host) (void)hipHostFree(ctx->host);
     if (ctx->own_ws && ctx->ws) (void)hipFree(ctx->ws);
     if (ctx->own_stream && ctx->stream) (void)hipStreamDestroy(ctx->stream);
     delete ctx;
@@ -1252,6 +1279,21 @@ int lbm_create(const lbm_domain_desc* domains, int32_t n_domains, const lbm_run_
             return bail(fail(nullptr, LBM_ENOMEM, std::string("hipMalloc: ") + hipGetErrorString(e)));
         }
         ctx->own_ws = true;
+    }
+
+    // the largest transfer of the domains, within the limit; stats always fit
+    ctx->host_bytes = 256;
+    static_assert((kNStat + 1) * sizeof(double) <= 256 && kNEns * sizeof(double) <= 256, "stats in the pinned buffer");
+    for (const auto& h : ctx->dom) {
+        const size_t f = h.n * h.q * sizeof(double), mom = h.n * (h.q == 9 ? 3 : 2) * sizeof(double);
+        const size_t probe = h.d.probe_x >= 0 ? size_t(ctx->probe_cap) * 2 * sizeof(float) : 0;
+        for (size_t b : {f, mom, probe})
+            ctx->host_bytes = std::max(ctx->host_bytes, std::min(b, kHostLimit));
+    }
+    e = hipHostMalloc(reinterpret_cast<void**>(&ctx->host), ctx->host_bytes);
+    if (e != hipSuccess) {
+        ctx->host = nullptr;
+        return bail(fail(nullptr, LBM_ENOMEM, std::string("hipHostMalloc: ") + hipGetErrorString(e)));
     }
 
     // budget histograms start zero; every selection level leaves them zero
@@ -1403,9 +1445,24 @@ static int gather_state(lbm_ctx* ctx, int32_t d, double* f, double* rho, double*
     double* sr = sf + size_t(h.q) * ctx->lay.max_n;
     double* su = sr + ctx->lay.max_n;
     const int parity = int(ctx->steps_done % 2);
+    // a small state straight into the pinned buffer
+    const size_t nf = f ? n * h.q : 0, nr = rho ? n : 0, nu = u ? n * dim : 0;
+    const bool small = (nf + nr + nu) * sizeof(double) <= ctx->host_bytes;
+    if (small) {
+        sf = reinterpret_cast<double*>(ctx->host);
+        sr = sf + nf;
+        su = sr + nr;
+    }
     hipError_t e = launch_gather(ctx->storage, h.d.lattice, h.d.bc, ctx->ws + h.off_buf[parity], h.plane, sf, h.d.nx,
                                  h.d.ny, h.shift, f != nullptr, rho ? sr : nullptr, u ? su : nullptr, ctx->stream);
     if (e != hipSuccess) return fail(ctx, LBM_EDEVICE, std::string("gather: ") + hipGetErrorString(e));
+    if (small) {
+        HIP_TRY(ctx, hipStreamSynchronize(ctx->stream));
+        if (f) std::memcpy(f, sf, nf * sizeof(double));
+        if (rho) std::memcpy(rho, sr, nr * sizeof(double));
+        if (u) std::memcpy(u, su, nu * sizeof(double));
+        return LBM_OK;
+    }
     if (f) HIP_TRY(ctx, hipMemcpyAsync(f, sf, n * h.q * sizeof(double), hipMemcpyDeviceToHost, ctx->stream));
     if (rho) HIP_TRY(ctx, hipMemcpyAsync(rho, sr, n * sizeof(double), hipMemcpyDeviceToHost, ctx->stream));
     if (u) HIP_TRY(ctx, hipMemcpyAsync(u, su, n * dim * sizeof(double), hipMemcpyDeviceToHost, ctx->stream));
@@ -1439,7 +1496,13 @@ int lbm_set_populations(lbm_ctx* ctx, int32_t domain, const double* f)
         if (!std::isfinite(f[s])) return fail(ctx, LBM_EINVAL, "f has non-finite values");
     double* sf = ctx->d_stage();
     const int parity = int(ctx->steps_done % 2);
-    HIP_TRY(ctx, hipMemcpyAsync(sf, f, h.n * h.q * sizeof(double), hipMemcpyHostToDevice, ctx->stream));
+    const size_t bytes = h.n * h.q * sizeof(double);
+    if (bytes <= ctx->host_bytes) {
+        sf = reinterpret_cast<double*>(ctx->host);
+        std::memcpy(sf, f, bytes);
+    } else {
+        HIP_TRY(ctx, hipMemcpyAsync(sf, f, bytes, hipMemcpyHostToDevice, ctx->stream));
+    }
     hipError_t e = launch_scatter(ctx->storage, h.d.lattice, h.d.bc, sf, ctx->ws + h.off_buf[parity], h.plane, h.d.nx,
                                   h.d.ny, h.shift, ctx->stream);
     if (e != hipSuccess) return fail(ctx, LBM_EDEVICE, std::string("scatter: ") + hipGetErrorString(e));
@@ -1471,6 +1534,12 @@ int lbm_probe_trace(lbm_ctx* ctx, int32_t domain, float* uv, int64_t max_samples
     const int64_t avail = std::min<int64_t>(ctx->steps_done, cap);
     const int64_t take = std::min<int64_t>(avail, max_samples);
     if (take == 0) return LBM_OK;
+    if (size_t(take) * 8 <= ctx->host_bytes && cap < (int64_t(1) << 29)) {
+        const int64_t slot = (ctx->steps_done - take) % cap;
+        if ((rc = read_words(ctx, uv, h.off_probe, size_t(slot) * 8, size_t(take) * 8, size_t(cap) * 8))) return rc;
+        *n_written = take;
+        return LBM_OK;
+    }
     std::vector<float> ring(size_t(cap) * 2);
     HIP_TRY(ctx, hipMemcpyAsync(ring.data(), ctx->ws + h.off_probe, ring.size() * sizeof(float), hipMemcpyDeviceToHost,
                                 ctx->stream));

@@ -307,5 +307,6 @@ hipError_t launch_scatter(int storage, int lattice, int bc, const double* f, voi
                           int ny, double shift, hipStream_t s);
 hipError_t launch_gather(int storage, int lattice, int bc, const void* buf, long long plane, double* f, int nx,
                          int ny, double shift, int want_f, double* rho, double* u, hipStream_t s);
+hipError_t launch_read(const void* ring, void* out, int words, int first, int cap, hipStream_t s);
 
 }  // namespace lbm
