@@ -198,6 +198,16 @@ __device__ __forceinline__ void st_shared(T* p, typename Store<T>::A v) { *p = (
 // square root (about 1 ulp), well inside the FP32 error budget.
 __device__ inline double rcp(double x) { return 1.0 / x; }
 __device__ inline float rcp(float x) { return __builtin_amdgcn_rcpf(x); }
+// FP32: the quotient with one residual correction, correctly rounded but for
+// rare last-bit cases in the normal range, at half the instructions of the
+// scaled IEEE sequence; where the residual is no number, without the correction
+__device__ inline double div_(double a, double b) { return a / b; }
+__device__ inline float div_(float a, float b)
+{
+    const float r = __builtin_amdgcn_rcpf(b), q = a * r;
+    const float p = __builtin_fmaf(__builtin_fmaf(-b, q, a), r, q);
+    return p == p ? p : q;
+}
 __device__ inline double sqrt_(double x) { return sqrt(x); }
 __device__ inline double pow_(double x, double y) { return pow(x, y); }
 __device__ inline float pow_(float x, float y) { return powf(x, y); }
@@ -230,8 +240,8 @@ __device__ inline A median9(A a0, A a1, A a2, A a3, A a4, A a5, A a6, A a7, A a8
 // cancels; there the alternating series x^2 sum_k (-x)^k / ((k+1)(k+2)) is
 // summed in Horner form.  The first omitted term bounds the truncation:
 // below 1e-17 relative in FP64 (8 terms for |x| <= 1/85, 16 for |x| <= 0.1);
-// in FP32 below 1.4e-8 for |x| <= 1/8 (7 terms, the usual case) and 1.4e-9
-// for |x| <= 0.5 (22 terms).
+// in FP32 below 4e-9 for |x| <= 1/64 (4 terms, the usual case), 1.4e-8 for
+// |x| <= 1/8 (7 terms) and 1.4e-9 for |x| <= 0.5 (22 terms).
 template <int N, class A>
 __device__ __forceinline__ A h_series(A x)
 {
@@ -251,8 +261,8 @@ struct HRange<double> {
 };
 template <>
 struct HRange<float> {
-    static constexpr float near = 0.125f, tiny = 0.0f, mid = 0.5f;
-    static constexpr int nnear = 7, ntiny = 7;
+    static constexpr float near = 0.125f, tiny = 0.015625f, mid = 0.5f;
+    static constexpr int nnear = 7, ntiny = 4;
 };
 // h and h' = ln(1 + x) beyond the short series: up to 1/2 a longer one, then
 // the logarithm.  FP64: with z = x / (2 + x), ln(1 + x) = 2 atanh z gives
@@ -309,6 +319,23 @@ __device__ __forceinline__ A pick(const A (&v)[Q], int i)
     return r;
 }
 
+// sum_i f*_i h(s x_i) where all arguments are within `reach` <= HRange::near
+template <int Q, class A>
+__device__ __forceinline__ A kull_near(const A (&fs)[Q], const A (&x)[Q], A s, A reach)
+{
+    using R = HRange<A>;
+    A sum = A(0);
+    if constexpr (R::ntiny < R::nnear) {
+        if (reach <= R::tiny) {
+#pragma unroll
+            for (int i = 0; i < Q; ++i) sum += fs[i] * h_series<R::ntiny>(s * x[i]);
+            return sum;
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < Q; ++i) sum += fs[i] * h_series<R::nnear>(s * x[i]);
+    return sum;
+}
 // sum_i f*_i h(s x_i).  The populations whose argument is beyond the series
 // (few, at strongly nonequilibrium nodes) are marked on the way and added
 // afterwards by one loop, so the logarithm stands in the code once: with a
@@ -609,9 +636,15 @@ __device__ __forceinline__ void moments_equilibrium(const A (&g)[Lat<LAT>::Q], A
 // the deviation (1 - alpha) x, so in s = alpha - 1 the equation is
 // G(s) = sum f*_i h(-s x_i) - sum f*_i h(x_i) = 0 with G convex and
 // increasing on [0, s_max], s_max the positivity boundary of f~, and
-// G(0) < 0.  Newton from the LBGK mirror s = 1 corrected by the cubic term
-// of h (h(y) = y^2/2 - y^3/6 + O(y^4) puts the root at
-// s = 1 - sum f*_i x_i^3 / (3 sum f*_i x_i^2) + O(x^2)), kept inside the bracket
+// G(0) < 0.  With m_k = sum f*_i x_i^k the series of h puts the root at
+// s = 1 - c + c^2 + O(x^3), c = m_3 / (3 m_2) (LBGK's mirror is s = 1).  Where
+// every |x_i| is within the series' range the slope comes from the moments,
+// G' = s m_2 + s^2 m_3 / 2 (+ s^3 m_4 / 3 in FP64): it only steers the
+// iteration, whose end is decided by G.  Near equilibrium one evaluation of G
+// then confirms the start, where Newton with the full slope took a reciprocal
+// per population and a second round (the vector units bound the kernel:
+// 1087 -> 853 instructions a wave, 1500 x 1501 FP32 60 -> 50 us a step).
+// Newton is kept inside the bracket
 // (bisection when a step leaves it), until G is at the rounding level of its
 // sums; the result is moved down to a point with G <= 0, so the entropy does
 // not decrease.  A root short of s_max exists iff G(s_max) >= 0; that is
@@ -624,17 +657,20 @@ __device__ A elbm_alpha(const A (&fs)[Q], const A (&x)[Q], bool& posrule)
 {
     constexpr A eps = sizeof(A) == 8 ? A(2.220446049250313e-16) : A(1.1920929e-7);
     const A inf = A(__builtin_huge_val());
-    A xmax = A(0), m2 = A(0), m3 = A(0);
-    const A target = kull_sum<true>(fs, x, A(1));
-    bool nonpos = false;
+    using R = HRange<A>;
+    constexpr bool fp64 = sizeof(A) == 8;
+    A xmax = A(0), xmin = A(0), m2 = A(0), m3 = A(0), m4 = A(0);
 #pragma unroll
     for (int i = 0; i < Q; ++i) {
         xmax = fmax(xmax, x[i]);
-        nonpos |= x[i] <= A(-1);
-        const A fx2 = fs[i] * x[i] * x[i];
+        xmin = fmin(xmin, x[i]);
+        const A x2 = x[i] * x[i], fx2 = fs[i] * x2;
         m2 += fx2;
         m3 += fx2 * x[i];
+        if constexpr (fp64) m4 += fx2 * x2;
     }
+    const bool nonpos = xmin <= A(-1);
+    const A xabs = fmax(xmax, -xmin);
     const A smax = A(1) / xmax;            // where the first population vanishes
     posrule = false;
     if (!(smax < inf)) return A(2);        // f = f*: every alpha gives f
@@ -642,16 +678,31 @@ __device__ A elbm_alpha(const A (&fs)[Q], const A (&x)[Q], bool& posrule)
         posrule = true;
         return A(1) + smax;
     }
-    // G(s) and G'(s) = -sum f*_i x_i ln(1 - s x_i)
+    const A target = xabs <= R::near ? kull_near(fs, x, A(1), xabs) : kull_sum<true>(fs, x, A(1));
+    // G(s), and with G'(s) = -sum f*_i x_i ln(1 - s x_i) or its leading terms
+    auto value = [&](A s) {
+        const A reach = s * xabs;
+        return (reach <= R::near ? kull_near(fs, x, -s, reach) : kull_sum<true>(fs, x, -s)) - target;
+    };
     auto eval = [&](A s, A& dg) {
+        const A reach = s * xabs;
+        if (reach <= R::near) {
+            A high = A(0.5) * m3;
+            if constexpr (fp64) high += s * (A(1.0 / 3.0) * m4);
+            dg = s * (m2 + s * high);
+            return kull_near(fs, x, -s, reach) - target;
+        }
         const A g = kull_sum_slope(fs, x, -s, dg) - target;
         dg = -dg;
         return g;
     };
     A s = A(1);
     if (m2 > A(0)) {
-        const A c = m3 / (A(3) * m2);
-        if (fabs(c) < A(0.5)) s -= c;
+        const A inv = rcp(m2), c = A(1.0 / 3.0) * m3 * inv;
+        if (fabs(c) < A(0.5)) {
+            s -= c;
+            if (xabs <= R::near) s += c * c;
+        }
     }
     A lo = A(0), hi = smax;
     s = fmin(s, A(0.5) * smax);
@@ -676,8 +727,7 @@ __device__ A elbm_alpha(const A (&fs)[Q], const A (&x)[Q], bool& posrule)
         A sn = s - g / dg;
         if (!(sn > lo && sn < hi)) {
             if (!above) {
-                A d;
-                if (eval(smax, d) < A(0)) {
+                if (value(smax) < A(0)) {
                     posrule = true;
                     return A(1) + smax;
                 }
@@ -693,15 +743,14 @@ __device__ A elbm_alpha(const A (&fs)[Q], const A (&x)[Q], bool& posrule)
             break;
         }
     }
-    A d;
-    if (!settled && !above && eval(smax, d) < A(0)) {
+    if (!settled && !above && value(smax) < A(0)) {
         posrule = true;
         return A(1) + smax;
     }
-    A gs = at_s ? g : eval(s, d);
+    A gs = at_s ? g : value(s);
     for (int k = 0; k < 4 && gs > A(0); ++k) {
         s *= A(1) - A(2) * eps;
-        gs = eval(s, d);
+        gs = value(s);
     }
     if (gs > A(0)) s = lo;
     return A(1) + s;
@@ -730,7 +779,7 @@ __device__ __forceinline__ void collide_site(const A (&g)[Lat<LAT>::Q], A shift,
         // beta = (c + 1) / 2
         A xe[Q];
 #pragma unroll
-        for (int i = 0; i < Q; ++i) xe[i] = o.d[i] / fs[i];
+        for (int i = 0; i < Q; ++i) xe[i] = div_(o.d[i], fs[i]);
         const A alpha = elbm_alpha<Q>(fs, xe, o.posrule);
         c = alpha * (A(0.5) * (c + A(1))) - A(1);
     }
