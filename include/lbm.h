@@ -309,7 +309,7 @@ LBM_API int lbm_probe_trace(lbm_ctx* ctx, int32_t domain, float* uv, int64_t max
  * the next step runs after a choice).  D2Q9: columns of the first domain's
  * collision row blocks (256, or 64 / 128 for a narrow domain), their rows
  * per workgroup, and the rows of a second-pass tile; the fused step: 248, 1
- * and the rows of a fused tile.  D1Q3: 254, 1, 1. */
+ * and the rows of a fused tile.  D1Q3: 190, 1, 1. */
 LBM_API int lbm_tile_config(const lbm_ctx* ctx, int32_t* tile_x, int32_t* tile_y, int32_t* tile_h);
 
 /* sync; profiling aid outside the method.  Advances the state by n_steps

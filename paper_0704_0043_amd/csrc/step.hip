@@ -1811,7 +1811,7 @@ hipError_t LBM_CAT(launch_step1d, LBM_SUFFIX)(int qe, int ds, int bc, const Step
     const int threads = threads1d(a.reach, a.steps);
     if (kernel == 0) return dispatch<0, 2>(qe, ds, bc, LBM_LAUNCH(a.ntiles, threads, k_step1d, false));
     if (kernel == 2) return dispatch<0, 2, true>(qe, ds, bc, LBM_LAUNCH(a.ntiles, threads, k_step1d, true));
-    return dispatch<0, 2>(qe, ds, bc, LBM_LAUNCH(a.ntiles, kThreads, k_ens1d));
+    return dispatch<0, 2>(qe, ds, bc, LBM_LAUNCH(a.ntiles, threads1d(0, 0), k_ens1d));
 }
 
 }  // namespace lbm
