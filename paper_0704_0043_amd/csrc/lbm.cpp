@@ -120,32 +120,43 @@ int max_steps1d(const lbm_domain_desc* doms, int32_t nd)
     }
     return reach1d(doms, nd) > 1 && sites > 65536 ? k1DMaxSteps / 2 : k1DMaxSteps;
 }
-// The next launch's share of `left` steps: odd, at most `most`, and such that
-// the rest can be split the same way (each launch swaps the buffers once, as a
-// step does), in launches of nearly equal length.  With `alone` the last step
-// is a launch of its own (the small-domain kernel forms the sums there).
-int next_launch(long long left, int most, bool alone)
+// The next launch's share of `left` steps, at most `most`, in launches of nearly
+// equal length.  Each launch swaps the buffers once, as a step does, so a
+// sequence takes an even number of launches for an even number of steps and
+// an odd one for an odd: `odd` says which the launches left must be (at first
+// that of the steps; it turns with every launch).  With `alone` the last step is
+// a launch of its own (the small-domain kernel forms the sums there).
+int next_launch(long long left, bool odd, int most, bool alone)
 {
     if (most == 1 || (alone && left == 1)) return 1;
-    if (alone) --left;
+    if (alone) {
+        --left;
+        odd = !odd;
+    }
     long long launches = (left + most - 1) / most;
-    if ((launches ^ left) & 1) ++launches;
-    long long n = (left + launches - 1) / launches;
-    if (n % 2 == 0) --n;
-    return int(std::max(n, left - (launches - 1) * most));
+    if ((launches % 2 != 0) != odd) ++launches;
+    return int((left + launches - 1) / launches);
 }
 
 // The small-domain form (k_block2d): tiles of w x h nodes, up to `steps` steps a
 // launch (w = 0: the domains keep the other forms).  Fusable domains of at most
 // kBlockNodes nodes in all take it: there launches and memory latency cost
-// more than the halo's work.  Three steps a launch while the halo leaves at
-// most two waves per SIMD (kBlockWaves), else one.  The tile is the one with
-// the fewest waves in all.
+// more than the halo's work.  Steps and tile are those of the least estimated
+// time per step, fitted to cavities of 32 to 256 nodes a side with the exact
+// Delta S in FP64 and the quadratic one in FP32: a launch and its first accesses
+// take 3.1 us; a step 3.9 us in FP64 (1.7 us in FP32) with one wave per SIMD and
+// 2.8 us (1.0 us) per wave with more.  One 100 x 100 FP64 cavity, us per step:
+// 7.0 with one step a launch, 6.6 with three on two waves per SIMD, 5.8 with
+// two on one; from 100k nodes on the waves count and single steps have the
+// fewest.  In FP64 several steps only while a SIMD has one wave: on a rough field
+// the halo's waves, which take the logarithms too, cost more than the launches
+// saved (200 x 300 noise, 16 steps: 146 us in pairs, 126 one by one).
 struct BlockForm {
     int w = 0, h = 0, steps = 1;
 };
 constexpr long long kBlockNodes = 400000;
-constexpr int kBlockWaves = 2048, kBlockThreads = 512;
+constexpr int kBlockThreads = 512;
+constexpr int kCUs = 256;
 BlockForm block_form(const lbm_domain_desc* doms, int32_t nd, const lbm_run_desc* run)
 {
     BlockForm best;
@@ -153,20 +164,29 @@ BlockForm block_form(const lbm_domain_desc* doms, int32_t nd, const lbm_run_desc
     long long nodes = 0;
     for (int k = 0; k < nd; ++k) nodes += (long long)doms[k].nx * doms[k].ny;
     if (nodes > kBlockNodes) return best;
-    for (int steps : {3, 1}) {
+    const bool fp64 = run->storage == LBM_F64;
+    const double lone = fp64 ? 3.9 : 1.7, shared = fp64 ? 2.8 : 1.0;
+    double least = 0.0;
+    long long fewest = 0;
+    for (int steps : {3, 2, 1}) {
         const int halo = 2 * steps - 1;
-        long long fewest = -1;
         for (int w = 4; w + 2 * halo <= 64; ++w)
             for (int h = 4; (w + 2 * halo) * (h + 2 * halo) <= kBlockThreads; ++h) {
                 long long tiles = 0;
                 for (int k = 0; k < nd; ++k) tiles += block_tiles_of(doms[k].nx, doms[k].ny, w, h);
-                const long long waves = tiles * (((w + 2 * halo) * (h + 2 * halo) + kWave - 1) / kWave);
-                if (fewest < 0 || waves < fewest) {
+                const int per_tile = ((w + 2 * halo) * (h + 2 * halo) + kWave - 1) / kWave;
+                const long long waves = tiles * per_tile, turns = (tiles + kCUs - 1) / kCUs;
+                // waves per SIMD: of the busiest CU while each has one tile or two
+                const double load = turns <= 2 ? double((turns * per_tile + 3) / 4)
+                                               : std::max(2.0, double(waves) / (4 * kCUs));
+                if (fp64 && steps > 1 && load > 1.0) continue;
+                const double cost = 3.1 / steps + (load <= 1.0 ? lone : shared * load);
+                if (best.w == 0 || cost < least || (cost == least && waves < fewest)) {
+                    least = cost;
                     fewest = waves;
                     best = BlockForm{w, h, steps};
                 }
             }
-        if (fewest <= kBlockWaves) break;
     }
     return best;
 }
@@ -943,9 +963,11 @@ int capture(lbm_ctx* ctx, int parity, int64_t len)
     hipGraph_t g = nullptr;
     HIP_TRY(ctx, hipStreamBeginCapture(ctx->stream, hipStreamCaptureModeThreadLocal));
     int rc = LBM_OK;
-    for (int64_t k = 0; k < len && rc == LBM_OK;) {
-        const int n = next_launch(len - k, ctx->most, ctx->block.w);
-        rc = launch_one(ctx, int((parity + k) % 2), k + n == len, nullptr, 0, n);
+    int p = parity;
+    bool odd = len % 2 != 0;
+    for (int64_t k = 0; k < len && rc == LBM_OK; p = 1 - p, odd = !odd) {
+        const int n = next_launch(len - k, odd, ctx->most, ctx->block.w);
+        rc = launch_one(ctx, p, k + n == len, nullptr, 0, n);
         k += n;
     }
     hipError_t e = hipStreamEndCapture(ctx->stream, &g);
@@ -1689,9 +1711,9 @@ int lbm_step_static(const lbm_domain_desc* domain, int32_t storage, void* stream
     a.block_w = block.w;
     a.block_h = block.h;
     if (d1) a.reach = reach1d(domain, 1);
-    for (int64_t t = 0; t < n_steps && e == hipSuccess;) {
-        a.parity = int(t % 2);
-        a.steps = next_launch(n_steps - t, most, block.w);
+    bool odd = n_steps % 2 != 0;
+    for (int64_t t = 0; t < n_steps && e == hipSuccess; a.parity = 1 - a.parity, odd = !odd) {
+        a.steps = next_launch(n_steps - t, odd, most, block.w);
         a.flags = k.ens_pass || (stats && t + a.steps == n_steps) ? kFlagStats : 0;
         e = launch_step(k, a, s);
         t += a.steps;

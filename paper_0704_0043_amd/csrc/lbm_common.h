@@ -148,8 +148,7 @@ constexpr int k1DWidth = 190;
 
 // D1Q3 steps of one launch.  A workgroup computes its k1DWidth sites with a
 // halo that each further step eats `reach` sites of on either side (1, with
-// the median filter 2).  A launch reads one buffer and writes the other, so it
-// takes an odd number of steps.
+// the median filter 2).
 constexpr int k1DMaxSteps = 33;
 constexpr int k1DMaxThreads = 384;
 inline int threads1d(int reach, int steps) { return (k1DWidth + 2 * reach * steps + kWave - 1) / kWave * kWave; }
@@ -278,7 +277,7 @@ struct StepArgs {
                             // a median candidate (Delta S' > delta_median) and stored its Delta S'
     long long* counter;     // [2] step index by parity
     int reach = 1;          // D1Q3: sites a step's result depends on, on either side
-    int steps = 1;          // D1Q3 and the small-domain kernel: steps of this launch (odd)
+    int steps = 1;          // D1Q3 and the small-domain kernel: steps of this launch
 };
 
 // Allocation-free stepping (lbm_step_static): bytes of the per-GPU static

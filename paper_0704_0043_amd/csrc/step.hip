@@ -1303,7 +1303,7 @@ __global__ void __launch_bounds__(kThreads) k_fused2d(StepArgs a)
 }
 
 // Small D2Q9 domains (LBGK, no ensemble limiter): whole steps of a tile in one
-// workgroup, one node per thread, a.steps (odd) of them.  A step needs the
+// workgroup, one node per thread, a.steps of them.  A step needs the
 // populations of the nodes around and, for the median, their Delta S', so the
 // threads cover the tile and a halo of 2 a.steps - 1 nodes; populations go from
 // step to step in LDS (rounded to storage, as a store would), Delta S' within a
