@@ -192,9 +192,12 @@ __global__ void __launch_bounds__(kHistThreads) k_budget_hist(StepArgs a, int le
     for (int g = g0; g < g1; ++g) {
         const Group t = a.groups[g];
         const DomainDev& D = a.dom[t.domain];
-        const bool run = (D.limiter & (kLimEnsBudget | kLimTopK)) && !D.bstate->done;
+        bool run = D.limiter & (kLimEnsBudget | kLimTopK);
         if (run) {
+            // the first nodes are on their way before `done` is looked at
+            const int done = D.bstate->done;
             const unsigned long long prefix = D.bstate->prefix;
+            run = !done;
             const A* ds = static_cast<const A*>(D.dsbuf);
             int cur = -1;
             unsigned cnt = 0;
@@ -207,6 +210,7 @@ __global__ void __launch_bounds__(kHistThreads) k_budget_hist(StepArgs a, int le
                     const int nk = n + k * kHistThreads;
                     v[k] = nk < t.n1 ? ds[nk] : A(__builtin_huge_val());
                 }
+                if (done) break;
 #pragma unroll
                 for (int k = 0; k < kAhead; ++k) {
                     if (!isfinite(v[k])) continue;
@@ -227,6 +231,7 @@ __global__ void __launch_bounds__(kHistThreads) k_budget_hist(StepArgs a, int le
                     sum += key_significand<K>(key);
                 }
             }
+            if (!run) continue;
             if (level == 0) flush_wave(cur, cnt, sum);
             else if (cnt) flush(cur, cnt, sum);
         }
@@ -298,9 +303,16 @@ __global__ void __launch_bounds__(kThreads) k_budget_select(StepArgs a, int leve
     const DomainDev& D = a.dom[blockIdx.x];
     if (!(D.limiter & kLimEnsBudget)) return;
     BudgetState* bs = D.bstate;
-    if (bs->done) return;
     const int tid = int(threadIdx.x);
+    // the state and the buckets come together, not one after the other
+    const int done = bs->done;
     const unsigned long long prefix = bs->prefix;
+    const double budget = bs->budget;
+    const double start[2] = {bs->s_above, bs->c_above};
+    BudgetBucket g[per];
+#pragma unroll
+    for (int i = 0; i < per; ++i) g[i] = D.bhist[tid * per + i];
+    if (done) return;
     const int lo = budget_lo(K::dbl, level), hi = budget_hi(K::dbl, level);
     const int w = hi - lo;
     auto edge_of = [&](int b) { return U(((prefix << w) | (unsigned long long)b) << lo); };
@@ -310,7 +322,7 @@ __global__ void __launch_bounds__(kThreads) k_budget_select(StepArgs a, int leve
     for (int i = per - 1; i >= 0; --i) {
         const int b = tid * per + i;
         BudgetBucket& gb = D.bhist[b];
-        const unsigned long long n = gb.n, l = gb.lo, h = gb.hi;
+        const unsigned long long n = g[i].n, l = g[i].lo, h = g[i].hi;
         gb.n = 0;
         gb.lo = 0;
         gb.hi = 0;
@@ -321,9 +333,7 @@ __global__ void __launch_bounds__(kThreads) k_budget_select(StepArgs a, int leve
     }
     if (tid == 0) best = -1;
     double above[2] = {my_s, my_c};
-    const double start[2] = {bs->s_above, bs->c_above};
     sums_above<2>(above, start, waves);
-    const double budget = bs->budget;
     const int nb = 1 << w;   // buckets of this digit (the rest stay empty)
     double S = above[0], C = above[1];
     double sa = 0.0, ca = 0.0, sa0 = 0.0, ca0 = 0.0;
@@ -393,9 +403,15 @@ __global__ void __launch_bounds__(kThreads) k_topk_select(StepArgs a, int level)
     const DomainDev& D = a.dom[blockIdx.x];
     if (!(D.limiter & kLimTopK)) return;
     BudgetState* bs = D.bstate;
-    if (bs->done) return;
     const int tid = int(threadIdx.x);
+    const int done = bs->done;
     const unsigned long long prefix = bs->prefix;
+    const double kk = bs->budget;
+    const double start[1] = {bs->c_above};
+    unsigned long long n[per];
+#pragma unroll
+    for (int i = 0; i < per; ++i) n[i] = D.bhist[tid * per + i].n;
+    if (done) return;
     const int lo = budget_lo(K::dbl, level), hi = budget_hi(K::dbl, level);
     const int w = hi - lo;
     const int nb = 1 << w;
@@ -404,7 +420,7 @@ __global__ void __launch_bounds__(kThreads) k_topk_select(StepArgs a, int level)
 #pragma unroll
     for (int i = per - 1; i >= 0; --i) {
         BudgetBucket& gb = D.bhist[tid * per + i];
-        c[i] = double(gb.n);
+        c[i] = double(n[i]);
         gb.n = 0;
         gb.lo = 0;
         gb.hi = 0;
@@ -412,9 +428,7 @@ __global__ void __launch_bounds__(kThreads) k_topk_select(StepArgs a, int level)
     }
     if (tid == 0) best = -1;
     double above[1] = {my_c};
-    const double start[1] = {bs->c_above};
     sums_above<1>(above, start, waves);
-    const double kk = bs->budget;
     double C = above[0], ca = 0.0, ca0 = 0.0;
     int mine = -1;
 #pragma unroll
