@@ -157,12 +157,16 @@ struct BlockForm {
 constexpr long long kBlockNodes = 400000;
 constexpr int kBlockThreads = 512;
 constexpr int kCUs = 256;
-BlockForm block_form(const lbm_domain_desc* doms, int32_t nd, const lbm_run_desc* run)
+BlockForm block_form(const lbm_domain_desc* doms, int32_t nd, const lbm_run_desc* run, bool adaptive)
 {
     BlockForm best;
-    if (!fusable(doms, nd) || run->tile_x == kFusedWidth || (run->flags & LBM_RUN_ADAPTIVE)) return best;
+    if (!fusable(doms, nd) || run->tile_x == kFusedWidth || adaptive) return best;
     long long nodes = 0;
-    for (int k = 0; k < nd; ++k) nodes += (long long)doms[k].nx * doms[k].ny;
+    int widest = 0;
+    for (int k = 0; k < nd; ++k) {
+        nodes += (long long)doms[k].nx * doms[k].ny;
+        widest = std::max(widest, int(doms[k].nx));
+    }
     if (nodes > kBlockNodes) return best;
     const bool fp64 = run->storage == LBM_F64;
     const double lone = fp64 ? 3.9 : 1.7, shared = fp64 ? 2.8 : 1.0;
@@ -170,11 +174,12 @@ BlockForm block_form(const lbm_domain_desc* doms, int32_t nd, const lbm_run_desc
     long long fewest = 0;
     for (int steps : {3, 2, 1}) {
         const int halo = 2 * steps - 1;
-        for (int w = 4; w + 2 * halo <= 64; ++w)
-            for (int h = 4; (w + 2 * halo) * (h + 2 * halo) <= kBlockThreads; ++h) {
+        for (int w = 4; w + 2 * halo <= 64 && w < widest + 4; ++w)
+            for (int per_tile = 1; per_tile <= kBlockThreads / kWave; ++per_tile) {
+                const int h = per_tile * kWave / (w + 2 * halo) - 2 * halo;      // the tallest of as many waves
+                if (h < 4) continue;
                 long long tiles = 0;
                 for (int k = 0; k < nd; ++k) tiles += block_tiles_of(doms[k].nx, doms[k].ny, w, h);
-                const int per_tile = ((w + 2 * halo) * (h + 2 * halo) + kWave - 1) / kWave;
                 const long long waves = tiles * per_tile, turns = (tiles + kCUs - 1) / kCUs;
                 // waves per SIMD: of the busiest CU while each has one tile or two
                 const double load = turns <= 2 ? double((turns * per_tile + 3) / 4)
@@ -475,7 +480,7 @@ void plan(std::vector<DomainHost>& dh, const lbm_domain_desc* doms, int32_t nd, 
     const unsigned flags = run->flags;
     const int cap = run->probe_capacity > 0 ? run->probe_capacity : 4096;
     const bool adaptive = adaptive_run(doms, nd, run);
-    const BlockForm block = block_form(doms, nd, run);
+    const BlockForm block = block_form(doms, nd, run, adaptive), plain = block_form(doms, nd, run, false);
     size_t off = 0;
     L.max_tiles = 0;
     L.nblocks = 0;
@@ -513,6 +518,8 @@ void plan(std::vector<DomainHost>& dh, const lbm_domain_desc* doms, int32_t nd, 
         if (block.w) tiles = block_tiles_of(h.d.nx, h.d.ny, block.w, block.h);
         // adaptive: the fused tiles (any tuned height) share the partial slots
         if (h.d.lattice == LBM_D2Q9 && adaptive) tiles = std::max(tiles, fused_tiles_of(h.d.nx, h.d.ny, kMinFusedH));
+        // (and an adaptive workspace holds the same domains' plain run)
+        if (adaptive && plain.w) tiles = std::max(tiles, block_tiles_of(h.d.nx, h.d.ny, plain.w, plain.h));
         L.max_tiles += tiles;
         if (h.d.lattice == LBM_D2Q9) {
             L.nblocks += blocks_of(h.d.nx, h.d.ny);
@@ -1258,7 +1265,7 @@ int lbm_create(const lbm_domain_desc* domains, int32_t n_domains, const lbm_run_
         ctx->reach = reach1d(domains, n_domains);
         ctx->most = max_steps1d(domains, n_domains);
     }
-    ctx->block = block_form(domains, n_domains, run);
+    ctx->block = block_form(domains, n_domains, run, run->flags & LBM_RUN_ADAPTIVE);
     if (ctx->block.w) ctx->most = ctx->block.steps;
     ctx->cap_h = second_height(domains, n_domains, kMaxTileH);
     ctx->fuse_ok = ctx->lattice == LBM_D2Q9 && !ctx->elbm && ctx->median_pass && !ctx->ens_pass;
@@ -1647,7 +1654,7 @@ int lbm_step_static(const lbm_domain_desc* domain, int32_t storage, void* stream
         return fail(nullptr, LBM_EINVAL, "no probe trace without a context (probe_x, probe_y must be -1)");
     DomainHost h;
     StaticLayout L;
-    BlockForm block = block_form(domain, 1, &run);
+    BlockForm block = block_form(domain, 1, &run, false);
     plan_static(*domain, storage, second_height(domain, 1, kMaxTileH), block, h, L);
     // shorter tiles have more partials: never at the price of refusing a domain
     if (L.total > kStaticScratchBytes) {
