@@ -132,8 +132,7 @@ enum lbm_storage { LBM_F64 = 0, LBM_F32 = 1, LBM_F16_SHIFT = 2, LBM_BF16_SHIFT =
 #define LBM_RUN_RECORD 1u    /* keep per-node mask and Delta S' of every step */
 #define LBM_RUN_ENTROPY 2u   /* also accumulate sum S(f) (Sec. 4.3.1) */
 #define LBM_RUN_NO_GRAPH 4u  /* launch steps one by one (no captured graphs) */
-#define LBM_RUN_NO_TUNE 8u   /* no timing of shapes: narrow row blocks where a domain allows
-                                them, tile_h (or 64) for the second pass */
+#define LBM_RUN_NO_TUNE 8u   /* no timing of shapes: tile_h (or 64) for the second pass */
 #define LBM_RUN_ADAPTIVE 16u /* D2Q9 LBGK domains with the median filter and no ensemble-
                                 dependent limiter, tile_x other than 248: keep both forms of
                                 the step, the two kernels (shapes tuned as usual) and the
@@ -196,12 +195,12 @@ typedef struct {
     int32_t device;             /* HIP device ordinal */
     int32_t stats_every;        /* >0: lbm_step synchronises every k steps and
                                    returns LBM_EUNSTABLE as lbm_entropy_stats does */
-    int32_t tile_x;             /* D2Q9 collision row blocks (one node per thread, 256 per
-                                   workgroup): 256 = one row of 256 columns per workgroup;
-                                   64 = for a domain at most 128 wide, the narrowest of 64
-                                   or 128 columns that spans its rows, with 4 or 2 rows per
-                                   workgroup (wider domains keep 256); 0 = chosen by the
-                                   autotuner (see lbm_create); 248 = the fused step: one kernel
+    int32_t tile_x;             /* 0, 64 or 256: the form the library takes for the domains
+                                   (small domains whose limiters are trimming, positivity and
+                                   the median filter run whole steps of a tile, up to three a
+                                   launch; others the collision kernel, 256 consecutive nodes
+                                   per workgroup, and the second pass); 64 and 256 differ in
+                                   what lbm_tile_config reports.  248 = the fused step: one kernel
                                    does the collision and the median filter (Sec. 3.5) over
                                    tiles of 248 columns (four waves of 62 owned columns each;
                                    LBGK domains with the median filter and no ensemble-dependent
@@ -255,9 +254,9 @@ LBM_API int lbm_workspace_bytes(const lbm_domain_desc* domains, int32_t n_domain
 /* Create a context: validates the descriptors, allocates (or carves the
  * workspace into) population buffers, builds f(x, 0) (f_init, or f*(rho, u))
  * and the work tables, and captures the step graphs.  D2Q9 autotuner: unless
- * LBM_RUN_NO_TUNE or fixed by tile_x / tile_h, the candidate shapes (row
- * blocks of 256 columns or narrow ones; second-pass tiles of 16, 32 or 64
- * rows; with tile_x = 248 the fused tile heights) are timed with HIP events
+ * LBM_RUN_NO_TUNE or fixed by tile_h, the candidate shapes (second-pass
+ * tiles of 16, 32 or 64 rows, shorter on small grids; with tile_x = 248 the
+ * fused tile heights) are timed with HIP events
  * on a few steps that all read the initial state (which they leave
  * unchanged), each scored by a step as it stands plus one whose second pass
  * walks every tile, and the fastest is kept; the choice is
@@ -306,9 +305,9 @@ LBM_API int lbm_probe_trace(lbm_ctx* ctx, int32_t domain, float* uv, int64_t max
                     int64_t* n_written);
 
 /* Shape in use (with LBM_RUN_ADAPTIVE, of the form the last step ran, or
- * the next step runs after a choice).  D2Q9: columns of the first domain's
- * collision row blocks (256, or 64 / 128 for a narrow domain), their rows
- * per workgroup, and the rows of a second-pass tile; the fused step: 248, 1
+ * the next step runs after a choice).  D2Q9: 256 (with tile_x 0 or 64 and a
+ * first domain at most 64 / 128 wide: 64 / 128), 256 divided by that,
+ * and the rows of a second-pass tile; the fused step: 248, 1
  * and the rows of a fused tile.  D1Q3: 190, 1, 1. */
 LBM_API int lbm_tile_config(const lbm_ctx* ctx, int32_t* tile_x, int32_t* tile_y, int32_t* tile_h);
 
@@ -318,7 +317,7 @@ LBM_API int lbm_tile_config(const lbm_ctx* ctx, int32_t* tile_x, int32_t* tile_y
  * average duration in milliseconds of the collision kernel to ms[0] and of
  * the rest of the step to ms[1]: the ensemble reductions and selection (when
  * an ensemble-dependent limiter is on) and the second pass (median filter,
- * ensemble factors); 0 when no second pass runs.  The stats of the
+ * ensemble factors); 0 when no second pass runs (the fused step, small domains).  The stats of the
  * last step stay readable afterwards.  ms is a
  * caller-owned host array of 2 doubles.  LBM_EINVAL for a bad count or a
  * NULL pointer. */
@@ -360,7 +359,9 @@ LBM_API void lbm_destroy(lbm_ctx* ctx);
  *            how lbm_set_populations stores a state.  f0 holds the state at
  *            entry; step t reads f0 when t is even and f1 when odd and
  *            writes the other, so after n_steps the state is in f0 for even
- *            n_steps and in f1 for odd.  Caller-owned.
+ *            n_steps and in f1 for odd, and the state before the last step
+ *            in the other (several steps of one launch leave no states
+ *            between them).  Caller-owned.
  *   n_steps  >= 0 (0 launches nothing).
  *   stats    nullable device array of LBM_STATIC_NSTATS doubles: the FP64
  *            sums of the last step in the order mass, mom_x, mom_y,

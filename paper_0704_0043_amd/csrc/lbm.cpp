@@ -307,7 +307,7 @@ struct lbm_ctx {
     std::vector<Block> blocks_host;
     std::vector<Group> groups_host;
     int cap_h = kMaxTileH;      // tallest second-pass tile of these domains (second_height)
-    int narrow = 1;             // report row blocks of 64 / 128 columns for narrow domains
+    int narrow = 1;             // report 64 / 128 columns for narrow domains
     int tuned = 0;              // 1 when the tile shape was chosen by timing
 
     DomainDev* d_dom() const { return reinterpret_cast<DomainDev*>(ws + act.off_dom); }
@@ -346,7 +346,7 @@ int validate(const lbm_domain_desc* doms, int32_t nd, const lbm_run_desc* run)
     if (run->struct_size < sizeof(lbm_run_desc)) return fail(nullptr, LBM_EINVAL, "lbm_run_desc.struct_size too small");
     if (run->storage < LBM_F64 || run->storage > LBM_BF16_SHIFT) return fail(nullptr, LBM_EINVAL, "bad storage");
     if (run->tile_x != 0 && run->tile_x != kWave && run->tile_x != kThreads && run->tile_x != kFusedWidth)
-        return fail(nullptr, LBM_EINVAL, "tile_x must be 0 (tuned), 64 (narrow row blocks), 256 or 248 (fused step)");
+        return fail(nullptr, LBM_EINVAL, "tile_x must be 0 (tuned), 64, 256 or 248 (fused step)");
     if (run->tile_y != 0 && run->tile_y != 1) return fail(nullptr, LBM_EINVAL, "tile_y must be 0 or 1");
     if (run->tile_h < 0 || run->tile_h > (run->tile_x == kFusedWidth ? kMaxFusedH : kMaxTileH))
         return fail(nullptr, LBM_EINVAL, "tile_h out of range [0, 64] (fused step: [0, 128])");
@@ -558,7 +558,7 @@ void plan(std::vector<DomainHost>& dh, const lbm_domain_desc* doms, int32_t nd, 
     L.total = off;
 }
 
-// Tiles in spatial order: domain, row block, column block.  A D2Q9 tile is
+// Tiles in spatial order: domain, row chunk, column strip.  A D2Q9 tile is
 // kThreads consecutive columns by `th` rows (one thread per column walking
 // the rows).  The kernels map workgroups to runs of this order XCD by XCD
 // (xcd_spatial), so vertically adjacent tiles, which share halo rows, run
@@ -814,19 +814,18 @@ void drop_graphs(lbm_ctx* ctx)
 }
 
 // ---- autotuner ---------------------------------------------------------------
-// Three shape choices change the speed of a D2Q9 step: the row blocks of the
-// collision kernel (256 columns per row, or several rows of a narrow domain
-// per workgroup), the height of the tiles the second pass walks, and, for
-// domains with the median filter and no ensemble-dependent limiter, the fused
-// step (collision and median filter in one pass over tiles of kFusedWidth
+// Two shape choices change the speed of a D2Q9 step: the height of the tiles the
+// second pass walks, and, for domains with the median filter and no
+// ensemble-dependent limiter, the fused step (collision and median filter in
+// one pass over tiles of kFusedWidth
 // columns) in place of the two kernels, taken when the run asks for it
 // (tile_x = kFusedWidth; the tuner then picks its tile height).  The fused
 // step costs the same whatever the filter does; the two kernels cost less
 // while few nodes move and more when many do (each moved node's stored state
 // is read and written again), which the steps timed at creation, from a
-// state where nothing has moved yet, cannot show.  Row blocks and tile heights change
-// nothing the step computes (the stats partials are grouped by fixed 64-row
-// groups, so E(Delta S') and every field come out the same; only the FP64
+// state where nothing has moved yet, cannot show.  Tile heights change
+// nothing the step computes (the collision partials are summed in fixed groups
+// of nodes, so E(Delta S') and every field come out the same; only the FP64
 // sums that the second pass adds to may differ in the last bits).  The fused
 // step forms a moved node's state f* - phi c d once, with phi the smallest
 // factor, where the two kernels rescale the stored trimmed state: the masks
@@ -884,8 +883,7 @@ int time_shape(lbm_ctx* ctx, int n, double& ms, unsigned extra_flags = 0)
     return rc;
 }
 
-// fused_alt: the fused form of an adaptive run (its tile height only; the
-// row blocks of the two-kernel form stay as tuned)
+// fused_alt: the fused form of an adaptive run (its tile height only)
 int autotune(lbm_ctx* ctx, const lbm_run_desc* run, bool fused_alt = false)
 {
     // (the collision kernel takes consecutive nodes whatever the rows: the
@@ -919,8 +917,7 @@ int autotune(lbm_ctx* ctx, const lbm_run_desc* run, bool fused_alt = false)
     if (ctx->block.w) return apply_shape(ctx, cand.back());
     if (cand.size() == 1) return apply_shape(ctx, cand[0]);
     if (ctx->flags & LBM_RUN_NO_TUNE) {
-        // narrow row blocks where a domain allows them, tile_h or 64 rows
-        // for the second pass; the fused step only when asked for
+        // tile_h or 64 rows for the second pass; the fused step only when asked for
         if (run->tile_x == kFusedWidth) return apply_shape(ctx, {narrow, run->tile_h > 0 ? run->tile_h : 64, true});
         return apply_shape(ctx, {narrow, heights.back(), false});
     }
@@ -1587,10 +1584,9 @@ int lbm_tile_config(const lbm_ctx* ctx, int32_t* tile_x, int32_t* tile_y, int32_
 {
     if (!ctx) return fail(nullptr, LBM_EINVAL, "NULL context");
     const bool d2 = ctx->lattice == LBM_D2Q9;
-    // D2Q9: columns of the first domain's row blocks (256, or 64 / 128 for a
-    // narrow domain), their rows per workgroup, and the second pass's tile
-    // height; D1Q3: sites per workgroup, 1, 1
-    // height; the fused step reports kFusedWidth, 1 and its tile height
+    // D2Q9: seg_width columns and their rows per 256 nodes, and the second
+    // pass's tile height; D1Q3: sites per workgroup, 1, 1; the fused step:
+    // kFusedWidth, 1 and its tile height
     const bool fused = ctx->act.fused;
     const int width = fused ? kFusedWidth : (d2 ? seg_width(ctx->dom[0].d.nx, ctx->narrow) : k1DWidth);
     if (tile_x) *tile_x = width;
@@ -1720,7 +1716,8 @@ int lbm_step_static(const lbm_domain_desc* domain, int32_t storage, void* stream
     if (d1) a.reach = reach1d(domain, 1);
     bool odd = n_steps % 2 != 0;
     for (int64_t t = 0; t < n_steps && e == hipSuccess; a.parity = 1 - a.parity, odd = !odd) {
-        a.steps = next_launch(n_steps - t, odd, most, block.w);
+        // (the last step alone: the other buffer then holds the state before it)
+        a.steps = next_launch(n_steps - t, odd, most, true);
         a.flags = k.ens_pass || (stats && t + a.steps == n_steps) ? kFlagStats : 0;
         e = launch_step(k, a, s);
         t += a.steps;

@@ -129,14 +129,10 @@ __host__ __device__ inline int xcd_spatial(int b, int T)
     return x * q + (x < r ? x : r) + j;
 }
 
-// One work item (one workgroup) over columns [x0, x1) of one domain.  The
-// median kernel takes the consecutive rows [y0, y1); the collision kernel the
-// rows ys, ys + ystep, ..., (yn of them).  With ystep = the number of row
-// chunks, the collision tiles that run together all work on one narrow band
-// of rows at a time, which keeps the DRAM pages they touch few and the rows
-// their neighbours pull from in L2.
+// One work item (one workgroup) of the second pass, the fused step, the tile
+// kernel or the D1Q3 step: columns [x0, x1) and rows [y0, y1) of one domain.
 struct Tile {
-    int domain, x0, x1, y0, y1, ys, ystep, yn;
+    int domain, x0, x1, y0, y1;
 };
 
 // Output sites of one D1Q3 workgroup: with the halo of the longest launch
@@ -188,8 +184,8 @@ __host__ __device__ inline Group group_entry2d(int domain, int n, int i)
 }
 inline int groups_of(int nx, int ny) { return (blocks_of(nx, ny) + kGroupParts - 1) / kGroupParts; }
 
-// Columns reported for a domain's row blocks: with `narrow` 64 or 128 for a
-// domain that narrow, else 256.
+// Columns lbm_tile_config reports for the collision workgroups (of 256
+// consecutive nodes): with `narrow` 64 or 128 for a domain that narrow, else 256.
 inline int seg_width(int nx, int narrow)
 {
     return (narrow && nx <= 64) ? 64 : ((narrow && nx <= 128) ? 128 : kThreads);
@@ -201,15 +197,13 @@ inline int seg_width(int nx, int narrow)
 __host__ __device__ inline Tile tile_entry2d(int domain, int nx, int ny, int th, int i)
 {
     const int strips = (nx + kThreads - 1) / kThreads;
-    const int chunks = (ny + th - 1) / th;
     const int r = i / strips, x0 = (i - r * strips) * kThreads;
-    return Tile{domain, x0, x0 + kThreads < nx ? x0 + kThreads : nx, r * th, r * th + th < ny ? r * th + th : ny,
-                r, chunks, (ny - r + chunks - 1) / chunks};
+    return Tile{domain, x0, x0 + kThreads < nx ? x0 + kThreads : nx, r * th, r * th + th < ny ? r * th + th : ny};
 }
 __host__ __device__ inline Tile tile_entry1d(int domain, int nx, int i)
 {
     const int x0 = i * k1DWidth;
-    return Tile{domain, x0, x0 + k1DWidth < nx ? x0 + k1DWidth : nx, 0, 1, 0, 1, 1};
+    return Tile{domain, x0, x0 + k1DWidth < nx ? x0 + k1DWidth : nx, 0, 1};
 }
 __host__ __device__ inline int tiles_of(int lattice, int nx, int ny, int th)
 {
@@ -230,10 +224,8 @@ __host__ __device__ inline int fused_tiles_of(int nx, int ny, int th)
 __host__ __device__ inline Tile fused_tile_entry(int domain, int nx, int ny, int th, int i)
 {
     const int strips = (nx + kFusedWidth - 1) / kFusedWidth;
-    const int chunks = (ny + th - 1) / th;
     const int r = i / strips, x0 = (i - r * strips) * kFusedWidth;
-    return Tile{domain, x0, x0 + kFusedWidth < nx ? x0 + kFusedWidth : nx, r * th, r * th + th < ny ? r * th + th : ny,
-                r, chunks, 1};
+    return Tile{domain, x0, x0 + kFusedWidth < nx ? x0 + kFusedWidth : nx, r * th, r * th + th < ny ? r * th + th : ny};
 }
 
 // Tiles of bw x bh nodes of the small-domain kernel (k_block2d)
@@ -245,7 +237,7 @@ __host__ __device__ inline Tile block_tile_entry(int domain, int nx, int ny, int
 {
     const int cols = (nx + bw - 1) / bw;
     const int r = i / cols, x0 = (i - r * cols) * bw, y0 = r * bh;
-    return Tile{domain, x0, x0 + bw < nx ? x0 + bw : nx, y0, y0 + bh < ny ? y0 + bh : ny, 0, 1, 1};
+    return Tile{domain, x0, x0 + bw < nx ? x0 + bw : nx, y0, y0 + bh < ny ? y0 + bh : ny};
 }
 
 struct StepArgs {

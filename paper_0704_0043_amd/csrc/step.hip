@@ -2,18 +2,20 @@
 //
 // Compiled once per population storage type (LBM_ST = 0..3).  A D2Q9 time
 // step of every domain is one launch of the collision kernel and, when a
-// limiter needs more than the node itself, one launch of the second pass:
+// limiter needs more than the node itself, one launch of the second pass
+// (small domains take k_block2d, which does both, D1Q3 k_step1d):
 //
-//  collision: one thread per node, one workgroup per row segment of 256
-//    columns, segments in row-major order, so the whole grid streams through
+//  collision: one thread per node, one workgroup per 256 consecutive nodes in
+//    row-major order, so the whole grid streams through
 //    a narrow band of rows at a time.  Free flight (pull form, read from
 //    buffer `parity`), moments, f*, the collision (LBGK, or ELBM in its own
 //    instantiation), Delta S', the trimming and positivity factors (they
 //    depend on the node alone), and the store of the limited post-collision
 //    state into the other buffer.  With the median filter or an
 //    ensemble-dependent limiter on, Delta S' also goes to a plane of its own.
-//    Each workgroup leaves one partial of the reduction terms; the FP64
-//    global sums are formed from these on demand, when the stats are read.
+//    In steps whose sums may be read (the last of a captured sequence) each
+//    workgroup leaves one partial of the reduction terms; the FP64 global sums
+//    are formed from these on demand, when the stats are read.
 //  second pass: the 3x3 median of that plane and the ensemble-dependent
 //    factors (thresholds from this step's E(Delta S') and selections) decide
 //    which nodes move further; their stored limited states are rescaled
@@ -275,8 +277,8 @@ __device__ __forceinline__ void moments_fp64(const A (&g)[9], double& dr, double
     }
 }
 
-// STREAM: the nontemporal hint, for a wave whose 64 lanes write whole
-// aligned row segments; a wave that writes a segment sharing its end sectors
+// STREAM: the nontemporal hint, for a wave whose 64 lanes write one whole
+// aligned piece; a wave that writes a segment sharing its end sectors
 // with another wave's (the fused step) stores plainly, so that L2 merges the
 // two halves of a sector before it goes to HBM
 template <class T, bool STREAM = true>

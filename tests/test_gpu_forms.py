@@ -275,3 +275,24 @@ def test_probe_ring_and_transfers():
             rho, u = L.lbm_moments(ctx)
         close(got, f0, 4e-16)       # stored less the rest state, one rounding each way
         close(rho, f0.sum(0), 1e-14)
+
+
+# several steps of one launch leave the states between them nowhere, but the
+# buffer that does not hold the result holds the state before the last step
+@pytest.mark.parametrize("lattice,nx,ny", [(D1Q3, 300, 1), (D2Q9, 60, 50)])
+@pytest.mark.parametrize("n", [1, 2, 7, 40])
+def test_static_buffers_after_several_steps(lattice, nx, ny, n):
+    import torch
+    L = lbm()
+    d = L.Domain(lattice=lattice, nx=nx, ny=ny, beta=0.95, qe=0, ds_form=1, limiter=3, delta_trim=1e-3,
+                 delta_median=1e-5)
+    f = torch.from_numpy(rough(3 if lattice == D1Q3 else 9, nx, ny, seed=4)).cuda()
+
+    def after(k):
+        bufs = [f.clone(), torch.zeros_like(f)]
+        L.lbm_step_static(d, 0, bufs[0].data_ptr(), bufs[1].data_ptr(), k, torch.cuda.current_stream().cuda_stream)
+        torch.cuda.synchronize()
+        return bufs[k % 2], bufs[1 - k % 2]
+
+    say(f"[static] lattice {lattice} {nx}x{ny} n {n}")
+    assert torch.equal(after(n)[1], after(n - 1)[0])
