@@ -98,6 +98,28 @@ int second_height(const lbm_domain_desc* doms, int32_t nd, int th)
     return std::min(th, kMinTileH);
 }
 
+// LDS that a collision workgroup of the steps without sums asks for and does not
+// use, so that six fit on a CU instead of eight.  The kernel streams from HBM,
+// and with rows of whole waves in FP32 fewer waves in flight keep to fewer DRAM
+// pages: 4096 x 4096 204.6 -> 198.9 us, 4096 x 2048 109.2 -> 104.0 us a step,
+// 3072 x 3072 120.3 -> 117.9.  With other widths the waves' pieces straddle
+// lines and eight are better (3600 x 3500: 157.4 us against 159.8), as with
+// 16-bit storage, whose loads carry half the bytes (6000 x 5000: 213 against
+// 252), and where the last-level cache holds the domains (1024 x 1024: 20.7
+// against 21.6).  The variant with sums needs all the waves it can get.
+constexpr int kSixPerCu = 26 << 10;
+constexpr long long kLastLevelCache = 256ll << 20;
+int collide_lds(const lbm_domain_desc* doms, int32_t nd, int storage)
+{
+    if (storage != LBM_F32) return 0;
+    long long nodes = 0;
+    for (int k = 0; k < nd; ++k) {
+        if (doms[k].lattice != LBM_D2Q9 || doms[k].nx % kWave) return 0;
+        nodes += (long long)doms[k].nx * doms[k].ny;
+    }
+    return nodes * 72 > kLastLevelCache ? kSixPerCu : 0;
+}
+
 // D1Q3: sites on either side that one step's result depends on (free flight,
 // and the Delta S' of the neighbours with the median filter)
 int reach1d(const lbm_domain_desc* doms, int32_t nd)
@@ -263,6 +285,7 @@ struct lbm_ctx {
     bool ens_pass = false;      // an ensemble-dependent limiter in some domain
     bool fuse_ok = false;       // the fused step applies (D2Q9 LBGK, median filter, no ensemble limiter)
     int reach = 1, most = 1;    // D1Q3: reach of a step; steps of the longest launch
+    int collide_lds = 0;        // idle LDS of the collision workgroups
     BlockForm block;            // the small-domain form (w = 0: not taken)
     int dense = 0;              // kDenseSome / kSparseSome: what second passes the domains need
     int budget = 0;             // kSelect* bits: budget threshold, top-k trimming in some domain
@@ -714,6 +737,7 @@ StepArgs step_args(const lbm_ctx* ctx, int parity)
     a.budget = ctx->budget;
     a.dense = ctx->dense;
     a.fused = ctx->block.w ? 2 : (ctx->act.fused ? 1 : 0);
+    a.collide_lds = ctx->collide_lds;
     a.block_w = ctx->block.w;
     a.block_h = ctx->block.h;
     a.blocks = ctx->blocks_host.empty() ? nullptr : ctx->d_blocks();
@@ -883,6 +907,11 @@ int time_shape(lbm_ctx* ctx, int n, double& ms, unsigned extra_flags = 0)
     return rc;
 }
 
+// Weight of a step as it stands against one whose second pass walks every tile:
+// in most steps of most runs few tiles have anything to move (4096 x 4096 FP32,
+// 16 or 64 rows: 212 or 209 us as it stands, 269 or 278 with every tile).
+constexpr double kAsItStands = 4.0;
+
 // fused_alt: the fused form of an adaptive run (its tile height only)
 int autotune(lbm_ctx* ctx, const lbm_run_desc* run, bool fused_alt = false)
 {
@@ -933,7 +962,7 @@ int autotune(lbm_ctx* ctx, const lbm_run_desc* run, bool fused_alt = false)
     // Warm the part up on the first candidate, then time every candidate in
     // two rounds (the second in reverse order) and keep each one's best.  How
     // much of the second pass has work depends on the flow (at the start
-    // often no tile has a candidate); a candidate is scored by the sum of a
+    // often no tile has a candidate); a candidate is scored by the weighted sum of a
     // step as it stands and a step whose second pass walks every tile (the
     // fused step does its median work on every node either way).
     int rc = apply_shape(ctx, cand[0]);
@@ -952,7 +981,7 @@ int autotune(lbm_ctx* ctx, const lbm_run_desc* run, bool fused_alt = false)
     if (rc) return rc;
     size_t pick = 0;
     for (size_t c = 1; c < cand.size(); ++c)
-        if (best[c] + best_all[c] < best[pick] + best_all[pick]) pick = c;
+        if (kAsItStands * best[c] + best_all[c] < kAsItStands * best[pick] + best_all[pick]) pick = c;
     {
         std::lock_guard<std::mutex> lock(g_tune_mu);
         g_tune_cache[key] = cand[pick];
@@ -1265,6 +1294,7 @@ int lbm_create(const lbm_domain_desc* domains, int32_t n_domains, const lbm_run_
     ctx->block = block_form(domains, n_domains, run, run->flags & LBM_RUN_ADAPTIVE);
     if (ctx->block.w) ctx->most = ctx->block.steps;
     ctx->cap_h = second_height(domains, n_domains, kMaxTileH);
+    ctx->collide_lds = collide_lds(domains, n_domains, ctx->storage);
     ctx->fuse_ok = ctx->lattice == LBM_D2Q9 && !ctx->elbm && ctx->median_pass && !ctx->ens_pass;
 
     auto bail = [&](int code) {
@@ -1714,6 +1744,7 @@ int lbm_step_static(const lbm_domain_desc* domain, int32_t storage, void* stream
     a.block_w = block.w;
     a.block_h = block.h;
     if (d1) a.reach = reach1d(domain, 1);
+    a.collide_lds = collide_lds(domain, 1, storage);
     bool odd = n_steps % 2 != 0;
     for (int64_t t = 0; t < n_steps && e == hipSuccess; a.parity = 1 - a.parity, odd = !odd) {
         // (the last step alone: the other buffer then holds the state before it)

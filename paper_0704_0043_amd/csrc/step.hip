@@ -1773,11 +1773,12 @@ static hipError_t dispatch(int qe, int ds, int bc, F f)
     return e == hipSuccess ? hipGetLastError() : e;
 }
 // a launch of KER<storage, f*, Delta S form, boundary, ...>
-#define LBM_LAUNCH(GRID, BLOCK, KER, ...)                                                                \
+#define LBM_LAUNCH_LDS(GRID, BLOCK, LDS, KER, ...)                                                       \
     [&](auto q, auto d, auto b) {                                                                        \
         constexpr int QE = decltype(q)::value, DS = decltype(d)::value, BC = decltype(b)::value;         \
-        hipLaunchKernelGGL((KER<StT, QE, DS, BC, ##__VA_ARGS__>), dim3(GRID), dim3(BLOCK), 0, s, a);      \
+        hipLaunchKernelGGL((KER<StT, QE, DS, BC, ##__VA_ARGS__>), dim3(GRID), dim3(BLOCK), LDS, s, a);    \
     }
+#define LBM_LAUNCH(GRID, BLOCK, KER, ...) LBM_LAUNCH_LDS(GRID, BLOCK, 0, KER, ##__VA_ARGS__)
 
 hipError_t LBM_CAT(launch_step2d, LBM_SUFFIX)(int qe, int ds, int bc, const StepArgs& a, int kernel,
                                              hipStream_t s)
@@ -1785,7 +1786,7 @@ hipError_t LBM_CAT(launch_step2d, LBM_SUFFIX)(int qe, int ds, int bc, const Step
     const bool stats = a.flags & kFlagStats;
     if (kernel == 0)
         return stats ? dispatch<0, 1>(qe, ds, bc, LBM_LAUNCH(a.nblocks, kThreads, k_collide2d, false, true))
-                     : dispatch<0, 1>(qe, ds, bc, LBM_LAUNCH(a.nblocks, kThreads, k_collide2d, false, false));
+                     : dispatch<0, 1>(qe, ds, bc, LBM_LAUNCH_LDS(a.nblocks, kThreads, a.collide_lds, k_collide2d, false, false));
     if (kernel == 2)
         return stats ? dispatch<0, 1, true>(qe, ds, bc, LBM_LAUNCH(a.nblocks, kThreads, k_collide2d, true, true))
                      : dispatch<0, 1, true>(qe, ds, bc, LBM_LAUNCH(a.nblocks, kThreads, k_collide2d, true, false));
