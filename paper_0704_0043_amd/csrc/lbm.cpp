@@ -106,7 +106,9 @@ int second_height(const lbm_domain_desc* doms, int32_t nd, int th)
 // lines and eight are better (3600 x 3500: 157.4 us against 159.8), as with
 // 16-bit storage, whose loads carry half the bytes (6000 x 5000: 213 against
 // 252), and where the last-level cache holds the domains (1024 x 1024: 20.7
-// against 21.6).  The variant with sums needs all the waves it can get.
+// against 21.6).  The variant with sums needs all the waves it can get.  The fused
+// step without sums has registers for four workgroups and likewise runs better
+// with three there (launch_step2d; 4096 x 4096 301 us a step against 282).
 constexpr int kSixPerCu = 26 << 10;
 constexpr long long kLastLevelCache = 256ll << 20;
 int collide_lds(const lbm_domain_desc* doms, int32_t nd, int storage)
@@ -910,7 +912,7 @@ int time_shape(lbm_ctx* ctx, int n, double& ms, unsigned extra_flags = 0)
 // Weight of a step as it stands against one whose second pass walks every tile:
 // in most steps of most runs few tiles have anything to move (4096 x 4096 FP32,
 // 16 or 64 rows: 212 or 209 us as it stands, 269 or 278 with every tile).
-constexpr double kAsItStands = 4.0;
+constexpr double kAsItStands = 8.0;
 
 // fused_alt: the fused form of an adaptive run (its tile height only)
 int autotune(lbm_ctx* ctx, const lbm_run_desc* run, bool fused_alt = false)
@@ -1344,7 +1346,7 @@ int lbm_create(const lbm_domain_desc* domains, int32_t n_domains, const lbm_run_
         const size_t f = h.n * h.q * sizeof(double), mom = h.n * (h.q == 9 ? 3 : 2) * sizeof(double);
         const size_t probe = h.d.probe_x >= 0 ? size_t(ctx->probe_cap) * 2 * sizeof(float) : 0;
         for (size_t b : {f, mom, probe})
-            ctx->host_bytes = std::max(ctx->host_bytes, std::min(b, kHostLimit));
+            if (b <= kHostLimit) ctx->host_bytes = std::max(ctx->host_bytes, b);
     }
     e = hipHostMalloc(reinterpret_cast<void**>(&ctx->host), ctx->host_bytes);
     if (e != hipSuccess) {
