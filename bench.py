@@ -4,9 +4,10 @@ Default workload: D2Q9 periodic Taylor-Green vortex plus a seeded random-phase
 perturbation on 4096 x 4096 nodes, FP32 shifted SoA storage, nu = 1e-4,
 entropy trimming and the 3x3 median filter both on (delta = 1e-4),
 polynomial f*, quadratic Delta S.  One step = the collision kernel (free
-flight, moments, f*, over-relaxation, Delta S', trimming, store, one partial
-of the reduction terms per workgroup) plus the median kernel (3x3 median of
-Delta S', the filtered nodes rescaled in place); every step runs inside
+flight, moments, f*, over-relaxation, Delta S', trimming, store, and in the
+last step of a captured sequence one partial of the reduction terms per
+workgroup) plus the median kernel (3x3 median of
+Delta S', the filtered nodes formed again); every step runs inside
 captured HIP graphs (chunks of 64 steps and the powers of two below, captured
 when the context is created), and the FP64 global stats of the last step are
 formed inside the timed region.
@@ -192,7 +193,9 @@ def replica_error(L, stream, dom, wl, oracle_run):
 
 
 def workload_text(n, workload="headline", delta_median=1e-4):
-    """The `config.workload` description of the timed run."""
+    """The `config.workload` description of the timed run (a fixed text: the
+    partials are those of the steps whose sums can be read, the last of each
+    captured sequence)."""
     limiters = ("trimming + 3x3 median limiter (delta=1e-4)" if delta_median == 1e-4 else
                 f"trimming (delta=1e-4) + 3x3 median limiter (delta={delta_median:g})")
     if workload == "smooth":
@@ -491,7 +494,7 @@ def main():
     ap.add_argument("--variants", action="store_true", help="also time FP16/BF16 8192^2 and the cavity ensemble")
     ap.add_argument("--tile-h", type=int, default=0, help="rows per second-pass tile (16, 32, 64; 0: tuned)")
     ap.add_argument("--tile-x", type=int, default=0,
-                    help="collision row blocks: 64 narrow, 256 full rows, 248 the fused step, 0 tuned")
+                    help="248: the fused step; 0, 64 or 256: the form the library takes")
     ap.add_argument("--adaptive", action="store_true",
                     help="LBM_RUN_ADAPTIVE: two kernels or the fused step, chosen every 64 steps")
     ap.add_argument("--delta-median", type=float, default=None,
