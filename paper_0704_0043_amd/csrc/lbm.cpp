@@ -400,7 +400,8 @@ int validate(const lbm_domain_desc* doms, int32_t nd, const lbm_run_desc* run)
         if (d.limiter < 0 || d.limiter > 127) return fail(nullptr, LBM_EINVAL, where + "bad limiter mask");
         // a second pass rebuilds the applied factor from Delta S' alone, which
         // the positivity factor is not; with the exact Delta S a node it acts
-        // on has Delta S' = +inf, and every second-pass limiter sends it to f*
+        // on has Delta S' = +inf, and a second-pass limiter that moves it sends it to
+        // f* (the pass that forms every node takes the positivity factor anew)
         if (d.lattice == LBM_D2Q9 && (d.limiter & LBM_LIM_POSITIVITY) &&
             (d.limiter & (LBM_LIM_MEDIAN | kLimEns)) && d.ds_form != LBM_DS_EXACT)
             return fail(nullptr, LBM_EINVAL,

@@ -1020,7 +1020,14 @@ __global__ void __launch_bounds__(kThreads) k_form2d(StepArgs a)
             acc.trim = h.trim;
             if (record && h.bits) to_global<unsigned char>(D.mask)[n] |= (unsigned char)h.bits;
             SiteState<kD2Q9, A> S;
-            const A phi = form_state<T, QE, DS>(D, g, dc, tgt, fac, true, S, acc.lim);
+            A phi = form_state<T, QE, DS>(D, g, dc, tgt, fac, true, S, acc.lim);
+            // Delta S' is infinite where the positivity rule acts, and none of the
+            // factors above need do so there: E(Delta S') is 0 where no node has a
+            // positive finite value, and a median may be infinite too
+            // (with the quadratic form the rule and these factors cannot be combined)
+            if constexpr (DS != kQuad) {
+                if (D.limiter & kLimPos) phi = fmin(phi, positivity_phi<kD2Q9>(S, A(D.shift)));
+            }
             store_limited<T>(dst, plane, 0, unsigned(sizeof(T)) * n, S, phi, S.c);
         }
     }

@@ -296,3 +296,39 @@ def test_static_buffers_after_several_steps(lattice, nx, ny, n):
 
     say(f"[static] lattice {lattice} {nx}x{ny} n {n}")
     assert torch.equal(after(n)[1], after(n - 1)[0])
+
+
+W9 = np.array([4 / 9] + [1 / 9] * 4 + [1 / 36] * 4)
+
+
+# a node the positivity rule acts on has Delta S' = +inf; where every node has,
+# E(Delta S') is 0 and the median infinite, so the rule's factor is the only one
+@pytest.mark.parametrize("limiter,kw", [(SMOOTH, dict(ens_k=0.5, delta_ens=0.01)),
+                                        (RATIONAL, dict(ens_c=2.0, ens_k=1.0))])
+@pytest.mark.parametrize("median", [0, 2])
+@pytest.mark.parametrize("storage", [0, 1])
+def test_dense_form_pass_keeps_the_positivity_rule(limiter, kw, median, storage):
+    L = lbm()
+    f0 = np.empty((9, 8, 8))
+    f0[:] = W9[:, None, None]
+    f0[[1, 3]] *= 3.5
+    d = L.Domain(lattice=D2Q9, nx=8, ny=8, beta=0.99, qe=0, ds_form=0, limiter=64 | limiter | median,
+                 delta_median=1e-5, **kw)
+    pr = Pair(d, f0, steps=1, storage=storage)
+    assert_masks_equal(pr)
+    assert pr.stats["n_positivity"] == pr.so["n_positivity"] == 64
+    assert pr.stats["n_ensemble"] == pr.so["n_ensemble"] == 0
+    # FP32: the rounding of the populations' excess over w_i, a few units of 6e-8 each
+    close(pr.f, pr.fo, 1e-13 if storage == 0 else 2e-6)
+    # one such node in an FP32 field at rest, whose other Delta S' are exactly 0:
+    # the positivity rule alone
+    if storage == 1 and not median:
+        f1 = np.empty((9, 8, 8))
+        f1[:] = W9[:, None, None]
+        f1[[1, 3], 3, 5] *= 3.5
+        lone = Pair(d, f1, steps=1, storage=1)
+        d.limiter = 64
+        alone = Pair(d, f1, steps=1, storage=1)
+        assert lone.stats["n_positivity"] == 1 and lone.stats["mean_dS"] == 0.0
+        assert np.array_equal(lone.mask, alone.mask)
+        close(lone.f, alone.fo, 2e-6)
