@@ -371,7 +371,7 @@ LBM_API void lbm_destroy(lbm_ctx* ctx);
  * Asynchronous (stream ordered).  Errors: LBM_EINVAL (descriptor, buffers,
  * n_steps < 0); LBM_ENOMEM when the domain needs more scratch than
  * LBM_STATIC_SCRATCH_BYTES (D2Q9 in FP32 with the median filter needs about
- * 4.7 bytes per node: up to some 14 million nodes; FP64 about 8.7); these
+ * 4.6 bytes per node: up to some 14 million nodes; FP64 about 8.6); these
  * are detected before anything is launched; LBM_EDEVICE for a HIP error.
  * The message is in lbm_last_error(NULL). */
 LBM_API int lbm_step_static(const lbm_domain_desc* domain, int32_t storage, void* stream, void* f0, void* f1,

@@ -37,20 +37,20 @@ hipError_t launch_step1d(int storage, int qe, int ds, int bc, const StepArgs& a,
 }
 
 // one workgroup per domain: the sums of the step just run
-__global__ void __launch_bounds__(kThreads) k_finalize(StepArgs a, int parity_done, long long step)
+__global__ void __launch_bounds__(kThreads) k_finalize(StepArgs a, long long step)
 {
     __shared__ double red[kThreads];
-    reduce_domain(a, parity_done, a.dom[blockIdx.x], a.median_pass, step, red);
+    reduce_domain(a, a.dom[blockIdx.x], a.median_pass, step, red);
 }
 
 // D2Q9: the set-0 partial of each group is the sum of the collision partials
 // of its workgroups, in order.
-__global__ void __launch_bounds__(kThreads) k_group_sums(StepArgs a, int parity_done)
+__global__ void __launch_bounds__(kThreads) k_group_sums(StepArgs a)
 {
     __shared__ double buf[kGroupParts * kNStat + 8 * kNStat];
     const Group t = a.groups[blockIdx.x];
     const long long p0 = (long long)a.dom[t.domain].part_first + t.n0 / kThreads;
-    sum_partials(a.partials + ((long long)parity_done * 2 * a.pstride + blockIdx.x) * kNStat, a.blockpart + p0 * kNStat,
+    sum_partials(a.partials + (long long)blockIdx.x * kNStat, a.blockpart + p0 * kNStat,
                  (t.n1 - t.n0 + kThreads - 1) / kThreads, buf);
 }
 
@@ -58,12 +58,12 @@ __global__ void __launch_bounds__(kThreads) k_group_sums(StepArgs a, int parity_
 // domain (Sec. 3.3, 3.4): the collision partials (set 0; for D2Q9 summed per
 // group beforehand) are reduced exactly as the stats are, so E equals the
 // reported mean_dS bit for bit.
-__global__ void __launch_bounds__(kThreads) k_ens_prepare(StepArgs a, int parity)
+__global__ void __launch_bounds__(kThreads) k_ens_prepare(StepArgs a)
 {
     __shared__ double red[kThreads];
     const DomainDev& D = a.dom[blockIdx.x];
     if (!(D.limiter & kLimEns)) return;
-    reduce_domain(a, parity, D, false, a.counter[parity], red);
+    reduce_domain(a, D, false, a.counter[a.parity], red);
     __syncthreads();
     if (threadIdx.x != 0) return;
     const double nf = D.stats[kSFluid];
@@ -492,33 +492,33 @@ hipError_t launch_budget(int storage, int bc, const StepArgs& a, hipStream_t s)
 hipError_t launch_ens_prepare(const StepArgs& a, hipStream_t s)
 {
     if (a.nblocks > 0) {
-        hipLaunchKernelGGL(k_group_sums, dim3(a.ngroups), dim3(kThreads), 0, s, a, a.parity);
+        hipLaunchKernelGGL(k_group_sums, dim3(a.ngroups), dim3(kThreads), 0, s, a);
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
-    hipLaunchKernelGGL(k_ens_prepare, dim3(a.ndomains), dim3(kThreads), 0, s, a, a.parity);
+    hipLaunchKernelGGL(k_ens_prepare, dim3(a.ndomains), dim3(kThreads), 0, s, a);
     return hipGetLastError();
 }
 
-hipError_t launch_finalize(const StepArgs& a, int parity_done, long long steps_done, hipStream_t s)
+hipError_t launch_finalize(const StepArgs& a, long long steps_done, hipStream_t s)
 {
     if (a.nblocks > 0 && !a.fused) {
-        hipLaunchKernelGGL(k_group_sums, dim3(a.ngroups), dim3(kThreads), 0, s, a, parity_done);
+        hipLaunchKernelGGL(k_group_sums, dim3(a.ngroups), dim3(kThreads), 0, s, a);
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
-    hipLaunchKernelGGL(k_finalize, dim3(a.ndomains), dim3(kThreads), 0, s, a, parity_done, steps_done);
+    hipLaunchKernelGGL(k_finalize, dim3(a.ndomains), dim3(kThreads), 0, s, a, steps_done);
     return hipGetLastError();
 }
 
-// The number of nodes the median filter moved in the step that read buffer
-// parity_done: the sum of the second-pass partials (set 1) of every tile,
+// The number of nodes the median filter moved in the step just run:
+// the sum of the second-pass partials (set 1) of every tile,
 // which the two kernels and the fused step both write.  One workgroup, a
 // fixed order of the sums.
-__global__ void __launch_bounds__(kThreads) k_filtered_count(StepArgs a, int parity_done, double* out)
+__global__ void __launch_bounds__(kThreads) k_filtered_count(StepArgs a, double* out)
 {
     __shared__ double red[kThreads];
-    const double* part = a.partials + ((long long)parity_done * 2 + 1) * a.pstride * kNStat;
+    const double* part = a.partials + (long long)a.pstride * kNStat;
     double s = 0.0;
     for (int t = int(threadIdx.x); t < a.ntiles; t += kThreads) s += part[(long long)t * kNStat + kSFilt];
     red[threadIdx.x] = s;
@@ -530,9 +530,9 @@ __global__ void __launch_bounds__(kThreads) k_filtered_count(StepArgs a, int par
     if (threadIdx.x == 0) out[0] = red[0];
 }
 
-hipError_t launch_filtered_count(const StepArgs& a, int parity_done, double* out, hipStream_t s)
+hipError_t launch_filtered_count(const StepArgs& a, double* out, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_filtered_count, dim3(1), dim3(kThreads), 0, s, a, parity_done, out);
+    hipLaunchKernelGGL(k_filtered_count, dim3(1), dim3(kThreads), 0, s, a, out);
     return hipGetLastError();
 }
 

@@ -570,7 +570,7 @@ void plan(std::vector<DomainHost>& dh, const lbm_domain_desc* doms, int32_t nd, 
     L.off_groups = off;
     off = align_up(off + L.ngroups * sizeof(Group), kAlign);
     L.off_partials = off;
-    off = align_up(off + size_t(4) * std::max(L.max_tiles, L.ngroups) * kNStat * sizeof(double), kAlign);
+    off = align_up(off + size_t(2) * std::max(L.max_tiles, L.ngroups) * kNStat * sizeof(double), kAlign);
     L.off_blocks = off;
     if (nd > 1) off = align_up(off + size_t(L.nblocks) * sizeof(Block), kAlign);
     L.off_blockpart = off;
@@ -1056,7 +1056,7 @@ int adapt(lbm_ctx* ctx)
     const int slot = int(ctx->adapt_points % 2);
     if (ctx->steps_done > 0) {
         const StepArgs a = step_args(ctx, 0);
-        hipError_t e = launch_filtered_count(a, int((ctx->steps_done - 1) % 2), ctx->d_adapt(), ctx->stream);
+        hipError_t e = launch_filtered_count(a, ctx->d_adapt(), ctx->stream);
         if (e == hipSuccess)
             e = hipMemcpyAsync(ctx->adapt_host + slot, ctx->d_adapt(), sizeof(double), hipMemcpyDeviceToHost,
                                ctx->stream);
@@ -1087,7 +1087,7 @@ int finalize_stats(lbm_ctx* ctx)
 {
     if (ctx->steps_done == 0 || ctx->finalized_for == ctx->steps_done) return LBM_OK;
     const StepArgs a = step_args(ctx, 0);
-    hipError_t e = launch_finalize(a, int((ctx->steps_done - 1) % 2), ctx->steps_done, ctx->stream);
+    hipError_t e = launch_finalize(a, ctx->steps_done, ctx->stream);
     if (e != hipSuccess) return fail(ctx, LBM_EDEVICE, std::string("finalize: ") + hipGetErrorString(e));
     ctx->finalized_for = ctx->steps_done;
     return LBM_OK;
@@ -1201,7 +1201,7 @@ void plan_static(const lbm_domain_desc& d, int storage, int th, const BlockForm&
     L.off_groups = off;
     off = align_up(off + size_t(L.ngroups) * sizeof(Group), kAlign);
     L.off_partials = off;
-    off = align_up(off + size_t(4) * std::max(L.ntiles, L.ngroups) * kNStat * sizeof(double), kAlign);
+    off = align_up(off + size_t(2) * std::max(L.ntiles, L.ngroups) * kNStat * sizeof(double), kAlign);
     L.off_blockpart = off;
     off = align_up(off + size_t(L.nblocks) * kNStat * sizeof(double), kAlign);
     L.off_above = off;
@@ -1757,7 +1757,7 @@ int lbm_step_static(const lbm_domain_desc* domain, int32_t storage, void* stream
         t += a.steps;
     }
     if (e == hipSuccess && stats) {
-        e = launch_finalize(a, int((n_steps - 1) % 2), n_steps, s);
+        e = launch_finalize(a, n_steps, s);
         if (e == hipSuccess) e = launch_static_stats(dom, h.shift * double(h.n), stats, s);
     }
     if (e != hipSuccess) return fail(nullptr, LBM_EDEVICE, std::string("lbm_step_static: ") + hipGetErrorString(e));

@@ -247,8 +247,9 @@ struct StepArgs {
     int ndomains;
     int parity;             // read buf[parity], write buf[1 - parity]
     unsigned flags;
-    double* partials;       // [2 parities][2 sets][pstride][kNStat]: FP64 stats, set 0 (collision)
-                            // per group, set 1 (second pass) per tile
+    double* partials;       // [2 sets][pstride][kNStat]: FP64 stats of a step, set 0 (collision)
+                            // per group, set 1 (second pass) per tile; what reads them is queued
+                            // before the next step
     const Group* groups;    // the collision-partial groups: fixed, so that the set-0 sums (and
                             // E(Delta S')) do not depend on the tile height
     int ngroups;
@@ -295,9 +296,9 @@ hipError_t launch_step1d(int storage, int qe, int ds, int bc, const StepArgs& a,
 hipError_t launch_ens_prepare(const StepArgs& a, hipStream_t s);
 // the budget threshold of the step just run (after launch_ens_prepare)
 hipError_t launch_budget(int storage, int bc, const StepArgs& a, hipStream_t s);
-hipError_t launch_finalize(const StepArgs& a, int parity_done, long long steps_done, hipStream_t s);
-// nodes moved by the median filter in the step that read buffer parity_done -> out[0]
-hipError_t launch_filtered_count(const StepArgs& a, int parity_done, double* out, hipStream_t s);
+hipError_t launch_finalize(const StepArgs& a, long long steps_done, hipStream_t s);
+// nodes moved by the median filter in the step just run -> out[0]
+hipError_t launch_filtered_count(const StepArgs& a, double* out, hipStream_t s);
 hipError_t launch_init_f(int lattice, int qe, const double* rho, const double* u, double* f, int nx, int ny,
                          hipStream_t s);
 hipError_t launch_scatter(int storage, int lattice, int bc, const double* f, void* buf, long long plane, int nx,

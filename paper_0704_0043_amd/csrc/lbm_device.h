@@ -1170,17 +1170,16 @@ __device__ __forceinline__ A exact_homothety(const SiteState<LAT, A>& o, A shift
 // depends on the slot counts only, and where set 1 holds zeros (mass, Delta S')
 // on the groups alone.
 constexpr int kSlices = kThreads / kNStat;
-__device__ inline void reduce_domain(const StepArgs& a, int parity, const DomainDev& D, bool second, long long step,
+__device__ inline void reduce_domain(const StepArgs& a, const DomainDev& D, bool second, long long step,
                                      double* lds /* [kThreads] */)
 {
     const int tid = int(threadIdx.x), k = tid % kNStat, j = tid / kNStat;
-    const double* part = a.partials + (long long)parity * 2 * a.pstride * kNStat;
     // the fused step writes set 1 only
     const int set0 = a.fused ? 1 : 0, nsets = (second && !D.dense) || a.fused ? 2 : 1;
     double v = 0.0;
     for (int set = set0; set < nsets; ++set) {
         const int first = set ? D.tile_first : D.group_first, count = set ? D.tile_count : D.group_count;
-        const double* p = part + ((long long)set * a.pstride + first) * kNStat + k;
+        const double* p = a.partials + ((long long)set * a.pstride + first) * kNStat + k;
 #pragma unroll 4
         for (int t = j; t < count; t += kSlices) {
             const double x = p[(long long)t * kNStat];

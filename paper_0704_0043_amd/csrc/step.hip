@@ -77,7 +77,7 @@ __device__ inline int tile_of_block(const StepArgs& a, int first)
 // kernel writes it directly), set 1 = median pass
 __device__ inline double* partial_slot(const StepArgs& a, int set, int tile)
 {
-    return a.partials + (((long long)a.parity * 2 + set) * a.pstride + tile) * kNStat;
+    return a.partials + ((long long)set * a.pstride + tile) * kNStat;
 }
 
 // The node of a thread of the collision kernel and of k_form2d: 64 consecutive

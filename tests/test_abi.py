@@ -186,3 +186,19 @@ def test_static_entry_refuses_domains_beyond_its_scratch(L):
     # safe to call without a GPU, and it is accepted
     L.lbm_step_static(L.Domain(nx=4096, ny=4096, limiter=L.LBM_LIM_TRIM), L.LBM_F32, F0, F1, 0)
     assert L.lib().lbm_step_static(None, 1, None, None, None, 1, None) == L.LBM_EINVAL
+
+
+# sizes that have been taken ever since the entry exists: the largest tubes
+# without and with the arrays of an ensemble limiter, the widest and the
+# narrowest grids (n_steps = 0 returns before any device call)
+@pytest.mark.parametrize("storage,dom", [
+    (0, dict(lattice=1, nx=31_333_440, ny=1, limiter=0)),
+    (1, dict(lattice=1, nx=31_333_440, ny=1, limiter=1)),
+    (2, dict(lattice=1, nx=31_333_440, ny=1, limiter=2)),
+    (0, dict(lattice=1, nx=3_699_040, ny=1, limiter=8, ens_k=0.5, delta_ens=0.1)),
+    (1, dict(lattice=1, nx=6_612_096, ny=1, limiter=32, ens_c=0.1)),
+    (1, dict(nx=64, ny=168_400, limiter=2)),
+    (0, dict(nx=64, ny=102_531, limiter=2)),
+])
+def test_static_entry_takes_the_sizes_it_took(L, storage, dom):
+    L.lbm_step_static(L.Domain(ds_form=L.LBM_DS_QUADRATIC, **dom), storage, F0, F1, 0)
