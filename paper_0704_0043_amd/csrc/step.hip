@@ -477,6 +477,15 @@ __global__ void __launch_bounds__(kThreads, DS == kExact && !STATS && !ELBM ? 4 
 constexpr int kMedChunk = 4;
 constexpr int kListRows = 8;                      // rows decided before their moved nodes are moved
 constexpr int kListCap = kListRows * kWave;
+// Beyond the last-level cache (whole_rows) a store of part of a 64-byte piece
+// makes memory read the piece first, and the scattered stores of many moved nodes
+// cost more than the nodes between them.  There a wave's row with at least
+// kRowMoves moved nodes lists every fluid node of a kPiece-column piece that has a
+// moved one; the others come out as the collision kernel stored them, bit for
+// bit (4096 x 4096 FP32, 16-row tiles: 10 % of the nodes moved 545 -> 479 us a
+// step, 6 %, in runs along filaments, 299 -> 305; 2048 x 2048 FP64, 43 % moved
+// 327 -> 267.  Within the cache it only adds nodes: 2000 x 2000 FP32 85 -> 91.)
+constexpr int kRowMoves = 8, kPiece = 16;
 
 // the filter's threshold and decision for a node with Delta S' = dc whose
 // stencil median is med (FLOOR or GATE reading of the tolerance delta)
@@ -875,7 +884,19 @@ __device__ __forceinline__ void second_pass2d(const StepArgs& a)
                     moves = fmin(fac, tgt < A(__builtin_huge_val()) ? sqrt_(tgt * rcp(dc)) : A(1)) < pt;
                     if constexpr (DS == kExactHom) moves = moves || (D.homothety && isfinite(dc) && pt > A(0));
                 }
-                const unsigned long long b = __ballot(moves);
+                unsigned long long b = __ballot(moves);
+                // (ELBM, the exact homothety and the positivity rule would need a root
+                // or a factor that the list does not hold)
+                if constexpr (!ELBM && DS != kExactHom) {
+                    if (a.whole_rows && int(__popcll(b)) >= kRowMoves && !(D.limiter & kLimPos)) {
+                        if (!moves && (b >> (lane & -kPiece) & ((1u << kPiece) - 1))) {
+                            tgt = A(__builtin_huge_val());
+                            fac = A(1);
+                            moves = fluid;
+                        }
+                        b = __ballot(moves);
+                    }
+                }
                 if (moves) {
                     const int at = listed + int(__builtin_amdgcn_mbcnt_hi(unsigned(b >> 32),
                                                                         __builtin_amdgcn_mbcnt_lo(unsigned(b), 0)));

@@ -332,3 +332,26 @@ def test_dense_form_pass_keeps_the_positivity_rule(limiter, kw, median, storage)
         assert lone.stats["n_positivity"] == 1 and lone.stats["mean_dS"] == 0.0
         assert np.array_equal(lone.mask, alone.mask)
         close(lone.f, alone.fo, 2e-6)
+
+
+# beside a domain beyond the last-level cache the second pass writes whole
+# pieces of the rows in which many nodes move: the same states
+@pytest.mark.parametrize("nx,ny", [(15, 9), (63, 5), (65, 17), (257, 33)])
+@pytest.mark.parametrize("storage,ds", [(0, 0), (1, 1)])
+@pytest.mark.parametrize("limiter,kw", [(3, dict(delta_median=0.0)), (7, dict(ens_c=1.0, delta_median=1e-5)),
+                                        (3, dict(delta_median=1e-5, top_k=40, trim_mode=1))])
+def test_whole_pieces_of_rows(nx, ny, storage, ds, limiter, kw):
+    L = lbm()
+    f0 = rough(9, nx, ny, seed=nx + ny)
+    d = L.Domain(lattice=D2Q9, nx=nx, ny=ny, beta=0.97, qe=0, ds_form=ds, limiter=limiter, delta_trim=1e-5, **kw)
+    far = L.Domain(lattice=D2Q9, nx=2600, ny=(1450, 2900)[storage], beta=0.97, qe=0, ds_form=ds, limiter=1)
+    flags = L.LBM_RUN_NO_TUNE | (L.LBM_RUN_ADAPTIVE if limiter == 3 and not d.top_k else 0)    # begins with two kernels
+    say(f"[pieces] {nx}x{ny} limiter {limiter} storage {storage}")
+    alone = run([d], [f0], [2], storage, flags=flags)[0]
+    with_far = run([d, far], [f0, None], [2], storage, flags=flags)[0]
+    assert np.array_equal(alone[0], with_far[0])
+    for key in ("n_trimmed", "n_filtered", "n_ensemble", "sum_dS_post", "max_dS"):
+        assert alone[1][key] == with_far[1][key], key
+    assert alone[1]["n_filtered"] + alone[1]["n_ensemble"] + alone[1]["n_trimmed"] > nx * ny // 8
+    # (the nodes are listed, and their terms added, in another order)
+    assert with_far[1]["limiter_production"] == pytest.approx(alone[1]["limiter_production"], rel=1e-12)
