@@ -1406,10 +1406,14 @@ __global__ void __launch_bounds__(kBlockMax) k_block2d(StepArgs a)
     const bool owned = inside && X >= t.x0 && X < t.x1 && Y >= t.y0 && Y < t.y1;
     const int cls = inside ? node_class<BC>(x, y, nx, ny) : int(kNodeNone);
     const unsigned node = unsigned(y) * unsigned(nx) + unsigned(x);
-    // neighbours in the workgroup (at its ends a node stands in for the
-    // missing one: nothing that is stored depends on it)
-    const int dl = lx > 0 ? -1 : 0, dr = lx < bw - 1 ? 1 : 0;
-    const int db = ly > 0 ? -bw : 0, dt = ly < bh - 1 ? bw : 0;
+    // neighbours in the workgroup (at the ends of its nodes a node stands in for
+    // the missing one: nothing that is stored depends on it.  What lies past a
+    // short tile in LDS does not: nobody writes it, and the logarithms and roots
+    // of what was left there held whole workgroups up, 40 x 40 periodic nodes
+    // with the exact homothety in FP64 20 us a step against 4)
+    const int lx1 = t.x1 - t.x0 + 2 * halo - 1, ly1 = t.y1 - t.y0 + 2 * halo - 1;
+    const int dl = lx > 0 ? -1 : 0, dr = lx < lx1 ? 1 : 0;
+    const int db = ly > 0 ? -bw : 0, dt = ly < ly1 ? bw : 0;
     const int at = ly < bh ? pos : 0;
 
     AccT<A> acc;
@@ -1592,13 +1596,14 @@ __global__ void __launch_bounds__(k1DMaxThreads) k_step1d(StepArgs a)
     const int halo = a.reach * a.steps;
     const int pos = tid < k1DWidth ? tid + halo : (tid < k1DWidth + halo ? tid - k1DWidth : tid);
     const int xr = t.x0 - halo + pos;
-    const int last_pos = k1DWidth + 2 * halo - 1;
-    const bool used = pos <= last_pos && xr < t.x1 + halo;
+    const int last_pos = t.x1 - t.x0 + 2 * halo - 1;
+    const bool used = pos <= last_pos;
     const bool inside = used && (BC == kPeriodic || (xr >= 0 && xr < nx));
     const int x = BC == kPeriodic ? wrapi(xr, nx) : xr;
     const bool owned = inside && xr >= t.x0 && xr < t.x1;
-    // neighbours in the workgroup (at its ends a site stands in for the
-    // missing one: nothing that is written depends on it)
+    // neighbours in the workgroup (at the ends of its sites a site stands in for
+    // the missing one: nothing that is written depends on it.  Not the LDS past a
+    // short tile, see k_block2d: 64 steps of 800 FP64 ELBM sites took 250 to 720 us)
     const int tl = pos > 0 ? pos - 1 : 0, tr = pos < last_pos ? pos + 1 : last_pos;
 
     Acc acc;
