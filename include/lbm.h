@@ -308,7 +308,7 @@ LBM_API int lbm_probe_trace(lbm_ctx* ctx, int32_t domain, float* uv, int64_t max
  * the next step runs after a choice).  D2Q9: 256 (with tile_x 0 or 64 and a
  * first domain at most 64 / 128 wide: 64 / 128), 256 divided by that,
  * and the rows of a second-pass tile; the fused step: 248, 1
- * and the rows of a fused tile.  D1Q3: 190, 1, 1. */
+ * and the rows of a fused tile.  D1Q3: 188, 1, 1. */
 LBM_API int lbm_tile_config(const lbm_ctx* ctx, int32_t* tile_x, int32_t* tile_y, int32_t* tile_h);
 
 /* sync; profiling aid outside the method.  Advances the state by n_steps

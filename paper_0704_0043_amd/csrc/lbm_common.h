@@ -136,17 +136,18 @@ struct Tile {
 };
 
 // Output sites of one D1Q3 workgroup: with the halo of the longest launch
-// (k1DMaxSteps, reach 1) four whole waves, one per SIMD.  A wave alone is a
+// (k1DMaxSteps, reach 1; half of it, reach 2) four waves, one per SIMD, and
+// with that of a single step three whole ones.  A wave alone is a
 // chain of latencies; a fifth wave shares a SIMD and delays the barrier (254
 // sites on 320 threads: 400 steps of 800 sites 959 us against 914, and of
 // 200000 sites, which then take fewer turns on the CUs, 3207 against 2028).
-constexpr int k1DWidth = 190;
+constexpr int k1DWidth = 188;
 
 // D1Q3 steps of one launch.  A workgroup computes its k1DWidth sites with a
 // halo that each further step eats `reach` sites of on either side (1, with
 // the median filter 2).
 constexpr int k1DMaxSteps = 33;
-constexpr int k1DMaxThreads = 384;
+constexpr int k1DMaxThreads = 320;
 inline int threads1d(int reach, int steps) { return (k1DWidth + 2 * reach * steps + kWave - 1) / kWave * kWave; }
 static_assert(k1DWidth + 4 * k1DMaxSteps <= k1DMaxThreads, "the halo of the longest launch fits");
 

@@ -382,3 +382,20 @@ def test_short_tiles_do_not_compute_what_lds_held():
     quadratic, exact = best(ds_form=1), best(ds_form=0, homothety=1)
     say(f"[short tiles] 64 steps: quadratic {quadratic * 1e6:.0f} us, exact homothety {exact * 1e6:.0f} us")
     assert exact < 4 * quadratic
+
+
+# a workgroup's sites (188), one less and one more, two workgroups and one site
+@pytest.mark.parametrize("nx", [187, 188, 377])
+@pytest.mark.parametrize("limiter,storage", [(1, 0), (3, 1)])
+def test_tube_workgroups(nx, limiter, storage):
+    L = lbm()
+    f0 = rough(3, nx, 1, seed=nx)
+    d = L.Domain(lattice=D1Q3, nx=nx, ny=1, beta=0.98, qe=0, ds_form=0, limiter=limiter, bc=TUBE, delta_trim=1e-3,
+                 delta_median=1e-5, probe=(nx // 2, 0))
+    say(f"[tube workgroups] nx {nx} limiter {limiter} storage {storage}")
+    steps = [1, 2, 33, 34, 67]
+    assert_same_runs(run([d], [f0], steps, storage), run([d], [f0], steps, storage, flags=L.LBM_RUN_NO_GRAPH))
+    if storage == 0:
+        d.probe = None
+        pr = Pair(d, f0, steps=4)
+        close(pr.f, pr.fo, 1e-12)
