@@ -1180,10 +1180,22 @@ __device__ inline void reduce_domain(const StepArgs& a, const DomainDev& D, bool
     for (int set = set0; set < nsets; ++set) {
         const int first = set ? D.tile_first : D.group_first, count = set ? D.tile_count : D.group_count;
         const double* p = a.partials + ((long long)set * a.pstride + first) * kNStat + k;
-#pragma unroll 4
-        for (int t = j; t < count; t += kSlices) {
-            const double x = p[(long long)t * kNStat];
-            v = k == kSMax ? fmax(v, x) : v + x;
+        // sixteen slots in flight: a chain of single loads is what a tube of many
+        // workgroups waits for (4 million FP32 sites with the smooth factor 272 us a step
+        // with four, 217 with sixteen; past the end a slot counts as 0)
+        constexpr int kAhead = 16;
+        for (int t0 = j; t0 < count; t0 += kAhead * kSlices) {
+            double x[kAhead];
+#pragma unroll
+            for (int u = 0; u < kAhead; ++u) {
+                const int t = t0 + u * kSlices;
+                x[u] = p[(long long)(t < count ? t : count - 1) * kNStat];
+            }
+#pragma unroll
+            for (int u = 0; u < kAhead; ++u) {
+                const double y = t0 + u * kSlices < count ? x[u] : 0.0;
+                v = k == kSMax ? fmax(v, y) : v + y;
+            }
         }
     }
     lds[tid] = v;
