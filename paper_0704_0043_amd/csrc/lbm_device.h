@@ -1008,20 +1008,20 @@ __device__ inline void sum_partials(double* out, const double* rp, int rn, doubl
 }
 
 // Partial of a workgroup whose threads hold at most one node each: the sums
-// (FP32 for reduced storage, FP64 for FP64 storage) by a fixed DPP scan in each
-// wave (the limiter and entropy sums only in waves that hold one), the 0/1
+// (FP32 for reduced storage, FP64 for FP64 storage; the limiter's in type SL) by a
+// fixed DPP scan in each wave (the limiter and entropy sums only in waves that hold one), the 0/1
 // counts by ballots; then the waves combined in FP64 in order.
-template <class S>
-__device__ inline void node_partial(const AccT<S>& acc, double* out, double* lds /* [waves * kNStat] */)
+template <class S, class SL>
+__device__ inline void node_partial(const AccT<S, SL>& acc, double* out, double* lds /* [waves * kNStat] */)
 {
-    S v[8] = {acc.mass, acc.jx, acc.jy, acc.dpre, acc.dpost, acc.maxd, acc.lim, acc.ent};
+    S v[8] = {acc.mass, acc.jx, acc.jy, acc.dpre, acc.dpost, acc.maxd, S(0), acc.ent};
 #pragma unroll
     for (int k = 0; k < 8; ++k) {
-        if (k == kSLim || k == kSEnt) {
-            if (!__ballot(v[k] != S(0))) continue;     // uniform: the wave holds none
-        }
+        if (k == kSLim || (k == kSEnt && !__ballot(v[k] != S(0)))) continue;     // uniform: the wave holds none
         v[k] = k == kSMax ? wave_reduce<true>(v[k]) : wave_reduce<false>(v[k]);
     }
+    SL lim = acc.lim;
+    if (__ballot(lim != SL(0))) lim = wave_reduce<false>(lim);
     const int tid = threadIdx.x;
     const int wave = tid >> 6, lane = tid & 63;
     // counts of a wave fit 32 bits
@@ -1031,7 +1031,7 @@ __device__ inline void node_partial(const AccT<S>& acc, double* out, double* lds
                            0.0, count(acc.ens != 0), count(acc.pos != 0)};
     if (lane == 63) {
 #pragma unroll
-        for (int k = 0; k < 8; ++k) lds[wave * kNStat + k] = double(v[k]);
+        for (int k = 0; k < 8; ++k) lds[wave * kNStat + k] = k == kSLim ? double(lim) : double(v[k]);
 #pragma unroll
         for (int k = 0; k < 8; ++k) lds[wave * kNStat + 8 + k] = cnt[k];
     }

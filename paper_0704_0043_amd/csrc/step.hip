@@ -1416,7 +1416,7 @@ __global__ void __launch_bounds__(kBlockMax) k_block2d(StepArgs a)
     const int db = ly > 0 ? -bw : 0, dt = ly < ly1 ? bw : 0;
     const int at = ly < bh ? pos : 0;
 
-    AccT<A> acc;
+    AccT<A, double> acc;      // (the second pass, whose terms these are too, adds them in FP64)
     A g[Q];
     if (inside) gather_at<BC>(src, plane, nx, ny, Node{node, x, y, true, false}, g);
     for (int n = 0; n < steps; ++n) {

@@ -399,3 +399,16 @@ def test_tube_workgroups(nx, limiter, storage):
         d.probe = None
         pr = Pair(d, f0, steps=4)
         close(pr.f, pr.fo, 1e-12)
+
+
+@pytest.mark.parametrize("storage", [1, 2])
+def test_limiter_production_of_tiles_in_fp64(storage):
+    """The nodes' terms are FP32, their sum is FP64 in every form of the step."""
+    L = lbm()
+    f0 = rough(9, 100, 90, seed=3)
+    d = L.Domain(lattice=D2Q9, nx=100, ny=90, beta=0.97, qe=0, ds_form=1, limiter=3, delta_trim=1e-4,
+                 delta_median=1e-5)
+    tiles = run([d], [f0], [1], storage)[0][1]
+    walk = run([d], [f0], [1], storage, tile_x=248, flags=L.LBM_RUN_NO_TUNE)[0][1]
+    assert tiles["n_filtered"] == walk["n_filtered"] > 0
+    assert tiles["limiter_production"] == pytest.approx(walk["limiter_production"], rel=1e-13)
