@@ -263,9 +263,6 @@ __device__ inline void sums_above(double (&v)[N], const double (&start)[N], doub
 {
     const int lane = int(threadIdx.x) & (kWave - 1), wave = int(threadIdx.x) / kWave;
     constexpr int nw = kThreads / kWave;
-    double own[N];
-#pragma unroll
-    for (int k = 0; k < N; ++k) own[k] = v[k];
 #pragma unroll
     for (int off = 1; off < kWave; off <<= 1)
 #pragma unroll
@@ -273,6 +270,14 @@ __device__ inline void sums_above(double (&v)[N], const double (&start)[N], doub
             const double o = __shfl_down(v[k], off, kWave);
             if (lane + off < kWave) v[k] += o;
         }
+    // (the next lane's sum: taking the own value off this lane's would lose the
+    // digits of few large values above many small ones)
+    double above[N];
+#pragma unroll
+    for (int k = 0; k < N; ++k) {
+        const double o = __shfl_down(v[k], 1, kWave);
+        above[k] = lane + 1 < kWave ? o : 0.0;
+    }
     if (lane == 0)
 #pragma unroll
         for (int k = 0; k < N; ++k) lds[wave * N + k] = v[k];
@@ -281,7 +286,7 @@ __device__ inline void sums_above(double (&v)[N], const double (&start)[N], doub
     for (int k = 0; k < N; ++k) {
         double s = start[k];
         for (int w = nw - 1; w > wave; --w) s += lds[w * N + k];
-        v[k] = s + (v[k] - own[k]);
+        v[k] = s + above[k];
     }
 }
 

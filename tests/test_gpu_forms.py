@@ -412,3 +412,36 @@ def test_limiter_production_of_tiles_in_fp64(storage):
     walk = run([d], [f0], [1], storage, tile_x=248, flags=L.LBM_RUN_NO_TUNE)[0][1]
     assert tiles["n_filtered"] == walk["n_filtered"] > 0
     assert tiles["limiter_production"] == pytest.approx(walk["limiter_production"], rel=1e-13)
+
+
+def test_budget_threshold_of_few_values_above_many():
+    """A node of 300 v and two of 100 v above 512 x 512 of v, all but the first in
+    the eight binary exponents that one thread of the selection adds up: the
+    threshold lies between them, at (the sum of the three - budget) / 3, and owes
+    nothing to the digits of the many."""
+    import math
+    L = lbm()
+    n, beta = 512, 0.99
+    c = 2 * beta - 1
+    v = 1.3 * 2.0 ** -23
+    e = np.full((n, n), math.sqrt(v / 18) / c)
+    e[100, 300] *= 10
+    e[301, 17] *= 10.1
+    e[400, 400] *= 17.3
+    f0 = np.empty((9, n, n))
+    f0[:] = W9[:, None, None]
+    f0[[1, 3]] += e
+    f0[[2, 4]] -= e
+    d = L.Domain(lattice=D2Q9, nx=n, ny=n, beta=beta, qe=0, ds_form=1, limiter=BUDGET,
+                 ens_c=350 / (n * n * (1 - c * c)), f_init=f0)
+    with L.lbm_create([d], L.Run(storage=0, flags=L.LBM_RUN_RECORD)) as ctx:
+        L.lbm_step(ctx, 1)
+        ds = L.lbm_limiter_mask(ctx)[1]
+        t = L.lbm_entropy_stats(ctx)["ens_threshold"]
+    budget = d.ens_c * (1 - c * c) * math.fsum(ds.ravel())
+    big = ds[ds > 50 * v]
+    want = (math.fsum(big) - budget) / 3
+    assert big.size == 3 and 10 * v < want < big.min()
+    say(f"[budget] threshold {t!r}, exactly {want!r}: rel {abs(t - want) / want:.1e}")
+    # the sum over all nodes is 20 roundings deep; 7/3 of its relative error is the threshold's
+    assert abs(t - want) <= 2.4 * 20 * 1.2e-16 * want
