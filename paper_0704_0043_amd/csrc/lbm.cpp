@@ -106,9 +106,10 @@ int second_height(const lbm_domain_desc* doms, int32_t nd, int th)
 // lines and eight are better (3600 x 3500: 157.4 us against 159.8), as with
 // 16-bit storage, whose loads carry half the bytes (6000 x 5000: 213 against
 // 252), and where the last-level cache holds the domains (1024 x 1024: 20.7
-// against 21.6).  The variant with sums needs all the waves it can get.  The fused
-// step without sums has registers for four workgroups and likewise runs better
-// with three there (launch_step2d; 4096 x 4096 301 us a step against 282).
+// against 21.6).  The variant with sums needs all the waves it can get.  (Eight or six,
+// us a step: 1984 x 1984 51.0 or 50.7, 5120 x 4096 248.6 or 243.0, 8192 x 3000 302.7
+// or 294.4, 512 x 16000 101.5 or 101.1, 64 x 120000 94.0 or 92.5; of 18 grids one loses,
+// 4160 x 4000 with 212.5 or 214.6.)
 constexpr int kSixPerCu = 26 << 10;
 constexpr long long kLastLevelCache = 256ll << 20;
 int collide_lds(const lbm_domain_desc* doms, int32_t nd, int storage)
@@ -129,6 +130,19 @@ size_t elem_size(int storage)
     case LBM_F32: return 4;
     default: return 2;
     }
+}
+
+// The fused step without sums has registers for four workgroups and likewise runs
+// better with three there (four or three, us a step: 4096 x 4096 300 or 281, 3584 x
+// 3584 216 or 206, 8192 x 3000 432 or 406, 512 x 16000 154 or 148, 256 x 30000 196 or
+// 190, 128 x 60000 143 or 142), but not where a row is one wave and three of a
+// workgroup's four have nothing to do (64 x 120000 157 or 199).
+constexpr int kThreePerCu = 23 << 10;
+int fused_lds(const lbm_domain_desc* doms, int32_t nd, int storage)
+{
+    for (int k = 0; k < nd; ++k)
+        if (doms[k].nx < 2 * kWave) return 0;
+    return collide_lds(doms, nd, storage) ? kThreePerCu : 0;
 }
 
 // The input of a step has left the last-level cache by the time the second pass
@@ -299,7 +313,7 @@ struct lbm_ctx {
     bool fuse_ok = false;       // the fused step applies (D2Q9 LBGK, median filter, no ensemble limiter)
     int reach = 1, most = 1;    // D1Q3: reach of a step; steps of the longest launch
     bool whole_rows = false;    // the second pass completes rows' pieces
-    int collide_lds = 0;        // idle LDS of the collision workgroups
+    int collide_lds = 0, fused_lds = 0;   // idle LDS of the workgroups of the collision and of the fused step
     BlockForm block;            // the small-domain form (w = 0: not taken)
     int dense = 0;              // kDenseSome / kSparseSome: what second passes the domains need
     int budget = 0;             // kSelect* bits: budget threshold, top-k trimming in some domain
@@ -753,6 +767,7 @@ StepArgs step_args(const lbm_ctx* ctx, int parity)
     a.dense = ctx->dense;
     a.fused = ctx->block.w ? 2 : (ctx->act.fused ? 1 : 0);
     a.collide_lds = ctx->collide_lds;
+    a.fused_lds = ctx->fused_lds;
     a.whole_rows = ctx->whole_rows ? 1 : 0;
     a.block_w = ctx->block.w;
     a.block_h = ctx->block.h;
@@ -1311,6 +1326,7 @@ int lbm_create(const lbm_domain_desc* domains, int32_t n_domains, const lbm_run_
     if (ctx->block.w) ctx->most = ctx->block.steps;
     ctx->cap_h = second_height(domains, n_domains, kMaxTileH);
     ctx->collide_lds = collide_lds(domains, n_domains, ctx->storage);
+    ctx->fused_lds = fused_lds(domains, n_domains, ctx->storage);
     ctx->whole_rows = whole_rows(domains, n_domains, ctx->storage);
     ctx->fuse_ok = ctx->lattice == LBM_D2Q9 && !ctx->elbm && ctx->median_pass && !ctx->ens_pass;
 

@@ -1806,9 +1806,6 @@ static hipError_t dispatch(int qe, int ds, int bc, F f)
     return e == hipSuccess ? hipGetLastError() : e;
 }
 // a launch of KER<storage, f*, Delta S form, boundary, ...>
-// idle LDS with which three workgroups of the fused step fit on a CU (see collide_lds)
-constexpr int kThreePerCu = 23 << 10;
-
 #define LBM_LAUNCH_LDS(GRID, BLOCK, LDS, KER, ...)                                                       \
     [&](auto q, auto d, auto b) {                                                                        \
         constexpr int QE = decltype(q)::value, DS = decltype(d)::value, BC = decltype(b)::value;         \
@@ -1828,7 +1825,7 @@ hipError_t LBM_CAT(launch_step2d, LBM_SUFFIX)(int qe, int ds, int bc, const Step
                      : dispatch<0, 1, true>(qe, ds, bc, LBM_LAUNCH(a.nblocks, kThreads, k_collide2d, true, false));
     if (kernel == 3)
         return stats ? dispatch<0, 1>(qe, ds, bc, LBM_LAUNCH(a.ntiles, kThreads, k_fused2d, true))
-                     : dispatch<0, 1>(qe, ds, bc, LBM_LAUNCH_LDS(a.ntiles, kThreads, a.collide_lds ? kThreePerCu : 0, k_fused2d, false));
+                     : dispatch<0, 1>(qe, ds, bc, LBM_LAUNCH_LDS(a.ntiles, kThreads, a.fused_lds, k_fused2d, false));
     if (kernel == 5) {
         const int halo = 2 * a.steps - 1;
         const int threads = ((a.block_w + 2 * halo) * (a.block_h + 2 * halo) + kWave - 1) / kWave * kWave;
