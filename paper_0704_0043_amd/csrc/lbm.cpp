@@ -938,10 +938,17 @@ int time_shape(lbm_ctx* ctx, int n, double& ms, unsigned extra_flags = 0)
     return rc;
 }
 
-// Weight of a step as it stands against one whose second pass walks every tile:
-// in most steps of most runs few tiles have anything to move (4096 x 4096 FP32,
-// 16 or 64 rows: 212 or 209 us as it stands, 269 or 278 with every tile).
+// Weight of a step as it stands against one whose second pass walks every tile.
+// With nothing to move tall tiles are 1 % better, where nodes move short ones 2 to 12 %
+// (FP32, 16 or 64 rows, us a step: 4096 x 4096 203.6 or 200.4 quiet, 305 or 313 with 6 %
+// of the nodes moved; 3600 x 3600 164.9 or 162.8, 239 or 254; 2500 x 2500 82.9 or 81.9,
+// 119 or 129; 5000 x 5000 FP16 198 or 195, 548 or 615 with a third moved).  Which of
+// the two a run will be cannot be seen at its start, so the state it starts from
+// counts most; one that filters throughout is better off with LBM_RUN_ADAPTIVE.
 constexpr double kAsItStands = 8.0;
+// Steps as it stands that are timed together: three could not tell 1 % apart (six
+// contexts of about 2500 x 2500 chose 16 rows twice and 64 four times)
+constexpr int kTunedSteps = 12;
 
 // fused_alt: the fused form of an adaptive run (its tile height only)
 int autotune(lbm_ctx* ctx, const lbm_run_desc* run, bool fused_alt = false)
@@ -1004,7 +1011,7 @@ int autotune(lbm_ctx* ctx, const lbm_run_desc* run, bool fused_alt = false)
         for (size_t j = 0; j < cand.size() && !rc; ++j) {
             const size_t c = round ? cand.size() - 1 - j : j;
             rc = apply_shape(ctx, cand[c]);
-            if (!rc) rc = time_shape(ctx, 3, ms);
+            if (!rc) rc = time_shape(ctx, kTunedSteps, ms);
             if (!rc) best[c] = std::min(best[c], ms);
             if (!rc && second) rc = time_shape(ctx, 3, ms, kFlagAllTiles);
             if (!rc && second) best_all[c] = std::min(best_all[c], ms);
