@@ -18,8 +18,9 @@
 //    are formed from these on demand, when the stats are read.
 //  second pass: the 3x3 median of that plane and the ensemble-dependent
 //    factors (thresholds from this step's E(Delta S') and selections) decide
-//    which nodes move further; their stored limited states are rescaled
-//    toward f* in place.
+//    which nodes move further; after LBGK these are formed anew from the step's
+//    input, after ELBM (whose f' needs the node's root) their stored limited
+//    states are rescaled toward f* in place.
 //
 // The collision kernel is a plain streaming pass with aligned loads and
 // stores and no barrier before its epilogue, the access pattern that
@@ -73,8 +74,9 @@ __device__ inline int tile_of_block(const StepArgs& a, int first)
     return xcd_spatial(int(blockIdx.x) - first, a.ntiles);
 }
 
-// per-tile FP64 partials: set 0 = collision rows (summed on demand; the D1Q3
-// kernel writes it directly), set 1 = median pass
+// FP64 partials: set 0 = the collision kernel's, per group (summed on demand; the
+// D1Q3 kernel writes them per workgroup), set 1 = second pass, per tile (and every
+// partial of the fused step and of the tile kernel)
 __device__ inline double* partial_slot(const StepArgs& a, int set, int tile)
 {
     return a.partials + ((long long)set * a.pstride + tile) * kNStat;
@@ -482,9 +484,10 @@ constexpr int kListCap = kListRows * kWave;
 // cost more than the nodes between them.  There a wave's row with at least
 // kRowMoves moved nodes lists every fluid node of a kPiece-column piece that has a
 // moved one; the others come out as the collision kernel stored them, bit for
-// bit (4096 x 4096 FP32, 16-row tiles: 10 % of the nodes moved 545 -> 479 us a
-// step, 6 %, in runs along filaments, 299 -> 305; 2048 x 2048 FP64, 43 % moved
-// 327 -> 267.  Within the cache it only adds nodes: 2000 x 2000 FP32 85 -> 91.)
+// bit (4096 x 4096 FP32, tiles of 16 or 64 rows: 10 % of the nodes moved 545 or 554 ->
+// 479 or 491 us a step, 6 %, in runs along filaments, 299 -> 305 or 313; 3600 x 3600,
+// 8 % 433 or 462 -> 376 or 420; 2048 x 2048 FP64, 43 % 327 -> 267.  Within the cache it
+// only adds nodes: 2000 x 2000 FP32 85 -> 91.)
 constexpr int kRowMoves = 8, kPiece = 16;
 
 // the filter's threshold and decision for a node with Delta S' = dc whose
@@ -678,7 +681,7 @@ __device__ __forceinline__ double rescale_node(const DD& D, gptr<T> buf, long lo
     return double(kull_sum<false>(fs, e, A(1)) - kull_sum<false>(fs, e, r));
 }
 
-template <class T, int QE, int DS, int BC, bool ENS, bool ELBM>
+template <class T, int QE, int DS, int BC, bool ENS, bool ELBM, bool WHOLE>
 __device__ __forceinline__ void second_pass2d(const StepArgs& a)
 {
     using A = typename Store<T>::A;
@@ -887,8 +890,8 @@ __device__ __forceinline__ void second_pass2d(const StepArgs& a)
                 unsigned long long b = __ballot(moves);
                 // (ELBM, the exact homothety and the positivity rule would need a root
                 // or a factor that the list does not hold)
-                if constexpr (!ELBM && DS != kExactHom) {
-                    if (a.whole_rows && int(__popcll(b)) >= kRowMoves && !(D.limiter & kLimPos)) {
+                if constexpr (WHOLE && !ELBM && DS != kExactHom) {
+                    if (int(__popcll(b)) >= kRowMoves && !(D.limiter & kLimPos)) {
                         if (!moves && (b >> (lane & -kPiece) & ((1u << kPiece) - 1))) {
                             tgt = A(__builtin_huge_val());
                             fac = A(1);
@@ -944,17 +947,18 @@ __device__ __forceinline__ void second_pass2d(const StepArgs& a)
 }
 
 // the second D2Q9 pass without and with ensemble-dependent limiters (the
-// latter needs more registers), after LBGK and after ELBM collisions
-template <class T, int QE, int DS, int BC, bool ELBM>
+// latter needs more registers), after LBGK and after ELBM collisions, and with whole
+// pieces of rows (whose code costs the others four registers and 0.5 % of a step)
+template <class T, int QE, int DS, int BC, bool ELBM, bool WHOLE>
 __global__ void __launch_bounds__(kThreads) k_median2d(StepArgs a)
 {
-    second_pass2d<T, QE, DS, BC, false, ELBM>(a);
+    second_pass2d<T, QE, DS, BC, false, ELBM, WHOLE>(a);
 }
 
-template <class T, int QE, int DS, int BC, bool ELBM>
+template <class T, int QE, int DS, int BC, bool ELBM, bool WHOLE>
 __global__ void __launch_bounds__(kThreads) k_median_ens2d(StepArgs a)
 {
-    second_pass2d<T, QE, DS, BC, true, ELBM>(a);
+    second_pass2d<T, QE, DS, BC, true, ELBM, WHOLE>(a);
 }
 
 // Second pass of the domains whose every node it moves (the smooth and the
@@ -1835,10 +1839,13 @@ hipError_t LBM_CAT(launch_step2d, LBM_SUFFIX)(int qe, int ds, int bc, const Step
     }
     if (kernel == 4) return dispatch<0, 1>(qe, ds, bc, LBM_LAUNCH(a.nblocks, kThreads, k_form2d));
     if (a.elbm)
-        return a.ens_pass ? dispatch<0, 1, true>(qe, ds, bc, LBM_LAUNCH(a.ntiles, kThreads, k_median_ens2d, true))
-                          : dispatch<0, 1, true>(qe, ds, bc, LBM_LAUNCH(a.ntiles, kThreads, k_median2d, true));
-    return a.ens_pass ? dispatch<0, 1>(qe, ds, bc, LBM_LAUNCH(a.ntiles, kThreads, k_median_ens2d, false))
-                      : dispatch<0, 1>(qe, ds, bc, LBM_LAUNCH(a.ntiles, kThreads, k_median2d, false));
+        return a.ens_pass ? dispatch<0, 1, true>(qe, ds, bc, LBM_LAUNCH(a.ntiles, kThreads, k_median_ens2d, true, false))
+                          : dispatch<0, 1, true>(qe, ds, bc, LBM_LAUNCH(a.ntiles, kThreads, k_median2d, true, false));
+    if (a.whole_rows)
+        return a.ens_pass ? dispatch<0, 1>(qe, ds, bc, LBM_LAUNCH(a.ntiles, kThreads, k_median_ens2d, false, true))
+                          : dispatch<0, 1>(qe, ds, bc, LBM_LAUNCH(a.ntiles, kThreads, k_median2d, false, true));
+    return a.ens_pass ? dispatch<0, 1>(qe, ds, bc, LBM_LAUNCH(a.ntiles, kThreads, k_median_ens2d, false, false))
+                      : dispatch<0, 1>(qe, ds, bc, LBM_LAUNCH(a.ntiles, kThreads, k_median2d, false, false));
 }
 
 hipError_t LBM_CAT(launch_step1d, LBM_SUFFIX)(int qe, int ds, int bc, const StepArgs& a, int kernel,
