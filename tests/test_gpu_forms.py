@@ -445,3 +445,19 @@ def test_budget_threshold_of_few_values_above_many():
     say(f"[budget] threshold {t!r}, exactly {want!r}: rel {abs(t - want) / want:.1e}")
     # the sum over all nodes is 20 roundings deep; 7/3 of its relative error is the threshold's
     assert abs(t - want) <= 2.4 * 20 * 1.2e-16 * want
+
+
+# the lists full: a threshold of 0 moves every fluid node, at the edges of the
+# second pass's waves (64 columns), tiles (256) and list flushes (8 rows)
+@pytest.mark.parametrize("nx", [63, 64, 65, 255, 256, 257])
+@pytest.mark.parametrize("ny", [7, 8, 9])
+@pytest.mark.parametrize("bc", [PERIODIC, CAVITY])
+def test_second_pass_lists_with_every_node(nx, ny, bc):
+    L = lbm()
+    d = L.Domain(lattice=D2Q9, nx=nx, ny=ny, beta=0.97, qe=0, ds_form=1, limiter=4, ens_c=0.0, delta_ens=1e-9, bc=bc,
+                 lid_ux=0.0 if bc == PERIODIC else 0.05)
+    pr = Pair(d, rough(9, nx, ny, seed=nx + ny), steps=1)
+    assert pr.stats["n_ensemble"] == pr.so["n_ensemble"] == pr.stats["n_fluid"]
+    assert_masks_equal(pr)
+    close(pr.f, pr.fo, 1e-13)
+    assert pr.stats["limiter_production"] == pytest.approx(pr.so["limiter_production"], rel=1e-11)
