@@ -207,10 +207,9 @@ typedef struct {
                                    limiter only, else LBM_EINVAL).  Its cost does not depend on
                                    how many nodes the filter moves; the two kernels cost less
                                    while few move and more when many do (each moved node's
-                                   stored state is read and written again).  The decisions are
-                                   the same; a moved node's state is formed once as
-                                   f* - phi c d (phi the smallest factor, eq. LimGenF), so its
-                                   populations agree with the two-kernel step to rounding */
+                                   populations are gathered and written again).  The decisions
+                                   are the same, a moved node's state f* - phi c d (phi the
+                                   smallest factor, eq. LimGenF) agrees to rounding */
     int32_t tile_y;             /* 0 (or 1) */
     int32_t tile_h;             /* rows per D2Q9 second-pass tile (1..64); 0 = chosen by the
                                    autotuner among 16, 32 and 64 (64 without a second pass).
@@ -305,9 +304,10 @@ LBM_API int lbm_probe_trace(lbm_ctx* ctx, int32_t domain, float* uv, int64_t max
                     int64_t* n_written);
 
 /* Shape in use (with LBM_RUN_ADAPTIVE, of the form the last step ran, or
- * the next step runs after a choice).  D2Q9: 256 (with tile_x 0 or 64 and a
+ * the next step runs after a choice); small domains that run whole steps of a tile
+ * (tile_x) report what their two kernels would be asked for.  D2Q9: 256 (with tile_x 0 or 64 and a
  * first domain at most 64 / 128 wide: 64 / 128), 256 divided by that,
- * and the rows of a second-pass tile; the fused step: 248, 1
+ * and the rows asked for a second-pass tile (fewer on small grids); the fused step: 248, 1
  * and the rows of a fused tile.  D1Q3: 188, 1, 1. */
 LBM_API int lbm_tile_config(const lbm_ctx* ctx, int32_t* tile_x, int32_t* tile_y, int32_t* tile_h);
 

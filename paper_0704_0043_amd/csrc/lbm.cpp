@@ -212,6 +212,17 @@ int next_launch(long long left, bool odd, int most, bool alone)
 struct BlockForm {
     int w = 0, h = 0, steps = 1;
 };
+// The line, us a step with tiles or two kernels (periodic, one step a launch), quiet:
+//   nodes             100k        200k        300k        400k        500k        800k
+//   FP32 quadratic  5.5 / 7.7   7.8 / 8.9   8.5 / 10.0  11.2 / 12.0  13.1 / 12.8  17.7 / 17.0
+//   FP16 quadratic  5.5 / 7.5   7.0 / 8.3   7.7 / 9.0    9.6 / 9.6   11.6 / 10.5  15.1 / 13.1
+//   FP64 quadratic  7.2 / 9.5  11.6 / 12.7 12.8 / 14.8  16.6 / 17.6  19.4 / 20.2  27.8 / 28.3
+//   FP64 exact      8.3 / 10.8 17.7 / 14.0 19.4 / 17.9  25.2 / 21.8  34.9 / 30.1  52.3 / 41.8
+// and with 43 % of the nodes moved in every step 11.3 / 24.5 (FP32) and 26.1 / 39.8
+// (FP64 exact) at 400k, 17.6 / 34.0 and 46.9 / 69.4 at 800k, where the fused step takes
+// 16.9 and 43.2.  So quiet flows lose beyond 400k nodes, in FP64 with the exact
+// Delta S from 200k on, and flows that filter win throughout; which one a run will
+// be cannot be seen at its start.
 constexpr long long kBlockNodes = 400000;
 constexpr int kBlockThreads = 512;
 constexpr int kCUs = 256;
@@ -283,7 +294,7 @@ struct DomainHost {
     bool dsbuf = false, phibuf = false;
     double shift = 0;
     int tile_first = 0, tile_count = 0;
-    int part_first = 0, part_count = 0;
+    int part_first = 0;
     int group_first = 0, group_count = 0;
 };
 
@@ -648,10 +659,10 @@ void build_blocks(lbm_ctx* ctx)
         h.group_first = int(ctx->groups_host.size());
         if (ctx->lattice == LBM_D2Q9) {
             h.part_first = part;
-            h.part_count = blocks_of(nx, ny);
-            part += h.part_count;
+            const int blocks = blocks_of(nx, ny);
+            part += blocks;
             if (ctx->dom.size() > 1)
-                for (int i = 0; i < h.part_count; ++i) ctx->blocks_host.push_back(Block{int(k), i});
+                for (int i = 0; i < blocks; ++i) ctx->blocks_host.push_back(Block{int(k), i});
             h.group_count = groups_of(nx, ny);
             for (int i = 0; i < h.group_count; ++i) ctx->groups_host.push_back(group_entry2d(int(k), n, i));
         } else {
@@ -702,7 +713,6 @@ DomainDev make_dev(const DomainHost& h, char* base, void* b0, void* b1, int prob
     d.tile_count = h.tile_count;
     d.inv_nx = inverse_nx(h.d.nx);
     d.part_first = h.part_first;
-    d.part_count = h.part_count;
     d.group_first = h.group_first;
     d.group_count = h.group_count;
     d.stats = reinterpret_cast<double*>(base + h.off_stats);
@@ -876,16 +886,15 @@ void drop_graphs(lbm_ctx* ctx)
 // columns) in place of the two kernels, taken when the run asks for it
 // (tile_x = kFusedWidth; the tuner then picks its tile height).  The fused
 // step costs the same whatever the filter does; the two kernels cost less
-// while few nodes move and more when many do (each moved node's stored state
-// is read and written again), which the steps timed at creation, from a
+// while few nodes move and more when many do (each moved node's populations
+// are gathered and written again), which the steps timed at creation, from a
 // state where nothing has moved yet, cannot show.  Tile heights change
 // nothing the step computes (the collision partials are summed in fixed groups
 // of nodes, so E(Delta S') and every field come out the same; only the FP64
 // sums that the second pass adds to may differ in the last bits).  The fused
-// step forms a moved node's state f* - phi c d once, with phi the smallest
-// factor, where the two kernels rescale the stored trimmed state: the masks
-// and every decision are the same, a moved node's populations agree to
-// rounding.  lbm_create times the candidate shapes on the live state with HIP
+// step and the second pass both form a moved node's state as f* - phi c d, phi the
+// smallest factor: the masks and every decision are the same, a moved node's
+// populations agree to rounding.  lbm_create times the candidate shapes on the live state with HIP
 // events and keeps the fastest; a process-wide cache keyed by the descriptors
 // gives the same choice to every later context of the same problem.
 
@@ -1076,7 +1085,7 @@ int capture_all(lbm_ctx* ctx)
 // the fluid nodes of all domains) above which the fused step takes over, and
 // below which the two kernels come back.  The two kernels cost less while
 // few nodes move; once the filter moves a few per mille their second pass
-// reads and rewrites most sectors of the population planes again.
+// gathers and writes in most sectors of the population planes again.
 constexpr double kAdaptOn = 5e-3;
 constexpr double kAdaptOff = 1e-3;
 
@@ -1227,7 +1236,6 @@ void plan_static(const lbm_domain_desc& d, int storage, int th, const BlockForm&
     h.group_first = 0;
     h.group_count = L.ngroups;
     h.part_first = 0;
-    h.part_count = L.nblocks;
     size_t off = 0;
     L.off_dom = off;
     off = align_up(off + sizeof(DomainDev), kAlign);

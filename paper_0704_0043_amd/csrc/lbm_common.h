@@ -108,7 +108,7 @@ struct DomainDev {
     double* ens;                  // [kNEns]: E(Delta S') and the thresholds of this step
     void* phibuf;                 // D1Q3 with ensemble limiters: phi applied by the first pass
     unsigned inv_nx;              // ceil(2^32 / nx) (nx >= 64 only), see row_of_node
-    int part_first, part_count;   // D2Q9: this domain's range of collision partials (one per workgroup)
+    int part_first;               // D2Q9: this domain's first collision partial (one per workgroup)
     int group_first, group_count; // this domain's range of collision-partial groups
     BudgetState* bstate;          // budget threshold: search state (budget limiter only)
     BudgetBucket* bhist;          // [kBudgetBuckets], left zero between levels
