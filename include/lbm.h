@@ -207,7 +207,7 @@ typedef struct {
                                    limiter only, else LBM_EINVAL).  Its cost does not depend on
                                    how many nodes the filter moves; the two kernels cost less
                                    while few move and more when many do (each moved node's
-                                   populations are gathered and written again).  The decisions
+                                   populations are read and written again).  The decisions
                                    are the same, a moved node's state f* - phi c d (phi the
                                    smallest factor, eq. LimGenF) agrees to rounding */
     int32_t tile_y;             /* 0 (or 1) */

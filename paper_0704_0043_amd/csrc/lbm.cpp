@@ -145,15 +145,24 @@ int fused_lds(const lbm_domain_desc* doms, int32_t nd, int storage)
     return collide_lds(doms, nd, storage) ? kThreePerCu : 0;
 }
 
-// The input of a step has left the last-level cache by the time the second pass
-// reads it: a population buffer is larger than the cache (kRowMoves; 2600 x 2600
-// FP32, 232 MiB: 199 us a step against 196 with whole pieces, 2400: 159.6 against
-// 160.4, 2800: 245 against 228).
-bool whole_rows(const lbm_domain_desc* doms, int32_t nd, int storage)
+// Well beyond the last-level cache the step's input has left it by the time the second
+// pass runs.  Forming many scattered moved nodes anew then reads the input's lines and
+// makes memory read the output's, of which each store writes a part; rescaling what is
+// stored reads the output's lines alone.  Anew or in place, us a step with tiles of 16
+// rows: FP32 4096 x 4096 541 or 464 with 10 % of the nodes moved, 608 or 497 with 16 %,
+// 296 or 296 with 6 % in runs along filaments; 3300 x 3300 360 or 311 and 198 or 198; 3000
+// x 3000 287 or 255 but 157 or 161 (64 rows: 210 or 227), 2000 x 2000 98 or 102 and 89 or
+// 97.  FP64 2048 x 2048 with 43 % moved 327 or 273, with 0.5 % 146 or 146.  So the line is
+// a population buffer of one and a half times the cache in FP32, of the cache in FP64.
+// In place rounds once more: the moved nodes' error against 64 bits is 6 % larger in the
+// mean square in FP32, 3 % in FP64, and 13 % in 16 bits, where it does not pay (5000 x 5000
+// FP16) and is not taken; nor with the exact homothety, whose roots it would solve twice.
+bool in_place(const lbm_domain_desc* doms, int32_t nd, int storage)
 {
-    long long nodes = 0;
-    for (int k = 0; k < nd; ++k) nodes += (long long)doms[k].nx * doms[k].ny;
-    return doms[0].lattice == LBM_D2Q9 && nodes * 9 * (long long)elem_size(storage) > kLastLevelCache;
+    if (doms[0].lattice != LBM_D2Q9 || elem_size(storage) < 4 || ds_kernel(doms, nd) == kExactHom) return false;
+    long long bytes = 0;
+    for (int k = 0; k < nd; ++k) bytes += (long long)doms[k].nx * doms[k].ny * 9 * (long long)elem_size(storage);
+    return bytes > (storage == LBM_F64 ? kLastLevelCache : kLastLevelCache * 3 / 2);
 }
 
 // D1Q3: sites on either side that one step's result depends on (free flight,
@@ -323,7 +332,7 @@ struct lbm_ctx {
     bool ens_pass = false;      // an ensemble-dependent limiter in some domain
     bool fuse_ok = false;       // the fused step applies (D2Q9 LBGK, median filter, no ensemble limiter)
     int reach = 1, most = 1;    // D1Q3: reach of a step; steps of the longest launch
-    bool whole_rows = false;    // the second pass completes rows' pieces
+    bool in_place = false;      // the second pass rescales the stored states
     int collide_lds = 0, fused_lds = 0;   // idle LDS of the workgroups of the collision and of the fused step
     BlockForm block;            // the small-domain form (w = 0: not taken)
     int dense = 0;              // kDenseSome / kSparseSome: what second passes the domains need
@@ -778,7 +787,7 @@ StepArgs step_args(const lbm_ctx* ctx, int parity)
     a.fused = ctx->block.w ? 2 : (ctx->act.fused ? 1 : 0);
     a.collide_lds = ctx->collide_lds;
     a.fused_lds = ctx->fused_lds;
-    a.whole_rows = ctx->whole_rows ? 1 : 0;
+    a.in_place = ctx->in_place ? 1 : 0;
     a.block_w = ctx->block.w;
     a.block_h = ctx->block.h;
     a.blocks = ctx->blocks_host.empty() ? nullptr : ctx->d_blocks();
@@ -887,14 +896,14 @@ void drop_graphs(lbm_ctx* ctx)
 // (tile_x = kFusedWidth; the tuner then picks its tile height).  The fused
 // step costs the same whatever the filter does; the two kernels cost less
 // while few nodes move and more when many do (each moved node's populations
-// are gathered and written again), which the steps timed at creation, from a
+// are read and written again), which the steps timed at creation, from a
 // state where nothing has moved yet, cannot show.  Tile heights change
 // nothing the step computes (the collision partials are summed in fixed groups
 // of nodes, so E(Delta S') and every field come out the same; only the FP64
 // sums that the second pass adds to may differ in the last bits).  The fused
 // step and the second pass both form a moved node's state as f* - phi c d, phi the
-// smallest factor: the masks and every decision are the same, a moved node's
-// populations agree to rounding.  lbm_create times the candidate shapes on the live state with HIP
+// smallest factor (or rescale the stored one to it, in_place): the masks and every
+// decision are the same, a moved node's populations agree to rounding.  lbm_create times the candidate shapes on the live state with HIP
 // events and keeps the fastest; a process-wide cache keyed by the descriptors
 // gives the same choice to every later context of the same problem.
 
@@ -949,8 +958,8 @@ int time_shape(lbm_ctx* ctx, int n, double& ms, unsigned extra_flags = 0)
 
 // Weight of a step as it stands against one whose second pass walks every tile.
 // With nothing to move tall tiles are 1 % better, where nodes move short ones 2 to 12 %
-// (FP32, 16 or 64 rows, us a step: 4096 x 4096 203.6 or 200.4 quiet, 305 or 313 with 6 %
-// of the nodes moved; 3600 x 3600 164.9 or 162.8, 239 or 254; 2500 x 2500 82.9 or 81.9,
+// (FP32, 16 or 64 rows, us a step: 4096 x 4096 203.6 or 200.4 quiet, 348 or 374 with 5 %
+// of the nodes moved; 3600 x 3600 164.9 or 162.8, 287 or 319; 2500 x 2500 82.9 or 81.9,
 // 119 or 129; 5000 x 5000 FP16 198 or 195, 548 or 615 with a third moved).  Which of
 // the two a run will be cannot be seen at its start, so the state it starts from
 // counts most; one that filters throughout is better off with LBM_RUN_ADAPTIVE.
@@ -1085,7 +1094,7 @@ int capture_all(lbm_ctx* ctx)
 // the fluid nodes of all domains) above which the fused step takes over, and
 // below which the two kernels come back.  The two kernels cost less while
 // few nodes move; once the filter moves a few per mille their second pass
-// gathers and writes in most sectors of the population planes again.
+// reads and writes in most sectors of the population planes again.
 constexpr double kAdaptOn = 5e-3;
 constexpr double kAdaptOff = 1e-3;
 
@@ -1342,7 +1351,7 @@ int lbm_create(const lbm_domain_desc* domains, int32_t n_domains, const lbm_run_
     ctx->cap_h = second_height(domains, n_domains, kMaxTileH);
     ctx->collide_lds = collide_lds(domains, n_domains, ctx->storage);
     ctx->fused_lds = fused_lds(domains, n_domains, ctx->storage);
-    ctx->whole_rows = whole_rows(domains, n_domains, ctx->storage);
+    ctx->in_place = in_place(domains, n_domains, ctx->storage);
     ctx->fuse_ok = ctx->lattice == LBM_D2Q9 && !ctx->elbm && ctx->median_pass && !ctx->ens_pass;
 
     auto bail = [&](int code) {
@@ -1793,7 +1802,7 @@ int lbm_step_static(const lbm_domain_desc* domain, int32_t storage, void* stream
     a.block_h = block.h;
     if (d1) a.reach = reach1d(domain, 1);
     a.collide_lds = collide_lds(domain, 1, storage);
-    a.whole_rows = whole_rows(domain, 1, storage) ? 1 : 0;
+    a.in_place = in_place(domain, 1, storage) ? 1 : 0;
     bool odd = n_steps % 2 != 0;
     for (int64_t t = 0; t < n_steps && e == hipSuccess; a.parity = 1 - a.parity, odd = !odd) {
         // (the last step alone: the other buffer then holds the state before it)

@@ -271,7 +271,7 @@ struct StepArgs {
                             // a median candidate (Delta S' > delta_median) and stored its Delta S'
     long long* counter;     // [2] step index by parity
     int reach = 1;          // D1Q3: sites a step's result depends on, on either side
-    int whole_rows = 0;     // the second pass writes whole pieces of rows where many nodes move (whole_rows)
+    int in_place = 0;       // after LBGK too the second pass rescales the stored states (in_place)
     int collide_lds = 0, fused_lds = 0;   // bytes of LDS that a workgroup of the collision and of the fused
                             // step without sums holds idle (collide_lds, fused_lds)
     int steps = 1;          // D1Q3 and the small-domain kernel: steps of this launch

@@ -19,8 +19,8 @@
 //  second pass: the 3x3 median of that plane and the ensemble-dependent
 //    factors (thresholds from this step's E(Delta S') and selections) decide
 //    which nodes move further; after LBGK these are formed anew from the step's
-//    input, after ELBM (whose f' needs the node's root) their stored limited
-//    states are rescaled toward f* in place.
+//    input, after ELBM (whose f' needs the node's root) and far beyond the
+//    last-level cache their stored limited states are rescaled in place.
 //
 // The collision kernel is a plain streaming pass with aligned loads and
 // stores and no barrier before its epilogue, the access pattern that
@@ -479,16 +479,6 @@ __global__ void __launch_bounds__(kThreads, DS == kExact && !STATS && !ELBM ? 4 
 constexpr int kMedChunk = 4;
 constexpr int kListRows = 8;                      // rows decided before their moved nodes are moved
 constexpr int kListCap = kListRows * kWave;
-// Beyond the last-level cache (whole_rows) a store of part of a 64-byte piece
-// makes memory read the piece first, and the scattered stores of many moved nodes
-// cost more than the nodes between them.  There a wave's row with at least
-// kRowMoves moved nodes lists every fluid node of a kPiece-column piece that has a
-// moved one; the others come out as the collision kernel stored them, bit for
-// bit (4096 x 4096 FP32, tiles of 16 or 64 rows: 10 % of the nodes moved 545 or 554 ->
-// 479 or 491 us a step, 6 %, in runs along filaments, 299 -> 305 or 313; 3600 x 3600,
-// 8 % 433 or 462 -> 376 or 420; 2048 x 2048 FP64, 43 % 327 -> 267.  Within the cache it
-// only adds nodes: 2000 x 2000 FP32 85 -> 91.)
-constexpr int kRowMoves = 8, kPiece = 16;
 
 // the filter's threshold and decision for a node with Delta S' = dc whose
 // stencil median is med (FLOOR or GATE reading of the tolerance delta)
@@ -623,7 +613,8 @@ __device__ __forceinline__ double form_node(const DD& D, gptr<const T> src, gptr
 }
 
 // The same after ELBM collisions, whose f' - f* = -(alpha beta - 1) d would
-// need the node's entropy root again: the limited state that the collision
+// need the node's entropy root again, and in FP32 and FP64 domains beyond the
+// last-level cache (in_place): the limited state that the collision
 // kernel stored is rescaled toward its f*, rebuilt from the state's own
 // moments (the limiter kept them): f* + r (f_stored - f*), r = pq / pt (the new
 // factor over the applied one).  With the exact homothety the stored state's
@@ -681,7 +672,7 @@ __device__ __forceinline__ double rescale_node(const DD& D, gptr<T> buf, long lo
     return double(kull_sum<false>(fs, e, A(1)) - kull_sum<false>(fs, e, r));
 }
 
-template <class T, int QE, int DS, int BC, bool ENS, bool ELBM, bool WHOLE>
+template <class T, int QE, int DS, int BC, bool ENS, bool STORED>
 __device__ __forceinline__ void second_pass2d(const StepArgs& a)
 {
     using A = typename Store<T>::A;
@@ -700,7 +691,7 @@ __device__ __forceinline__ void second_pass2d(const StepArgs& a)
             return;
         }
     } else {
-        if (!ELBM && D.dense) return;          // k_form2d's
+        if (D.dense) return;          // k_form2d's
     }
     AccT<A, double> acc;
     const int nx = D.nx, ny = D.ny;
@@ -887,19 +878,7 @@ __device__ __forceinline__ void second_pass2d(const StepArgs& a)
                     moves = fmin(fac, tgt < A(__builtin_huge_val()) ? sqrt_(tgt * rcp(dc)) : A(1)) < pt;
                     if constexpr (DS == kExactHom) moves = moves || (D.homothety && isfinite(dc) && pt > A(0));
                 }
-                unsigned long long b = __ballot(moves);
-                // (ELBM, the exact homothety and the positivity rule would need a root
-                // or a factor that the list does not hold)
-                if constexpr (WHOLE && !ELBM && DS != kExactHom) {
-                    if (int(__popcll(b)) >= kRowMoves && !(D.limiter & kLimPos)) {
-                        if (!moves && (b >> (lane & -kPiece) & ((1u << kPiece) - 1))) {
-                            tgt = A(__builtin_huge_val());
-                            fac = A(1);
-                            moves = fluid;
-                        }
-                        b = __ballot(moves);
-                    }
-                }
+                const unsigned long long b = __ballot(moves);
                 if (moves) {
                     const int at = listed + int(__builtin_amdgcn_mbcnt_hi(unsigned(b >> 32),
                                                                         __builtin_amdgcn_mbcnt_lo(unsigned(b), 0)));
@@ -932,7 +911,7 @@ __device__ __forceinline__ void second_pass2d(const StepArgs& a)
                 A fac = A(1);
                 if constexpr (ENS) fac = list_fac[wave][e];
                 const A dc = Store<A>::ld(dsb + (unsigned(yn) * unsigned(nx) + unsigned(xn)));
-                if constexpr (ELBM)
+                if constexpr (STORED)
                     acc.lim += rescale_node<T, QE, DS>(D, dst, plane, xn, yn, dc, tgt, fac);
                 else
                     acc.lim += form_node<T, QE, DS, BC>(D, to_global<T>(static_cast<const void*>(D.buf[a.parity])), dst,
@@ -947,18 +926,18 @@ __device__ __forceinline__ void second_pass2d(const StepArgs& a)
 }
 
 // the second D2Q9 pass without and with ensemble-dependent limiters (the
-// latter needs more registers), after LBGK and after ELBM collisions, and with whole
-// pieces of rows (whose code costs the others four registers and 0.5 % of a step)
-template <class T, int QE, int DS, int BC, bool ELBM, bool WHOLE>
+// latter needs more registers), forming the moved nodes anew or, after ELBM and
+// beyond the last-level cache, from the stored states
+template <class T, int QE, int DS, int BC, bool STORED>
 __global__ void __launch_bounds__(kThreads) k_median2d(StepArgs a)
 {
-    second_pass2d<T, QE, DS, BC, false, ELBM, WHOLE>(a);
+    second_pass2d<T, QE, DS, BC, false, STORED>(a);
 }
 
-template <class T, int QE, int DS, int BC, bool ELBM, bool WHOLE>
+template <class T, int QE, int DS, int BC, bool STORED>
 __global__ void __launch_bounds__(kThreads) k_median_ens2d(StepArgs a)
 {
-    second_pass2d<T, QE, DS, BC, true, ELBM, WHOLE>(a);
+    second_pass2d<T, QE, DS, BC, true, STORED>(a);
 }
 
 // Second pass of the domains whose every node it moves (the smooth and the
@@ -1839,13 +1818,15 @@ hipError_t LBM_CAT(launch_step2d, LBM_SUFFIX)(int qe, int ds, int bc, const Step
     }
     if (kernel == 4) return dispatch<0, 1>(qe, ds, bc, LBM_LAUNCH(a.nblocks, kThreads, k_form2d));
     if (a.elbm)
-        return a.ens_pass ? dispatch<0, 1, true>(qe, ds, bc, LBM_LAUNCH(a.ntiles, kThreads, k_median_ens2d, true, false))
-                          : dispatch<0, 1, true>(qe, ds, bc, LBM_LAUNCH(a.ntiles, kThreads, k_median2d, true, false));
-    if (a.whole_rows)
-        return a.ens_pass ? dispatch<0, 1>(qe, ds, bc, LBM_LAUNCH(a.ntiles, kThreads, k_median_ens2d, false, true))
-                          : dispatch<0, 1>(qe, ds, bc, LBM_LAUNCH(a.ntiles, kThreads, k_median2d, false, true));
-    return a.ens_pass ? dispatch<0, 1>(qe, ds, bc, LBM_LAUNCH(a.ntiles, kThreads, k_median_ens2d, false, false))
-                      : dispatch<0, 1>(qe, ds, bc, LBM_LAUNCH(a.ntiles, kThreads, k_median2d, false, false));
+        return a.ens_pass ? dispatch<0, 1, true>(qe, ds, bc, LBM_LAUNCH(a.ntiles, kThreads, k_median_ens2d, true))
+                          : dispatch<0, 1, true>(qe, ds, bc, LBM_LAUNCH(a.ntiles, kThreads, k_median2d, true));
+    if constexpr (sizeof(StT) >= 4) {
+        if (a.in_place)
+            return a.ens_pass ? dispatch<0, 1>(qe, ds, bc, LBM_LAUNCH(a.ntiles, kThreads, k_median_ens2d, true))
+                              : dispatch<0, 1>(qe, ds, bc, LBM_LAUNCH(a.ntiles, kThreads, k_median2d, true));
+    }
+    return a.ens_pass ? dispatch<0, 1>(qe, ds, bc, LBM_LAUNCH(a.ntiles, kThreads, k_median_ens2d, false))
+                      : dispatch<0, 1>(qe, ds, bc, LBM_LAUNCH(a.ntiles, kThreads, k_median2d, false));
 }
 
 hipError_t LBM_CAT(launch_step1d, LBM_SUFFIX)(int qe, int ds, int bc, const StepArgs& a, int kernel,

@@ -334,27 +334,32 @@ def test_dense_form_pass_keeps_the_positivity_rule(limiter, kw, median, storage)
         close(lone.f, alone.fo, 2e-6)
 
 
-# beside a domain beyond the last-level cache the second pass writes whole
-# pieces of the rows in which many nodes move: the same states
+# beside a domain beyond the last-level cache the second pass rescales what is
+# stored instead of forming the moved nodes anew: the same decisions, states to
+# rounding (FP32: a few units of 6e-8 of a node's excess over w_i)
 @pytest.mark.parametrize("nx,ny", [(15, 9), (63, 5), (65, 17), (257, 33)])
 @pytest.mark.parametrize("storage,ds", [(0, 0), (1, 1)])
 @pytest.mark.parametrize("limiter,kw", [(3, dict(delta_median=0.0)), (7, dict(ens_c=1.0, delta_median=1e-5)),
-                                        (3, dict(delta_median=1e-5, top_k=40, trim_mode=1))])
-def test_whole_pieces_of_rows(nx, ny, storage, ds, limiter, kw):
+                                        (3, dict(delta_median=1e-5, top_k=40, trim_mode=1)),
+                                        (66, dict(delta_median=1e-5))])
+def test_moved_nodes_from_the_stored_state(nx, ny, storage, ds, limiter, kw):
     L = lbm()
+    if limiter & 64 and ds:
+        pytest.skip("the positivity rule needs the exact Delta S here")
     f0 = rough(9, nx, ny, seed=nx + ny)
     d = L.Domain(lattice=D2Q9, nx=nx, ny=ny, beta=0.97, qe=0, ds_form=ds, limiter=limiter, delta_trim=1e-5, **kw)
-    far = L.Domain(lattice=D2Q9, nx=2600, ny=(1450, 2900)[storage], beta=0.97, qe=0, ds_form=ds, limiter=1)
-    flags = L.LBM_RUN_NO_TUNE | (L.LBM_RUN_ADAPTIVE if limiter == 3 and not d.top_k else 0)    # begins with two kernels
-    say(f"[pieces] {nx}x{ny} limiter {limiter} storage {storage}")
-    alone = run([d], [f0], [2], storage, flags=flags)[0]
-    with_far = run([d, far], [f0, None], [2], storage, flags=flags)[0]
-    assert np.array_equal(alone[0], with_far[0])
-    for key in ("n_trimmed", "n_filtered", "n_ensemble", "sum_dS_post", "max_dS"):
-        assert alone[1][key] == with_far[1][key], key
-    assert alone[1]["n_filtered"] + alone[1]["n_ensemble"] + alone[1]["n_trimmed"] > nx * ny // 8
-    # (the nodes are listed, and their terms added, in another order)
-    assert with_far[1]["limiter_production"] == pytest.approx(alone[1]["limiter_production"], rel=1e-12)
+    far = L.Domain(lattice=D2Q9, nx=2600, ny=(1450, 4400)[storage], beta=0.97, qe=0, ds_form=ds, limiter=1)
+    flags = L.LBM_RUN_NO_TUNE | (0 if limiter & 4 or d.top_k else L.LBM_RUN_ADAPTIVE)    # begins with two kernels
+    say(f"[stored] {nx}x{ny} limiter {limiter} storage {storage}")
+    anew = run([d], [f0], [1], storage, flags=flags)[0]
+    stored = run([d, far], [f0, None], [1], storage, flags=flags)[0]
+    close(stored[0], anew[0], 1e-13 if storage == 0 else 1e-6)
+    for key in ("n_trimmed", "n_filtered", "n_ensemble", "n_positivity", "sum_dS_post", "max_dS"):
+        assert anew[1][key] == stored[1][key], key
+    assert anew[1]["n_filtered"] + anew[1]["n_ensemble"] + anew[1]["n_trimmed"] > nx * ny // 8
+    # differences of the entropies of a node before and after
+    assert stored[1]["limiter_production"] == pytest.approx(anew[1]["limiter_production"],
+                                                            rel=1e-10 if storage == 0 else 1e-4)
 
 
 def test_short_tiles_do_not_compute_what_lds_held():
