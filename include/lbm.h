@@ -257,7 +257,7 @@ LBM_API int lbm_workspace_bytes(const lbm_domain_desc* domains, int32_t n_domain
  * tiles of 16, 32 or 64 rows, shorter on small grids; with tile_x = 248 the
  * fused tile heights) are timed with HIP events
  * on a few steps that all read the initial state (which they leave
- * unchanged), each scored by eight steps as it stands plus one whose second pass
+ * unchanged), each scored by four steps as it stands plus one whose second pass
  * walks every tile, and the fastest is kept; the choice is
  * cached for the process under the descriptors, so later contexts of the
  * same problem reuse it.  The shapes do not change the fields or E(Delta S');

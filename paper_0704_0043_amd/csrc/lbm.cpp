@@ -957,13 +957,17 @@ int time_shape(lbm_ctx* ctx, int n, double& ms, unsigned extra_flags = 0)
 }
 
 // Weight of a step as it stands against one whose second pass walks every tile.
-// With nothing to move tall tiles are 1 % better, where nodes move short ones 2 to 12 %
+// With nothing to move tall tiles are 1 % better, where nodes move short ones up to 12 %
 // (FP32, 16 or 64 rows, us a step: 4096 x 4096 203.6 or 200.4 quiet, 348 or 374 with 5 %
 // of the nodes moved; 3600 x 3600 164.9 or 162.8, 287 or 319; 2500 x 2500 82.9 or 81.9,
 // 119 or 129; 5000 x 5000 FP16 198 or 195, 548 or 615 with a third moved).  Which of
 // the two a run will be cannot be seen at its start, so the state it starts from
-// counts most; one that filters throughout is better off with LBM_RUN_ADAPTIVE.
-constexpr double kAsItStands = 8.0;
+// counts most; one that filters throughout is better off with LBM_RUN_ADAPTIVE.  Not
+// so much, though, that a difference of 1 us decides: 256 cavities at rest take 98.5 or
+// 97.5 us as they stand, 137 or 146 with every tile, and 120 or 131 from the first
+// step on; eight times chose 64 rows there, at 4096 x 4096 (204 or 201, 270 or 267) four
+// times does as well.
+constexpr double kAsItStands = 4.0;
 // Steps as it stands that are timed together: three could not tell 1 % apart (six
 // contexts of about 2500 x 2500 chose 16 rows twice and 64 four times)
 constexpr int kTunedSteps = 12;
