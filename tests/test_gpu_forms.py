@@ -466,3 +466,20 @@ def test_second_pass_lists_with_every_node(nx, ny, bc):
     assert_masks_equal(pr)
     close(pr.f, pr.fo, 1e-13)
     assert pr.stats["limiter_production"] == pytest.approx(pr.so["limiter_production"], rel=1e-11)
+
+
+# a node so fast that a population of its polynomial f* is negative: the rule's
+# factor is negative too, and the smallest, whatever the mean says
+@pytest.mark.parametrize("limiter,kw", [(SMOOTH, dict(ens_k=0.5, delta_ens=0.01)),
+                                        (RATIONAL, dict(ens_c=2.0, ens_k=1.0))])
+def test_dense_form_pass_with_a_negative_equilibrium(limiter, kw):
+    L = lbm()
+    f0 = rough(9, 70, 9, seed=4, amp=0.01)
+    f0[:, 4, 20] = 0.01
+    f0[1, 4, 20] = 2.0
+    assert orc().equilibrium(2, 0, 2.08, 2.0 / 2.08, 0.0).min() < 0
+    d = L.Domain(lattice=D2Q9, nx=70, ny=9, beta=0.97, qe=0, ds_form=0, limiter=64 | limiter, **kw)
+    pr = Pair(d, f0, steps=1)
+    assert pr.stats["n_positivity"] == pr.so["n_positivity"] > 0
+    assert_masks_equal(pr, ens_noise=True)
+    close(pr.f, pr.fo, 1e-13)
